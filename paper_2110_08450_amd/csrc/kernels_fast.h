@@ -53,7 +53,144 @@ __global__ void __launch_bounds__(kThreads) k_insert_seeds(const Launch P) {
   }
 }
 
-// d lanes cooperate on one destination, lane s of the group owns slot s; a wave holds
+// (destination, slot) of the idx-th padded sample of a tile: idx = r * d + s.
+struct DivD {
+  uint64_t inv;  // ceil(2^32 / d); the quotient is exact for idx < 2^27
+  uint32_t d;
+  __device__ __forceinline__ explicit DivD(uint32_t d_) : inv((0xFFFFFFFFull / d_) + 1ull), d(d_) {}
+  __device__ __forceinline__ void split(uint32_t idx, uint32_t& r, uint32_t& s) const {
+    r = static_cast<uint32_t>((static_cast<uint64_t>(idx) * inv) >> 32);
+    s = idx - r * d;
+  }
+};
+
+// ---- the draw (section 2.2: at most d neighbours, uniformly, without replacement) ------------------
+// A block draws for up to draw_rows(d) consecutive destinations at a time, in four steps, each with its
+// own assignment of the work to the threads:
+//   rows    a thread per destination: node id, row offsets;
+//   words   a thread per (destination, four slots): one Philox block gives the draws of four slots;
+//   settle  a thread per destination: Floyd's rule slot by slot, the picks so far in registers (the
+//           array set); D is the fanout rounded up to 8, 16 or 32, so that they are;
+//   reads   a thread per sample, kDrawAhead of them in flight: the neighbour ids, in position order.
+// Instruction issue bounds it while a destination has many slots, the lines of the scattered reads
+// otherwise.  With a lane per slot in all steps (draw_neighbour below: every lane its own Philox block
+// for one word of it, the rule settled by a shuffle and a ballot per slot, three destinations of
+// fanout 20 per wave) a hop of 1.47 M destinations x 20 took 415 us, this way 222 us, and 61 -> 22 us
+// for one of 77 K; 1.41 M x 5 stays at 116 us, which is 0.58 GB of 128-byte lines at 5 TB/s.
+constexpr int kDrawWords = 4096;  // LDS words for the draws of a turn
+constexpr int kDrawAhead = 4;
+constexpr uint32_t draw_stride(uint32_t d) { return d | 1u; }  // odd: the settling lanes hit different banks
+__host__ __device__ inline int draw_rows(int d) {
+  const int r = kDrawWords / static_cast<int>(draw_stride(static_cast<uint32_t>(d)));
+  return r < kThreads ? r : kThreads;
+}
+// Destinations per turn of a block that owns `rows` of them: turns of equal size.
+__device__ __forceinline__ int draw_turn(int d, int rows) {
+  const int most = draw_rows(d);
+  const int turns = (rows + most - 1) / most;
+  return (rows + turns - 1) / turns;
+}
+
+struct DrawLds {
+  int64_t start[kThreads];    // first CSR position of the destination's row
+  uint32_t node[kThreads];
+  uint32_t deg[kThreads];
+  uint32_t draw[kDrawWords];  // [destination][slot], rows of draw_stride(d): row positions
+};
+
+// Destinations i0 .. i0 + rows (rows <= draw_rows(d)).  on_row(i, node, samples) is called once per
+// destination, on_sample(position, neighbour) once per sample; positions are i * d + slot.  All threads of
+// the block call; the block must synchronise before the LDS is used again.
+template <int D, typename OnRow, typename OnSample>
+__device__ __forceinline__ void draw_tile(const Launch& P, const BatchCtx& B, DrawLds& S, int i0, int rows,
+                                          OnRow on_row, OnSample on_sample) {
+  static_assert(D <= 32, "the picks of a destination are kept in registers");
+  const uint32_t d = static_cast<uint32_t>(P.d);
+  const uint32_t ld = draw_stride(d);
+  if (static_cast<int>(threadIdx.x) < rows) {
+    const int i = i0 + threadIdx.x;
+    const int32_t id = B.node_ids[i];
+    const uint32_t v = static_cast<uint32_t>(id);
+    int64_t a = 0;
+    uint32_t deg = 0;
+    // the seeds are caller data: none may index the graph unchecked
+    if (P.h == 0 && (id < 0 || static_cast<int64_t>(id) >= P.num_nodes)) {
+      set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
+    } else {
+      a = P.indptr[v];
+      deg = static_cast<uint32_t>(P.indptr[v + 1] - a);
+    }
+    S.start[threadIdx.x] = a;
+    S.node[threadIdx.x] = v;
+    S.deg[threadIdx.x] = deg;
+    on_row(i, v, deg > d ? d : deg);
+  }
+  __syncthreads();
+  {
+    const uint32_t blocks = (d + 3u) >> 2;  // Philox blocks per destination
+    const DivD div(blocks);
+    for (uint32_t q = threadIdx.x; q < static_cast<uint32_t>(rows) * blocks; q += kThreads) {
+      uint32_t r, blk;
+      div.split(q, r, blk);
+      const uint32_t deg = S.deg[r];
+      if (deg > d) {
+        uint32_t w[4];
+        philox_block(S.node[r], static_cast<uint32_t>(P.h), blk, B.key0, B.key1, w);
+        const uint32_t j = deg - d + 4u * blk;  // slot s draws an index in [0, deg - d + s]
+#pragma unroll
+        for (uint32_t u = 0; u < 4u; ++u)
+          if (4u * blk + u < d) S.draw[r * ld + 4u * blk + u] = __umulhi(w[u], j + u + 1u);
+      }
+    }
+  }
+  __syncthreads();
+  if (static_cast<int>(threadIdx.x) < rows && S.deg[threadIdx.x] > d) {
+    // Floyd's subset algorithm: pick t_s unless an earlier slot holds it, then pick j_s
+    uint32_t* t = S.draw + threadIdx.x * ld;
+    const uint32_t j0 = S.deg[threadIdx.x] - d;
+    uint32_t p[D];
+#pragma unroll
+    for (int s = 0; s < D; ++s) p[s] = s < static_cast<int>(d) ? t[s] : 0u;
+#pragma unroll
+    for (int s = 1; s < D; ++s) {
+      if (s < static_cast<int>(d)) {
+        bool held = false;
+#pragma unroll
+        for (int q = 0; q < s; ++q) held |= p[q] == p[s];
+        if (held) {
+          p[s] = j0 + static_cast<uint32_t>(s);
+          t[s] = p[s];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const DivD div(d);
+  const uint32_t cnt = static_cast<uint32_t>(rows) * d;
+  const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
+  for (uint32_t base = threadIdx.x; base < cnt; base += kThreads * kDrawAhead) {
+    uint32_t g[kDrawAhead];
+    bool has[kDrawAhead];
+#pragma unroll
+    for (int u = 0; u < kDrawAhead; ++u) {
+      const uint32_t idx = base + u * kThreads;
+      uint32_t r = 0, s = 0;
+      if (idx < cnt) div.split(idx, r, s);
+      const uint32_t deg = S.deg[r];
+      has[u] = idx < cnt && s < deg;
+      const uint32_t p = deg > d ? S.draw[r * ld + s] : s;  // whole row in CSR order when deg <= d
+      // a neighbour id is read once per batch: keep it out of the way of data that is reused
+      g[u] = has[u] ? static_cast<uint32_t>(__builtin_nontemporal_load(P.indices + (S.start[r] + p))) : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kDrawAhead; ++u)
+      if (has[u]) on_sample(pos0 + base + u * kThreads, g[u]);
+  }
+}
+
+// The table strategy's draw: few destinations per launch, where the steps above with their three
+// barriers cost more than they save (a hop of 250 destinations x 10: 62 against 64 us for the whole
+// call).  d lanes cooperate on one destination, lane s of the group owns slot s; a wave holds
 // floor(64 / d) groups (its last 64 mod d lanes idle).
 struct LaneGroups {
   int d, per_wave, per_block, grp, s, gbase, row_in_block;
@@ -93,8 +230,10 @@ __device__ __forceinline__ bool draw_neighbour(const Launch& P, const BatchCtx& 
   uint32_t p = static_cast<uint32_t>(s);  // whole row in CSR order when deg <= d
   uint32_t t = 0, j = 0;
   if (floyd) {
-    const uint32_t w = philox_word(v, static_cast<uint32_t>(P.h), static_cast<uint32_t>(s) >> 2,
-                                   B.key0, B.key1, static_cast<uint32_t>(s) & 3u);
+    uint32_t w4[4];
+    philox_block(v, static_cast<uint32_t>(P.h), static_cast<uint32_t>(s) >> 2, B.key0, B.key1, w4);
+    const uint32_t lo = (s & 1) ? w4[1] : w4[0], hi = (s & 1) ? w4[3] : w4[2];
+    const uint32_t w = (s & 2) ? hi : lo;
     j = deg - static_cast<uint32_t>(d) + static_cast<uint32_t>(s);
     t = __umulhi(w, j + 1u);  // index in [0, j]
   }
@@ -148,17 +287,6 @@ __global__ void __launch_bounds__(kThreads) k_sample_insert(const Launch P) {
     if (row && G.s == 0) B.rowk[i] = static_cast<int32_t>(k);
   }
 }
-
-// (destination, slot) of the idx-th padded sample of a tile: idx = r * d + s.
-struct DivD {
-  uint64_t inv;  // ceil(2^32 / d); the quotient is exact for idx < 2^27
-  uint32_t d;
-  __device__ __forceinline__ explicit DivD(uint32_t d_) : inv((0xFFFFFFFFull / d_) + 1ull), d(d_) {}
-  __device__ __forceinline__ void split(uint32_t idx, uint32_t& r, uint32_t& s) const {
-    r = static_cast<uint32_t>((static_cast<uint64_t>(idx) * inv) >> 32);
-    s = idx - r * d;
-  }
-};
 
 // One block per tile of kTileRows destinations.  The padded samples of a tile are one contiguous
 // span of ent (and lostto), read flat and coalesced.  NOTES: the table strategy's displacement

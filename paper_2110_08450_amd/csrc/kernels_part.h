@@ -101,7 +101,9 @@ __global__ void __launch_bounds__(kThreads) k_begin(const Launch P) {
 }
 
 // Samples of the block's destinations -> gsrc, rowk; per-bucket record counts -> hist row.
+template <int D>
 __global__ void __launch_bounds__(kThreads) k_sample_hist(const Launch P) {
+  __shared__ DrawLds S;
   __shared__ uint32_t hist[1 << kPartMaxLgB];
   const BatchCtx& B = P.b[batch_of_block(P)];
   const int blk = block_in_batch(P);
@@ -113,28 +115,20 @@ __global__ void __launch_bounds__(kThreads) k_sample_hist(const Launch P) {
   const int nB = 1 << P.lgB;
   for (int b = threadIdx.x; b < nB; b += kThreads) hist[b] = 0u;
   __syncthreads();
-  const LaneGroups G(P.d);
-  for (int i0 = r0; i0 < r1; i0 += G.per_block) {
-    const int i = i0 + G.row_in_block;
-    bool row = G.lane_used && i < r1;
-    if (P.h == 0 && row) {  // the seeds are caller data: none may index the graph unchecked
-      const int32_t seed = B.node_ids[i];
-      if (seed < 0 || static_cast<int64_t>(seed) >= P.num_nodes) {
-        set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
-        row = false;
-      }
-    }
-    uint32_t v, k, g;
-    if (draw_neighbour(P, B, G, i, row, v, k, g)) {
-      B.gsrc[static_cast<uint32_t>(i) * static_cast<uint32_t>(G.d) + static_cast<uint32_t>(G.s)] = static_cast<int32_t>(g);
-      atomicAdd(&hist[part_bucket(g, P.lgB)], 1u);
-    }
-    if (row && G.s == 0) {
-      B.rowk[i] = static_cast<int32_t>(k);
-      atomicAdd(&hist[part_bucket(v, P.lgB)], 1u);  // the destination itself, a known node
-    }
+  const int turn = draw_turn(P.d, P.block_rows);
+  for (int i0 = r0; i0 < r1; i0 += turn) {
+    draw_tile<D>(
+        P, B, S, i0, r1 - i0 < turn ? r1 - i0 : turn,
+        [&](int i, uint32_t v, uint32_t k) {
+          B.rowk[i] = static_cast<int32_t>(k);
+          atomicAdd(&hist[part_bucket(v, P.lgB)], 1u);  // the destination itself, a known node
+        },
+        [&](uint32_t pos, uint32_t g) {
+          B.gsrc[pos] = static_cast<int32_t>(g);
+          atomicAdd(&hist[part_bucket(g, P.lgB)], 1u);
+        });
+    __syncthreads();
   }
-  __syncthreads();
   uint32_t* out = B.hist + static_cast<size_t>(blk) * nB;
   for (int b = threadIdx.x; b < nB; b += kThreads) out[b] = hist[b];
 }

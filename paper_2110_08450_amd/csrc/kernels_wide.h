@@ -125,9 +125,17 @@ __device__ __forceinline__ void floyd_positions(const Launch& P, const BatchCtx&
   constexpr uint32_t kKnown = 0x80000000u, kRefused = 0x40000000u, kRefMask = 0x3FFFFFFFu;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t j0 = deg - k;
-  for (uint32_t s = lane; s < k; s += 64u) {
-    const uint32_t w = philox_word(v, static_cast<uint32_t>(P.h), s >> 2, B.key0, B.key1, s & 3u);
-    draws[s] = __umulhi(w, j0 + s + 1u);  // index in [0, j_s]
+  // a lane draws for four slots at a time; the arrays are rounded up to a multiple of 64 words, and what
+  // lies at or beyond slot k is not looked at
+  for (uint32_t s = 4u * lane; s < k; s += 4u * 64u) {
+    uint32_t w[4];
+    philox_block(v, static_cast<uint32_t>(P.h), s >> 2, B.key0, B.key1, w);
+    uint4 t;  // an index in [0, j_s] each
+    t.x = __umulhi(w[0], j0 + s + 1u);
+    t.y = __umulhi(w[1], j0 + s + 2u);
+    t.z = __umulhi(w[2], j0 + s + 3u);
+    t.w = __umulhi(w[3], j0 + s + 4u);
+    *reinterpret_cast<uint4*>(draws + s) = t;
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();

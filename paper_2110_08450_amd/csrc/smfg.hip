@@ -420,6 +420,13 @@ int static_scratch_of(int device, void** out) {
   return SMFG_OK;
 }
 
+// A kernel that keeps the picks of a destination in registers: the variant for up to 8, 16 or 32 of them.
+using LaunchKernel = void (*)(const Launch);
+void launch_by_fanout(int d, unsigned blocks, hipStream_t st, const Launch& P, LaunchKernel to8, LaunchKernel to16,
+                      LaunchKernel to32) {
+  (d <= 8 ? to8 : d <= 16 ? to16 : to32)<<<blocks, kThreads, 0, st>>>(P);
+}
+
 // The gather launch shared by smfg_sample_mfg_many and smfg_gather_many.
 template <int ROWS>
 void launch_gather_rows(const Launch& P, int64_t max_rows, int vb, unsigned G, hipStream_t st) {
@@ -799,7 +806,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
       const unsigned buckets = 1u << P.lgB;
       {
         StageTimer t_(SMFG_STAGE_SAMPLE, st);
-        k_sample_hist<<<row_blocks * G, kThreads, 0, st>>>(P);
+        launch_by_fanout(P.d, row_blocks * G, st, P, k_sample_hist<8>, k_sample_hist<16>, k_sample_hist<32>);
       }
       {
         StageTimer t_(SMFG_STAGE_PARTITION, st);
