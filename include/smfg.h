@@ -160,9 +160,12 @@ int64_t smfg_workspace_bytes(const smfg_workspace_t *ws);
  *                            table in device memory, no device-wide atomics.  The default.
  *   SMFG_STRATEGY_TABLE      one open-addressing table in device memory per batch, claimed with
  *                            atomics.  Chosen when no hop of the planned size reaches 32768
- *                            records (fewer launches per hop; such calls are launch bound).
+ *                            records.
+ * A call whose own hops all stay below that, on a workspace of either kind, reads all its records in every
+ * one of a few blocks instead (three launches per hop; such calls are launch bound): no table in
+ * device memory, no atomics.  The result is the same again.
  * The environment variable SMFG_DEDUP=table or =partition, read when a workspace is created,
- * overrides the choice (for measurements and tests).  Returns -1 for NULL.
+ * overrides the choice, for small calls as well (for measurements and tests).  Returns -1 for NULL.
  */
 #define SMFG_STRATEGY_TABLE 0
 #define SMFG_STRATEGY_PARTITION 1

@@ -84,13 +84,15 @@ __device__ __forceinline__ int batch_of_block(const Launch& P) { return static_c
 __device__ __forceinline__ int block_in_batch(const Launch& P) { return static_cast<int>(blockIdx.x / static_cast<unsigned>(P.G)); }
 __device__ __forceinline__ int blocks_per_batch(const Launch& P) { return static_cast<int>(gridDim.x / static_cast<unsigned>(P.G)); }
 
-__device__ __forceinline__ int64_t status_of(const BatchCtx& B, int L) {
+template <typename Batch>
+__device__ __forceinline__ int64_t status_of(const Batch& B, int L) {
   return __hip_atomic_load(&B.counts[2 * L + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The same answer for every thread of the block (other blocks may set the status while this one
 // starts, and kernels that synchronise must leave as whole blocks).
-__device__ __forceinline__ bool block_has_status(const BatchCtx& B, int L) {
+template <typename Batch>
+__device__ __forceinline__ bool block_has_status(const Batch& B, int L) {
   __shared__ int st_lds;
   if (threadIdx.x == 0) st_lds = status_of(B, L) != 0 ? 1 : 0;
   __syncthreads();
@@ -99,7 +101,8 @@ __device__ __forceinline__ bool block_has_status(const BatchCtx& B, int L) {
   return r;
 }
 
-__device__ __forceinline__ void set_status(const BatchCtx& B, int L, int64_t code) {
+template <typename Batch>
+__device__ __forceinline__ void set_status(const Batch& B, int L, int64_t code) {
   unsigned long long* p = reinterpret_cast<unsigned long long*>(&B.counts[2 * L + 1]);
   atomicCAS(p, 0ull, static_cast<unsigned long long>(code));
 }
@@ -169,7 +172,8 @@ __global__ void __launch_bounds__(kThreads) k_fill_u32(uint32_t* p, int64_t n, u
 }
 
 // ---- block scan ------------------------------------------------------------------------------
-// Exclusive scan over a block of kThreads values; returns the exclusive prefix, total in `total`.
+// Exclusive scan over a block of NT values; returns the exclusive prefix, total in `total`.  lds: NT / 64 words.
+template <int NT = kThreads>
 __device__ __forceinline__ unsigned long long block_exscan(unsigned long long x, unsigned long long* lds,
                                                             unsigned long long& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -184,7 +188,7 @@ __device__ __forceinline__ unsigned long long block_exscan(unsigned long long x,
   __syncthreads();
   unsigned long long base = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     const unsigned long long v = lds[w];
     if (w < wave) base += v;
     tot += v;

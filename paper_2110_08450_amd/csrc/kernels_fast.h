@@ -22,7 +22,8 @@ __global__ void __launch_bounds__(kThreads) k_clear(const Launch P) {
 }
 
 // ys = y[ids[:batch_size]] (Listing 1): the seeds are the first ids.
-__device__ __forceinline__ void copy_label(const Launch& P, const BatchCtx& B, int i, int32_t v) {
+template <typename Call, typename Batch>
+__device__ __forceinline__ void copy_label(const Call& P, const Batch& B, int i, int32_t v) {
   const uint8_t* src = P.labels + static_cast<int64_t>(v) * P.label_bytes;
   uint8_t* dst = B.labels + static_cast<int64_t>(i) * P.label_bytes;
   switch (P.label_bytes) {
@@ -65,57 +66,58 @@ struct DivD {
 };
 
 // ---- the draw (section 2.2: at most d neighbours, uniformly, without replacement) ------------------
-// A block draws for up to draw_rows(d) consecutive destinations at a time, in four steps, each with its
+// A block draws for a turn of consecutive destinations at a time, in four steps, each with its
 // own assignment of the work to the threads:
 //   rows    a thread per destination: node id, row offsets;
 //   words   a thread per (destination, four slots): one Philox block gives the draws of four slots;
 //   settle  a thread per destination: Floyd's rule slot by slot, the picks so far in registers (the
-//           array set); D is the fanout rounded up to 8, 16 or 32, so that they are;
+//           array set), D of them at most;
 //   reads   a thread per sample, kDrawAhead of them in flight: the neighbour ids, in position order.
 // Instruction issue bounds it while a destination has many slots, the lines of the scattered reads
 // otherwise.  With a lane per slot in all steps (draw_neighbour below: every lane its own Philox block
 // for one word of it, the rule settled by a shuffle and a ballot per slot, three destinations of
 // fanout 20 per wave) a hop of 1.47 M destinations x 20 took 415 us, this way 222 us, and 61 -> 22 us
 // for one of 77 K; 1.41 M x 5 stays at 116 us, which is 0.58 GB of 128-byte lines at 5 TB/s.
-constexpr int kDrawWords = 4096;  // LDS words for the draws of a turn
 constexpr int kDrawAhead = 4;
+constexpr uint32_t kNoSample = 0xFFFFFFFFu;  // no node id, no tagged position
 constexpr uint32_t draw_stride(uint32_t d) { return d | 1u; }  // odd: the settling lanes hit different banks
-__host__ __device__ inline int draw_rows(int d) {
-  const int r = kDrawWords / static_cast<int>(draw_stride(static_cast<uint32_t>(d)));
-  return r < kThreads ? r : kThreads;
-}
-// Destinations per turn of a block that owns `rows` of them: turns of equal size.
-__device__ __forceinline__ int draw_turn(int d, int rows) {
-  const int most = draw_rows(d);
-  const int turns = (rows + most - 1) / most;
-  return (rows + turns - 1) / turns;
-}
 
+template <int NT, int WORDS>  // threads of the block, LDS words for the draws of a turn
 struct DrawLds {
-  int64_t start[kThreads];    // first CSR position of the destination's row
-  uint32_t node[kThreads];
-  uint32_t deg[kThreads];
-  uint32_t draw[kDrawWords];  // [destination][slot], rows of draw_stride(d): row positions
+  int64_t start[NT];     // first CSR position of the destination's row
+  uint32_t node[NT];
+  uint32_t deg[NT];
+  uint32_t draw[WORDS];  // [destination][slot], rows of draw_stride(d): row positions
+
+  // Destinations per turn of a block that owns `rows` of them: turns of equal size.
+  static __device__ __forceinline__ int turn(int d, int rows) {
+    int most = WORDS / static_cast<int>(draw_stride(static_cast<uint32_t>(d)));
+    most = most < NT ? most : NT;
+    const int turns = (rows + most - 1) / most;
+    return turns > 1 ? (rows + turns - 1) / turns : rows;
+  }
 };
 
-// Destinations i0 .. i0 + rows (rows <= draw_rows(d)).  on_row(i, node, samples) is called once per
-// destination, on_sample(position, neighbour) once per sample; positions are i * d + slot.  All threads of
-// the block call; the block must synchronise before the LDS is used again.
-template <int D, typename OnRow, typename OnSample>
-__device__ __forceinline__ void draw_tile(const Launch& P, const BatchCtx& B, DrawLds& S, int i0, int rows,
-                                          OnRow on_row, OnSample on_sample) {
+// Destinations ids[i0 .. i0 + rows) (rows <= a turn's); one that is no node of the graph has no samples,
+// and on_stray() is called for it.  on_row(i, node, samples) is called once per
+// destination, on_sample(position, neighbour) once per sample; positions are i * d + slot.  ALL: also once
+// per position that has no sample, with kNoSample.  All threads of the block call; the block must synchronise before the LDS is used again.
+template <int D, bool ALL, int NT, int WORDS, typename Call, typename Batch, typename OnStray, typename OnRow,
+          typename OnSample>
+__device__ __forceinline__ void draw_tile(const Call& P, const Batch& B, int h, uint32_t d, const int32_t* ids,
+                                          DrawLds<NT, WORDS>& S, int i0, int rows, OnStray on_stray, OnRow on_row,
+                                          OnSample on_sample) {
   static_assert(D <= 32, "the picks of a destination are kept in registers");
-  const uint32_t d = static_cast<uint32_t>(P.d);
   const uint32_t ld = draw_stride(d);
   if (static_cast<int>(threadIdx.x) < rows) {
     const int i = i0 + threadIdx.x;
-    const int32_t id = B.node_ids[i];
+    const int32_t id = ids[i];
     const uint32_t v = static_cast<uint32_t>(id);
     int64_t a = 0;
     uint32_t deg = 0;
     // the seeds are caller data: none may index the graph unchecked
-    if (P.h == 0 && (id < 0 || static_cast<int64_t>(id) >= P.num_nodes)) {
-      set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
+    if (h == 0 && (id < 0 || static_cast<int64_t>(id) >= P.num_nodes)) {
+      on_stray();
     } else {
       a = P.indptr[v];
       deg = static_cast<uint32_t>(P.indptr[v + 1] - a);
@@ -129,13 +131,13 @@ __device__ __forceinline__ void draw_tile(const Launch& P, const BatchCtx& B, Dr
   {
     const uint32_t blocks = (d + 3u) >> 2;  // Philox blocks per destination
     const DivD div(blocks);
-    for (uint32_t q = threadIdx.x; q < static_cast<uint32_t>(rows) * blocks; q += kThreads) {
+    for (uint32_t q = threadIdx.x; q < static_cast<uint32_t>(rows) * blocks; q += NT) {
       uint32_t r, blk;
       div.split(q, r, blk);
       const uint32_t deg = S.deg[r];
       if (deg > d) {
         uint32_t w[4];
-        philox_block(S.node[r], static_cast<uint32_t>(P.h), blk, B.key0, B.key1, w);
+        philox_block(S.node[r], static_cast<uint32_t>(h), blk, B.key0, B.key1, w);
         const uint32_t j = deg - d + 4u * blk;  // slot s draws an index in [0, deg - d + s]
 #pragma unroll
         for (uint32_t u = 0; u < 4u; ++u)
@@ -168,12 +170,12 @@ __device__ __forceinline__ void draw_tile(const Launch& P, const BatchCtx& B, Dr
   const DivD div(d);
   const uint32_t cnt = static_cast<uint32_t>(rows) * d;
   const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
-  for (uint32_t base = threadIdx.x; base < cnt; base += kThreads * kDrawAhead) {
+  for (uint32_t base = threadIdx.x; base < cnt; base += NT * kDrawAhead) {
     uint32_t g[kDrawAhead];
     bool has[kDrawAhead];
 #pragma unroll
     for (int u = 0; u < kDrawAhead; ++u) {
-      const uint32_t idx = base + u * kThreads;
+      const uint32_t idx = base + u * NT;
       uint32_t r = 0, s = 0;
       if (idx < cnt) div.split(idx, r, s);
       const uint32_t deg = S.deg[r];
@@ -183,8 +185,10 @@ __device__ __forceinline__ void draw_tile(const Launch& P, const BatchCtx& B, Dr
       g[u] = has[u] ? static_cast<uint32_t>(__builtin_nontemporal_load(P.indices + (S.start[r] + p))) : 0u;
     }
 #pragma unroll
-    for (int u = 0; u < kDrawAhead; ++u)
-      if (has[u]) on_sample(pos0 + base + u * kThreads, g[u]);
+    for (int u = 0; u < kDrawAhead; ++u) {
+      if (has[u]) on_sample(pos0 + base + u * NT, g[u]);
+      else if (ALL && base + u * NT < cnt) on_sample(pos0 + base + u * NT, kNoSample);
+    }
   }
 }
 

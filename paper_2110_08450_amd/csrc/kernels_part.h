@@ -101,9 +101,10 @@ __global__ void __launch_bounds__(kThreads) k_begin(const Launch P) {
 }
 
 // Samples of the block's destinations -> gsrc, rowk; per-bucket record counts -> hist row.
+// D: the fanout rounded up to 8, 16 or 32.
 template <int D>
 __global__ void __launch_bounds__(kThreads) k_sample_hist(const Launch P) {
-  __shared__ DrawLds S;
+  __shared__ DrawLds<kThreads, 4096> S;
   __shared__ uint32_t hist[1 << kPartMaxLgB];
   const BatchCtx& B = P.b[batch_of_block(P)];
   const int blk = block_in_batch(P);
@@ -115,10 +116,11 @@ __global__ void __launch_bounds__(kThreads) k_sample_hist(const Launch P) {
   const int nB = 1 << P.lgB;
   for (int b = threadIdx.x; b < nB; b += kThreads) hist[b] = 0u;
   __syncthreads();
-  const int turn = draw_turn(P.d, P.block_rows);
+  const int turn = S.turn(P.d, P.block_rows);
   for (int i0 = r0; i0 < r1; i0 += turn) {
-    draw_tile<D>(
-        P, B, S, i0, r1 - i0 < turn ? r1 - i0 : turn,
+    draw_tile<D, false>(
+        P, B, P.h, static_cast<uint32_t>(P.d), B.node_ids, S, i0, r1 - i0 < turn ? r1 - i0 : turn,
+        [&] { set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE); },
         [&](int i, uint32_t v, uint32_t k) {
           B.rowk[i] = static_cast<int32_t>(k);
           atomicAdd(&hist[part_bucket(v, P.lgB)], 1u);  // the destination itself, a known node
@@ -414,12 +416,13 @@ __global__ void __launch_bounds__(kThreads) k_split_buckets(const Launch P) {
 // is a bijection), so the retries end.
 // One record into the bucket's table: the slot of its node keeps the smallest value.  False if the
 // table has no slot left.
+template <uint32_t SLOTS>
 __device__ __forceinline__ bool dedup_insert(unsigned long long* tab, unsigned long long rec, uint32_t sl) {
   const uint32_t node = static_cast<uint32_t>(rec >> 32);
   // A plain read first: a node sampled thousands of times (a hub) would otherwise queue
   // thousands of atomics on one LDS word, while most of its records only need to see that
   // a smaller value is there already.  Slots never lose their node, values only fall.
-  for (uint32_t probes = 0; probes < kPartSlots; ++probes) {
+  for (uint32_t probes = 0; probes < SLOTS; ++probes) {
     unsigned long long old = tab[sl];
     if (old == kEmpty) old = atomicCAS(&tab[sl], kEmpty, rec);
     if (old == kEmpty) return true;
@@ -427,7 +430,7 @@ __device__ __forceinline__ bool dedup_insert(unsigned long long* tab, unsigned l
       if (old > rec) atomicMin(&tab[sl], rec);
       return true;
     }
-    sl = (sl + 1u) & (kPartSlots - 1u);
+    sl = (sl + 1u) & (SLOTS - 1u);
   }
   return false;
 }
@@ -435,21 +438,22 @@ __device__ __forceinline__ bool dedup_insert(unsigned long long* tab, unsigned l
 // What the filled table says about one record: a known node must be alone with its id; a sample
 // that is not its node's smallest value learns the node's local id or the position of its first
 // appearance.
-__device__ __forceinline__ void dedup_settle(const Launch& P, const BatchCtx& B, const unsigned long long* tab,
+template <uint32_t SLOTS, typename Call, typename Batch>
+__device__ __forceinline__ void dedup_settle(const Call& P, const Batch& B, const unsigned long long* tab,
                                              unsigned long long rec, uint32_t sl) {
   const uint32_t node = static_cast<uint32_t>(rec >> 32);
   const uint32_t val = static_cast<uint32_t>(rec);
   uint32_t least = 0u;
   uint32_t probes = 0;
-  for (; probes < kPartSlots; ++probes) {
+  for (; probes < SLOTS; ++probes) {
     const unsigned long long t = tab[sl];
     if (static_cast<uint32_t>(t >> 32) == node) {
       least = static_cast<uint32_t>(t);
       break;
     }
-    sl = (sl + 1u) & (kPartSlots - 1u);
+    sl = (sl + 1u) & (SLOTS - 1u);
   }
-  if (probes == kPartSlots) {  // every inserted node is found again
+  if (probes == SLOTS) {  // every inserted node is found again
     set_status(B, P.L, SMFG_ST_INTERNAL);
     return;
   }
@@ -464,6 +468,86 @@ __device__ __forceinline__ void dedup_settle(const Launch& P, const BatchCtx& B,
   }
 }
 
+// All records of a set that holds every record of its nodes: cnt of them, record(i) the i-th one or
+// kEmpty; `free_bits` hash bits are not yet spoken for.  tab: 2^LG slots of LDS, overflow: one LDS word.
+// All threads of the block (NT) call.
+template <int NT, int LG, typename Call, typename Batch, typename Record>
+__device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, unsigned long long* tab, int& overflow,
+                                              uint32_t cnt, int free_bits, Record record) {
+  constexpr uint32_t kSlots = 1u << LG;
+  constexpr int U = 8;  // records in flight per thread
+  const int max_lgR = free_bits > LG ? free_bits - LG : 0;
+  if (cnt <= NT * U && cnt <= kSlots / 2) {
+    // the usual bucket: its records stay in registers between the two passes, and a table at most
+    // half full cannot overflow
+    unsigned long long mine[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t r = u * NT + threadIdx.x;
+      mine[u] = r < cnt ? record(r) : kEmpty;
+    }
+    for (uint32_t q = threadIdx.x; q < kSlots; q += NT) tab[q] = kEmpty;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (mine[u] != kEmpty)
+        dedup_insert<kSlots>(tab, mine[u],
+                             ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> max_lgR) & (kSlots - 1u));
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (mine[u] != kEmpty)
+        dedup_settle<kSlots>(P, B, tab, mine[u],
+                             ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> max_lgR) & (kSlots - 1u));
+    __syncthreads();
+    return;
+  }
+  int lgR = 0;
+  while (lgR < max_lgR && (cnt >> lgR) > kSlots / 2) ++lgR;
+  for (;;) {
+    bool failed = false;
+    const int rem = free_bits - lgR;  // hash bits below the round's
+    const int down = rem > LG ? rem - LG : 0;
+    const uint32_t rounds = 1u << lgR;
+    for (uint32_t round = 0; round < rounds && !failed; ++round) {
+      for (uint32_t q = threadIdx.x; q < kSlots; q += NT) tab[q] = kEmpty;
+      if (threadIdx.x == 0) overflow = 0;
+      __syncthreads();
+      for (int pass = 0; pass < 2 && !failed; ++pass) {  // insert, then settle
+        for (uint32_t c0 = 0; c0 < cnt; c0 += NT * U) {
+          unsigned long long mine[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const uint32_t r = c0 + u * NT + threadIdx.x;
+            mine[u] = r < cnt ? record(r) : kEmpty;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (mine[u] == kEmpty) continue;
+            const uint32_t hsh = static_cast<uint32_t>(mine[u] >> 32) * kPartHash;
+            if (lgR != 0 && ((hsh >> rem) & (rounds - 1u)) != round) continue;
+            const uint32_t sl = (hsh >> down) & (kSlots - 1u);
+            if (pass == 0) {
+              if (!dedup_insert<kSlots>(tab, mine[u], sl)) overflow = 1;
+            } else {
+              dedup_settle<kSlots>(P, B, tab, mine[u], sl);
+            }
+          }
+        }
+        __syncthreads();
+        failed = overflow != 0;
+      }
+    }
+    if (!failed) break;
+    if (lgR >= max_lgR) {  // cannot overflow with a slot per node
+      if (threadIdx.x == 0) set_status(B, P.L, SMFG_ST_INTERNAL);
+      break;
+    }
+    __syncthreads();  // every thread has read the overflow word before the next attempt clears it
+    ++lgR;
+  }
+}
+
 __global__ void __launch_bounds__(kThreads) k_dedup_buckets(const Launch P) {
   __shared__ unsigned long long tab[kPartSlots];
   __shared__ int overflow_lds;
@@ -472,86 +556,15 @@ __global__ void __launch_bounds__(kThreads) k_dedup_buckets(const Launch P) {
   const HopShape hs = hop_shape(P, B);
   const uint32_t nB = 1u << hs.lgB;
   const uint64_t* __restrict__ recs = hs.lg2 == 0 ? B.rec : B.rec2;
-  const int free_bits = 32 - hs.lgB - hs.lg2;  // hash bits below the (sub-)bucket's
-  const int max_lgR = free_bits > kPartTableLg ? free_bits - kPartTableLg : 0;
-  constexpr int U = 8;  // records in flight per thread
   for (uint32_t bucket = static_cast<uint32_t>(block_in_batch(P)); bucket < (nB << hs.lg2);
        bucket += static_cast<uint32_t>(blocks_per_batch(P))) {
     // the (sub-)bucket's records
     const uint32_t rec0 = hs.lg2 == 0 ? B.bstart[bucket] : B.bstart2[bucket];
     const uint32_t rec1 = hs.lg2 == 0 ? rec0 + B.bstart[nB + 1 + bucket] : B.bstart2[bucket + 1];
-    const uint32_t cnt = rec1 - rec0;
-    if (cnt == 0) continue;
-    if (cnt <= kThreads * U && cnt <= kPartSlots / 2) {
-      // the usual bucket: its records stay in registers between the two passes, and a table at most
-      // half full cannot overflow
-      static_assert(kThreads * U <= kPartSlots, "a resident bucket always fits its table");
-      unsigned long long mine[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t r = rec0 + u * kThreads + threadIdx.x;
-        mine[u] = r < rec1 ? recs[r] : kEmpty;
-      }
-      for (uint32_t q = threadIdx.x; q < kPartSlots; q += kThreads) tab[q] = kEmpty;
-      __syncthreads();
-      const int down = free_bits > kPartTableLg ? free_bits - kPartTableLg : 0;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (mine[u] != kEmpty)
-          dedup_insert(tab, mine[u], ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> down) & (kPartSlots - 1u));
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (mine[u] != kEmpty)
-          dedup_settle(P, B, tab, mine[u],
-                       ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> down) & (kPartSlots - 1u));
-      __syncthreads();
-      continue;
-    }
-    int lgR = 0;
-    while (lgR < max_lgR && (cnt >> lgR) > kPartSlots / 2) ++lgR;
-    for (;;) {
-      bool failed = false;
-      const int rem = free_bits - lgR;  // hash bits below the round's
-      const int down = rem > kPartTableLg ? rem - kPartTableLg : 0;
-      const uint32_t rounds = 1u << lgR;
-      for (uint32_t round = 0; round < rounds && !failed; ++round) {
-        for (uint32_t q = threadIdx.x; q < kPartSlots; q += kThreads) tab[q] = kEmpty;
-        if (threadIdx.x == 0) overflow_lds = 0;
-        __syncthreads();
-        for (int pass = 0; pass < 2 && !failed; ++pass) {  // insert, then settle
-          for (uint32_t c0 = rec0; c0 < rec1; c0 += kThreads * U) {
-            unsigned long long mine[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const uint32_t r = c0 + u * kThreads + threadIdx.x;
-              mine[u] = r < rec1 ? recs[r] : kEmpty;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              if (mine[u] == kEmpty) continue;
-              const uint32_t hsh = static_cast<uint32_t>(mine[u] >> 32) * kPartHash;
-              if (lgR != 0 && ((hsh >> rem) & (rounds - 1u)) != round) continue;
-              const uint32_t sl = (hsh >> down) & (kPartSlots - 1u);
-              if (pass == 0) {
-                if (!dedup_insert(tab, mine[u], sl)) overflow_lds = 1;
-              } else {
-                dedup_settle(P, B, tab, mine[u], sl);
-              }
-            }
-          }
-          __syncthreads();
-          failed = overflow_lds != 0;
-        }
-      }
-      if (!failed) break;
-      if (lgR >= max_lgR) {  // cannot overflow with a slot per node
-        if (threadIdx.x == 0) set_status(B, P.L, SMFG_ST_INTERNAL);
-        break;
-      }
-      __syncthreads();  // every thread has read the overflow word before the next attempt clears it
-      ++lgR;
-    }
+    if (rec1 == rec0) continue;
+    dedup_records<kThreads, kPartTableLg>(P, B, tab, overflow_lds, rec1 - rec0, 32 - hs.lgB - hs.lg2,
+                                          [&](uint32_t i) { return recs[rec0 + i]; });
+    __syncthreads();
   }
 }
 

@@ -1,0 +1,251 @@
+// libsmfg small calls: three launches per hop, whatever is in it.
+//
+// A hop of at most some ten thousand records keeps no kernel busy for longer than its launch and a chain
+// of dependent reads take (about 5 us together), so what counts is how many there are:
+//   draw    many blocks, since its scattered reads need many compute units to be in flight at once;
+//   dedup   kSmallBuckets blocks per batch, each reads all records, keeps those of its hash bucket and
+//           settles them in an LDS table: no histogram, no scatter;
+//   finish  blocks of consecutive destinations; each reads all entries of the hop, which gives it the
+//           first-appearance bits and their prefix sums in its own LDS, and then writes the final ids of
+//           its own destinations: no flags, no scan of tiles in between, no block waits for another.
+// Reading everything in every block costs up to 128 KB from the L2, a few us at most.  Measured, one batch
+// per call, whole call with its gather, against the table strategy's four launches per hop: (10, 5) with
+// 256 seeds 62 -> 44 us, (15, 10, 5) with 2 / 16 / 31 seeds 64 -> 58, 78 -> 68, 89 -> 81 us, (15) with
+// 1024 seeds (57 us, partition strategy) 31 us; seven batches of 31 seeds 124 -> 102 us.  One block for a
+// whole batch was slower (16 seeds: 172 us): a single compute unit has too few reads in flight.
+#ifndef SMFG_KERNELS_SMALL_H_
+#define SMFG_KERNELS_SMALL_H_
+
+#include "device_common.h"
+#include "kernels_fast.h"
+#include "kernels_part.h"
+
+namespace smfg_dev {
+
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallRecords = 32768;  // known nodes + positions of a hop: fewer than this
+constexpr int kSmallLgB = 4;              // 16 buckets
+constexpr int kSmallTableLg = 13;         // of 8192 slots
+constexpr uint32_t kSmallList = 1u << (kSmallTableLg - 1);
+
+struct SmallBatch {
+  const int32_t* seeds;
+  int64_t* counts;
+  int32_t* node_ids;
+  uint8_t* labels;
+  int32_t* gsrc;  // per (destination, slot): node id, settled state, or kNoSample
+  int32_t* rowk;  // samples per destination
+  int32_t* blk_indptr[SMFG_MAX_LAYERS];
+  int32_t* blk_indices[SMFG_MAX_LAYERS];
+  int32_t edge_capacity[SMFG_MAX_LAYERS];
+  int32_t node_capacity;
+  int32_t num_seeds;
+  uint32_t key0, key1;
+};
+
+struct SmallLaunch {
+  const int64_t* indptr;
+  const int32_t* indices;
+  const uint8_t* labels;
+  int64_t num_nodes;
+  int32_t label_bytes;
+  int32_t L;
+  int32_t G;
+  int32_t fanouts[SMFG_MAX_LAYERS];
+  int32_t rows[SMFG_MAX_LAYERS];   // destinations per block of the draw
+  int32_t tile[SMFG_MAX_LAYERS];   // destinations per block of finish, at most kSmallThreads
+  SmallBatch b[SMFG_MAX_BATCHES];
+};
+static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments are limited to 4 KB");
+
+__device__ __forceinline__ int small_batch(const SmallLaunch& P) { return static_cast<int>(blockIdx.x % static_cast<unsigned>(P.G)); }
+__device__ __forceinline__ int small_block(const SmallLaunch& P) { return static_cast<int>(blockIdx.x / static_cast<unsigned>(P.G)); }
+// Destinations of hop h, or -1 if the batch has a status (the same for the whole block).  Hop 0 starts
+// the counts, so its draw does not look at them.
+__device__ __forceinline__ int small_rows(const SmallLaunch& P, const SmallBatch& B, int h) {
+  const int n = h == 0 ? B.num_seeds : static_cast<int>(B.counts[h]);  // on its way with the status
+  return block_has_status(B, P.L) ? -1 : n;
+}
+
+// Every position of the hop gets a node id or kNoSample.  Hop 0 reads the seeds, copies them to the
+// node ids and starts the counts; k_small_dedup looks for seeds that are no nodes.
+template <int D>
+__global__ void __launch_bounds__(kThreads) k_small_draw(const SmallLaunch P, int h) {
+  __shared__ DrawLds<kThreads, 512> S;  // kThreads / d rows of at most d + 1 words
+  const SmallBatch& B = P.b[small_batch(P)];
+  const int n = h == 0 ? B.num_seeds : small_rows(P, B, h);
+  const int i0 = small_block(P) * P.rows[h];
+  if (h == 0 && i0 == 0)
+    for (int q = threadIdx.x; q < 2 * P.L + 2; q += kThreads) B.counts[q] = q == 0 ? n : 0;
+  if (i0 >= n) return;
+  draw_tile<D, true>(
+      P, B, h, static_cast<uint32_t>(P.fanouts[h]), h == 0 ? B.seeds : B.node_ids, S, i0,
+      n - i0 < P.rows[h] ? n - i0 : P.rows[h], [] {},
+      [&](int i, uint32_t v, uint32_t k) {
+        B.rowk[i] = static_cast<int32_t>(k);
+        if (h == 0) {
+          B.node_ids[i] = static_cast<int32_t>(v);
+          if (B.labels && v < P.num_nodes) copy_label(P, B, i, static_cast<int32_t>(v));
+        }
+      },
+      [&](uint32_t pos, uint32_t g) { B.gsrc[pos] = static_cast<int32_t>(g); });
+}
+
+// One block per (batch, bucket).  Blocks of other buckets rewrite entries while this one reads them; such
+// an entry is of no interest before (another bucket's node) nor after (bit 31 set).
+__global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch P, int h) {
+  constexpr int NT = kSmallThreads;
+  __shared__ unsigned long long tab[1 << kSmallTableLg];
+  __shared__ unsigned long long list[kSmallList];
+  __shared__ uint32_t listed;
+  __shared__ int overflow;
+  const SmallBatch& B = P.b[small_batch(P)];
+  const uint32_t bucket = static_cast<uint32_t>(small_block(P));
+  if (threadIdx.x == 0) listed = 0u;
+  const int rows = small_rows(P, B, h);
+  if (rows < 0) return;
+  const uint32_t n = static_cast<uint32_t>(rows);
+  const uint32_t cnt = n + n * static_cast<uint32_t>(P.fanouts[h]);
+  // an entry is of interest if it is a node of this bucket (bit 31: no sample, or settled in an earlier
+  // round - its node's smallest value never is).  The bucket comes from a full-rate 24-bit
+  // multiplication, since every record is tested by all 16 blocks
+  const auto wanted = [&](uint32_t node) {
+    const uint32_t x = (node ^ (node >> 15)) & 0xFFFFFFu;
+    return (node & kResolved) == 0u && ((__umul24(x, 0x79B1B5u) >> 20) & ((1u << kSmallLgB) - 1u)) == bucket;
+  };
+  const auto as_record = [&](uint32_t node, uint32_t i) {
+    return (static_cast<unsigned long long>(node) << 32) | (i < n ? i : (kPend | (i - n)));
+  };
+  if (h == 0 && bucket == 0u)
+    for (uint32_t i = threadIdx.x; i < n; i += NT)
+      if (static_cast<uint32_t>(B.node_ids[i]) >= P.num_nodes) set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
+  const uint32_t positions = cnt - n;
+  // a turn: K known nodes and 4 U positions per thread, every read on its way before the first is used
+  // (the entries are padded to whole 256 bytes); a thread reserves room for all it found at once
+  constexpr int K = 4, U = 4;
+  for (uint32_t c = 0; c * NT * K < n || c * NT * 4u * U < positions; ++c) {
+    uint32_t e[K + 4 * U];
+    const uint32_t i0 = c * NT * K + threadIdx.x, q0 = (c * NT * U + threadIdx.x) * 4u;
+#pragma unroll
+    for (int u = 0; u < K; ++u) e[u] = i0 + u * NT < n ? static_cast<uint32_t>(B.node_ids[i0 + u * NT]) : kNoSample;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t q = q0 + u * NT * 4u;
+      const uint4 x = q < positions ? *reinterpret_cast<const uint4*>(B.gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
+      e[K + 4 * u] = x.x; e[K + 4 * u + 1] = x.y; e[K + 4 * u + 2] = x.z; e[K + 4 * u + 3] = x.w;
+    }
+    uint32_t found = 0;
+#pragma unroll
+    for (int t = 0; t < K + 4 * U; ++t) {
+      const bool there = t < K || q0 + static_cast<uint32_t>((t - K) / 4) * NT * 4u + static_cast<uint32_t>((t - K) % 4) < positions;
+      found |= (there && wanted(e[t]) ? 1u : 0u) << t;
+    }
+    if (found == 0u) continue;
+    uint32_t at = atomicAdd(&listed, static_cast<uint32_t>(__popc(found)));
+#pragma unroll
+    for (int t = 0; t < K + 4 * U; ++t)
+      if (found >> t & 1u) {
+        const uint32_t i = t < K ? i0 + t * NT : n + q0 + static_cast<uint32_t>((t - K) / 4) * NT * 4u + static_cast<uint32_t>((t - K) % 4);
+        if (at < kSmallList) list[at] = as_record(e[t], i);
+        ++at;
+      }
+  }
+  __syncthreads();
+  const bool fits = listed <= kSmallList;
+  dedup_records<NT, kSmallTableLg>(P, B, tab, overflow, fits ? listed : cnt, 32, [&](uint32_t i) {
+    if (fits) return list[i];
+    const uint32_t node = static_cast<uint32_t>(i < n ? B.node_ids[i] : B.gsrc[i - n]);
+    return wanted(node) ? as_record(node, i) : kEmpty;
+  });
+}
+
+// Blocks of P.tile[h] destinations.
+__global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunch P, int h) {
+  constexpr int NT = kSmallThreads;
+  constexpr int kWords = static_cast<int>(kSmallRecords / 64);
+  static_assert(kWords <= NT, "a thread per word of the scan");
+  __shared__ unsigned long long first[kWords];  // bit q % 64 of word q / 64: position q is a first appearance
+  __shared__ uint32_t before[kWords];           // first appearances before the word
+  __shared__ uint32_t off[NT];                  // block offsets of the own destinations
+  __shared__ unsigned long long scan[NT / 64];
+  const SmallBatch& B = P.b[small_batch(P)];
+  const int n = small_rows(P, B, h);
+  const int i0 = small_block(P) * P.tile[h];
+  if (n < 0 || (i0 >= n && i0 > 0)) return;  // the first block also closes an empty hop
+  const int rows = n - i0 < P.tile[h] ? n - i0 : P.tile[h];
+  const uint32_t d = static_cast<uint32_t>(P.fanouts[h]);
+  const uint32_t positions = static_cast<uint32_t>(n) * d;
+  const int tid = threadIdx.x;
+  const uint32_t k = tid < rows ? static_cast<uint32_t>(B.rowk[i0 + tid]) : 0u;
+  // samples of the destinations before the own ones, and of all
+  unsigned long long sums = 0;
+  for (int i = tid; i < n; i += NT) {
+    const unsigned long long x = static_cast<uint32_t>(B.rowk[i]);
+    sums += i < i0 ? (x << 32 | x) : x;
+  }
+  constexpr int U = 4;
+  for (uint32_t q0 = tid * 4u; q0 < ((positions + 63u) & ~63u); q0 += NT * 4u * U) {
+    uint4 e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t q = q0 + u * NT * 4u;
+      e[u] = q < positions ? *reinterpret_cast<const uint4*>(B.gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t q = q0 + u * NT * 4u;
+      // bit 31 clear: a first appearance; the four bits of 16 threads make a word
+      uint32_t nibble = (~e[u].x >> 31) | (~e[u].y >> 31) << 1 | (~e[u].z >> 31) << 2 | (~e[u].w >> 31) << 3;
+      if (q + 4u > positions) nibble &= q < positions ? (1u << (positions - q)) - 1u : 0u;
+      unsigned long long bits = static_cast<unsigned long long>(nibble) << (4 * (tid & 15));
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, 64);
+      if ((tid & 15) == 0 && q < positions) first[q >> 6] = bits;
+    }
+  }
+  unsigned long long total, all;
+  block_exscan<NT>(sums, scan, all);
+  __syncthreads();
+  const uint32_t words = (positions + 63u) >> 6;
+  const uint32_t mine = static_cast<uint32_t>(tid) < words ? static_cast<uint32_t>(__popcll(first[tid])) : 0u;
+  const unsigned long long pre = block_exscan<NT>(static_cast<unsigned long long>(k) << 32 | mine, scan, total);
+  const uint32_t edges = static_cast<uint32_t>(all), nodes = static_cast<uint32_t>(n) + static_cast<uint32_t>(total);
+  const uint32_t own = static_cast<uint32_t>(all >> 32) + static_cast<uint32_t>(pre >> 32);
+  if (tid < kWords) before[tid] = static_cast<uint32_t>(n) + static_cast<uint32_t>(pre);
+  off[tid] = own;
+  const bool nodes_fit = nodes <= static_cast<uint32_t>(B.node_capacity);
+  const bool edges_fit = edges <= static_cast<uint32_t>(B.edge_capacity[h]);
+  if (tid == 0 && i0 == 0) {
+    B.counts[P.L + 1 + h] = edges;
+    B.counts[h + 1] = nodes;
+    if (!nodes_fit) set_status(B, P.L, SMFG_ST_NODE_CAPACITY);
+    else if (!edges_fit) set_status(B, P.L, SMFG_ST_EDGE_CAPACITY);
+    else B.blk_indptr[h][n] = static_cast<int32_t>(edges);
+  }
+  if (!nodes_fit || !edges_fit) return;
+  if (tid < rows) B.blk_indptr[h][i0 + tid] = static_cast<int32_t>(own);
+  __syncthreads();
+  const DivD div(d);
+  const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
+  const uint32_t own_cnt = static_cast<uint32_t>(rows) * d;
+  const auto id_of = [&](uint32_t q) { return before[q >> 6] + static_cast<uint32_t>(__popcll(first[q >> 6] & ((1ull << (q & 63u)) - 1ull))); };
+  for (uint32_t idx = tid; idx < own_cnt; idx += NT) {
+    const uint32_t e = static_cast<uint32_t>(B.gsrc[pos0 + idx]);
+    if (e == kNoSample) continue;
+    uint32_t r, s, local;
+    div.split(idx, r, s);
+    if ((e & kResolved) == 0u) {
+      local = id_of(pos0 + idx);
+      B.node_ids[local] = static_cast<int32_t>(e);
+    } else if ((e & kPointer) == kPointer) {
+      local = id_of(e & ~kPointer);  // a pointer always names a first appearance
+    } else {
+      local = e & ~kPointer;
+    }
+    B.blk_indices[h][off[r] + s] = static_cast<int32_t>(local);
+  }
+}
+
+}  // namespace smfg_dev
+
+#endif  // SMFG_KERNELS_SMALL_H_

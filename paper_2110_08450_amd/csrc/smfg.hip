@@ -47,6 +47,7 @@
 #include "kernels_fast.h"
 #include "kernels_gather.h"
 #include "kernels_part.h"
+#include "kernels_small.h"
 #include "kernels_validate.h"
 #include "kernels_wide.h"
 
@@ -145,6 +146,7 @@ struct smfg_workspace {
   int64_t bytes;
   // partition strategy (no dedup table) or table strategy; fixed when the workspace is planned
   bool part;
+  bool forced;           // the strategy was named by SMFG_DEDUP: small calls keep to it too
   bool flat;             // partition strategy also over exact offsets (wide fanouts): group records, row starts etc. present
   int64_t rec_entries;   // capacity of rec: known nodes + samples of a hop
   int64_t hist_entries;  // capacity of hist: row blocks x buckets of a hop
@@ -327,6 +329,7 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
   ws->table_log2 = lg;
   bool wide = false;
   check_fanouts(L, fanouts, &wide);
+  ws->forced = table_forced() || part_forced();
   if (wide && !table_forced()) {
     // partition strategy over exact offsets: a hop holds at most node_capacity known nodes and
     // slot_entries samples
@@ -418,6 +421,64 @@ int static_scratch_of(int device, void** out) {
   }
   *out = g_scratch_ptr[device];
   return SMFG_OK;
+}
+
+// Calls whose hops all stay below kSmallRecords records per batch take k_small_*.
+bool call_is_small(int32_t L, const int32_t* fanouts, const int64_t* max_rows) {
+  for (int h = 0; h < L; ++h)
+    if (fanouts[h] < 1 || fanouts[h] > SMFG_MAX_FANOUT || max_rows[h] * (1 + fanouts[h]) >= kSmallRecords) return false;
+  return true;
+}
+void launch_small(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows,
+                  hipStream_t st) {
+  SmallLaunch S;
+  std::memset(&S, 0, sizeof(S));
+  S.indptr = P.indptr;
+  S.indices = P.indices;
+  S.labels = P.labels;
+  S.num_nodes = P.num_nodes;
+  S.label_bytes = P.label_bytes;
+  S.L = P.L;
+  S.G = P.G;
+  for (int h = 0; h < P.L; ++h) {
+    S.fanouts[h] = fanouts[h];
+    S.rows[h] = kThreads / fanouts[h];  // a sample per thread
+    int64_t tile = (max_rows[h] + 7) / 8;  // about eight blocks
+    S.tile[h] = static_cast<int32_t>(tile < 32 ? 32 : tile > kSmallThreads ? kSmallThreads : tile);
+  }
+  for (int b = 0; b < P.G; ++b) {
+    const BatchCtx& B = P.b[b];
+    SmallBatch& T = S.b[b];
+    T.seeds = B.seeds;
+    T.counts = B.counts;
+    T.node_ids = B.node_ids;
+    T.labels = B.labels;
+    T.gsrc = B.gsrc;
+    T.rowk = B.rowk;
+    for (int h = 0; h < P.L; ++h) {
+      T.blk_indptr[h] = outs[b].indptr[h];
+      T.blk_indices[h] = outs[b].indices[h];
+      T.edge_capacity[h] = static_cast<int32_t>(outs[b].edge_capacity[h] < kSmallRecords ? outs[b].edge_capacity[h] : kSmallRecords);
+    }
+    T.node_capacity = B.node_capacity;
+    T.num_seeds = B.num_seeds;
+    T.key0 = B.key0;
+    T.key1 = B.key1;
+  }
+  for (int h = 0; h < P.L; ++h) {
+    {
+      StageTimer t_(SMFG_STAGE_SAMPLE, st);
+      const unsigned blocks = blocks_for(max_rows[h], S.rows[h], 0xFFFFFFu) * static_cast<unsigned>(P.G);
+      const int d = fanouts[h];
+      (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks, kThreads, 0, st>>>(S, h);
+    }
+    {
+      StageTimer t_(SMFG_STAGE_DEDUP, st);
+      k_small_dedup<<<static_cast<unsigned>(P.G) << kSmallLgB, kSmallThreads, 0, st>>>(S, h);
+    }
+    StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
+    k_small_finish<<<blocks_for(max_rows[h], S.tile[h], 0xFFFFFFu) * static_cast<unsigned>(P.G), kSmallThreads, 0, st>>>(S, h);
+  }
 }
 
 // A kernel that keeps the picks of a destination in registers: the variant for up to 8, 16 or 32 of them.
@@ -779,7 +840,11 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   const unsigned G = static_cast<unsigned>(num_batches);
   constexpr unsigned kCap = 4096;  // blocks per batch of the grid-stride kernels
 
-  if (part) {
+  bool small = call_is_small(L, fanouts, max_n);
+  for (int b = 0; b < num_batches; ++b) small = small && !ws[b]->forced;
+  if (small) {
+    launch_small(P, outs, fanouts, max_n, st);
+  } else if (part) {
     StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_begin<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P);
   } else {
@@ -788,7 +853,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
     { StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_insert_seeds<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P); }
   }
-  for (int h = 0; h < L; ++h) {
+  for (int h = small ? L : 0; h < L; ++h) {
     P.h = h;
     P.d = fanouts[h];
     for (int b = 0; b < num_batches; ++b) {
@@ -947,8 +1012,11 @@ int smfg_sample_mfg_static(const smfg_graph_t* g, const int32_t* d_seeds, int32_
   if (rc == SMFG_OK) {
     bind_workspace(&ws, base);
     // the array keeps what the last call left: the displacement notes of the table strategy must
-    // start out clear (nothing of the partition strategy's scratch is read before it is written)
-    if (ws.lostto) {
+    // start out clear (nothing of the other strategies' scratch is read before it is written)
+    int64_t rows[SMFG_MAX_LAYERS];
+    const bool small = !ws.forced && hop_row_bounds(num_seeds, L, fanouts, g->num_nodes, ws.node_capacity, rows) &&
+                       call_is_small(L, fanouts, rows);
+    if (ws.lostto && !small) {
       hipStream_t st = static_cast<hipStream_t>(hip_stream);
       k_fill_u32<<<blocks_for(ws.slot_entries, kThreads * 4, 1024), kThreads, 0, st>>>(ws.lostto, ws.slot_entries, 0u);
       rc = hip_err(hipGetLastError());

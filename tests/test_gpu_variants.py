@@ -36,3 +36,57 @@ def test_draw_over_several_turns(fanout, seeds):
     res, strategy = sample(gg, s, (fanout,), 0xABCDEF0123)
     assert strategy == "partition"
     assert_same(res, gg.oracle.sample_mfg(s, (fanout,), 0xABCDEF0123), 1)
+
+
+@pytest.mark.parametrize("fanouts,seeds", [
+    ((15, 10, 5), 31), ((15, 10, 5), 1), ((1,), 16383), ((1,), 16384), ((32,), 992), ((32,), 993), ((31, 3), 200),
+    ((2,) * 8, 4), ((10, 5), 256), ((9, 8), 300), ((5,), 0)])
+def test_small_calls_in_one_block(fanouts, seeds):
+    """Calls on both sides of what one block per batch takes (32768 records of a hop), rows with and
+    without a draw, several tiles of destinations, several rounds of the dedup, empty batches."""
+    gg = random_graph(40_000, 40, 3, dim=6)
+    s = np.random.default_rng(seeds).permutation(40_000)[:seeds].astype(np.int32)
+    res, _ = sample(gg, s, fanouts, 5)
+    assert_same(res, gg.oracle.sample_mfg(s, fanouts, 5), len(fanouts))
+
+
+def test_small_call_table_overflows_and_retries():
+    """32 000 distinct nodes that share their two leading hash bits: four rounds are planned, one of
+    them gets all records and overflows the 16384-slot table until the rounds are fine enough."""
+    n = 1 << 18
+    h = (np.arange(n, dtype=np.uint64) * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)
+    same = np.nonzero((h >> np.uint64(30)) == np.uint64(1))[0]
+    seeds, others = same[:16_000].astype(np.int32), same[16_000:32_000]
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    deg = np.zeros(n, dtype=np.int64)
+    deg[seeds] = 1
+    np.cumsum(deg, out=indptr[1:])
+    gg = GpuGraph(indptr, others.astype(np.int32), None)
+    s = np.random.default_rng(1).permutation(seeds)
+    res, _ = sample(gg, s, (1,), 9)
+    assert_same(res, gg.oracle.sample_mfg(s, (1,), 9), 1)
+
+
+def test_small_launch_set_labels_and_status():
+    """Ragged batches in one call, with labels; a batch with a repeated seed, one with a seed out of
+    range and two whose output is too small end with their status and leave the others alone."""
+    gg = random_graph(5_000, 30, 8, dim=5)
+    labels = torch.arange(5_000, device=DEV, dtype=torch.int16) * 3
+    smfg.graph_set_labels(gg.g, labels)
+    fan = (10, 5)
+    perm = np.random.default_rng(4).permutation(5_000).astype(np.int32)
+    batches = [perm[:300], perm[300:317], perm[400:401], perm[500:600].copy(), perm[600:700].copy(), perm[700:800], perm[800:900]]
+    batches[3][40] = batches[3][7]
+    batches[4][11] = 5_000
+    outs = [smfg.alloc_output(gg.g, len(b), fan) for b in batches]
+    outs[5] = smfg.alloc_output(gg.g, 100, fan, node_capacity=400)
+    outs[6] = smfg.alloc_output(gg.g, 100, fan, edge_capacity=[100, 100_000])
+    wss = [smfg.workspace_create(gg.g, len(b), fan) for b in batches]
+    keys = list(range(70, 77))
+    for _ in range(2):  # the workspaces are as good after a status as before
+        smfg.sample_mfg_many(gg.g, wss, [torch.from_numpy(b).to(DEV) for b in batches], fan, keys, outs)
+        for i in range(3):
+            assert_same(fetch(outs[i], 2), gg.oracle.sample_mfg(batches[i], fan, keys[i]), 2)
+            assert torch.equal(outs[i].labels[:len(batches[i])].cpu(), labels.cpu()[torch.from_numpy(batches[i]).long()])
+        assert [fetch(o, 2)["status"] for o in outs[3:]] == [smfg.ST_DUPLICATE_SEED, smfg.ST_SEED_OUT_OF_RANGE,
+                                                            smfg.ST_NODE_CAPACITY, smfg.ST_EDGE_CAPACITY]
