@@ -423,14 +423,16 @@ int static_scratch_of(int device, void** out) {
   return SMFG_OK;
 }
 
-// Calls whose hops all stay below kSmallRecords records per batch take k_small_*.
+// A hop below kSmallRecords records in every batch takes k_small_*, whatever the call's other hops take: hop
+// 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's seven
+// launches, 21 us so.
+bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 bool call_is_small(int32_t L, const int32_t* fanouts, const int64_t* max_rows) {
   for (int h = 0; h < L; ++h)
-    if (fanouts[h] < 1 || fanouts[h] > SMFG_MAX_FANOUT || max_rows[h] * (1 + fanouts[h]) >= kSmallRecords) return false;
+    if (!hop_is_small(fanouts[h], max_rows[h])) return false;
   return true;
 }
-void launch_small(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows,
-                  hipStream_t st) {
+SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows) {
   SmallLaunch S;
   std::memset(&S, 0, sizeof(S));
   S.indptr = P.indptr;
@@ -441,9 +443,10 @@ void launch_small(const Launch& P, const smfg_output_t* outs, const int32_t* fan
   S.L = P.L;
   S.G = P.G;
   for (int h = 0; h < P.L; ++h) {
+    if (!hop_is_small(fanouts[h], max_rows[h])) continue;
     S.fanouts[h] = fanouts[h];
     S.rows[h] = kThreads / fanouts[h];  // a sample per thread
-    int64_t tile = (max_rows[h] + 7) / 8;  // about eight blocks
+    const int64_t tile = (max_rows[h] + 7) / 8;  // about eight blocks
     S.tile[h] = static_cast<int32_t>(tile < 32 ? 32 : tile > kSmallThreads ? kSmallThreads : tile);
   }
   for (int b = 0; b < P.G; ++b) {
@@ -465,20 +468,22 @@ void launch_small(const Launch& P, const smfg_output_t* outs, const int32_t* fan
     T.key0 = B.key0;
     T.key1 = B.key1;
   }
-  for (int h = 0; h < P.L; ++h) {
-    {
-      StageTimer t_(SMFG_STAGE_SAMPLE, st);
-      const unsigned blocks = blocks_for(max_rows[h], S.rows[h], 0xFFFFFFu) * static_cast<unsigned>(P.G);
-      const int d = fanouts[h];
-      (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks, kThreads, 0, st>>>(S, h);
-    }
-    {
-      StageTimer t_(SMFG_STAGE_DEDUP, st);
-      k_small_dedup<<<static_cast<unsigned>(P.G) << kSmallLgB, kSmallThreads, 0, st>>>(S, h);
-    }
-    StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
-    k_small_finish<<<blocks_for(max_rows[h], S.tile[h], 0xFFFFFFu) * static_cast<unsigned>(P.G), kSmallThreads, 0, st>>>(S, h);
+  return S;
+}
+void launch_small_hop(const SmallLaunch& S, int h, int64_t max_rows, hipStream_t st) {
+  const unsigned G = static_cast<unsigned>(S.G);
+  {
+    StageTimer t_(SMFG_STAGE_SAMPLE, st);
+    const unsigned blocks = blocks_for(max_rows, S.rows[h], 0xFFFFFFu) * G;
+    const int d = S.fanouts[h];
+    (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks, kThreads, 0, st>>>(S, h);
   }
+  {
+    StageTimer t_(SMFG_STAGE_DEDUP, st);
+    k_small_dedup<<<G << kSmallLgB, kSmallThreads, 0, st>>>(S, h);
+  }
+  StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
+  k_small_finish<<<blocks_for(max_rows, S.tile[h], 0xFFFFFFu) * G, kSmallThreads, 0, st>>>(S, h);
 }
 
 // A kernel that keeps the picks of a destination in registers: the variant for up to 8, 16 or 32 of them.
@@ -840,10 +845,20 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   const unsigned G = static_cast<unsigned>(num_batches);
   constexpr unsigned kCap = 4096;  // blocks per batch of the grid-stride kernels
 
-  bool small = call_is_small(L, fanouts, max_n);
-  for (int b = 0; b < num_batches; ++b) small = small && !ws[b]->forced;
-  if (small) {
-    launch_small(P, outs, fanouts, max_n, st);
+  // the hops that take the small path: the first ones of a call without a device table; with one (which
+  // every hop has to enter) all hops or none
+  int small_hops = 0;
+  while (small_hops < L && hop_is_small(fanouts[small_hops], max_n[small_hops])) ++small_hops;
+  if (table && small_hops < L) small_hops = 0;
+  for (int b = 0; b < num_batches; ++b) {
+    if (ws[b]->forced) small_hops = 0;
+    // its samples sit at padded positions, which a call with wide fanouts need not have room for
+    for (int h = 0; h < small_hops; ++h)
+      if (max_n[h] * fanouts[h] > ws[b]->slot_entries) small_hops = h;
+  }
+  SmallLaunch S;
+  if (small_hops > 0) {
+    S = small_launch(P, outs, fanouts, max_n);
   } else if (part) {
     StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_begin<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P);
@@ -853,7 +868,11 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
     { StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_insert_seeds<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P); }
   }
-  for (int h = small ? L : 0; h < L; ++h) {
+  for (int h = 0; h < L; ++h) {
+    if (h < small_hops) {
+      launch_small_hop(S, h, max_n[h], st);
+      continue;
+    }
     P.h = h;
     P.d = fanouts[h];
     for (int b = 0; b < num_batches; ++b) {

@@ -40,10 +40,11 @@ def test_draw_over_several_turns(fanout, seeds):
 
 @pytest.mark.parametrize("fanouts,seeds", [
     ((15, 10, 5), 31), ((15, 10, 5), 1), ((1,), 16383), ((1,), 16384), ((32,), 992), ((32,), 993), ((31, 3), 200),
-    ((2,) * 8, 4), ((10, 5), 256), ((9, 8), 300), ((5,), 0)])
-def test_small_calls_in_one_block(fanouts, seeds):
-    """Calls on both sides of what one block per batch takes (32768 records of a hop), rows with and
-    without a draw, several tiles of destinations, several rounds of the dedup, empty batches."""
+    ((2,) * 8, 4), ((10, 5), 256), ((9, 8), 300), ((5,), 0), ((15, 10, 5), 1024), ((5, 100), 60), ((3, 40, 2), 900)])
+def test_small_calls_and_hops(fanouts, seeds):
+    """Calls and first hops on both sides of the small path's limit (32768 records of a hop), rows with
+    and without a draw, several tiles of destinations, several rounds of the dedup, empty batches, hops
+    of the other paths after a small one."""
     gg = random_graph(40_000, 40, 3, dim=6)
     s = np.random.default_rng(seeds).permutation(40_000)[:seeds].astype(np.int32)
     res, _ = sample(gg, s, fanouts, 5)
@@ -90,3 +91,16 @@ def test_small_launch_set_labels_and_status():
             assert torch.equal(outs[i].labels[:len(batches[i])].cpu(), labels.cpu()[torch.from_numpy(batches[i]).long()])
         assert [fetch(o, 2)["status"] for o in outs[3:]] == [smfg.ST_DUPLICATE_SEED, smfg.ST_SEED_OUT_OF_RANGE,
                                                             smfg.ST_NODE_CAPACITY, smfg.ST_EDGE_CAPACITY]
+
+
+def test_small_hop_of_a_wide_call_needs_room_for_padded_positions():
+    """A wide call's workspace holds the samples that are drawn, not destinations x fanout: with room for
+    1000 samples, 500 destinations of one neighbour each must not be laid out 20 apart."""
+    n = 3_000
+    rng = np.random.default_rng(2)
+    gg = GpuGraph(np.arange(n + 1, dtype=np.int64), rng.integers(0, n, size=n).astype(np.int32), None)
+    s, fan = rng.permutation(n)[:500].astype(np.int32), (20, 100)
+    ws = smfg.workspace_create(gg.g, 500, fan, sample_capacity=1_000)
+    out = smfg.alloc_output(gg.g, 500, fan)
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), fan, 3, out)
+    assert_same(fetch(out, 2), gg.oracle.sample_mfg(s, fan, 3), 2)
