@@ -57,15 +57,19 @@ struct HopShape {
 // 2^lg buckets in all: one level up to 2^kPartMaxLgB of them; beyond that two levels, the first of
 // only 2^kPartSplitLgB buckets (more if the second would exceed 2^kPartMaxLg2), so that what a
 // block sends to a bucket per round is a run of a sector or more and the lines it is filling stay
-// in the L2 until they are full.
+// in the L2 until they are full.  One or two batches take twice as many, because each first-level bucket
+// is one block of k_split_buckets and 128 of them leave half the chip idle (one batch of 29 M records:
+// scatter + split 414 -> 345 us; four batches of 2.4 M are 10 us better off with 128).
 constexpr int kPartSplitLgB = 7;
-__host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2) {
+constexpr int part_split_lg(int batches) { return batches <= 2 ? kPartSplitLgB + 1 : kPartSplitLgB; }
+__host__ __device__ inline void part_levels(int lg, int batches, int& lgB, int& lg2) {
   if (lg <= kPartMaxLgB) {
     lgB = lg;
     lg2 = 0;
     return;
   }
-  lgB = lg - kPartMaxLg2 > kPartSplitLgB ? lg - kPartMaxLg2 : kPartSplitLgB;
+  const int least = part_split_lg(batches);
+  lgB = lg - kPartMaxLg2 > least ? lg - kPartMaxLg2 : least;
   lg2 = lg - lgB;
 }
 __device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B) {
@@ -74,7 +78,7 @@ __device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B
     const long long records = B.counts[P.h] + B.counts[P.L + 1 + P.h];
     int lg = 0;
     while (lg < P.lgB + P.lg2 && (records >> lg) > kPartBucketRecords) ++lg;
-    part_levels(lg, s.lgB, s.lg2);
+    part_levels(lg, P.G, s.lgB, s.lg2);
   }
   return s;
 }
@@ -196,29 +200,30 @@ __global__ void __launch_bounds__(kThreads) k_scan_hist(const Launch P) {
 }
 
 // ---- records to buckets, in rounds staged through LDS ------------------------------------------
-// A block that moves records to buckets takes them in rounds of kScatterRound (kScatterPer per
-// thread): the round's records are counted per bucket (each gets its rank within its bucket by an
+// A block that moves records to buckets takes them in rounds of kScatterPer per thread: the round's records are counted per bucket (each gets its rank within its bucket by an
 // LDS atomicAdd), the counts are scanned, the records are put in bucket order into a staging
 // array in LDS and written out in that order, so that what a bucket receives from a round leaves
 // as one run of consecutive addresses.  gbase[b] is where the block's next record of bucket b goes.
 constexpr int kScatterPer = 8;
-constexpr int kScatterRound = kScatterPer * kThreads;
 constexpr int kStageBuckets = 1 << (kPartMaxLgB > kPartMaxLg2 ? kPartMaxLgB : kPartMaxLg2);
-constexpr int kStagePer = kStageBuckets / kThreads;  // buckets per thread in the block scans
 
+template <int NT>  // threads of the block
 struct StageLds {
+  static constexpr int kRound = kScatterPer * NT;
+  static constexpr int kPer = kStageBuckets / NT;  // buckets per thread in the block scans
   uint32_t gbase[kStageBuckets];
   uint32_t cnt[kStageBuckets];
   uint32_t lstart[kStageBuckets];
-  unsigned long long stage[kScatterRound];
-  unsigned long long scan[kThreads / 64];
+  unsigned long long stage[kRound];
+  unsigned long long scan[NT / 64];
 };
 
 // gbase[b] <- first + exclusive scan of sizes[b] (+ offs[b] if given), b < nb; returns the total
 // of the sizes.  `write_starts`, if given, also receives first + the exclusive scan.
-template <typename SizeOf, typename OffOf, typename StartTo>
-__device__ __forceinline__ uint32_t stage_set_bases(StageLds& L, int nb, uint32_t first, SizeOf size_of, OffOf off_of,
+template <int NT, typename SizeOf, typename OffOf, typename StartTo>
+__device__ __forceinline__ uint32_t stage_set_bases(StageLds<NT>& L, int nb, uint32_t first, SizeOf size_of, OffOf off_of,
                                                      StartTo start_to) {
+  constexpr int kStagePer = StageLds<NT>::kPer;
   uint32_t sz[kStagePer];
   uint32_t mine = 0;
 #pragma unroll
@@ -228,7 +233,7 @@ __device__ __forceinline__ uint32_t stage_set_bases(StageLds& L, int nb, uint32_
     mine += sz[u];
   }
   unsigned long long total;
-  uint32_t pre = first + static_cast<uint32_t>(block_exscan(mine, L.scan, total));
+  uint32_t pre = first + static_cast<uint32_t>(block_exscan<NT>(mine, L.scan, total));
 #pragma unroll
   for (int u = 0; u < kStagePer; ++u) {
     const int b = threadIdx.x * kStagePer + u;
@@ -244,11 +249,12 @@ __device__ __forceinline__ uint32_t stage_set_bases(StageLds& L, int nb, uint32_
 
 // One round: r[u] are this thread's records (kEmpty = none), bucket_of maps a node to its bucket
 // in [0, nb).  All threads of the block call.
-template <typename BucketOf>
-__device__ __forceinline__ void stage_round(StageLds& L, int nb, const unsigned long long (&r)[kScatterPer],
+template <int NT, typename BucketOf>
+__device__ __forceinline__ void stage_round(StageLds<NT>& L, int nb, const unsigned long long (&r)[kScatterPer],
                                             BucketOf bucket_of, uint64_t* __restrict__ dst) {
+  constexpr int kStagePer = StageLds<NT>::kPer;
   __syncthreads();  // the previous round has been written out
-  for (int b = threadIdx.x; b < nb; b += kThreads) L.cnt[b] = 0u;
+  for (int b = threadIdx.x; b < nb; b += NT) L.cnt[b] = 0u;
   __syncthreads();
   uint32_t bk[kScatterPer], rk[kScatterPer];
 #pragma unroll
@@ -270,7 +276,7 @@ __device__ __forceinline__ void stage_round(StageLds& L, int nb, const unsigned 
     mine += c[u];
   }
   unsigned long long total;
-  uint32_t pre = static_cast<uint32_t>(block_exscan(mine, L.scan, total));
+  uint32_t pre = static_cast<uint32_t>(block_exscan<NT>(mine, L.scan, total));
 #pragma unroll
   for (int u = 0; u < kStagePer; ++u) {
     const int b = threadIdx.x * kStagePer + u;
@@ -283,7 +289,7 @@ __device__ __forceinline__ void stage_round(StageLds& L, int nb, const unsigned 
     if (r[u] != kEmpty) L.stage[L.lstart[bk[u]] + rk[u]] = r[u];
   __syncthreads();
   const uint32_t staged = static_cast<uint32_t>(total);
-  for (uint32_t t = threadIdx.x; t < staged; t += kThreads) {
+  for (uint32_t t = threadIdx.x; t < staged; t += NT) {
     const unsigned long long x = L.stage[t];
     const uint32_t b = bucket_of(static_cast<uint32_t>(x >> 32));
     dst[L.gbase[b] + (t - L.lstart[b])] = x;
@@ -298,7 +304,8 @@ __device__ __forceinline__ void stage_round(StageLds& L, int nb, const unsigned 
 
 // The first record of every bucket (exclusive scan of the bucket sizes k_scan_hist left) plus this
 // block's offset within each bucket; block 0 also stores the bucket starts for k_dedup_buckets.
-__device__ __forceinline__ void stage_bucket_bases(StageLds& L, const BatchCtx& B, int nB, int blk) {
+template <int NT>
+__device__ __forceinline__ void stage_bucket_bases(StageLds<NT>& L, const BatchCtx& B, int nB, int blk) {
   const uint32_t* offs = B.hist + static_cast<size_t>(blk) * nB;
   const uint32_t total = stage_set_bases(
       L, nB, 0u, [&](int b) { return B.bstart[nB + 1 + b]; }, [&](int b) { return offs[b]; },
@@ -310,8 +317,9 @@ __device__ __forceinline__ void stage_bucket_bases(StageLds& L, const BatchCtx& 
 
 // Records of the block's destinations (its known nodes first, then its samples in position
 // order) -> their buckets.
-__global__ void __launch_bounds__(kThreads) k_scatter(const Launch P) {
-  __shared__ StageLds L;
+template <int NT>
+__global__ void __launch_bounds__(NT) k_scatter(const Launch P) {
+  __shared__ StageLds<NT> L;
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const int blk = block_in_batch(P);
@@ -326,12 +334,12 @@ __global__ void __launch_bounds__(kThreads) k_scatter(const Launch P) {
   const uint32_t known = static_cast<uint32_t>(r1 - r0);
   const uint32_t pos0 = static_cast<uint32_t>(r0) * d;
   const uint32_t stream = known + known * d;  // known nodes, then the padded sample positions
-  for (uint32_t c0 = 0; c0 < stream; c0 += kScatterRound) {
+  for (uint32_t c0 = 0; c0 < stream; c0 += StageLds<NT>::kRound) {
     unsigned long long rec[kScatterPer];
     uint32_t k[kScatterPer], sl[kScatterPer], g[kScatterPer];
 #pragma unroll
     for (int u = 0; u < kScatterPer; ++u) {
-      const uint32_t e = c0 + u * kThreads + threadIdx.x;
+      const uint32_t e = c0 + u * NT + threadIdx.x;
       k[u] = 0u;
       sl[u] = 0u;
       g[u] = 0u;
@@ -347,7 +355,7 @@ __global__ void __launch_bounds__(kThreads) k_scatter(const Launch P) {
     }
 #pragma unroll
     for (int u = 0; u < kScatterPer; ++u) {
-      const uint32_t e = c0 + u * kThreads + threadIdx.x;
+      const uint32_t e = c0 + u * NT + threadIdx.x;
       rec[u] = kEmpty;
       if (e < stream && sl[u] < k[u]) {
         // a known node (destination i has local id i), or a sample: tag | position
@@ -361,9 +369,15 @@ __global__ void __launch_bounds__(kThreads) k_scatter(const Launch P) {
 
 // Grid-stride over the buckets: a bucket's records, ordered by the lg2 hash bits below the
 // bucket's, go to the same range of rec2; the sub-buckets' first records go to bstart2.  A counting
-// pass over the bucket, then the staged rounds.
-__global__ void __launch_bounds__(kThreads) k_split_buckets(const Launch P) {
-  __shared__ StageLds L;
+// pass over the bucket, then the staged rounds.  There are only 128 buckets or so, one block each, so
+// a block has to keep its compute unit busy alone: 16 waves, rounds of 8192 records (at 128 sub-buckets
+// a run of 512 bytes each), and a round's records are requested before the round before it is moved.
+// With 4 waves, 128 buckets and nothing requested ahead one batch's 29 M records took 449 us and 7.3 M 78
+// us; 241 and 41 us with 16 waves, 148 and 30 us with 256 buckets on top (part_split_lg).
+template <int NT>
+__global__ void __launch_bounds__(NT) k_split_buckets(const Launch P) {
+  constexpr uint32_t kRound = StageLds<NT>::kRound;
+  __shared__ StageLds<NT> L;
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const HopShape hs = hop_shape(P, B);
@@ -377,32 +391,36 @@ __global__ void __launch_bounds__(kThreads) k_split_buckets(const Launch P) {
        b1 += static_cast<uint32_t>(blocks_per_batch(P))) {
     const uint32_t rec0 = B.bstart[b1];
     const uint32_t rec1 = rec0 + B.bstart[nB1 + 1 + b1];
-    __syncthreads();  // the previous bucket is done with the LDS arrays
-    for (int b = threadIdx.x; b < n2; b += kThreads) L.cnt[b] = 0u;
-    __syncthreads();
-    for (uint32_t c0 = rec0; c0 < rec1; c0 += kScatterRound) {
-      unsigned long long r[kScatterPer];
+    const auto fetch = [&](uint32_t c0, unsigned long long (&r)[kScatterPer]) {
 #pragma unroll
       for (int u = 0; u < kScatterPer; ++u) {
-        const uint32_t q = c0 + u * kThreads + threadIdx.x;
+        const uint32_t q = c0 + u * NT + threadIdx.x;
         r[u] = q < rec1 ? B.rec[q] : kEmpty;
       }
+    };
+    unsigned long long r[kScatterPer], ahead[kScatterPer];
+    __syncthreads();  // the previous bucket is done with the LDS arrays
+    for (int b = threadIdx.x; b < n2; b += NT) L.cnt[b] = 0u;
+    __syncthreads();
+    fetch(rec0, ahead);
+    for (uint32_t c0 = rec0; c0 < rec1; c0 += kRound) {
+#pragma unroll
+      for (int u = 0; u < kScatterPer; ++u) r[u] = ahead[u];
+      fetch(c0 + kRound, ahead);
 #pragma unroll
       for (int u = 0; u < kScatterPer; ++u)
         if (r[u] != kEmpty) atomicAdd(&L.cnt[sub_of(static_cast<uint32_t>(r[u] >> 32))], 1u);
     }
+    fetch(rec0, ahead);
     __syncthreads();
     stage_set_bases(
         L, n2, rec0, [&](int b) { return L.cnt[b]; }, [](int) { return 0u; },
         [&](int b, uint32_t start) { B.bstart2[(static_cast<size_t>(b1) << hs.lg2) + b] = start; });
     if (b1 == nB1 - 1 && threadIdx.x == 0) B.bstart2[static_cast<size_t>(nB1) << hs.lg2] = rec1;
-    for (uint32_t c0 = rec0; c0 < rec1; c0 += kScatterRound) {
-      unsigned long long r[kScatterPer];
+    for (uint32_t c0 = rec0; c0 < rec1; c0 += kRound) {
 #pragma unroll
-      for (int u = 0; u < kScatterPer; ++u) {
-        const uint32_t q = c0 + u * kThreads + threadIdx.x;
-        r[u] = q < rec1 ? B.rec[q] : kEmpty;
-      }
+      for (int u = 0; u < kScatterPer; ++u) r[u] = ahead[u];
+      fetch(c0 + kRound, ahead);
       stage_round(L, n2, r, sub_of, B.rec2);
     }
   }

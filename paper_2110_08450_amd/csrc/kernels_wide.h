@@ -310,7 +310,7 @@ __global__ void __launch_bounds__(kThreads) k_hist_flat(const Launch P) {
 
 // Records of a flat block -> their buckets, in the staged rounds of k_scatter.
 __global__ void __launch_bounds__(kThreads) k_scatter_flat(const Launch P) {
-  __shared__ StageLds L;
+  __shared__ StageLds<kThreads> L;
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
@@ -322,7 +322,7 @@ __global__ void __launch_bounds__(kThreads) k_scatter_flat(const Launch P) {
     __syncthreads();  // the previous flat block is done with the LDS arrays
     stage_bucket_bases(L, B, nB, blk);
     const uint32_t e0 = static_cast<uint32_t>(blk) * kFlatBlock;
-    for (uint32_t c0 = e0; c0 < e0 + kFlatBlock && c0 < total_e; c0 += kScatterRound) {
+    for (uint32_t c0 = e0; c0 < e0 + kFlatBlock && c0 < total_e; c0 += StageLds<kThreads>::kRound) {
       unsigned long long r[kScatterPer];
 #pragma unroll
       for (int u = 0; u < kScatterPer; ++u) {

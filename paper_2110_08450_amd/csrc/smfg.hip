@@ -234,7 +234,7 @@ HopPlan plan_hop(int64_t max_rows, int d, int batches) {
   const int64_t records = max_rows * (1 + d);
   int lg = 0;
   while (lg < kPartMaxLgB + kPartMaxLg2 && (records >> lg) > kPartBucketRecords) ++lg;
-  part_levels(lg, hp.lgB, hp.lg2);
+  part_levels(lg, batches, hp.lgB, hp.lg2);
   int64_t cap = (max_rows + 511) / 512;
   const int64_t least = batches > 8 ? 128 : 512;  // fewer, longer row blocks when many batches fill the chip anyway
   cap = cap < least ? least : (cap > 4096 ? 4096 : cap);
@@ -484,6 +484,16 @@ void launch_small_hop(const SmallLaunch& S, int h, int64_t max_rows, hipStream_t
   }
   StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
   k_small_finish<<<blocks_for(max_rows, S.tile[h], 0xFFFFFFu) * G, kSmallThreads, 0, st>>>(S, h);
+}
+
+// A block per first-level bucket of the bound (the kernel strides over more): while that is not more
+// blocks than compute units, of 16 waves each; 8 waves when two and more share one (2.4 M records in each of
+// four batches: 50 us with 16 waves, 40 with 8, 47 with 4).
+void launch_split(const Launch& P, hipStream_t st) {
+  const int lg = P.lgB < part_split_lg(P.G) ? P.lgB : part_split_lg(P.G);
+  const unsigned blocks = static_cast<unsigned>(P.G) << lg;
+  if (blocks <= 256) k_split_buckets<1024><<<blocks, 1024, 0, st>>>(P);
+  else k_split_buckets<512><<<blocks, 512, 0, st>>>(P);
 }
 
 // A kernel that keeps the picks of a destination in registers: the variant for up to 8, 16 or 32 of them.
@@ -895,8 +905,11 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
       {
         StageTimer t_(SMFG_STAGE_PARTITION, st);
         k_scan_hist<<<((buckets + kScanCols - 1) / kScanCols) * G, kThreads, 0, st>>>(P);
-        k_scatter<<<row_blocks * G, kThreads, 0, st>>>(P);
-        if (P.lg2 > 0) k_split_buckets<<<buckets * G, kThreads, 0, st>>>(P);
+        // with two levels a block has some 16 K records for its 128 or 256 buckets: rounds of 8192 instead of
+        // 2048 make the runs four times as long (29 M records 197 -> 173 us); with one level it has 2304
+        if (P.lg2 > 0) k_scatter<1024><<<row_blocks * G, 1024, 0, st>>>(P);
+        else k_scatter<kThreads><<<row_blocks * G, kThreads, 0, st>>>(P);
+        if (P.lg2 > 0) launch_split(P, st);
       }
       {
         StageTimer t_(SMFG_STAGE_DEDUP, st);
@@ -943,7 +956,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
           k_hist_flat<<<stream_blocks * G, kThreads, 0, st>>>(P);
           k_scan_hist<<<((buckets + kScanCols - 1) / kScanCols) * G, kThreads, 0, st>>>(P);
           k_scatter_flat<<<stream_blocks * G, kThreads, 0, st>>>(P);
-          if (P.lg2 > 0) k_split_buckets<<<buckets * G, kThreads, 0, st>>>(P);
+          if (P.lg2 > 0) launch_split(P, st);
         }
         {
           StageTimer t_(SMFG_STAGE_DEDUP, st);
