@@ -2,6 +2,8 @@
 #ifndef SMFG_KERNELS_GATHER_H_
 #define SMFG_KERNELS_GATHER_H_
 
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace smfg_dev {
@@ -86,12 +88,26 @@ __device__ __forceinline__ void load_pair_streaming(const V* p0, const V* p1, V&
   }
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// A row as 16-byte vectors from its own first byte on, whatever its address and length (at least 16): the
+// last one ends with the row and overlaps the one before, and both write the same bytes there.  The
+// target reads and writes vectors at any byte address.  Used where nothing wider than 4 bytes is
+// aligned; vectors as narrow as that cost instructions (400 K rows of 602 bytes 133 -> 102 us, 800 K
+// of 77 bytes 64 -> 40, 800 K of 66 bytes 42 -> 36, 300 K of 404 bytes 56 -> 52), while rows of 200 bytes
+// stay with 8-byte vectors (420 against 431 us).  Putting an aligned vector together from the end of one
+// row and the beginning of the next instead of overlapping took 109 us for the 602-byte rows.
+struct AnyRow {};
+
 template <typename V, int ROWS>
 __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, int64_t row_stride,
-                                            uint32_t vec_per_row, int64_t num_nodes,
+                                            int64_t row_bytes, int64_t num_nodes,
                                             const int32_t* __restrict__ ids, int64_t n,
                                             uint8_t* __restrict__ out) {
   static_assert(ROWS <= kThreads, "a thread per row fetches its id");
+  constexpr bool kAny = __is_same(V, AnyRow);
+  using W = typename std::conditional<kAny, u32x4, V>::type;
+  const uint32_t vec_per_row = static_cast<uint32_t>((row_bytes + (kAny ? 15 : 0)) / static_cast<int64_t>(sizeof(W)));
   __shared__ int64_t row_byte[ROWS];  // byte offset of each source row
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * ROWS;
   if (r0 >= n) return;
@@ -103,32 +119,36 @@ __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, in
     row_byte[threadIdx.x] = id * row_stride;
   }
   __syncthreads();
-  V* __restrict__ o = reinterpret_cast<V*>(out) + static_cast<uint64_t>(r0) * vec_per_row;
+  uint8_t* __restrict__ o = out + r0 * row_bytes;
   // (row, column) of a vector of the chunk by multiplication: ceil(2^32 / vec_per_row) gives the
   // exact quotient as long as index * vec_per_row < 2^32, which holds for every index of a chunk
   // when a row has at most 8192 vectors; longer rows divide
   const bool by_mul = vec_per_row <= 8192u;
   const uint64_t inv = 0xFFFFFFFFull / vec_per_row + 1ull;
-  const auto source = [&](uint32_t idx) {
+  const auto place = [&](uint32_t idx, const W*& from, W*& to) {
     const uint32_t jrow = by_mul ? static_cast<uint32_t>((idx * inv) >> 32) : idx / vec_per_row;
-    return reinterpret_cast<const V*>(feat + row_byte[jrow]) + (idx - jrow * vec_per_row);
+    uint32_t byte = (idx - jrow * vec_per_row) * static_cast<uint32_t>(sizeof(W));
+    if (kAny && idx - jrow * vec_per_row == vec_per_row - 1u) byte = static_cast<uint32_t>(row_bytes) - 16u;
+    from = reinterpret_cast<const W*>(feat + row_byte[jrow] + byte);
+    to = kAny ? reinterpret_cast<W*>(o + jrow * row_bytes + byte) : reinterpret_cast<W*>(o) + idx;
   };
   // a round: two independent row reads per thread, then the two stores; the last round of a
   // thread may hold one vector only
   for (uint32_t base = threadIdx.x; base < cnt; base += kThreads * 2) {
+    const W *f0, *f1;
+    W *t0, *t1;
+    place(base, f0, t0);
     if (base + kThreads < cnt) {
-      V v0, v1;
-      load_pair_streaming(source(base), source(base + kThreads), v0, v1);
-      store_streaming(v0, o + base);
-      store_streaming(v1, o + base + kThreads);
+      W v0, v1;
+      place(base + kThreads, f1, t1);
+      load_pair_streaming(f0, f1, v0, v1);
+      store_streaming(v0, t0);
+      store_streaming(v1, t1);
     } else {
-      store_streaming(load_streaming(source(base)), o + base);
+      store_streaming(load_streaming(f0), t0);
     }
   }
 }
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename V, int ROWS>
 __global__ void __launch_bounds__(kThreads) k_gather(const Launch P) {
@@ -136,8 +156,7 @@ __global__ void __launch_bounds__(kThreads) k_gather(const Launch P) {
   if (B.features == nullptr || status_of(B, P.L) != 0) return;
   int64_t n = B.counts[P.L];
   if (n > B.node_capacity) n = B.node_capacity;
-  gather_rows<V, ROWS>(P.feat, P.row_stride, static_cast<uint32_t>(P.row_bytes / sizeof(V)), P.num_nodes,
-                 B.node_ids, n, B.features);
+  gather_rows<V, ROWS>(P.feat, P.row_stride, P.row_bytes, P.num_nodes, B.node_ids, n, B.features);
 }
 
 template <typename V, int ROWS>
@@ -148,7 +167,7 @@ __global__ void __launch_bounds__(kThreads) k_gather_plain(const uint8_t* feat, 
   int64_t n = *num_rows;
   if (n > max_rows) n = max_rows;
   if (n < 0) n = 0;
-  gather_rows<V, ROWS>(feat, row_stride, static_cast<uint32_t>(row_bytes / sizeof(V)), num_nodes, ids, n, out);
+  gather_rows<V, ROWS>(feat, row_stride, row_bytes, num_nodes, ids, n, out);
 }
 
 }  // namespace smfg_dev

@@ -65,11 +65,13 @@ using namespace smfg_dev;
 inline int hip_err(hipError_t e) { return e == hipSuccess ? SMFG_OK : SMFG_ERR_HIP_BASE - static_cast<int>(e); }
 
 
+constexpr int kAnyRow = 7;  // between the vectors of 8 and of 4 bytes: see AnyRow
 inline int vec_bytes(uintptr_t a, uintptr_t b, int64_t row_bytes, int64_t row_stride) {
   const uint64_t x = static_cast<uint64_t>(a) | static_cast<uint64_t>(b) | static_cast<uint64_t>(row_bytes) |
                      static_cast<uint64_t>(row_stride);
   if ((x & 15) == 0) return 16;
   if ((x & 7) == 0) return 8;
+  if (row_bytes >= 16 && row_bytes <= 0x7FFFFFFF) return kAnyRow;
   if ((x & 3) == 0) return 4;
   if ((x & 1) == 0) return 2;
   return 1;
@@ -509,6 +511,7 @@ void launch_gather_rows(const Launch& P, int64_t max_rows, int vb, unsigned G, h
   const unsigned gb = blocks_for(max_rows, ROWS, 0x7FFFFFFFu);
   switch (vb) {
     case 16: k_gather<u32x4, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
+    case kAnyRow: k_gather<AnyRow, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
     case 8: k_gather<u32x2, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
     case 4: k_gather<uint32_t, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
     case 2: k_gather<uint16_t, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
@@ -521,6 +524,7 @@ void launch_gather_plain(const smfg_graph* g, int vb, const int32_t* d_node_ids,
   const unsigned gb = blocks_for(max_rows, ROWS, 0x7FFFFFFFu);
   switch (vb) {
     case 16: k_gather_plain<u32x4, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
+    case kAnyRow: k_gather_plain<AnyRow, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
     case 8: k_gather_plain<u32x2, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
     case 4: k_gather_plain<uint32_t, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
     case 2: k_gather_plain<uint16_t, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;

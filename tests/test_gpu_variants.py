@@ -104,3 +104,22 @@ def test_small_hop_of_a_wide_call_needs_room_for_padded_positions():
     out = smfg.alloc_output(gg.g, 500, fan)
     smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), fan, 3, out)
     assert_same(fetch(out, 2), gg.oracle.sample_mfg(s, fan, 3), 2)
+
+
+@pytest.mark.parametrize("dim", [8, 9, 15, 16, 17, 24, 31, 33, 100, 301, 12_345])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_gather_rows_at_any_address(dim, shift):
+    """2-byte elements from a wider table at an odd column, into an output that starts `shift` elements
+    after an aligned address: every alignment of source and output, rows shorter than, equal to and
+    just beyond whole 16-byte vectors, a partial last block, nothing written outside."""
+    n, rows = 300, 131
+    table = torch.randint(-30_000, 30_000, (n, dim + 5), dtype=torch.int16, device=DEV)
+    feat = table[:, shift:shift + dim]
+    g = smfg.graph_create(torch.zeros(n + 1, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)[:0], feat)
+    ids = torch.randint(0, n, (rows,), dtype=torch.int32, device=DEV)
+    flat = torch.full((shift + (rows + 2) * dim,), 31_000, dtype=torch.int16, device=DEV)
+    out = flat[shift:].view(rows + 2, dim)
+    smfg.gather_rows(g, ids, torch.tensor([rows], device=DEV), rows + 2, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:rows], feat[ids.long()])
+    assert (out[rows:] == 31_000).all() and (flat[:shift] == 31_000).all()
