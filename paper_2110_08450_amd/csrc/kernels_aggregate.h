@@ -20,8 +20,13 @@ constexpr int kAggDepth = 10;
 constexpr int kAggGroups = kThreads / kAggLanes;
 constexpr int kAggRows = kAggGroups * kAggSpan;  // destinations per block of k_mean_aggregate
 
-template <typename T, int V>
-struct alignas(sizeof(T) * V) RowVec {
+// ALIGNED: the vectors of a row lie at multiples of their size.  Else they lie at any element (the target
+// reads vectors from any address) and the last one of a row ends with it: it overlaps the one before,
+// and both lanes compute and write the same means there.  Rows of 100 halfs in 13 vectors of 8 are one
+// column round of the 16 lanes; in vectors of 4, the widest aligned ones, they were two, the second
+// with 9 lanes in use (96 K destinations x 5: 36 -> 28 us; 203 halfs 142 -> 54, 33 floats 32 -> 16).
+template <typename T, int V, bool ALIGNED>
+struct alignas(ALIGNED ? sizeof(T) * V : sizeof(T)) RowVec {
   T v[V];
 };
 
@@ -46,13 +51,14 @@ __device__ __forceinline__ void load_group_offsets(int* off, const int32_t* __re
 
 // Means of the group's rows_here (<= SPAN) destinations; emit(r, c, mean) receives, once per
 // destination r and column round, the V means of columns c .. c + V (zeros for an empty row).
-template <typename T, int V, typename Emit>
+template <typename T, int V, bool ALIGNED, typename Emit>
 __device__ __forceinline__ void walk_group_means(const int* off, int rows_here,
                                                  const int32_t* __restrict__ indices, const T* __restrict__ x,
                                                  uint32_t nsrc, int dim, int lane, Emit emit) {
-  typedef RowVec<T, V> Vec;
+  typedef RowVec<T, V, ALIGNED> Vec;
   const int e_begin = off[0];
-  for (int c = lane * V; c < dim; c += kAggLanes * V) {
+  for (int c0 = lane * V; c0 < dim; c0 += kAggLanes * V) {
+    const int c = ALIGNED || c0 + V <= dim ? c0 : dim - V;
     float acc[V];
 #pragma unroll
     for (int t = 0; t < V; ++t) acc[t] = 0.f;
@@ -108,7 +114,7 @@ __device__ __forceinline__ void walk_group_means(const int* off, int rows_here,
   }
 }
 
-template <typename T, int V>
+template <typename T, int V, bool ALIGNED>
 __global__ void __launch_bounds__(kThreads) k_mean_aggregate(const int32_t* __restrict__ indptr,
                                                              const int32_t* __restrict__ indices,
                                                              int64_t max_edges,
@@ -125,7 +131,7 @@ __global__ void __launch_bounds__(kThreads) k_mean_aggregate(const int32_t* __re
   __syncthreads();
   if (i0 >= n) return;
   const int rows_here = static_cast<int>(n - i0 < kAggSpan ? n - i0 : kAggSpan);
-  walk_group_means<T, V>(s_off[grp], rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
+  walk_group_means<T, V, ALIGNED>(s_off[grp], rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
                          [&](int r, int c, const float* mean) {
                            float* o = out + (i0 + r) * dim + c;
 #pragma unroll
@@ -210,7 +216,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_sage_layer(const int32_t* __res
   if (i0 < n) {
     const int rows_here = static_cast<int>(n - i0 < kLayerSpan ? n - i0 : kLayerSpan);
     _Float16* a_grp = a_lds + (grp * kLayerSpan) * lda + dim;
-    walk_group_means<_Float16, 8>(s_off[grp], rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
+    walk_group_means<_Float16, 8, true>(s_off[grp], rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
                                   [&](int r, int c, const float* mean) {
                                     half8_t h;
 #pragma unroll

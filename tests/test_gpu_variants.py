@@ -123,3 +123,23 @@ def test_gather_rows_at_any_address(dim, shift):
     torch.cuda.synchronize()
     assert torch.equal(out[:rows], feat[ids.long()])
     assert (out[rows:] == 31_000).all() and (flat[:shift] == 31_000).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("dim,shift", [(3, 1), (4, 1), (7, 0), (8, 1), (9, 0), (128, 1), (129, 0), (131, 3)])
+def test_mean_aggregate_at_any_address(dim, shift, dtype):
+    """Rows of any width from any element on; columns that two lanes compute; nothing written outside.
+    Small whole numbers and row lengths of 1, 2 and 4: every sum and quotient is exact."""
+    gen = torch.Generator().manual_seed(dim)
+    src, lens = 90, torch.tensor([0, 1, 2, 4] * 16 + [4])
+    flat = torch.randint(-50, 50, (shift + src * dim,), generator=gen).to(dtype).to(DEV)
+    x = flat[shift:].view(src, dim)
+    indptr = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(lens, 0)])
+    indices = torch.randint(0, src, (int(indptr[-1]),), generator=gen)
+    out = torch.full((len(lens) + 1, dim), 7.5, dtype=torch.float32, device=DEV)
+    smfg.mean_aggregate(indptr.to(torch.int32).to(DEV), indices.to(torch.int32).to(DEV), torch.tensor([len(lens)], device=DEV),
+                        len(lens), x, out)
+    torch.cuda.synchronize()
+    h = x.float().cpu()
+    want = torch.stack([h[indices[a:b]].sum(0) / max(1, b - a) for a, b in zip(indptr[:-1].tolist(), indptr[1:].tolist())])
+    assert torch.equal(out[:-1].cpu(), want) and (out[-1] == 7.5).all()
