@@ -367,30 +367,55 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows(const Launch P) {
   }
 }
 
-__global__ void __launch_bounds__(kThreads) k_scan_tiles(const Launch P) {
-  __shared__ unsigned long long lds[kThreads / 64];
-  const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const int n = static_cast<int>(B.counts[P.h]);
-  const int tiles = (n + kTileRows - 1) / kTileRows;
+// Exclusive scan of sums[0 .. tiles) in place by one block of kTileScanThreads; returns the total.  A
+// thread takes kTileScanPer consecutive tiles, so that 5.4 K tiles are one turn (16 us in turns of 256, 7 us
+// now).
+constexpr int kTileScanThreads = 1024;
+constexpr int kTileScanPer = 8;
+__device__ __forceinline__ unsigned long long scan_tile_sums(uint64_t* sums, uint32_t tiles) {
+  __shared__ unsigned long long lds[kTileScanThreads / 64];
   unsigned long long carry = 0;
-  for (int t0 = 0; t0 < tiles; t0 += kThreads) {
-    const int t = t0 + threadIdx.x;
-    const unsigned long long x = t < tiles ? B.tile_sums[t] : 0ull;
-    unsigned long long total;
-    const unsigned long long ex = block_exscan(x, lds, total);
-    if (t < tiles) B.tile_sums[t] = carry + ex;
+  for (uint32_t t0 = 0; t0 < tiles; t0 += kTileScanThreads * kTileScanPer) {
+    const uint32_t t = t0 + threadIdx.x * kTileScanPer;
+    unsigned long long x[kTileScanPer], mine = 0, total;
+#pragma unroll
+    for (int u = 0; u < kTileScanPer; ++u) {
+      x[u] = t + u < tiles ? sums[t + u] : 0ull;
+      mine += x[u];
+    }
+    unsigned long long pre = carry + block_exscan<kTileScanThreads>(mine, lds, total);
+#pragma unroll
+    for (int u = 0; u < kTileScanPer; ++u) {
+      if (t + u < tiles) sums[t + u] = pre;
+      pre += x[u];
+    }
     carry += total;
   }
-  if (threadIdx.x == 0) {
-    const int64_t edges = static_cast<int64_t>(carry >> 32);
-    const int64_t nodes = static_cast<int64_t>(n) + static_cast<int64_t>(carry & 0xFFFFFFFFull);
+  return carry;
+}
+
+// E_h, n_{h+1} and the end of the block's indptr from the totals of a hop; false (and the status) if
+// they do not fit.
+__device__ __forceinline__ bool close_hop(const Launch& P, const BatchCtx& B, int n, unsigned long long totals, bool publish) {
+  const int64_t edges = static_cast<int64_t>(totals >> 32);
+  const int64_t nodes = static_cast<int64_t>(n) + static_cast<int64_t>(totals & 0xFFFFFFFFull);
+  const bool nodes_fit = nodes <= B.node_capacity, edges_fit = edges <= B.edge_capacity;
+  if (publish) {
     B.counts[P.L + 1 + P.h] = edges;
     B.counts[P.h + 1] = nodes;
     B.blk_indptr[n] = static_cast<int32_t>(edges);
-    if (nodes > B.node_capacity) set_status(B, P.L, SMFG_ST_NODE_CAPACITY);
-    else if (edges > B.edge_capacity) set_status(B, P.L, SMFG_ST_EDGE_CAPACITY);
+    if (!nodes_fit) set_status(B, P.L, SMFG_ST_NODE_CAPACITY);
+    else if (!edges_fit) set_status(B, P.L, SMFG_ST_EDGE_CAPACITY);
   }
+  return nodes_fit && edges_fit;
+}
+
+__global__ void __launch_bounds__(kTileScanThreads) k_scan_tiles(const Launch P) {
+  const BatchCtx& B = P.b[batch_of_block(P)];
+  if (block_has_status(B, P.L)) return;
+  const int n = static_cast<int>(B.counts[P.h]);
+  const unsigned long long totals = scan_tile_sums(B.tile_sums, static_cast<uint32_t>((n + kTileRows - 1) / kTileRows));
+  if (threadIdx.x == 0) close_hop(P, B, n, totals, true);
 }
 
 // One block per tile of kTileRows destinations; samples are walked flat like in k_flag_rows.

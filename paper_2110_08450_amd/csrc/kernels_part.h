@@ -644,8 +644,15 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
 
 // assemble for those entries: block indptr; block indices = final local ids; node ids of the
 // first appearances.  A pointer always names a first appearance, so one lookup of that
-// destination's record settles it.
+// destination's record settles it.  SCAN (hops of at most kAssembleTiles tiles, one per block): every block
+// scans the tile totals for itself, a few kilobytes from the L2, instead of k_scan_tiles before it -
+// 3 to 5 us of a launch that does nothing else, for less than 1 us here.
+constexpr int kAssembleTiles = 1024;
+template <bool SCAN>
 __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
+  constexpr int kPer = kAssembleTiles / kThreads;
+  __shared__ uint32_t tile_new[SCAN ? kAssembleTiles : 1];  // new nodes before each tile
+  __shared__ unsigned long long own_lds, scan_lds[kThreads / 64];
   __shared__ int k_lds[kTileRows];
   __shared__ unsigned int mask_lds[kTileRows];
   __shared__ unsigned int off_lds[kTileRows];   // global edge offset of the destination
@@ -657,11 +664,32 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
   const DivD div(d);
   const int tiles = (n + kTileRows - 1) / kTileRows;
   const int nblocks = blocks_per_batch(P);
+  if (SCAN) {
+    if (block_in_batch(P) >= (tiles > 0 ? tiles : 1)) return;  // the first block also closes an empty hop
+    unsigned long long x[kPer], mine = 0, total;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int t = threadIdx.x * kPer + u;
+      x[u] = t < tiles ? B.tile_sums[t] : 0ull;
+      mine += x[u];
+    }
+    unsigned long long pre = block_exscan(mine, scan_lds, total);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int t = threadIdx.x * kPer + u;
+      tile_new[t] = static_cast<uint32_t>(pre);
+      if (t == block_in_batch(P)) own_lds = pre;
+      pre += x[u];
+    }
+    if (!close_hop(P, B, n, total, block_in_batch(P) == 0 && threadIdx.x == 0)) return;
+    __syncthreads();
+  }
+  const auto tile_before = [&](uint32_t t) { return SCAN ? tile_new[t] : static_cast<uint32_t>(B.tile_sums[t] & 0xFFFFFFFFull); };
   for (int tile = block_in_batch(P); tile < tiles; tile += nblocks) {
     const int i0 = tile * kTileRows;
     const int nrows = n - i0 < kTileRows ? n - i0 : kTileRows;
     const int tr = threadIdx.x;
-    const unsigned long long tpre = B.tile_sums[tile];
+    const unsigned long long tpre = SCAN ? own_lds : B.tile_sums[tile];
     __syncthreads();
     if (tr < nrows) {
       const uint32_t off = static_cast<uint32_t>(tpre >> 32) + static_cast<uint32_t>(B.rowoff[i0 + tr]);
@@ -706,7 +734,7 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         mn[u] = B.rowmn[qi[u]];
-        ts[u] = static_cast<uint32_t>(B.tile_sums[qi[u] / kTileRows] & 0xFFFFFFFFull);
+        ts[u] = tile_before(qi[u] / kTileRows);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {

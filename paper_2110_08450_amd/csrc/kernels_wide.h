@@ -52,26 +52,16 @@ __global__ void __launch_bounds__(kThreads) k_count_rows(const Launch P) {
 }
 
 // Exclusive scan of the per-tile sample counts; E_h and its capacity checks.
-__global__ void __launch_bounds__(kThreads) k_scan_count_tiles(const Launch P) {
-  __shared__ unsigned long long lds[kThreads / 64];
+__global__ void __launch_bounds__(kTileScanThreads) k_scan_count_tiles(const Launch P) {
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const int n = static_cast<int>(B.counts[P.h]);
-  const int tiles = (n + kTileRows - 1) / kTileRows;
-  unsigned long long carry = 0;
-  for (int t0 = 0; t0 < tiles; t0 += kThreads) {
-    const int t = t0 + threadIdx.x;
-    const unsigned long long x = t < tiles ? B.tile_sums[t] : 0ull;
-    unsigned long long total;
-    const unsigned long long ex = block_exscan(x, lds, total);
-    if (t < tiles) B.tile_sums[t] = carry + ex;
-    carry += total;
-  }
+  const unsigned long long edges = scan_tile_sums(B.tile_sums, static_cast<uint32_t>((n + kTileRows - 1) / kTileRows));
   if (threadIdx.x == 0) {
-    const bool fits = carry <= static_cast<unsigned long long>(B.edge_capacity) &&
-                      carry <= static_cast<unsigned long long>(B.lostto_entries);
-    B.counts[P.L + 1 + P.h] = static_cast<int64_t>(carry);
-    if (fits) B.blk_indptr[n] = static_cast<int32_t>(carry);
+    const bool fits = edges <= static_cast<unsigned long long>(B.edge_capacity) &&
+                      edges <= static_cast<unsigned long long>(B.lostto_entries);
+    B.counts[P.L + 1 + P.h] = static_cast<int64_t>(edges);
+    if (fits) B.blk_indptr[n] = static_cast<int32_t>(edges);
     else set_status(B, P.L, SMFG_ST_EDGE_CAPACITY);
   }
 }
@@ -463,24 +453,14 @@ __global__ void __launch_bounds__(kThreads) k_flag_flat(const Launch P) {
 }
 
 // Exclusive scan of the per-tile counts of new nodes; n_{h+1} and its capacity check.
-__global__ void __launch_bounds__(kThreads) k_scan_flat_tiles(const Launch P) {
-  __shared__ unsigned long long lds[kThreads / 64];
+__global__ void __launch_bounds__(kTileScanThreads) k_scan_flat_tiles(const Launch P) {
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const int n = static_cast<int>(B.counts[P.h]);
   const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-  const uint32_t tiles = (E + kWideTile - 1) / kWideTile;
-  unsigned long long carry = 0;
-  for (uint32_t t0 = 0; t0 < tiles; t0 += kThreads) {
-    const uint32_t t = t0 + threadIdx.x;
-    const unsigned long long x = t < tiles ? B.stile_sums[t] : 0ull;
-    unsigned long long total;
-    const unsigned long long ex = block_exscan(x, lds, total);
-    if (t < tiles) B.stile_sums[t] = carry + ex;
-    carry += total;
-  }
+  const unsigned long long fresh = scan_tile_sums(B.stile_sums, (E + kWideTile - 1) / kWideTile);
   if (threadIdx.x == 0) {
-    const int64_t nodes = static_cast<int64_t>(n) + static_cast<int64_t>(carry);
+    const int64_t nodes = static_cast<int64_t>(n) + static_cast<int64_t>(fresh);
     B.counts[P.h + 1] = nodes;
     if (nodes > B.node_capacity) set_status(B, P.L, SMFG_ST_NODE_CAPACITY);
   }

@@ -923,13 +923,15 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
         StageTimer t_(SMFG_STAGE_FLAG, st);
         k_flag_rows_part<<<tile_blocks * G, kThreads, 0, st>>>(P);
       }
-      {
+      const bool scans = (rows + kTileRows - 1) / kTileRows <= kAssembleTiles;  // then a block per tile, too
+      if (!scans) {
         StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
-        k_scan_tiles<<<G, kThreads, 0, st>>>(P);
+        k_scan_tiles<<<G, kTileScanThreads, 0, st>>>(P);
       }
       {
         StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
-        k_assemble_part<<<tile_blocks * G, kThreads, 0, st>>>(P);
+        if (scans) k_assemble_part<true><<<tile_blocks * G, kThreads, 0, st>>>(P);
+        else k_assemble_part<false><<<tile_blocks * G, kThreads, 0, st>>>(P);
       }
       continue;
     }
@@ -942,14 +944,15 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
       {
         StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
         k_count_rows<<<tile_blocks * G, kThreads, 0, st>>>(P);
-        k_scan_count_tiles<<<G, kThreads, 0, st>>>(P);
+        k_scan_count_tiles<<<G, kTileScanThreads, 0, st>>>(P);
       }
       if (part) {
         P.flat = 1;
         P.lgB = flat_plan.lgB;
         P.lg2 = flat_plan.lg2;
         int64_t stream_bound = rows + samples;  // known nodes + samples of this hop, at most
-        const unsigned stream_blocks = blocks_for(stream_bound, kFlatBlock, kCap);
+        // the bound is loose when whole neighbourhoods are taken; blocks of 8192 elements each stride over more
+        const unsigned stream_blocks = blocks_for(stream_bound, kFlatBlock, 1024);
         const unsigned buckets = 1u << P.lgB;
         {
           StageTimer t_(SMFG_STAGE_SAMPLE, st);
@@ -972,7 +975,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
         }
         {
           StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
-          k_scan_flat_tiles<<<G, kThreads, 0, st>>>(P);
+          k_scan_flat_tiles<<<G, kTileScanThreads, 0, st>>>(P);
         }
         {
           StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
@@ -990,7 +993,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
       }
       {
         StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
-        k_scan_flat_tiles<<<G, kThreads, 0, st>>>(P);
+        k_scan_flat_tiles<<<G, kTileScanThreads, 0, st>>>(P);
       }
       {
         StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
@@ -1009,7 +1012,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
     }
     {
       StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
-      k_scan_tiles<<<G, kThreads, 0, st>>>(P);
+      k_scan_tiles<<<G, kTileScanThreads, 0, st>>>(P);
     }
     {
       StageTimer t_(SMFG_STAGE_ASSEMBLE, st);

@@ -143,3 +143,12 @@ def test_mean_aggregate_at_any_address(dim, shift, dtype):
     h = x.float().cpu()
     want = torch.stack([h[indices[a:b]].sum(0) / max(1, b - a) for a, b in zip(indptr[:-1].tolist(), indptr[1:].tolist())])
     assert torch.equal(out[:-1].cpu(), want) and (out[-1] == 7.5).all()
+
+
+@pytest.mark.parametrize("seeds", [262_144, 262_145])
+def test_assemble_with_and_without_its_own_scan(seeds):
+    """1024 tiles of 256 destinations, the most that every block scans for itself, and one more."""
+    gg = random_graph(300_000, 4, 11)
+    s = np.random.default_rng(seeds).permutation(300_000)[:seeds].astype(np.int32)
+    res, _ = sample(gg, s, (2,), 17)
+    assert_same(res, gg.oracle.sample_mfg(s, (2,), 17), 1)
