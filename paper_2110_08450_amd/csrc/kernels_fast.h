@@ -368,9 +368,9 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows(const Launch P) {
 }
 
 // Exclusive scan of sums[0 .. tiles) in place by one block of kTileScanThreads; returns the total.  A
-// thread takes kTileScanPer consecutive tiles, so that 5.4 K tiles are one turn (16 us in turns of 256, 7 us
-// now).
-constexpr int kTileScanThreads = 1024;
+// thread takes kTileScanPer consecutive tiles, so that 5.4 K tiles are three turns; the 21
+// turns of a tile per thread took 16 us.
+constexpr int kTileScanThreads = kThreads;
 constexpr int kTileScanPer = 8;
 __device__ __forceinline__ unsigned long long scan_tile_sums(uint64_t* sums, uint32_t tiles) {
   __shared__ unsigned long long lds[kTileScanThreads / 64];

@@ -73,13 +73,21 @@ __global__ void __launch_bounds__(kTileScanThreads) k_scan_count_tiles(const Lau
 // s = 64 r + l: first the rows that are one plain round (whole row taken, at most 64 samples; several
 // in flight), then the others one by one - a row taken whole kWideCopyRounds rounds at a time, a
 // row with drawn positions after Floyd's rule has settled them in the wave's part of the LDS
-// (two arrays of the fanout rounded up to 64 words per wave, sized by the launch; none for
-// SMFG_FANOUT_ALL, where nothing is drawn).  INSERT: the sample goes into
+// (per wave two arrays of the fanout rounded up to 64 words and a hash table of at least twice that, sized
+// by the launch; none for SMFG_FANOUT_ALL, where nothing is drawn).  INSERT: the sample goes into
 // the dedup table at once (table strategy); else only its node id is stored (partition strategy).
 constexpr int kWideRows = 16;
 constexpr int kWideCopyRounds = 8;
 constexpr uint32_t wide_lds_words(int d) { return d < 0 ? 0u : (static_cast<uint32_t>(d) + 63u) & ~63u; }
-constexpr size_t wide_lds_bytes(int d) { return sizeof(uint32_t) * 2 * (kThreads / 64) * wide_lds_words(d); }
+constexpr uint32_t wide_table_words(int d) {
+  uint32_t w = d < 0 ? 0u : 128u;
+  while (w < 2u * wide_lds_words(d)) w *= 2u;
+  return w;
+}
+constexpr size_t wide_lds_bytes(int d) {
+  return sizeof(uint32_t) * (kThreads / 64) * (2 * wide_lds_words(d) + wide_table_words(d));
+}
+static_assert(wide_lds_bytes(SMFG_MAX_WIDE_FANOUT) <= 65536, "LDS of a block");
 
 // What happens to a drawn sample: recorded (partition strategy), or also inserted into the dedup
 // table right away (table strategy; see k_sample_insert for the three cases).
@@ -108,13 +116,19 @@ __device__ __forceinline__ void wide_emit(const Launch& P, const BatchCtx& B, ui
 // q = t_s - (deg - k) can be) and slot q took its j, i.e. was itself refused.  (a) needs no other
 // slot's outcome; (b) refers to one earlier slot.  So every slot is refused outright, accepted
 // outright, or "as slot q": chains of such references are shortcut by pointer jumping, at most
-// log2 k + 1 passes.  `draws` keeps the t_s, `picks` the states and in the end the positions p_s
-// (both LDS, k entries, private to the wave).
+// log2 k + 1 passes.  (a) is settled by a hash table that keeps the first slot of every value; a scan over
+// all earlier draws, four per LDS read, kept the wave issuing k^2 / 256 rounds of compares (k_sample_wide
+// of a launch set of four batches with fanouts (100, 100) 136 us against 88 us, a call of 1024
+// destinations x 1000 185 against 84 us, (40, 40) 203 against 200 us).  `draws` keeps the t_s, `picks` the
+// states and in the end the positions p_s, `table` the first slots (all LDS, private to the wave).
 __device__ __forceinline__ void floyd_positions(const Launch& P, const BatchCtx& B, uint32_t v, uint32_t deg,
-                                                uint32_t k, uint32_t* picks, uint32_t* draws) {
+                                                uint32_t k, uint32_t* picks, uint32_t* draws, uint32_t* table,
+                                                uint32_t table_mask) {
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
   constexpr uint32_t kKnown = 0x80000000u, kRefused = 0x40000000u, kRefMask = 0x3FFFFFFFu;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t j0 = deg - k;
+  for (uint32_t q = lane; q <= table_mask; q += 64u) table[q] = kNone;
   // a lane draws for four slots at a time; the arrays are rounded up to a multiple of 64 words, and what
   // lies at or beyond slot k is not looked at
   for (uint32_t s = 4u * lane; s < k; s += 4u * 64u) {
@@ -129,23 +143,28 @@ __device__ __forceinline__ void floyd_positions(const Launch& P, const BatchCtx&
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  const uint4* draws4 = reinterpret_cast<const uint4*>(draws);
-  for (uint32_t s0 = 0; s0 < k; s0 += 64u) {
-    const uint32_t s = s0 + lane;
-    const bool active = s < k;
-    const uint32_t t = active ? draws[s] : 0u;
-    bool dup = false;
-    const uint32_t upto = s0 + 64u < k ? s0 + 64u : k;
-    // every lane reads the same four draws at a time (a broadcast read); entries at or beyond s
-    // are masked out, so the read may run past k inside the array
-#pragma unroll 4
-    for (uint32_t q = 0; q + 1u < upto; q += 4u) {
-      const uint4 x = draws4[q >> 2];
-      dup = dup | ((q < s) & (x.x == t)) | ((q + 1u < s) & (x.y == t)) | ((q + 2u < s) & (x.z == t)) |
-            ((q + 3u < s) & (x.w == t));
+  for (uint32_t s = lane; s < k; s += 64u) {
+    const uint32_t t = draws[s];
+    uint32_t at = (t * kPartHash) >> 16;
+    for (;;) {  // ends: more words than slots, and a word once taken keeps its value
+      at &= table_mask;
+      const uint32_t old = atomicCAS(&table[at], kNone, s);
+      if (old == kNone) break;
+      if (draws[old] == t) {
+        atomicMin(&table[at], s);
+        break;
+      }
+      ++at;
     }
+    picks[s] = at;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t s = lane; s < k; s += 64u) {
+    const uint32_t t = draws[s];
+    const bool dup = table[picks[s]] < s;
     const bool refers = !dup && t >= j0 && t - j0 < s;
-    if (active) picks[s] = dup ? (kKnown | kRefused) : (refers ? t - j0 : kKnown);
+    picks[s] = dup ? (kKnown | kRefused) : (refers ? t - j0 : kKnown);
   }
   for (;;) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -179,8 +198,10 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
   const int n = static_cast<int>(B.counts[P.h]);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  uint32_t* draws = wide_lds + 2 * wave * wide_lds_words(P.d);
-  uint32_t* picks = draws + wide_lds_words(P.d);
+  const uint32_t words = wide_lds_words(P.d), table_words = wide_table_words(P.d);
+  uint32_t* draws = wide_lds + wave * (2 * words + table_words);
+  uint32_t* picks = draws + words;
+  uint32_t* table = picks + words;
   const int waves_total = blocks_per_batch(P) * (kThreads / 64);
   int per = (n + waves_total - 1) / waves_total;  // destinations per wave and turn
   per = per < 1 ? 1 : (per > kWideRows ? kWideRows : per);
@@ -240,7 +261,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
         }
         continue;
       }
-      floyd_positions(P, B, v, deg, k, picks, draws);
+      floyd_positions(P, B, v, deg, k, picks, draws, table, table_words - 1u);
       for (uint32_t s0 = 0; s0 < k; s0 += 128) {  // two rounds at a time
         const uint32_t sa = s0 + static_cast<uint32_t>(lane), sb = sa + 64u;
         uint32_t ga = 0, gb = 0;

@@ -152,3 +152,19 @@ def test_assemble_with_and_without_its_own_scan(seeds):
     s = np.random.default_rng(seeds).permutation(300_000)[:seeds].astype(np.int32)
     res, _ = sample(gg, s, (2,), 17)
     assert_same(res, gg.oracle.sample_mfg(s, (2,), 17), 1)
+
+
+@pytest.mark.parametrize("fanout", [33, 64, 65, 128, 129, 1000, 1024])
+def test_wide_draw_with_its_hash_table(fanout):
+    """Both sides of the sizes at which a row's table of drawn values grows, degrees just above the
+    fanout, where many draws repeat or refer to an earlier slot, and far above it."""
+    rng = np.random.default_rng(fanout)
+    n = 6_000
+    deg = np.concatenate([rng.integers(fanout - 3, fanout + 40, size=40), rng.integers(0, 5 * fanout, size=40),
+                          np.zeros(n - 80, dtype=np.int64)])
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(deg, out=indptr[1:])
+    gg = GpuGraph(indptr, rng.integers(0, n, size=int(indptr[-1])).astype(np.int32), None)
+    s = rng.permutation(80).astype(np.int32)
+    res, _ = sample(gg, s, (fanout,), 31)
+    assert_same(res, gg.oracle.sample_mfg(s, (fanout,), 31), 1)
