@@ -62,7 +62,7 @@ struct HopShape {
 // scatter + split 414 -> 345 us; four batches of 2.4 M are 10 us better off with 128).
 constexpr int kPartSplitLgB = 7;
 constexpr int part_split_lg(int batches) { return batches <= 2 ? kPartSplitLgB + 1 : kPartSplitLgB; }
-__host__ __device__ inline void part_levels(int lg, int batches, int& lgB, int& lg2) {
+__host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2, int batches = SMFG_MAX_BATCHES) {
   if (lg <= kPartMaxLgB) {
     lgB = lg;
     lg2 = 0;
@@ -78,7 +78,7 @@ __device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B
     const long long records = B.counts[P.h] + B.counts[P.L + 1 + P.h];
     int lg = 0;
     while (lg < P.lgB + P.lg2 && (records >> lg) > kPartBucketRecords) ++lg;
-    part_levels(lg, P.G, s.lgB, s.lg2);
+    part_levels(lg, s.lgB, s.lg2, P.G);
   }
   return s;
 }

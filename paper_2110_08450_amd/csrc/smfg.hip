@@ -236,7 +236,7 @@ HopPlan plan_hop(int64_t max_rows, int d, int batches) {
   const int64_t records = max_rows * (1 + d);
   int lg = 0;
   while (lg < kPartMaxLgB + kPartMaxLg2 && (records >> lg) > kPartBucketRecords) ++lg;
-  part_levels(lg, batches, hp.lgB, hp.lg2);
+  part_levels(lg, hp.lgB, hp.lg2, batches);
   int64_t cap = (max_rows + 511) / 512;
   const int64_t least = batches > 8 ? 128 : 512;  // fewer, longer row blocks when many batches fill the chip anyway
   cap = cap < least ? least : (cap > 4096 ? 4096 : cap);
