@@ -425,9 +425,10 @@ int static_scratch_of(int device, void** out) {
   return SMFG_OK;
 }
 
-// A hop below kSmallRecords records in every batch takes k_small_*, whatever the call's other hops take: hop
+// A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: hop
 // 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's seven
 // launches, 21 us so.
+constexpr int kSmallHopBatches = 6;  // the most batches of a call with larger hops that do so
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 bool call_is_small(int32_t L, const int32_t* fanouts, const int64_t* max_rows) {
   for (int h = 0; h < L; ++h)
@@ -864,6 +865,9 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   int small_hops = 0;
   while (small_hops < L && hop_is_small(fanouts[small_hops], max_n[small_hops])) ++small_hops;
   if (table && small_hops < L) small_hops = 0;
+  // launch sets of many larger batches run beside the gather of another set (8633 instead of 9.5 K batches/s
+  // on the papers100M-shaped workload, sets of 10): there a block of 16 waves waits long for a free unit
+  if (small_hops < L && num_batches > kSmallHopBatches) small_hops = 0;
   for (int b = 0; b < num_batches; ++b) {
     if (ws[b]->forced) small_hops = 0;
     // its samples sit at padded positions, which a call with wide fanouts need not have room for
