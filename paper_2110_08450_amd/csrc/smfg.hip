@@ -430,10 +430,26 @@ int static_scratch_of(int device, void** out) {
 // launches, 21 us so.
 constexpr int kSmallHopBatches = 6;  // the most batches of a call with larger hops that do so
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
-bool call_is_small(int32_t L, const int32_t* fanouts, const int64_t* max_rows) {
-  for (int h = 0; h < L; ++h)
-    if (!hop_is_small(fanouts[h], max_rows[h])) return false;
-  return true;
+// How many of a call's hops, counted from the first one, take the small path; rows[b][h] bounds the
+// destinations of hop h of batch b.  Each batch is held against its own workspace: its samples sit at
+// padded positions, which a workspace planned for a smaller batch, or for a call with wide fanouts, need
+// not have room for.  With device tables it is all hops or none, whatever made a hop drop out: the small
+// path leaves the table uncleared and the nodes of its hops out of it.
+int small_hops_of(const smfg_workspace* const* ws, const int64_t (*rows)[SMFG_MAX_LAYERS + 1], const int32_t* fanouts,
+                  int32_t L, int32_t num_batches) {
+  int hops = L;
+  bool table = false;
+  for (int b = 0; b < num_batches; ++b) {
+    if (ws[b]->forced) return 0;
+    table = table || !ws[b]->part;
+    int h = 0;
+    while (h < hops && hop_is_small(fanouts[h], rows[b][h]) && rows[b][h] * fanouts[h] <= ws[b]->slot_entries) ++h;
+    hops = h;
+  }
+  if (hops == L) return L;
+  // launch sets of many larger batches run beside the gather of another set (8633 instead of 9.5 K batches/s
+  // on the papers100M-shaped workload, sets of 10): there a block of 16 waves waits long for a free unit
+  return table || num_batches > kSmallHopBatches ? 0 : hops;
 }
 SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows) {
   SmallLaunch S;
@@ -703,9 +719,12 @@ int smfg_workspace_strategy(const smfg_workspace_t* ws) {
   return ws ? (ws->part ? SMFG_STRATEGY_PARTITION : SMFG_STRATEGY_TABLE) : -1;
 }
 
-int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const int32_t* const* d_seeds,
-                         const int32_t* num_seeds, const int32_t* fanouts, int32_t L, const uint64_t* rng_keys,
-                         const smfg_output_t* outs, int32_t num_batches, void* hip_stream) {
+// smfg_sample_mfg_many; stale_notes: the workspaces' memory was used for something else before, so the
+// displacement notes of the table strategy, if the call takes it, have to be cleared first (of the other
+// strategies' scratch nothing is read before it is written).
+static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const int32_t* const* d_seeds,
+                       const int32_t* num_seeds, const int32_t* fanouts, int32_t L, const uint64_t* rng_keys,
+                       const smfg_output_t* outs, int32_t num_batches, void* hip_stream, bool stale_notes) {
   if (!g || !ws || !d_seeds || !num_seeds || !rng_keys || !outs) return SMFG_ERR_NULL_PTR;
   bool wide = false;
   int rc = check_fanouts(L, fanouts, &wide);
@@ -725,7 +744,8 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   P.L = L;
   P.G = num_batches;
 
-  int64_t max_n[SMFG_MAX_LAYERS + 1];  // per hop, the largest destination count over the batches
+  int64_t bound[SMFG_MAX_BATCHES][SMFG_MAX_LAYERS + 1];  // per batch and hop, the most destinations
+  int64_t max_n[SMFG_MAX_LAYERS + 1];                    // per hop, the most over the batches
   for (int h = 0; h <= L; ++h) max_n[h] = 0;
   uint32_t max_table_log2 = 0;
   int32_t max_seeds = 0;
@@ -811,6 +831,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
     int64_t n = num_seeds[b] < g->num_nodes ? num_seeds[b] : g->num_nodes;
     for (int h = 0; h <= L; ++h) {
       if (n > ncap) n = ncap;
+      bound[b][h] = n;
       if (n > max_n[h]) max_n[h] = n;
       if (h < L) {
         n = fanouts[h] < 0 ? g->num_nodes : n + n * fanouts[h];
@@ -832,16 +853,16 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   if (part && wide) {
     // exact offsets: every workspace must have been planned for wide fanouts; the shape of a hop
     // is settled on the device, the host only bounds it by the roomiest workspace
-    int64_t bound = 1;
+    int64_t records = 1;
     for (int b = 0; b < num_batches; ++b) {
       if (!ws[b]->flat) return SMFG_ERR_CAPACITY;
-      if (ws[b]->rec_entries > bound) bound = ws[b]->rec_entries;
+      if (ws[b]->rec_entries > records) records = ws[b]->rec_entries;
     }
     int lg = 0;
-    while (lg < kPartMaxLgB + kPartMaxLg2 && (bound >> lg) > kPartBucketRecords) ++lg;
+    while (lg < kPartMaxLgB + kPartMaxLg2 && (records >> lg) > kPartBucketRecords) ++lg;
     flat_plan.lgB = lg < kPartMaxLgB ? lg : kPartMaxLgB;
     flat_plan.lg2 = lg - flat_plan.lgB;
-    flat_plan.row_blocks = (bound + kFlatBlock - 1) / kFlatBlock;
+    flat_plan.row_blocks = (records + kFlatBlock - 1) / kFlatBlock;
   } else if (part) {
     for (int h = 0; h < L; ++h) {
       plan[h] = plan_hop(max_n[h], fanouts[h], num_batches);
@@ -860,20 +881,7 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   const unsigned G = static_cast<unsigned>(num_batches);
   constexpr unsigned kCap = 4096;  // blocks per batch of the grid-stride kernels
 
-  // the hops that take the small path: the first ones of a call without a device table; with one (which
-  // every hop has to enter) all hops or none
-  int small_hops = 0;
-  while (small_hops < L && hop_is_small(fanouts[small_hops], max_n[small_hops])) ++small_hops;
-  if (table && small_hops < L) small_hops = 0;
-  // launch sets of many larger batches run beside the gather of another set (8633 instead of 9.5 K batches/s
-  // on the papers100M-shaped workload, sets of 10): there a block of 16 waves waits long for a free unit
-  if (small_hops < L && num_batches > kSmallHopBatches) small_hops = 0;
-  for (int b = 0; b < num_batches; ++b) {
-    if (ws[b]->forced) small_hops = 0;
-    // its samples sit at padded positions, which a call with wide fanouts need not have room for
-    for (int h = 0; h < small_hops; ++h)
-      if (max_n[h] * fanouts[h] > ws[b]->slot_entries) small_hops = h;
-  }
+  const int small_hops = small_hops_of(ws, bound, fanouts, L, num_batches);
   SmallLaunch S;
   if (small_hops > 0) {
     S = small_launch(P, outs, fanouts, max_n);
@@ -881,6 +889,8 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
     StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_begin<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P);
   } else {
+    for (int b = 0; stale_notes && b < num_batches; ++b)
+      k_fill_u32<<<blocks_for(ws[b]->slot_entries, kThreads * 4, 1024), kThreads, 0, st>>>(ws[b]->lostto, ws[b]->slot_entries, 0u);
     { StageTimer t_(SMFG_STAGE_CLEAR, st);
     k_clear<<<blocks_for(int64_t(1) << max_table_log2, kThreads * 8, 2048) * G, kThreads, 0, st>>>(P); }
     { StageTimer t_(SMFG_STAGE_SEEDS, st);
@@ -1030,6 +1040,12 @@ int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, con
   return hip_err(e);
 }
 
+int smfg_sample_mfg_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const int32_t* const* d_seeds,
+                         const int32_t* num_seeds, const int32_t* fanouts, int32_t L, const uint64_t* rng_keys,
+                         const smfg_output_t* outs, int32_t num_batches, void* hip_stream) {
+  return sample_many(g, ws, d_seeds, num_seeds, fanouts, L, rng_keys, outs, num_batches, hip_stream, false);
+}
+
 int smfg_sample_mfg(const smfg_graph_t* g, smfg_workspace_t* ws, const int32_t* d_seeds, int32_t num_seeds,
                     const int32_t* fanouts, int32_t L, uint64_t rng_key, const smfg_output_t* out,
                     void* hip_stream) {
@@ -1052,23 +1068,11 @@ int smfg_sample_mfg_static(const smfg_graph_t* g, const int32_t* d_seeds, int32_
   if (cur != g->device) (void)hipSetDevice(g->device);
   void* base = nullptr;
   rc = static_scratch_of(g->device, &base);
-  if (rc == SMFG_OK) {
-    bind_workspace(&ws, base);
-    // the array keeps what the last call left: the displacement notes of the table strategy must
-    // start out clear (nothing of the other strategies' scratch is read before it is written)
-    int64_t rows[SMFG_MAX_LAYERS];
-    const bool small = !ws.forced && hop_row_bounds(num_seeds, L, fanouts, g->num_nodes, ws.node_capacity, rows) &&
-                       call_is_small(L, fanouts, rows);
-    if (ws.lostto && !small) {
-      hipStream_t st = static_cast<hipStream_t>(hip_stream);
-      k_fill_u32<<<blocks_for(ws.slot_entries, kThreads * 4, 1024), kThreads, 0, st>>>(ws.lostto, ws.slot_entries, 0u);
-      rc = hip_err(hipGetLastError());
-    }
-  }
   if (cur != g->device) (void)hipSetDevice(cur);
   if (rc != SMFG_OK) return rc;
+  bind_workspace(&ws, base);
   smfg_workspace* wsp = &ws;
-  return smfg_sample_mfg_many(g, &wsp, &d_seeds, &num_seeds, fanouts, L, &rng_key, out, 1, hip_stream);
+  return sample_many(g, &wsp, &d_seeds, &num_seeds, fanouts, L, &rng_key, out, 1, hip_stream, true);
 }
 
 int smfg_gather_many(const smfg_graph_t* g, const smfg_output_t* outs, int32_t num_batches, int32_t L,

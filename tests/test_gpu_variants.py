@@ -27,6 +27,21 @@ def sample(gg, seeds, fanouts, key):
     return fetch(out, len(fanouts)), ws.strategy
 
 
+def launches(call):
+    """Launches per stage of a call.  Three per hop (sample_insert, dedup_buckets, assemble) and none
+    before the first one: the call took the small path."""
+    smfg.profile_begin(2, 200)
+    try:
+        call()
+    finally:
+        prof = smfg.profile_end()
+    return {stage: n for stage, (_, n) in prof.items() if n}
+
+
+def small_launches(hops, features=True):
+    return dict(sample_insert=hops, dedup_buckets=hops, assemble=hops, **({"gather": 1} if features else {}))
+
+
 @pytest.mark.parametrize("fanout,seeds", [(8, 140_000), (9, 70_000), (16, 131_072), (17, 131_073), (32, 70_001)])
 def test_draw_over_several_turns(fanout, seeds):
     """Row blocks of more destinations than one turn of the draw takes, fanouts on both sides of the
@@ -91,6 +106,39 @@ def test_small_launch_set_labels_and_status():
             assert torch.equal(outs[i].labels[:len(batches[i])].cpu(), labels.cpu()[torch.from_numpy(batches[i]).long()])
         assert [fetch(o, 2)["status"] for o in outs[3:]] == [smfg.ST_DUPLICATE_SEED, smfg.ST_SEED_OUT_OF_RANGE,
                                                             smfg.ST_NODE_CAPACITY, smfg.ST_EDGE_CAPACITY]
+
+
+@pytest.mark.parametrize("sizes", [(256, 100), (256, 250), (31, 30, 1)])
+def test_small_set_with_a_workspace_per_batch(sizes):
+    """Workspaces planned for their own batch each, none with room for the largest one; twice, with other
+    seeds, so that the second call finds what the first one left."""
+    gg = random_graph(8_000, 30, 9, dim=5)
+    fan = (10, 5)
+    wss = [smfg.workspace_create(gg.g, n, fan) for n in sizes]
+    assert all(w.strategy == "table" for w in wss)
+    outs = [smfg.alloc_output(gg.g, n, fan) for n in sizes]
+    for turn in range(2):
+        rng = np.random.default_rng(turn)
+        batches = [rng.permutation(8_000)[:n].astype(np.int32) for n in sizes]
+        keys = [100 * turn + i for i in range(len(sizes))]
+        seeds = [torch.from_numpy(b).to(DEV) for b in batches]
+        assert launches(lambda: smfg.sample_mfg_many(gg.g, wss, seeds, fan, keys, outs)) == small_launches(2)
+        for b, key, out in zip(batches, keys, outs):
+            assert_same(fetch(out, 2), gg.oracle.sample_mfg(b, fan, key), 2)
+
+
+@pytest.mark.parametrize("strategy", ["table", "partition"])
+def test_static_scratch_under_a_forced_strategy(strategy, monkeypatch):
+    """The library's own scratch array, left by one strategy and shape and used by the next."""
+    gg = random_graph(8_000, 30, 10, dim=5)
+    rng = np.random.default_rng(3)
+    for forced, fan, n in [(strategy, (10, 5), 200), ("", (6, 4), 150), (strategy, (10, 5), 120), (strategy, (40, 3), 50)]:
+        monkeypatch.setenv("SMFG_DEDUP", forced)
+        s = rng.permutation(8_000)[:n].astype(np.int32)
+        out = smfg.alloc_output(gg.g, n, fan)
+        ran = launches(lambda: smfg.sample_mfg_static(gg.g, torch.from_numpy(s).to(DEV), fan, n, out))
+        assert (ran == small_launches(2)) == (forced == "")
+        assert_same(fetch(out, 2), gg.oracle.sample_mfg(s, fan, n), 2)
 
 
 def test_small_hop_of_a_wide_call_needs_room_for_padded_positions():

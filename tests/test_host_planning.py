@@ -1,0 +1,120 @@
+"""Host logic of a sampling call (workspace plans, the path a call takes), run without a GPU: the
+library's source is compiled together with a few exports of the functions that decide."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2110_08450_amd import build
+
+SMALL_RECORDS = 32768   # a hop of the small path has fewer known nodes + sample positions than this
+MAX_LAYERS = 8
+I32P, I64P = ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int64)
+
+EXPORTS = r"""
+#include "smfg.hip"
+extern "C" {
+void* plan(int64_t num_nodes, int32_t max_seeds, int32_t L, const int32_t* fanouts, int64_t node_capacity, int64_t sample_capacity) {
+  smfg_graph g;
+  std::memset(&g, 0, sizeof(g));
+  g.num_nodes = num_nodes;
+  smfg_workspace* ws = new smfg_workspace;
+  if (plan_workspace(ws, &g, max_seeds, L, fanouts, node_capacity, sample_capacity) == SMFG_OK) return ws;
+  delete ws;
+  return nullptr;
+}
+void drop(void* ws) { delete static_cast<smfg_workspace*>(ws); }
+int32_t is_part(const void* ws) { return static_cast<const smfg_workspace*>(ws)->part ? 1 : 0; }
+int64_t slots(const void* ws) { return static_cast<const smfg_workspace*>(ws)->slot_entries; }
+int32_t row_bounds(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t num_nodes, int64_t node_capacity, int64_t* rows) {
+  return hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows) ? 1 : 0;
+}
+int32_t small_hops(void** ws, const int64_t* rows, const int32_t* fanouts, int32_t L, int32_t num_batches) {
+  return small_hops_of(reinterpret_cast<const smfg_workspace* const*>(ws),
+                       reinterpret_cast<const int64_t (*)[SMFG_MAX_LAYERS + 1]>(rows), fanouts, L, num_batches);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host")
+    src, lib = d / "host.hip", d / "host.so"
+    src.write_text(EXPORTS)
+    subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC", "-shared",
+                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-I", os.path.dirname(build.SRC), "-I", build.INCLUDE, str(src), "-o", str(lib)],
+                   check=True, capture_output=True, timeout=300)
+    h = ctypes.CDLL(str(lib))
+    i32, i64, vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
+    h.plan.argtypes, h.plan.restype = [i64, i32, i32, I32P, i64, i64], vp
+    h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
+    h.slots.restype = i64
+    h.row_bounds.argtypes = [i32, i32, I32P, i64, i64, I64P]
+    h.small_hops.argtypes = [ctypes.POINTER(vp), I64P, I32P, i32, i32]
+    return h
+
+
+def fan_array(fanouts):
+    return (ctypes.c_int32 * len(fanouts))(*fanouts)
+
+
+def rows_of(host, seeds, fanouts, num_nodes, node_capacity=1 << 29):
+    rows = (ctypes.c_int64 * len(fanouts))()
+    assert host.row_bounds(seeds, len(fanouts), fan_array(fanouts), num_nodes, node_capacity, rows)
+    return list(rows)
+
+
+def small_hops(host, ws, rows, fanouts):
+    """rows[b][h]: the most destinations of hop h of batch b."""
+    flat = [x for r in rows for x in list(r) + [0] * (MAX_LAYERS + 1 - len(r))]
+    return host.small_hops((ctypes.c_void_p * len(ws))(*ws), (ctypes.c_int64 * len(flat))(*flat), fan_array(fanouts),
+                           len(fanouts), len(ws))
+
+
+@pytest.mark.parametrize("sizes", [(256, 100), (300, 100), (256, 250), (31, 30, 1), (300, 17, 1, 100)])
+def test_set_of_own_sized_table_workspaces_takes_the_small_path(host, sizes):
+    """A workspace per batch, planned for that batch: every hop of every batch is small and has room."""
+    fan = (10, 5)
+    ws = [host.plan(1 << 20, n, 2, fan_array(fan), 0, 0) for n in sizes]
+    assert not any(host.is_part(w) for w in ws)
+    assert small_hops(host, ws, [rows_of(host, n, fan, 1 << 20) for n in sizes], fan) == 2
+    for w in ws:
+        host.drop(w)
+
+
+def test_small_hops_of_ragged_sets(host):
+    """Random launch sets of batches and workspaces of different sizes.  With device tables a call takes
+    the small path for all hops or for none (a hop on the table after one off it would find the table
+    uncleared and without the nodes so far); a hop on the small path is below its limit and has room for
+    its padded positions in every batch's own workspace."""
+    rnd = random.Random(5)
+    seen = {"table": set(), "part": set()}
+    for _ in range(4000):
+        L = rnd.randint(1, 4)
+        fan = [rnd.choice([rnd.randint(1, 32), rnd.randint(1, 8), rnd.randint(33, 200) if rnd.random() < 0.3 else 3])
+               for _ in range(L)]
+        num_nodes = int(10 ** rnd.uniform(1, 7))
+        top = int(10 ** rnd.uniform(0, 3.2)) + 1
+        seeds = [rnd.randint(max(1, top // rnd.choice([2, 10, 100])), top) for _ in range(rnd.randint(1, 9))]
+        sized = lambda n: n if rnd.random() < 0.7 else top
+        capacity = rnd.choice([0, 0, rnd.randint(top, 40 * top)])
+        samples = rnd.randint(1, 20 * top) if max(fan) > 32 and rnd.random() < 0.5 else 0
+        ws = [host.plan(num_nodes, sized(n), L, fan_array(fan), capacity, samples) for n in seeds]
+        if all(ws) and len({host.is_part(w) for w in ws}) == 1:
+            rows = [rows_of(host, n, fan, num_nodes, capacity or 1 << 29) for n in seeds]
+            hops = small_hops(host, ws, rows, fan)
+            assert 0 <= hops <= L
+            if not host.is_part(ws[0]):
+                assert hops in (0, L), (fan, seeds)
+            for w, r in zip(ws, rows):
+                for h in range(hops):
+                    assert fan[h] <= 32 and r[h] * (1 + fan[h]) < SMALL_RECORDS and r[h] * fan[h] <= host.slots(w)
+            seen["part" if host.is_part(ws[0]) else "table"].add("none" if hops == 0 else "all" if hops == L else "some")
+        for w in ws:
+            if w:
+                host.drop(w)
+    assert seen["table"] >= {"all"} and seen["part"] >= {"none", "some"}
