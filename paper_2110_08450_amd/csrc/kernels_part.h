@@ -89,12 +89,23 @@ __device__ __forceinline__ int hop_blocks(const Launch& P, const BatchCtx& B) {
 }
 
 // counts <- (n_0, 0, ..., status 0); node_ids[0, n_0) <- seeds; labels of the seeds.  Seeds are
-// range-checked by the first hop's k_sample_hist, which runs after the status word is zero.
+// range-checked by the first hop's k_sample_hist, which runs after the status word is zero.  A batch of more
+// seeds than the graph has nodes holds a stray or a repeated one; it ends here, since grids, rows and
+// positions of a hop are bounded by the number of nodes.
 __global__ void __launch_bounds__(kThreads) k_begin(const Launch P) {
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_in_batch(P) == 0) {
+    int64_t status = SMFG_ST_OK;
+    if (B.num_seeds > P.num_nodes) {
+      int stray = 0;
+      for (int i = threadIdx.x; i < B.num_seeds; i += kThreads) {
+        const int32_t v = B.seeds[i];
+        stray |= v < 0 || static_cast<int64_t>(v) >= P.num_nodes;
+      }
+      status = __syncthreads_or(stray) ? SMFG_ST_SEED_OUT_OF_RANGE : SMFG_ST_DUPLICATE_SEED;
+    }
     const int m = 2 * P.L + 2;
-    for (int q = threadIdx.x; q < m; q += kThreads) B.counts[q] = (q == 0) ? B.num_seeds : 0;
+    for (int q = threadIdx.x; q < m; q += kThreads) B.counts[q] = q == 0 ? B.num_seeds : q == m - 1 ? status : 0;
   }
   const int stride = blocks_per_batch(P) * kThreads;
   for (int i = block_in_batch(P) * kThreads + threadIdx.x; i < B.num_seeds; i += stride) {

@@ -127,6 +127,28 @@ def test_small_set_with_a_workspace_per_batch(sizes):
             assert_same(fetch(out, 2), gg.oracle.sample_mfg(b, fan, key), 2)
 
 
+@pytest.mark.parametrize("forced", ["table", "partition"])
+@pytest.mark.parametrize("fan", [(32,), (5, 3), (40, 2)])
+def test_more_seeds_than_nodes(fan, forced, monkeypatch):
+    """Such a batch holds a repeated seed or one that is no node, if only after every node was there once;
+    it ends with that status, and the other batch of the call is as it should be."""
+    monkeypatch.setenv("SMFG_DEDUP", forced)
+    n = 100
+    gg = random_graph(n, 60, 12, dim=5)
+    perm = np.random.default_rng(6).permutation(n).astype(np.int32)
+    good = perm[:40].copy()
+    for seeds, status in [(np.append(perm, perm[3]), smfg.ST_DUPLICATE_SEED),
+                          (np.append(perm, np.int32(n)), smfg.ST_SEED_OUT_OF_RANGE),
+                          (np.append(np.int32(-1), perm), smfg.ST_SEED_OUT_OF_RANGE),
+                          (np.tile(perm, 50), smfg.ST_DUPLICATE_SEED)]:
+        batches = [good, seeds]
+        wss = [smfg.workspace_create(gg.g, len(seeds), fan) for _ in batches]
+        outs = [smfg.alloc_output(gg.g, len(b), fan, node_capacity=max(n, len(b))) for b in batches]
+        smfg.sample_mfg_many(gg.g, wss, [torch.from_numpy(b).to(DEV) for b in batches], fan, [1, 2], outs)
+        assert_same(fetch(outs[0], len(fan)), gg.oracle.sample_mfg(good, fan, 1), len(fan))
+        assert fetch(outs[1], len(fan))["status"] == status
+
+
 @pytest.mark.parametrize("strategy", ["table", "partition"])
 def test_static_scratch_under_a_forced_strategy(strategy, monkeypatch):
     """The library's own scratch array, left by one strategy and shape and used by the next."""
