@@ -434,13 +434,15 @@ bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANO
 // destinations of hop h of batch b.  Each batch is held against its own workspace: its samples sit at
 // padded positions, which a workspace planned for a smaller batch, or for a call with wide fanouts, need
 // not have room for.  With device tables it is all hops or none, whatever made a hop drop out: the small
-// path leaves the table uncleared and the nodes of its hops out of it.
-int small_hops_of(const smfg_workspace* const* ws, const int64_t (*rows)[SMFG_MAX_LAYERS + 1], const int32_t* fanouts,
-                  int32_t L, int32_t num_batches) {
+// path leaves the table uncleared and the nodes of its hops out of it.  No hop of a call with a batch
+// of more seeds than nodes: the small path reads all seeds of a batch, but has rows for num_nodes of them;
+// the other paths end such a batch with a status before its first hop.
+int small_hops_of(const smfg_workspace* const* ws, const int32_t* num_seeds, int64_t num_nodes,
+                  const int64_t (*rows)[SMFG_MAX_LAYERS + 1], const int32_t* fanouts, int32_t L, int32_t num_batches) {
   int hops = L;
   bool table = false;
   for (int b = 0; b < num_batches; ++b) {
-    if (ws[b]->forced) return 0;
+    if (ws[b]->forced || num_seeds[b] > num_nodes) return 0;
     table = table || !ws[b]->part;
     int h = 0;
     while (h < hops && hop_is_small(fanouts[h], rows[b][h]) && rows[b][h] * fanouts[h] <= ws[b]->slot_entries) ++h;
@@ -881,7 +883,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
   const unsigned G = static_cast<unsigned>(num_batches);
   constexpr unsigned kCap = 4096;  // blocks per batch of the grid-stride kernels
 
-  const int small_hops = small_hops_of(ws, bound, fanouts, L, num_batches);
+  const int small_hops = small_hops_of(ws, num_seeds, g->num_nodes, bound, fanouts, L, num_batches);
   SmallLaunch S;
   if (small_hops > 0) {
     S = small_launch(P, outs, fanouts, max_n);

@@ -127,7 +127,7 @@ def test_small_set_with_a_workspace_per_batch(sizes):
             assert_same(fetch(out, 2), gg.oracle.sample_mfg(b, fan, key), 2)
 
 
-@pytest.mark.parametrize("forced", ["table", "partition"])
+@pytest.mark.parametrize("forced", ["", "table", "partition"])
 @pytest.mark.parametrize("fan", [(32,), (5, 3), (40, 2)])
 def test_more_seeds_than_nodes(fan, forced, monkeypatch):
     """Such a batch holds a repeated seed or one that is no node, if only after every node was there once;

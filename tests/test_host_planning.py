@@ -31,8 +31,9 @@ int64_t slots(const void* ws) { return static_cast<const smfg_workspace*>(ws)->s
 int32_t row_bounds(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t num_nodes, int64_t node_capacity, int64_t* rows) {
   return hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows) ? 1 : 0;
 }
-int32_t small_hops(void** ws, const int64_t* rows, const int32_t* fanouts, int32_t L, int32_t num_batches) {
-  return small_hops_of(reinterpret_cast<const smfg_workspace* const*>(ws),
+int32_t small_hops(void** ws, const int32_t* num_seeds, int64_t num_nodes, const int64_t* rows, const int32_t* fanouts, int32_t L,
+                   int32_t num_batches) {
+  return small_hops_of(reinterpret_cast<const smfg_workspace* const*>(ws), num_seeds, num_nodes,
                        reinterpret_cast<const int64_t (*)[SMFG_MAX_LAYERS + 1]>(rows), fanouts, L, num_batches);
 }
 }
@@ -54,7 +55,7 @@ def host(tmp_path_factory):
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
     h.row_bounds.argtypes = [i32, i32, I32P, i64, i64, I64P]
-    h.small_hops.argtypes = [ctypes.POINTER(vp), I64P, I32P, i32, i32]
+    h.small_hops.argtypes = [ctypes.POINTER(vp), I32P, i64, I64P, I32P, i32, i32]
     return h
 
 
@@ -68,11 +69,11 @@ def rows_of(host, seeds, fanouts, num_nodes, node_capacity=1 << 29):
     return list(rows)
 
 
-def small_hops(host, ws, rows, fanouts):
+def small_hops(host, ws, seeds, num_nodes, rows, fanouts):
     """rows[b][h]: the most destinations of hop h of batch b."""
     flat = [x for r in rows for x in list(r) + [0] * (MAX_LAYERS + 1 - len(r))]
-    return host.small_hops((ctypes.c_void_p * len(ws))(*ws), (ctypes.c_int64 * len(flat))(*flat), fan_array(fanouts),
-                           len(fanouts), len(ws))
+    return host.small_hops((ctypes.c_void_p * len(ws))(*ws), fan_array(seeds), num_nodes, (ctypes.c_int64 * len(flat))(*flat),
+                           fan_array(fanouts), len(fanouts), len(ws))
 
 
 @pytest.mark.parametrize("sizes", [(256, 100), (300, 100), (256, 250), (31, 30, 1), (300, 17, 1, 100)])
@@ -81,7 +82,7 @@ def test_set_of_own_sized_table_workspaces_takes_the_small_path(host, sizes):
     fan = (10, 5)
     ws = [host.plan(1 << 20, n, 2, fan_array(fan), 0, 0) for n in sizes]
     assert not any(host.is_part(w) for w in ws)
-    assert small_hops(host, ws, [rows_of(host, n, fan, 1 << 20) for n in sizes], fan) == 2
+    assert small_hops(host, ws, sizes, 1 << 20, [rows_of(host, n, fan, 1 << 20) for n in sizes], fan) == 2
     for w in ws:
         host.drop(w)
 
@@ -97,7 +98,7 @@ def test_small_hops_of_ragged_sets(host):
         L = rnd.randint(1, 4)
         fan = [rnd.choice([rnd.randint(1, 32), rnd.randint(1, 8), rnd.randint(33, 200) if rnd.random() < 0.3 else 3])
                for _ in range(L)]
-        num_nodes = int(10 ** rnd.uniform(1, 7))
+        num_nodes = int(10 ** rnd.uniform(0, 7))
         top = int(10 ** rnd.uniform(0, 3.2)) + 1
         seeds = [rnd.randint(max(1, top // rnd.choice([2, 10, 100])), top) for _ in range(rnd.randint(1, 9))]
         sized = lambda n: n if rnd.random() < 0.7 else top
@@ -106,12 +107,14 @@ def test_small_hops_of_ragged_sets(host):
         ws = [host.plan(num_nodes, sized(n), L, fan_array(fan), capacity, samples) for n in seeds]
         if all(ws) and len({host.is_part(w) for w in ws}) == 1:
             rows = [rows_of(host, n, fan, num_nodes, capacity or 1 << 29) for n in seeds]
-            hops = small_hops(host, ws, rows, fan)
+            hops = small_hops(host, ws, seeds, num_nodes, rows, fan)
             assert 0 <= hops <= L
             if not host.is_part(ws[0]):
                 assert hops in (0, L), (fan, seeds)
-            for w, r in zip(ws, rows):
+            for w, r, n in zip(ws, rows, seeds):
                 for h in range(hops):
+                    # the kernels read the seeds as the destinations of hop 0, all of them
+                    assert max(r[h], n if h == 0 else 0) * fan[h] <= host.slots(w)
                     assert fan[h] <= 32 and r[h] * (1 + fan[h]) < SMALL_RECORDS and r[h] * fan[h] <= host.slots(w)
             seen["part" if host.is_part(ws[0]) else "table"].add("none" if hops == 0 else "all" if hops == L else "some")
         for w in ws:
