@@ -303,6 +303,24 @@ bool part_needs(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t nu
   return true;
 }
 
+// The shape of one hop of a call under the partition strategy; false if a workspace has no room for it.
+// The bucket counts of a workspace are sized for the row blocks of the most seeds.  Fewer rows can be
+// cut into more blocks (block_rows doubles once they exceed the cap: 600 seeds of fanouts (15, 10, 5) make 275
+// blocks in the last hop, 515 make 473), so a call with fewer seeds takes longer row blocks until they fit.
+bool plan_part_hop(const smfg_workspace* const* ws, int num_batches, int64_t max_rows, int d, HopPlan* hp) {
+  *hp = plan_hop(max_rows, d, num_batches);
+  for (int b = 0; b < num_batches; ++b) {
+    if (max_rows * (1 + d) > ws[b]->rec_entries) return false;
+    if (hp->lg2 > 0 && hp->lgB + hp->lg2 > ws[b]->split_lg) return false;
+    while ((hp->row_blocks << hp->lgB) > ws[b]->hist_entries) {
+      if (hp->row_blocks == 1) return false;
+      hp->block_rows *= 2;
+      hp->row_blocks = (max_rows + hp->block_rows - 1) / hp->block_rows;
+    }
+  }
+  return true;
+}
+
 // Sizes of a workspace for up to max_seeds seeds, the given fanouts and capacities: fills every
 // field of *ws but the pointers (slab stays null).  Host only.
 int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, int32_t L, const int32_t* fanouts,
@@ -866,14 +884,8 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     flat_plan.lg2 = lg - flat_plan.lgB;
     flat_plan.row_blocks = (records + kFlatBlock - 1) / kFlatBlock;
   } else if (part) {
-    for (int h = 0; h < L; ++h) {
-      plan[h] = plan_hop(max_n[h], fanouts[h], num_batches);
-      const int64_t records = max_n[h] * (1 + fanouts[h]);
-      for (int b = 0; b < num_batches; ++b)
-        if (records > ws[b]->rec_entries || (plan[h].row_blocks << plan[h].lgB) > ws[b]->hist_entries ||
-            (plan[h].lg2 > 0 && plan[h].lgB + plan[h].lg2 > ws[b]->split_lg))
-          return SMFG_ERR_CAPACITY;
-    }
+    for (int h = 0; h < L; ++h)
+      if (!plan_part_hop(ws, num_batches, max_n[h], fanouts[h], &plan[h])) return SMFG_ERR_CAPACITY;
   }
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);

@@ -53,6 +53,18 @@ def test_draw_over_several_turns(fanout, seeds):
     assert_same(res, gg.oracle.sample_mfg(s, (fanout,), 0xABCDEF0123), 1)
 
 
+@pytest.mark.parametrize("fanouts,planned,seeds", [((15, 10, 5), 600, 515), ((20, 20, 20), 515, 133), ((12, 7), 2060, 1295)])
+def test_partition_workspace_made_for_more_seeds(fanouts, planned, seeds):
+    """Fewer rows that would be cut into more row blocks than the workspace has counters for."""
+    gg = random_graph(1_300_000, 30, 14)
+    s = np.random.default_rng(seeds).permutation(1_300_000)[:seeds].astype(np.int32)
+    ws = smfg.workspace_create(gg.g, planned, fanouts)
+    assert ws.strategy == "partition"
+    out = smfg.alloc_output(gg.g, seeds, fanouts)
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), fanouts, 7, out)
+    assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(s, fanouts, 7), len(fanouts))
+
+
 @pytest.mark.parametrize("fanouts,seeds", [
     ((15, 10, 5), 31), ((15, 10, 5), 1), ((1,), 16383), ((1,), 16384), ((32,), 992), ((32,), 993), ((31, 3), 200),
     ((2,) * 8, 4), ((10, 5), 256), ((9, 8), 300), ((5,), 0), ((15, 10, 5), 1024), ((5, 100), 60), ((3, 40, 2), 900)])

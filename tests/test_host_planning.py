@@ -31,6 +31,14 @@ int64_t slots(const void* ws) { return static_cast<const smfg_workspace*>(ws)->s
 int32_t row_bounds(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t num_nodes, int64_t node_capacity, int64_t* rows) {
   return hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows) ? 1 : 0;
 }
+int64_t hist_entries(const void* ws) { return static_cast<const smfg_workspace*>(ws)->hist_entries; }
+// row_blocks << lgB of a hop and the rows its blocks cover, or -1 if a workspace has no room for it
+int64_t part_hop(void** ws, int32_t num_batches, int64_t max_rows, int32_t d, int64_t* covered) {
+  HopPlan hp;
+  if (!plan_part_hop(reinterpret_cast<const smfg_workspace* const*>(ws), num_batches, max_rows, d, &hp)) return -1;
+  *covered = hp.row_blocks * hp.block_rows;
+  return hp.row_blocks << hp.lgB;
+}
 int32_t small_hops(void** ws, const int32_t* num_seeds, int64_t num_nodes, const int64_t* rows, const int32_t* fanouts, int32_t L,
                    int32_t num_batches) {
   return small_hops_of(reinterpret_cast<const smfg_workspace* const*>(ws), num_seeds, num_nodes,
@@ -54,6 +62,8 @@ def host(tmp_path_factory):
     h.plan.argtypes, h.plan.restype = [i64, i32, i32, I32P, i64, i64], vp
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
+    h.hist_entries.argtypes, h.hist_entries.restype = [vp], i64
+    h.part_hop.argtypes, h.part_hop.restype = [ctypes.POINTER(vp), i32, i64, i32, I64P], i64
     h.row_bounds.argtypes = [i32, i32, I32P, i64, i64, I64P]
     h.small_hops.argtypes = [ctypes.POINTER(vp), I32P, i64, I64P, I32P, i32, i32]
     return h
@@ -121,3 +131,26 @@ def test_small_hops_of_ragged_sets(host):
             if w:
                 host.drop(w)
     assert seen["table"] >= {"all"} and seen["part"] >= {"none", "some"}
+
+
+@pytest.mark.parametrize("num_nodes", [1 << 28, 500_000])
+@pytest.mark.parametrize("fanouts", [(15, 10, 5), (12, 7), (25, 10), (20, 20, 20), (3, 3, 3, 3)])
+def test_a_workspace_takes_fewer_seeds_than_it_was_made_for(host, fanouts, num_nodes):
+    """Every number of seeds up to a partition workspace's own, alone or in a launch set, fits it: a
+    hop's rows are covered by row blocks that the workspace has counters for."""
+    rnd = random.Random(1)
+    covered = ctypes.c_int64()
+    planned = 0
+    for top in [515, 600, 1000, 1024] + [int(10 ** rnd.uniform(1.5, 3.8)) for _ in range(60)]:
+        w = host.plan(num_nodes, top, len(fanouts), fan_array(fanouts), 0, 0)
+        if not w or not host.is_part(w):
+            continue
+        planned += 1
+        for n in {top, top - 1, top - top // 7, top // 2 + 1, *(rnd.randint(1, top) for _ in range(40))}:
+            for d, rows in zip(fanouts, rows_of(host, n, fanouts, num_nodes)):
+                for batches in (1, 2, 8, 9, 16):
+                    got = host.part_hop((ctypes.c_void_p * batches)(*[w] * batches), batches, rows, d, covered)
+                    assert 0 < got <= host.hist_entries(w), (top, n, d, batches)
+                    assert covered.value >= rows
+        host.drop(w)
+    assert planned > 10
