@@ -14,7 +14,9 @@ namespace smfg_dev {
 // reach a higher copy rate on this chip than a persistent grid-stride loop.  Inside a block the output chunk is addressed as one flat vector array, so
 // stores are fully coalesced and the lanes that share a row read one contiguous span of it.
 // A row id outside [0, num_nodes) is read as row 0, so that no id can cause a read outside x.
-constexpr int gather_rows_per_block(int64_t row_bytes) { return row_bytes < 256 ? 64 : 32; }
+// Rows of more than 512 MiB go one to a block, as AnyRow with 64-bit indices: 32 of them would outgrow
+// the 32-bit ones.
+constexpr int gather_rows_per_block(int64_t row_bytes) { return row_bytes < 256 ? 64 : row_bytes <= (int64_t(1) << 29) ? 32 : 1; }
 
 // The copy's loads and stores are written out as instructions, for two reasons.  Cache policy:
 // rows are read once and written once, and the compiler's non-temporal builtins set `nt` alone.
@@ -107,12 +109,13 @@ __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, in
   static_assert(ROWS <= kThreads, "a thread per row fetches its id");
   constexpr bool kAny = __is_same(V, AnyRow);
   using W = typename std::conditional<kAny, u32x4, V>::type;
-  const uint32_t vec_per_row = static_cast<uint32_t>((row_bytes + (kAny ? 15 : 0)) / static_cast<int64_t>(sizeof(W)));
+  using Index = typename std::conditional<ROWS == 1, uint64_t, uint32_t>::type;
+  const Index vec_per_row = static_cast<Index>((row_bytes + (kAny ? 15 : 0)) / static_cast<int64_t>(sizeof(W)));
   __shared__ int64_t row_byte[ROWS];  // byte offset of each source row
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * ROWS;
   if (r0 >= n) return;
   const uint32_t rows = static_cast<uint32_t>(n - r0 < ROWS ? n - r0 : ROWS);
-  const uint32_t cnt = rows * vec_per_row;
+  const Index cnt = rows * vec_per_row;
   if (threadIdx.x < ROWS) {
     int64_t id = threadIdx.x < rows ? ids[r0 + threadIdx.x] : 0;
     if (id < 0 || id >= num_nodes) id = 0;
@@ -125,16 +128,16 @@ __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, in
   // when a row has at most 8192 vectors; longer rows divide
   const bool by_mul = vec_per_row <= 8192u;
   const uint64_t inv = 0xFFFFFFFFull / vec_per_row + 1ull;
-  const auto place = [&](uint32_t idx, const W*& from, W*& to) {
-    const uint32_t jrow = by_mul ? static_cast<uint32_t>((idx * inv) >> 32) : idx / vec_per_row;
-    uint32_t byte = (idx - jrow * vec_per_row) * static_cast<uint32_t>(sizeof(W));
-    if (kAny && idx - jrow * vec_per_row == vec_per_row - 1u) byte = static_cast<uint32_t>(row_bytes) - 16u;
+  const auto place = [&](Index idx, const W*& from, W*& to) {
+    const uint32_t jrow = ROWS == 1 ? 0u : static_cast<uint32_t>(by_mul ? (idx * inv) >> 32 : idx / vec_per_row);
+    Index byte = (idx - jrow * vec_per_row) * static_cast<Index>(sizeof(W));
+    if (kAny && idx - jrow * vec_per_row == vec_per_row - 1u) byte = static_cast<Index>(row_bytes) - 16u;
     from = reinterpret_cast<const W*>(feat + row_byte[jrow] + byte);
     to = kAny ? reinterpret_cast<W*>(o + jrow * row_bytes + byte) : reinterpret_cast<W*>(o) + idx;
   };
   // a round: two independent row reads per thread, then the two stores; the last round of a
   // thread may hold one vector only
-  for (uint32_t base = threadIdx.x; base < cnt; base += kThreads * 2) {
+  for (Index base = threadIdx.x; base < cnt; base += kThreads * 2) {
     const W *f0, *f1;
     W *t0, *t1;
     place(base, f0, t0);

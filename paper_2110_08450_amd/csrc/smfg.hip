@@ -71,7 +71,7 @@ inline int vec_bytes(uintptr_t a, uintptr_t b, int64_t row_bytes, int64_t row_st
                      static_cast<uint64_t>(row_stride);
   if ((x & 15) == 0) return 16;
   if ((x & 7) == 0) return 8;
-  if (row_bytes >= 16 && row_bytes <= 0x7FFFFFFF) return kAnyRow;
+  if (row_bytes >= 16) return kAnyRow;
   if ((x & 3) == 0) return 4;
   if ((x & 1) == 0) return 2;
   return 1;
@@ -542,36 +542,58 @@ void launch_by_fanout(int d, unsigned blocks, hipStream_t st, const Launch& P, L
   (d <= 8 ? to8 : d <= 16 ? to16 : to32)<<<blocks, kThreads, 0, st>>>(P);
 }
 
-// The gather launch shared by smfg_sample_mfg_many and smfg_gather_many.
-template <int ROWS>
-void launch_gather_rows(const Launch& P, int64_t max_rows, int vb, unsigned G, hipStream_t st) {
-  const unsigned gb = blocks_for(max_rows, ROWS, 0x7FFFFFFFu);
-  switch (vb) {
-    case 16: k_gather<u32x4, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
-    case kAnyRow: k_gather<AnyRow, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
-    case 8: k_gather<u32x2, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
-    case 4: k_gather<uint32_t, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
-    case 2: k_gather<uint16_t, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
-    default: k_gather<uint8_t, ROWS><<<dim3(gb, G), kThreads, 0, st>>>(P); break;
-  }
-}
-template <int ROWS>
-void launch_gather_plain(const smfg_graph* g, int vb, const int32_t* d_node_ids, const int64_t* d_num_rows,
-                         int64_t max_rows, uint8_t* o, hipStream_t st) {
-  const unsigned gb = blocks_for(max_rows, ROWS, 0x7FFFFFFFu);
-  switch (vb) {
-    case 16: k_gather_plain<u32x4, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
-    case kAnyRow: k_gather_plain<AnyRow, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
-    case 8: k_gather_plain<u32x2, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
-    case 4: k_gather_plain<uint32_t, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
-    case 2: k_gather_plain<uint16_t, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
-    default: k_gather_plain<uint8_t, ROWS><<<gb, kThreads, 0, st>>>(g->feat, g->row_bytes, g->row_stride, g->num_nodes, d_node_ids, d_num_rows, max_rows, o); break;
-  }
-}
+// The gather launch shared by smfg_sample_mfg_many and smfg_gather_many.  Vectors of 4 bytes and less only
+// serve rows below 16 bytes, 64 to a block.
 void launch_gather(const Launch& P, int64_t max_rows, int vb, unsigned G, hipStream_t st) {
   StageTimer t_(SMFG_STAGE_GATHER, st);
-  if (gather_rows_per_block(P.row_bytes) == 64) launch_gather_rows<64>(P, max_rows, vb, G, st);
-  else launch_gather_rows<32>(P, max_rows, vb, G, st);
+  const int per_block = gather_rows_per_block(P.row_bytes);
+  const dim3 grid(blocks_for(max_rows, per_block, 0x7FFFFFFFu), G);
+  if (per_block == 1) {
+    k_gather<AnyRow, 1><<<grid, kThreads, 0, st>>>(P);
+    return;
+  }
+  if (per_block == 32) {
+    switch (vb) {
+      case 16: k_gather<u32x4, 32><<<grid, kThreads, 0, st>>>(P); break;
+      case kAnyRow: k_gather<AnyRow, 32><<<grid, kThreads, 0, st>>>(P); break;
+      default: k_gather<u32x2, 32><<<grid, kThreads, 0, st>>>(P); break;
+    }
+    return;
+  }
+  switch (vb) {
+    case 16: k_gather<u32x4, 64><<<grid, kThreads, 0, st>>>(P); break;
+    case kAnyRow: k_gather<AnyRow, 64><<<grid, kThreads, 0, st>>>(P); break;
+    case 8: k_gather<u32x2, 64><<<grid, kThreads, 0, st>>>(P); break;
+    case 4: k_gather<uint32_t, 64><<<grid, kThreads, 0, st>>>(P); break;
+    case 2: k_gather<uint16_t, 64><<<grid, kThreads, 0, st>>>(P); break;
+    default: k_gather<uint8_t, 64><<<grid, kThreads, 0, st>>>(P); break;
+  }
+}
+void launch_gather_plain(const smfg_graph* g, int vb, const int32_t* ids, const int64_t* num_rows, int64_t max_rows,
+                         uint8_t* o, hipStream_t st) {
+  const int64_t bytes = g->row_bytes, stride = g->row_stride, n = g->num_nodes;
+  const int per_block = gather_rows_per_block(bytes);
+  const unsigned grid = blocks_for(max_rows, per_block, 0x7FFFFFFFu);
+  if (per_block == 1) {
+    k_gather_plain<AnyRow, 1><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o);
+    return;
+  }
+  if (per_block == 32) {
+    switch (vb) {
+      case 16: k_gather_plain<u32x4, 32><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+      case kAnyRow: k_gather_plain<AnyRow, 32><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+      default: k_gather_plain<u32x2, 32><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+    }
+    return;
+  }
+  switch (vb) {
+    case 16: k_gather_plain<u32x4, 64><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+    case kAnyRow: k_gather_plain<AnyRow, 64><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+    case 8: k_gather_plain<u32x2, 64><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+    case 4: k_gather_plain<uint32_t, 64><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+    case 2: k_gather_plain<uint16_t, 64><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+    default: k_gather_plain<uint8_t, 64><<<grid, kThreads, 0, st>>>(g->feat, bytes, stride, n, ids, num_rows, max_rows, o); break;
+  }
 }
 
 }  // namespace
@@ -1142,8 +1164,7 @@ int smfg_gather_rows(const smfg_graph_t* g, const int32_t* d_node_ids, const int
   int cur = 0;
   (void)hipGetDevice(&cur);
   if (cur != g->device) (void)hipSetDevice(g->device);
-  if (gather_rows_per_block(g->row_bytes) == 64) launch_gather_plain<64>(g, vb, d_node_ids, d_num_rows, max_rows, o, st);
-  else launch_gather_plain<32>(g, vb, d_node_ids, d_num_rows, max_rows, o, st);
+  launch_gather_plain(g, vb, d_node_ids, d_num_rows, max_rows, o, st);
   hipError_t e = hipGetLastError();
   if (cur != g->device) (void)hipSetDevice(cur);
   return hip_err(e);

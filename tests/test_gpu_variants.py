@@ -207,6 +207,26 @@ def test_gather_rows_at_any_address(dim, shift):
     assert (out[rows:] == 31_000).all() and (flat[:shift] == 31_000).all()
 
 
+@pytest.mark.parametrize("dim,dtype,rows", [(600_000_003, torch.int64, 2), ((1 << 30) + 5, torch.int16, 33)])
+def test_gather_rows_beyond_32_bits(dim, dtype, rows):
+    """Rows of 4.8 GB, and more rows of 2 GiB than a block of ordinary rows takes."""
+    table = torch.empty((2, dim), dtype=dtype, device=DEV).random_()
+    indptr = torch.tensor([0, 1, 1], dtype=torch.int64, device=DEV)
+    g = smfg.graph_create(indptr, torch.ones(1, dtype=torch.int32, device=DEV), table)
+    ids = (torch.arange(rows, dtype=torch.int32, device=DEV) + 1) % 2
+    out = torch.zeros((rows, dim), dtype=dtype, device=DEV)
+    smfg.gather_rows(g, ids, torch.tensor([rows], device=DEV), rows, out)
+    for i in range(rows):
+        assert torch.equal(out[i], table[(i + 1) % 2])
+    del out
+    sampled = smfg.alloc_output(g, 2, (1,))
+    smfg.sample_mfg(g, smfg.workspace_create(g, 2, (1,)), ids[:2].contiguous(), (1,), 1, sampled)
+    assert smfg.read_counts(sampled)[:2] == [2, 2]
+    assert torch.equal(sampled.features[0], table[1]) and torch.equal(sampled.features[1], table[0])
+    del sampled, table, g
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
 @pytest.mark.parametrize("dim,shift", [(3, 1), (4, 1), (7, 0), (8, 1), (9, 0), (128, 1), (129, 0), (131, 3)])
 def test_mean_aggregate_at_any_address(dim, shift, dtype):

@@ -31,6 +31,11 @@ int64_t slots(const void* ws) { return static_cast<const smfg_workspace*>(ws)->s
 int32_t row_bounds(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t num_nodes, int64_t node_capacity, int64_t* rows) {
   return hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows) ? 1 : 0;
 }
+int32_t gather_block(int64_t row_bytes) { return gather_rows_per_block(row_bytes); }
+int32_t gather_vector(int64_t address, int64_t row_bytes) {
+  const int v = vec_bytes(static_cast<uintptr_t>(address), 0, row_bytes, 0);
+  return v == kAnyRow ? 16 : v;
+}
 int64_t hist_entries(const void* ws) { return static_cast<const smfg_workspace*>(ws)->hist_entries; }
 // row_blocks << lgB of a hop and the rows its blocks cover, or -1 if a workspace has no room for it
 int64_t part_hop(void** ws, int32_t num_batches, int64_t max_rows, int32_t d, int64_t* covered) {
@@ -62,6 +67,7 @@ def host(tmp_path_factory):
     h.plan.argtypes, h.plan.restype = [i64, i32, i32, I32P, i64, i64], vp
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
+    h.gather_block.argtypes, h.gather_vector.argtypes = [i64], [i64, i64]
     h.hist_entries.argtypes, h.hist_entries.restype = [vp], i64
     h.part_hop.argtypes, h.part_hop.restype = [ctypes.POINTER(vp), i32, i64, i32, I64P], i64
     h.row_bounds.argtypes = [i32, i32, I32P, i64, i64, I64P]
@@ -154,3 +160,16 @@ def test_a_workspace_takes_fewer_seeds_than_it_was_made_for(host, fanouts, num_n
                     assert covered.value >= rows
         host.drop(w)
     assert planned > 10
+
+
+def test_gather_blocks_stay_within_their_indices(host):
+    """A block of several rows counts vectors and bytes of a row in 32 bits; the last round of a thread
+    may look 2 x 256 vectors beyond the block's last one."""
+    sizes = {x for e in range(37) for x in range((1 << e) - 9, (1 << e) + 10) if x > 0}
+    for row_bytes in sizes | {x * 16 for x in sizes} | {(1 << 31) - 8192, 600_000_003 * 8}:
+        for address in (0, 8, 4, 2, 1):
+            rows, vec = host.gather_block(row_bytes), host.gather_vector(address, row_bytes)
+            if rows > 1:
+                assert rows * -(-row_bytes // vec) + 512 < 1 << 32 and row_bytes < 1 << 32
+            if rows != 64:      # the rows per block for which vectors of 4 bytes and less are not built
+                assert vec >= 8
