@@ -78,21 +78,50 @@ def test_small_calls_and_hops(fanouts, seeds):
     assert_same(res, gg.oracle.sample_mfg(s, fanouts, 5), len(fanouts))
 
 
+def small_bucket(node):
+    """The bucket of 16 that k_small_dedup deals a node to (a 24-bit product, bits 20 to 23)."""
+    x = (node ^ (node >> np.uint64(15))) & np.uint64(0xFFFFFF)
+    return (x * np.uint64(0x79B1B5) >> np.uint64(20)) & np.uint64(15)
+
+
+def test_small_call_with_a_hub_beyond_the_list():
+    """6000 rows that all hold one hub: its bucket has more records than the list of 4096 that a block keeps
+    of what it found, so the block reads the hop again in every round, with entries settled meanwhile."""
+    n, hub = 60_000, 12_345
+    rng = np.random.default_rng(21)
+    rows = rng.integers(0, n, size=(n, 3)).astype(np.int32)
+    rows[np.arange(n), rng.integers(0, 3, size=n)] = hub
+    gg = GpuGraph(np.arange(n + 1, dtype=np.int64) * 3, rows.ravel(), None)
+    for s in (rng.permutation(n)[:6_000].astype(np.int32), np.append(rng.permutation(hub)[:5_999], hub).astype(np.int32)):
+        ws, out = smfg.workspace_create(gg.g, len(s), (3,)), smfg.alloc_output(gg.g, len(s), (3,))
+        seeds = torch.from_numpy(s).to(DEV)
+        assert launches(lambda: smfg.sample_mfg(gg.g, ws, seeds, (3,), 9, out)) == small_launches(1, features=False)
+        assert_same(fetch(out, 1), gg.oracle.sample_mfg(s, (3,), 9), 1)
+
+
 def test_small_call_table_overflows_and_retries():
-    """32 000 distinct nodes that share their two leading hash bits: four rounds are planned, one of
-    them gets all records and overflows the 16384-slot table until the rounds are fine enough."""
-    n = 1 << 18
-    h = (np.arange(n, dtype=np.uint64) * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)
-    same = np.nonzero((h >> np.uint64(30)) == np.uint64(1))[0]
-    seeds, others = same[:16_000].astype(np.int32), same[16_000:32_000]
+    """20 000 distinct nodes of one bucket that share the three leading bits of the other hash: eight rounds
+    are planned (20 000 / 8 records each, at most half a table of 8192 slots), but one gets all records and
+    overflows the table; 16 rounds leave 10 000 nodes in one, 32 rounds 5000, which fit."""
+    n = 1 << 22
+    node = np.arange(n, dtype=np.uint64)
+    h = (node * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)
+    same = node[(small_bucket(node) == 5) & (h >> np.uint64(29) == 3)]
+    assert len(same) >= 20_000
+    same, h = same[:20_000], h[same[:20_000].astype(np.int64)]
+    most = [np.bincount((h >> np.uint64(32 - lg)).astype(np.int64)).max() for lg in (3, 4, 5)]
+    assert most[0] > 8192 and most[1] > 8192 > most[2]
+    seeds, others = same[:10_000].astype(np.int32), same[10_000:]
     indptr = np.zeros(n + 1, dtype=np.int64)
     deg = np.zeros(n, dtype=np.int64)
     deg[seeds] = 1
     np.cumsum(deg, out=indptr[1:])
     gg = GpuGraph(indptr, others.astype(np.int32), None)
     s = np.random.default_rng(1).permutation(seeds)
-    res, _ = sample(gg, s, (1,), 9)
-    assert_same(res, gg.oracle.sample_mfg(s, (1,), 9), 1)
+    ws, out = smfg.workspace_create(gg.g, len(s), (1,)), smfg.alloc_output(gg.g, len(s), (1,))
+    on_device = torch.from_numpy(s).to(DEV)
+    assert launches(lambda: smfg.sample_mfg(gg.g, ws, on_device, (1,), 9, out)) == small_launches(1, features=False)
+    assert_same(fetch(out, 1), gg.oracle.sample_mfg(s, (1,), 9), 1)
 
 
 def test_small_launch_set_labels_and_status():
@@ -112,7 +141,8 @@ def test_small_launch_set_labels_and_status():
     wss = [smfg.workspace_create(gg.g, len(b), fan) for b in batches]
     keys = list(range(70, 77))
     for _ in range(2):  # the workspaces are as good after a status as before
-        smfg.sample_mfg_many(gg.g, wss, [torch.from_numpy(b).to(DEV) for b in batches], fan, keys, outs)
+        seeds = [torch.from_numpy(b).to(DEV) for b in batches]
+        assert launches(lambda: smfg.sample_mfg_many(gg.g, wss, seeds, fan, keys, outs)) == small_launches(2)
         for i in range(3):
             assert_same(fetch(outs[i], 2), gg.oracle.sample_mfg(batches[i], fan, keys[i]), 2)
             assert torch.equal(outs[i].labels[:len(batches[i])].cpu(), labels.cpu()[torch.from_numpy(batches[i]).long()])

@@ -31,6 +31,12 @@ int64_t slots(const void* ws) { return static_cast<const smfg_workspace*>(ws)->s
 int32_t row_bounds(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t num_nodes, int64_t node_capacity, int64_t* rows) {
   return hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows) ? 1 : 0;
 }
+// lgB, lg2 and the least lgB of a hop of two levels
+void levels(int32_t lg, int32_t batches, int32_t* out) {
+  part_levels(lg, out[0], out[1], batches);
+  out[2] = part_split_lg(batches);
+}
+int32_t max_levels(int32_t which) { return which == 0 ? kPartMaxLgB : kPartMaxLg2; }
 int32_t gather_block(int64_t row_bytes) { return gather_rows_per_block(row_bytes); }
 int32_t gather_vector(int64_t address, int64_t row_bytes) {
   const int v = vec_bytes(static_cast<uintptr_t>(address), 0, row_bytes, 0);
@@ -67,6 +73,7 @@ def host(tmp_path_factory):
     h.plan.argtypes, h.plan.restype = [i64, i32, i32, I32P, i64, i64], vp
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
+    h.levels.argtypes = [i32, i32, I32P]
     h.gather_block.argtypes, h.gather_vector.argtypes = [i64], [i64, i64]
     h.hist_entries.argtypes, h.hist_entries.restype = [vp], i64
     h.part_hop.argtypes, h.part_hop.restype = [ctypes.POINTER(vp), i32, i64, i32, I64P], i64
@@ -173,3 +180,16 @@ def test_gather_blocks_stay_within_their_indices(host):
                 assert rows * -(-row_bytes // vec) + 512 < 1 << 32 and row_bytes < 1 << 32
             if rows != 64:      # the rows per block for which vectors of 4 bytes and less are not built
                 assert vec >= 8
+
+
+def test_bucket_levels_for_every_number_of_batches(host):
+    """How 2^lg hash buckets are laid out in one or two levels: within what the kernels' LDS arrays hold;
+    together always 2^lg, so that the capacity of a workspace does not depend on the launch set; a hop of two
+    levels starts with at least as many buckets as its number of batches asks for."""
+    most_b, most_2 = host.max_levels(0), host.max_levels(1)
+    out = (ctypes.c_int32 * 3)()
+    for batches in range(1, 17):
+        for lg in range(most_b + most_2 + 1):
+            host.levels(lg, batches, out)
+            assert out[0] + out[1] == lg and 0 <= out[0] <= most_b and 0 <= out[1] <= most_2
+            assert out[1] == 0 if lg <= most_b else (out[1] > 0 and out[0] >= out[2])
