@@ -446,7 +446,6 @@ int static_scratch_of(int device, void** out) {
 // A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: hop
 // 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's seven
 // launches, 21 us so.
-constexpr int kSmallHopBatches = 6;  // the most batches of a call with larger hops that do so
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 // How many of a call's hops, counted from the first one, take the small path; rows[b][h] bounds the
 // destinations of hop h of batch b.  Each batch is held against its own workspace: its samples sit at
@@ -455,8 +454,11 @@ bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANO
 // path leaves the table uncleared and the nodes of its hops out of it.  No hop of a call with a batch
 // of more seeds than nodes: the small path reads all seeds of a batch, but has rows for num_nodes of them;
 // the other paths end such a batch with a status before its first hop.
+//
+// crowded (see below): a call with larger hops has no small ones.
 int small_hops_of(const smfg_workspace* const* ws, const int32_t* num_seeds, int64_t num_nodes,
-                  const int64_t (*rows)[SMFG_MAX_LAYERS + 1], const int32_t* fanouts, int32_t L, int32_t num_batches) {
+                  const int64_t (*rows)[SMFG_MAX_LAYERS + 1], const int32_t* fanouts, int32_t L, int32_t num_batches,
+                  bool crowded) {
   int hops = L;
   bool table = false;
   for (int b = 0; b < num_batches; ++b) {
@@ -467,9 +469,21 @@ int small_hops_of(const smfg_workspace* const* ws, const int32_t* num_seeds, int
     hops = h;
   }
   if (hops == L) return L;
-  // launch sets of many larger batches run beside the gather of another set (8633 instead of 9.5 K batches/s
-  // on the papers100M-shaped workload, sets of 10): there a block of 16 waves waits long for a free unit
-  return table || num_batches > kSmallHopBatches ? 0 : hops;
+  return table || crowded ? 0 : hops;
+}
+// A call that leaves the gather to another one is prepared beside the gather of another set, whose many short
+// blocks keep taking the places that a block of 16 waves waits for.  Sets of one or two batches gain more
+// from fewer launches than they lose by the wait; so do, or neither way, those whose feature table lies in the
+// 256 MB cache behind the L2, from which a gather is short.  Time per batch without / with small first hops, fanouts
+// (15, 10, 5), 1024 seeds; graphs and tables as papers100M (28 GB), products (490 MB) and arxiv (87 MB) have:
+//                        1 batch                      2 batches                4 batches               8 batches
+//   the call gathers     256/228, 243/204, 171/150    189/171, 163/142, 98/86  152/141, 121/113, 62/55 131/124, 99/96, 42/39 us
+//   beside a gather      243/237, 154/141, 146/127    163/171, 109/107, 62/56  129/142,  90/92,  42/41 111/122, 83/84, 34/33 us
+// and beside a gather with tables of 78, 173, 196 and 980 MB: 2 batches 80/77, 79/74, 89/85, 136/139, 6 batches
+// 59/59, 55/55, 68/68, 125/124.
+constexpr int64_t kCachedTable = 128ll << 20;
+bool crowded_by_a_gather(const smfg_graph* g, bool gathers, int num_batches) {
+  return g->feat && !gathers && num_batches > 2 && g->num_nodes * g->row_stride > kCachedTable;
 }
 SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows) {
   SmallLaunch S;
@@ -917,7 +931,8 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
   const unsigned G = static_cast<unsigned>(num_batches);
   constexpr unsigned kCap = 4096;  // blocks per batch of the grid-stride kernels
 
-  const int small_hops = small_hops_of(ws, num_seeds, g->num_nodes, bound, fanouts, L, num_batches);
+  const int small_hops = small_hops_of(ws, num_seeds, g->num_nodes, bound, fanouts, L, num_batches,
+                                       crowded_by_a_gather(g, want_feat, num_batches));
   SmallLaunch S;
   if (small_hops > 0) {
     S = small_launch(P, outs, fanouts, max_n);

@@ -169,6 +169,32 @@ def test_small_set_with_a_workspace_per_batch(sizes):
             assert_same(fetch(out, 2), gg.oracle.sample_mfg(b, fan, key), 2)
 
 
+@pytest.mark.parametrize("num_batches,own_gather,small", [(16, True, True), (16, False, False), (3, False, False), (2, False, True)])
+def test_small_first_hop_of_a_larger_set(num_batches, own_gather, small):
+    """Ragged sets whose first hop is small and whose second one is not, gathered by the call or, with a
+    feature table beyond the cache, by another one."""
+    n, fan = 60_000, (6, 12)
+    gg = random_graph(n, 24, 15)
+    feat = torch.arange(n, dtype=torch.int32, device=DEV)[:, None].expand(n, 600).contiguous()
+    g = smfg.graph_create(gg.indptr, gg.indices, feat)
+    rng = np.random.default_rng(num_batches)
+    batches = [rng.permutation(n)[:k].astype(np.int32) for k in rng.integers(500, 2_000, size=num_batches)]
+    wss = [smfg.workspace_create(g, 2_000, fan) for _ in batches]
+    assert all(w.strategy == "partition" for w in wss)
+    outs = [smfg.alloc_output(g, 2_000, fan, with_features=own_gather) for _ in batches]
+    seeds, keys = [torch.from_numpy(b).to(DEV) for b in batches], list(range(num_batches))
+    for _ in range(2):
+        ran = launches(lambda: smfg.sample_mfg_many(g, wss, seeds, fan, keys, outs, with_features=own_gather))
+        assert ran["partition"] == (1 if small else 2) and ("seeds" in ran) == (not small)
+        for b, key, out in zip(batches, keys, outs):
+            ref = gg.oracle.sample_mfg(b, fan, key)
+            got = fetch(out, 2)
+            got.pop("features", None)
+            assert_same(got, ref, 2)
+            if own_gather:
+                assert torch.equal(out.features[:got["n"][2]], feat[out.node_ids[:got["n"][2]].long()])
+
+
 @pytest.mark.parametrize("forced", ["", "table", "partition"])
 @pytest.mark.parametrize("fan", [(32,), (5, 3), (40, 2)])
 def test_more_seeds_than_nodes(fan, forced, monkeypatch):

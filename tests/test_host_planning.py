@@ -42,6 +42,14 @@ int32_t gather_vector(int64_t address, int64_t row_bytes) {
   const int v = vec_bytes(static_cast<uintptr_t>(address), 0, row_bytes, 0);
   return v == kAnyRow ? 16 : v;
 }
+int32_t crowded(int64_t num_nodes, int64_t row_stride, int32_t gathers, int32_t num_batches) {
+  smfg_graph g;
+  std::memset(&g, 0, sizeof(g));
+  g.num_nodes = num_nodes;
+  g.row_stride = row_stride;
+  g.feat = row_stride > 0 ? reinterpret_cast<const uint8_t*>(256) : nullptr;
+  return crowded_by_a_gather(&g, gathers != 0, num_batches) ? 1 : 0;
+}
 int64_t hist_entries(const void* ws) { return static_cast<const smfg_workspace*>(ws)->hist_entries; }
 // row_blocks << lgB of a hop and the rows its blocks cover, or -1 if a workspace has no room for it
 int64_t part_hop(void** ws, int32_t num_batches, int64_t max_rows, int32_t d, int64_t* covered) {
@@ -51,9 +59,9 @@ int64_t part_hop(void** ws, int32_t num_batches, int64_t max_rows, int32_t d, in
   return hp.row_blocks << hp.lgB;
 }
 int32_t small_hops(void** ws, const int32_t* num_seeds, int64_t num_nodes, const int64_t* rows, const int32_t* fanouts, int32_t L,
-                   int32_t num_batches) {
+                   int32_t num_batches, int32_t crowded) {
   return small_hops_of(reinterpret_cast<const smfg_workspace* const*>(ws), num_seeds, num_nodes,
-                       reinterpret_cast<const int64_t (*)[SMFG_MAX_LAYERS + 1]>(rows), fanouts, L, num_batches);
+                       reinterpret_cast<const int64_t (*)[SMFG_MAX_LAYERS + 1]>(rows), fanouts, L, num_batches, crowded != 0);
 }
 }
 """
@@ -73,12 +81,13 @@ def host(tmp_path_factory):
     h.plan.argtypes, h.plan.restype = [i64, i32, i32, I32P, i64, i64], vp
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
+    h.crowded.argtypes = [i64, i64, i32, i32]
     h.levels.argtypes = [i32, i32, I32P]
     h.gather_block.argtypes, h.gather_vector.argtypes = [i64], [i64, i64]
     h.hist_entries.argtypes, h.hist_entries.restype = [vp], i64
     h.part_hop.argtypes, h.part_hop.restype = [ctypes.POINTER(vp), i32, i64, i32, I64P], i64
     h.row_bounds.argtypes = [i32, i32, I32P, i64, i64, I64P]
-    h.small_hops.argtypes = [ctypes.POINTER(vp), I32P, i64, I64P, I32P, i32, i32]
+    h.small_hops.argtypes = [ctypes.POINTER(vp), I32P, i64, I64P, I32P, i32, i32, i32]
     return h
 
 
@@ -92,11 +101,11 @@ def rows_of(host, seeds, fanouts, num_nodes, node_capacity=1 << 29):
     return list(rows)
 
 
-def small_hops(host, ws, seeds, num_nodes, rows, fanouts):
+def small_hops(host, ws, seeds, num_nodes, rows, fanouts, crowded=False):
     """rows[b][h]: the most destinations of hop h of batch b."""
     flat = [x for r in rows for x in list(r) + [0] * (MAX_LAYERS + 1 - len(r))]
     return host.small_hops((ctypes.c_void_p * len(ws))(*ws), fan_array(seeds), num_nodes, (ctypes.c_int64 * len(flat))(*flat),
-                           fan_array(fanouts), len(fanouts), len(ws))
+                           fan_array(fanouts), len(fanouts), len(ws), crowded)
 
 
 @pytest.mark.parametrize("sizes", [(256, 100), (300, 100), (256, 250), (31, 30, 1), (300, 17, 1, 100)])
@@ -132,6 +141,9 @@ def test_small_hops_of_ragged_sets(host):
             rows = [rows_of(host, n, fan, num_nodes, capacity or 1 << 29) for n in seeds]
             hops = small_hops(host, ws, seeds, num_nodes, rows, fan)
             assert 0 <= hops <= L
+            # beside another set's gather: the same, but a call with larger hops has no small ones
+            crowded = small_hops(host, ws, seeds, num_nodes, rows, fan, crowded=True)
+            assert crowded == (hops if hops == L else 0)
             if not host.is_part(ws[0]):
                 assert hops in (0, L), (fan, seeds)
             for w, r, n in zip(ws, rows, seeds):
@@ -144,6 +156,15 @@ def test_small_hops_of_ragged_sets(host):
             if w:
                 host.drop(w)
     assert seen["table"] >= {"all"} and seen["part"] >= {"none", "some"}
+
+
+def test_which_calls_run_beside_a_gather(host):
+    """Only sets of three batches and more that leave the gather of a large table to another call."""
+    papers = (111_000_000, 256)
+    assert [host.crowded(*papers, 0, n) for n in (1, 2, 3, 8, 16)] == [0, 0, 1, 1, 1]
+    assert not host.crowded(*papers, 1, 8)                 # gathers itself
+    assert not host.crowded(papers[0], 0, 0, 8)            # no features: nobody gathers
+    assert [host.crowded(1 << 18, row, 0, 8) for row in (512, 513)] == [0, 1]
 
 
 @pytest.mark.parametrize("num_nodes", [1 << 28, 500_000])
