@@ -169,7 +169,7 @@ def test_small_set_with_a_workspace_per_batch(sizes):
             assert_same(fetch(out, 2), gg.oracle.sample_mfg(b, fan, key), 2)
 
 
-@pytest.mark.parametrize("num_batches,own_gather,small", [(16, True, True), (16, False, False), (3, False, False), (2, False, True)])
+@pytest.mark.parametrize("num_batches,own_gather,small", [(16, True, True), (16, False, False), (5, False, False), (4, False, True)])
 def test_small_first_hop_of_a_larger_set(num_batches, own_gather, small):
     """Ragged sets whose first hop is small and whose second one is not, gathered by the call or, with a
     feature table beyond the cache, by another one."""

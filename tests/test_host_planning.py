@@ -159,9 +159,9 @@ def test_small_hops_of_ragged_sets(host):
 
 
 def test_which_calls_run_beside_a_gather(host):
-    """Only sets of three batches and more that leave the gather of a large table to another call."""
+    """Only sets of five batches and more that leave the gather of a large table to another call."""
     papers = (111_000_000, 256)
-    assert [host.crowded(*papers, 0, n) for n in (1, 2, 3, 8, 16)] == [0, 0, 1, 1, 1]
+    assert [host.crowded(*papers, 0, n) for n in (1, 2, 4, 5, 16)] == [0, 0, 0, 1, 1]
     assert not host.crowded(*papers, 1, 8)                 # gathers itself
     assert not host.crowded(papers[0], 0, 0, 8)            # no features: nobody gathers
     assert [host.crowded(1 << 18, row, 0, 8) for row in (512, 513)] == [0, 1]
