@@ -163,7 +163,8 @@ int64_t smfg_workspace_bytes(const smfg_workspace_t *ws);
  *                            records.
  * A call whose own hops all stay below that, on a workspace of either kind, reads all its records in every
  * one of a few blocks instead (three launches per hop; such calls are launch bound): no table in
- * device memory, no atomics.  The result is the same again.
+ * device memory, no atomics.  On partition workspaces the first hops of a larger call do so as well, unless
+ * it is a set of more than four batches that leaves the gather to another call.  The result is the same again.
  * The environment variable SMFG_DEDUP=table or =partition, read when a workspace is created,
  * overrides the choice, for small calls as well (for measurements and tests).  Returns -1 for NULL.
  */

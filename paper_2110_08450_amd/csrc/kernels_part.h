@@ -2,7 +2,7 @@
 //
 // Procedure OneHopMFG keeps one map from global to local ids and gives a node its local id at the
 // first encounter.  Here the map never exists as one structure in memory.  Per hop:
-//   sample_hist   draws the neighbours (as k_sample_insert does) into gsrc and counts, per block
+//   sample_hist   draws the neighbours (draw_tile) into gsrc and counts, per block
 //                 of destinations, how many records fall into each hash bucket; a record is
 //                 (node, value): one per known node (value = its local id) and one per sample
 //                 (value = tag | scan position);
@@ -19,8 +19,8 @@
 //                 overwritten with kResolved | final local id (known node) or kPointer | position
 //                 of the first appearance.  In the outer hops most samples are first appearances,
 //                 so few entries are rewritten.
-// flag_rows_part / scan_tiles / assemble_part then number the first appearances in scan order,
-// exactly the ids the serial first-encounter rule gives.  Which thread inserts first never
+// flag_rows_part / assemble_part then number the first appearances in scan order (with scan_tiles between
+// them in hops of more than kAssembleTiles tiles), exactly the ids the serial first-encounter rule gives.  Which thread inserts first never
 // matters: only minima are kept.  All global traffic but the neighbour reads and those scattered
 // 4-byte rewrites is streaming, and there are no global atomics.
 #ifndef SMFG_KERNELS_PART_H_
@@ -58,8 +58,10 @@ struct HopShape {
 // only 2^kPartSplitLgB buckets (more if the second would exceed 2^kPartMaxLg2), so that what a
 // block sends to a bucket per round is a run of a sector or more and the lines it is filling stay
 // in the L2 until they are full.  One or two batches take twice as many, because each first-level bucket
-// is one block of k_split_buckets and 128 of them leave half the chip idle (one batch of 29 M records:
-// scatter + split 414 -> 345 us; four batches of 2.4 M are 10 us better off with 128).
+// is one block of k_split_buckets: 128 of them leave half the chip idle (one batch of 29 M records: scatter +
+// split 414 -> 345 us), and 256 in all leave it waiting for the largest (two batches of 256 seeds with whole
+// neighbourhoods on the products-shaped graph 397 -> 391 us per batch; without such hubs it is even: (20,20,20) 2735
+// against 2744, (100,100) 256 against 257).  Four batches of 2.4 M records are 10 us better off with 128.
 constexpr int kPartSplitLgB = 7;
 constexpr int part_split_lg(int batches) { return batches <= 2 ? kPartSplitLgB + 1 : kPartSplitLgB; }
 __host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2, int batches = SMFG_MAX_BATCHES) {
@@ -211,10 +213,11 @@ __global__ void __launch_bounds__(kThreads) k_scan_hist(const Launch P) {
 }
 
 // ---- records to buckets, in rounds staged through LDS ------------------------------------------
-// A block that moves records to buckets takes them in rounds of kScatterPer per thread: the round's records are counted per bucket (each gets its rank within its bucket by an
-// LDS atomicAdd), the counts are scanned, the records are put in bucket order into a staging
-// array in LDS and written out in that order, so that what a bucket receives from a round leaves
-// as one run of consecutive addresses.  gbase[b] is where the block's next record of bucket b goes.
+// A block that moves records to buckets takes them in rounds of kScatterPer per thread: the round's
+// records are counted per bucket (each gets its rank within its bucket by an LDS atomicAdd), the
+// counts are scanned, the records are put in bucket order into a staging array in LDS and written
+// out in that order, so that what a bucket receives from a round leaves as one run of consecutive
+// addresses.  gbase[b] is where the block's next record of bucket b goes.
 constexpr int kScatterPer = 8;
 constexpr int kStageBuckets = 1 << (kPartMaxLgB > kPartMaxLg2 ? kPartMaxLgB : kPartMaxLg2);
 

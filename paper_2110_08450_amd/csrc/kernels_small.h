@@ -1,9 +1,9 @@
-// libsmfg small calls: three launches per hop, whatever is in it.
+// libsmfg small hops: three launches per hop, whatever is in it.
 //
-// A hop of at most some ten thousand records keeps no kernel busy for longer than its launch and a chain
-// of dependent reads take (about 5 us together), so what counts is how many there are:
+// A hop of fewer than kSmallRecords records keeps no kernel busy for much longer than its launch and a
+// chain of dependent reads take (about 5 us together), so what counts is how many there are:
 //   draw    many blocks, since its scattered reads need many compute units to be in flight at once;
-//   dedup   kSmallBuckets blocks per batch, each reads all records, keeps those of its hash bucket and
+//   dedup   2^kSmallLgB blocks per batch, each reads all records, keeps those of its hash bucket and
 //           settles them in an LDS table: no histogram, no scatter;
 //   finish  blocks of consecutive destinations; each reads all entries of the hop, which gives it the
 //           first-appearance bits and their prefix sums in its own LDS, and then writes the final ids of

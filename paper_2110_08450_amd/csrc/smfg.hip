@@ -1,11 +1,13 @@
 // libsmfg: sampled mini-batch preparation on gfx950 (MI355X).  Implements include/smfg.h.
 // This file is the host side (handles, validation, launch sequences); the kernels live in
-// device_common.h (launch parameters, Philox, dedup table), kernels_fast.h (fanouts up to 32),
-// kernels_wide.h (larger fanouts, full neighbourhoods), kernels_gather.h, kernels_aggregate.h,
-// kernels_validate.h (the optional check of the input arrays).
+// device_common.h (launch parameters, Philox, dedup table), kernels_fast.h (the draw for fanouts up to 32,
+// table strategy), kernels_part.h (partition strategy), kernels_small.h (small hops), kernels_wide.h (larger
+// fanouts, full neighbourhoods), kernels_gather.h, kernels_aggregate.h, kernels_validate.h (the optional
+// check of the input arrays).
 //
-// One hop h of one batch is four launches (all batches of a call share each launch through
-// blockIdx.y):
+// All batches of a call share each launch (the batch is the fastest-varying part of the block index).  A
+// hop is three launches where it is small, six or more under the partition strategy (their files describe
+// both), and four under the table strategy:
 //   sample_insert  per destination: degree, Floyd/Philox row positions, neighbour ids, and an
 //                  insert of each neighbour into the batch's dedup table carrying the sample's
 //                  scan position (section 4.1 "fusing sampling and MFG construction": the edge
@@ -276,9 +278,11 @@ bool part_forced() {
   return e && std::strcmp(e, "partition") == 0;
 }
 
-// Calls whose largest hop stays below kPartMinRecords keep the table strategy: its four launches per
-// hop cost less than the partition strategy's seven when every kernel is launch-bound anyway.
+// Workspaces whose largest hop stays below kPartMinRecords are planned for the table strategy.  Such calls take
+// the small path as a rule (the limits are the same); the table serves those it does not take, with four
+// launches per hop against the partition strategy's six, all of them launch-bound.
 constexpr int64_t kPartMinRecords = 32768;
+static_assert(kPartMinRecords == kSmallRecords, "a table workspace's own calls are small");
 
 bool part_needs(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t num_nodes, int64_t node_capacity,
                 int64_t* rec_entries, int64_t* hist_entries, int* split_lg) {
@@ -444,7 +448,7 @@ int static_scratch_of(int device, void** out) {
 }
 
 // A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: hop
-// 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's seven
+// 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's six
 // launches, 21 us so.
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 // How many of a call's hops, counted from the first one, take the small path; rows[b][h] bounds the
