@@ -478,18 +478,17 @@ int small_hops_of(const smfg_workspace* const* ws, const int32_t* num_seeds, int
 // A call that leaves the gather to another one is prepared beside the gather of another set, whose many short
 // blocks keep taking the places that a block of 16 waves waits for.  How much that costs depends on what else
 // runs: with a model behind the pipeline (a layer per hop) sets of up to four batches still gain from fewer
-// launches, larger ones no longer; with nothing behind it all sets of two and more lose.  Tables that fit the
-// 256 MB cache behind the L2 make the gather short and neither way matters.  Time per batch without / with
-// small first hops, fanouts (15, 10, 5), 1024 seeds; graphs and tables as papers100M (28 GB), products (490 MB)
-// and arxiv (87 MB) have, and an eighth of papers100M (3.5 GB) with the model:
+// launches, larger ones hardly; with nothing behind it the largest graph loses from two batches on, all from
+// five.  Time per batch without / with small first hops, fanouts (15, 10, 5), 1024 seeds; graphs and tables as
+// papers100M (28 GB), products (490 MB) and arxiv (87 MB) have, and an eighth of papers100M with the model:
 //                        1 batch                  2 batches             4 batches              8 batches
 //   the call gathers     256/228 243/204 171/150  189/171 163/142 98/86 152/141 121/113 62/55  131/124 99/96 42/39 us
 //   beside a gather      243/237 154/141 146/127  163/171 109/107 62/56 129/142  90/92  42/41  111/122 83/84 34/33 us
 //   ... and a model      3, 4, 6, 7, 8 and 16 batches: 238/231, 234/228, 225/227, 228/226, 245/242, 230/228 us
+// The arxiv shape in long passes, sets of 5, 6, 8 and 16 beside a gather: 35.4/36.0, 33.0/33.5, 28.7/29.2, 25.2/26.5 us.
 constexpr int kCrowdedBatches = 4;
-constexpr int64_t kCachedTable = 128ll << 20;
 bool crowded_by_a_gather(const smfg_graph* g, bool gathers, int num_batches) {
-  return g->feat && !gathers && num_batches > kCrowdedBatches && g->num_nodes * g->row_stride > kCachedTable;
+  return g->feat && !gathers && num_batches > kCrowdedBatches;
 }
 SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows) {
   SmallLaunch S;

@@ -171,8 +171,7 @@ def test_small_set_with_a_workspace_per_batch(sizes):
 
 @pytest.mark.parametrize("num_batches,own_gather,small", [(16, True, True), (16, False, False), (5, False, False), (4, False, True)])
 def test_small_first_hop_of_a_larger_set(num_batches, own_gather, small):
-    """Ragged sets whose first hop is small and whose second one is not, gathered by the call or, with a
-    feature table beyond the cache, by another one."""
+    """Ragged sets whose first hop is small and whose second one is not, gathered by the call or by another one."""
     n, fan = 60_000, (6, 12)
     gg = random_graph(n, 24, 15)
     feat = torch.arange(n, dtype=torch.int32, device=DEV)[:, None].expand(n, 600).contiguous()

@@ -42,10 +42,9 @@ int32_t gather_vector(int64_t address, int64_t row_bytes) {
   const int v = vec_bytes(static_cast<uintptr_t>(address), 0, row_bytes, 0);
   return v == kAnyRow ? 16 : v;
 }
-int32_t crowded(int64_t num_nodes, int64_t row_stride, int32_t gathers, int32_t num_batches) {
+int32_t crowded(int64_t row_stride, int32_t gathers, int32_t num_batches) {
   smfg_graph g;
   std::memset(&g, 0, sizeof(g));
-  g.num_nodes = num_nodes;
   g.row_stride = row_stride;
   g.feat = row_stride > 0 ? reinterpret_cast<const uint8_t*>(256) : nullptr;
   return crowded_by_a_gather(&g, gathers != 0, num_batches) ? 1 : 0;
@@ -81,7 +80,7 @@ def host(tmp_path_factory):
     h.plan.argtypes, h.plan.restype = [i64, i32, i32, I32P, i64, i64], vp
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
-    h.crowded.argtypes = [i64, i64, i32, i32]
+    h.crowded.argtypes = [i64, i32, i32]
     h.levels.argtypes = [i32, i32, I32P]
     h.gather_block.argtypes, h.gather_vector.argtypes = [i64], [i64, i64]
     h.hist_entries.argtypes, h.hist_entries.restype = [vp], i64
@@ -159,12 +158,10 @@ def test_small_hops_of_ragged_sets(host):
 
 
 def test_which_calls_run_beside_a_gather(host):
-    """Only sets of five batches and more that leave the gather of a large table to another call."""
-    papers = (111_000_000, 256)
-    assert [host.crowded(*papers, 0, n) for n in (1, 2, 4, 5, 16)] == [0, 0, 0, 1, 1]
-    assert not host.crowded(*papers, 1, 8)                 # gathers itself
-    assert not host.crowded(papers[0], 0, 0, 8)            # no features: nobody gathers
-    assert [host.crowded(1 << 18, row, 0, 8) for row in (512, 513)] == [0, 1]
+    """Only sets of five batches and more that leave the gather to another call."""
+    assert [host.crowded(256, 0, n) for n in (1, 2, 4, 5, 16)] == [0, 0, 0, 1, 1]
+    assert not host.crowded(256, 1, 8)      # gathers itself
+    assert not host.crowded(0, 0, 8)        # no features: nobody gathers
 
 
 @pytest.mark.parametrize("num_nodes", [1 << 28, 500_000])
