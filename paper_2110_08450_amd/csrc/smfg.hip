@@ -449,7 +449,7 @@ int static_scratch_of(int device, void** out) {
 
 // A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: hop
 // 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's six
-// launches, 21 us so.
+// launches, 21 to 29 us so.
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 // How many of a call's hops, counted from the first one, take the small path; rows[b][h] bounds the
 // destinations of hop h of batch b.  Each batch is held against its own workspace: its samples sit at
