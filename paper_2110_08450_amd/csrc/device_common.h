@@ -48,11 +48,10 @@ struct BatchCtx {
   uint32_t table_shift;  // slot = hash >> shift
   uint32_t table_mask;
   // partition path (no table): records of a hop grouped by hash bucket
-  uint64_t* rec;         // (node << 32 | value) per known node and per sample, bucket by bucket
-  uint32_t* hist;        // [blocks x buckets] records per (row block, bucket), later their offsets
-  uint32_t* bstart;      // [buckets + 1] first record of each bucket; [buckets + 1 .. 2 buckets + 1) bucket sizes
-  uint64_t* rec2;        // the records once more, each bucket split into sub-buckets (hops with lg2 > 0)
-  uint32_t* bstart2;     // [buckets * sub-buckets + 1] first record of each sub-bucket in rec2
+  uint64_t* rec;         // (node << 32 | value) per known node and per sample, in segments sorted by bucket
+  uint16_t* hist;        // per segment, the first record of each bucket within it and the end of the last
+  uint64_t* rec2;        // the records once more, each bucket's of a range of segments sorted by sub-bucket (hops with lg2 > 0)
+  uint32_t* bstart2;     // [ranges][buckets][sub-buckets + 1] where each begins in rec2, and the end of the last
 };
 
 struct Launch {
@@ -68,11 +67,10 @@ struct Launch {
   int32_t h;       // current hop
   int32_t d;       // its fanout
   int32_t G;       // batches
-  int32_t lgB;     // partition path: log2 of the hash buckets of this hop
-  int32_t lg2;     // partition path: log2 of the sub-buckets each bucket is split into (0: not split)
-  int32_t block_rows;  // partition path: destinations per row block of this hop
-  int32_t flat;    // partition path over exact offsets: lgB / lg2 are upper bounds, the hop's own
-                   // shape follows from its record count on the device (hop_shape)
+  int32_t lgB;     // partition path: log2 of the most hash buckets of this hop in one level
+  int32_t lg;      // partition path: log2 of the most buckets, or sub-buckets in all (see hop_shape)
+  int32_t block_rows;  // partition path: destinations per segment of this hop
+  int32_t flat;    // partition path over exact offsets: the hop's number of samples is known
   BatchCtx b[SMFG_MAX_BATCHES];
 };
 static_assert(sizeof(Launch) <= 4096, "kernel arguments are limited to 4 KB");
@@ -172,29 +170,64 @@ __global__ void __launch_bounds__(kThreads) k_fill_u32(uint32_t* p, int64_t n, u
 }
 
 // ---- block scan ------------------------------------------------------------------------------
-// Exclusive scan over a block of NT values; returns the exclusive prefix, total in `total`.  lds: NT / 64 words.
-template <int NT = kThreads>
-__device__ __forceinline__ unsigned long long block_exscan(unsigned long long x, unsigned long long* lds,
-                                                            unsigned long long& total) {
+// Inclusive scan over a wave: within rows of 16 lanes by shifts of 1, 2, 4 and 8, then the last lane of a row
+// to the row behind it, then of the lower half to the upper.  Six additions with the other lane's operand read in
+// place; the same by shuffles is six round trips through the LDS unit, with nothing to hide them in a block
+// that waits for its scan.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t from_lane(uint32_t x) {  // 0 where there is no such lane
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xF, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long from_lane(unsigned long long x) {
+  return static_cast<unsigned long long>(from_lane<CTRL, ROWS>(static_cast<uint32_t>(x >> 32))) << 32 |
+         from_lane<CTRL, ROWS>(static_cast<uint32_t>(x));
+}
+template <typename T>
+__device__ __forceinline__ T wave_inscan(T x) {
+  x += from_lane<0x111, 0xF>(x);  // row_shr:1
+  x += from_lane<0x112, 0xF>(x);
+  x += from_lane<0x114, 0xF>(x);
+  x += from_lane<0x118, 0xF>(x);
+  x += from_lane<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x += from_lane<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Exclusive scan over a block of NT values (uint32_t or unsigned long long); returns the exclusive prefix, total in
+// `total`.  lds: NT / 64 words.
+template <int NT = kThreads, typename T>
+__device__ __forceinline__ T block_exscan(T x, T* lds, T& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long inc = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long y = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += y;
-  }
+  const T inc = wave_inscan(x);
   __syncthreads();
   if (lane == 63) lds[wave] = inc;
   __syncthreads();
-  unsigned long long base = 0, tot = 0;
+  T base = 0, tot = 0;
 #pragma unroll
   for (int w = 0; w < NT / 64; ++w) {
-    const unsigned long long v = lds[w];
+    const T v = lds[w];
     if (w < wave) base += v;
     tot += v;
   }
   total = tot;
   return base + inc - x;
+}
+
+// The largest value over a block of NT.
+template <int NT>
+__device__ __forceinline__ uint32_t block_max(uint32_t x, uint32_t* lds) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_xor(x, o, 64);
+    x = x > y ? x : y;
+  }
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) x = x > lds[w] ? x : lds[w];
+  return x;
 }
 
 }  // namespace smfg_dev

@@ -78,39 +78,28 @@ struct DivD {
 // for one word of it, the rule settled by a shuffle and a ballot per slot, three destinations of
 // fanout 20 per wave) a hop of 1.47 M destinations x 20 took 415 us, this way 222 us, and 61 -> 22 us
 // for one of 77 K; 1.41 M x 5 stays at 116 us, which is 0.58 GB of 128-byte lines at 5 TB/s.
-constexpr int kDrawAhead = 4;
 constexpr uint32_t kNoSample = 0xFFFFFFFFu;  // no node id, no tagged position
 constexpr uint32_t draw_stride(uint32_t d) { return d | 1u; }  // odd: the settling lanes hit different banks
 
-template <int NT, int WORDS>  // threads of the block, LDS words for the draws of a turn
+template <int ROWS, int WORDS>  // most destinations of a turn, LDS words for their draws
 struct DrawLds {
-  int64_t start[NT];     // first CSR position of the destination's row
-  uint32_t node[NT];
-  uint32_t deg[NT];
+  int64_t start[ROWS];   // first CSR position of the destination's row
+  uint32_t node[ROWS];
+  uint32_t deg[ROWS];
   uint32_t draw[WORDS];  // [destination][slot], rows of draw_stride(d): row positions
-
-  // Destinations per turn of a block that owns `rows` of them: turns of equal size.
-  static __device__ __forceinline__ int turn(int d, int rows) {
-    int most = WORDS / static_cast<int>(draw_stride(static_cast<uint32_t>(d)));
-    most = most < NT ? most : NT;
-    const int turns = (rows + most - 1) / most;
-    return turns > 1 ? (rows + turns - 1) / turns : rows;
-  }
 };
 
-// Destinations ids[i0 .. i0 + rows) (rows <= a turn's); one that is no node of the graph has no samples,
-// and on_stray() is called for it.  on_row(i, node, samples) is called once per
-// destination, on_sample(position, neighbour) once per sample; positions are i * d + slot.  ALL: also once
-// per position that has no sample, with kNoSample.  All threads of the block call; the block must synchronise before the LDS is used again.
-template <int D, bool ALL, int NT, int WORDS, typename Call, typename Batch, typename OnStray, typename OnRow,
-          typename OnSample>
-__device__ __forceinline__ void draw_tile(const Call& P, const Batch& B, int h, uint32_t d, const int32_t* ids,
-                                          DrawLds<NT, WORDS>& S, int i0, int rows, OnStray on_stray, OnRow on_row,
-                                          OnSample on_sample) {
+// Destinations ids[i0 .. i0 + rows) (at most ROWS of them): their rows and, where one is not taken whole, the
+// row positions of its samples -> S.  One that is no node of the graph has no samples, and on_stray() is
+// called for it.  on_row(i, node, samples) is called once per destination.  All threads of the block call,
+// and all find S complete on return.
+template <int D, int NT, int ROWS, int WORDS, typename Call, typename Batch, typename OnStray, typename OnRow>
+__device__ __forceinline__ void draw_positions(const Call& P, const Batch& B, int h, uint32_t d, const int32_t* ids,
+                                               DrawLds<ROWS, WORDS>& S, int i0, int rows, OnStray on_stray, OnRow on_row) {
   static_assert(D <= 32, "the picks of a destination are kept in registers");
   const uint32_t ld = draw_stride(d);
-  if (static_cast<int>(threadIdx.x) < rows) {
-    const int i = i0 + threadIdx.x;
+  for (int r = threadIdx.x; r < rows; r += NT) {
+    const int i = i0 + r;
     const int32_t id = ids[i];
     const uint32_t v = static_cast<uint32_t>(id);
     int64_t a = 0;
@@ -122,9 +111,9 @@ __device__ __forceinline__ void draw_tile(const Call& P, const Batch& B, int h, 
       a = P.indptr[v];
       deg = static_cast<uint32_t>(P.indptr[v + 1] - a);
     }
-    S.start[threadIdx.x] = a;
-    S.node[threadIdx.x] = v;
-    S.deg[threadIdx.x] = deg;
+    S.start[r] = a;
+    S.node[r] = v;
+    S.deg[r] = deg;
     on_row(i, v, deg > d ? d : deg);
   }
   __syncthreads();
@@ -146,10 +135,11 @@ __device__ __forceinline__ void draw_tile(const Call& P, const Batch& B, int h, 
     }
   }
   __syncthreads();
-  if (static_cast<int>(threadIdx.x) < rows && S.deg[threadIdx.x] > d) {
+  for (int r = threadIdx.x; r < rows; r += NT) {
+    if (S.deg[r] <= d) continue;
     // Floyd's subset algorithm: pick t_s unless an earlier slot holds it, then pick j_s
-    uint32_t* t = S.draw + threadIdx.x * ld;
-    const uint32_t j0 = S.deg[threadIdx.x] - d;
+    uint32_t* t = S.draw + r * ld;
+    const uint32_t j0 = S.deg[r] - d;
     uint32_t p[D];
 #pragma unroll
     for (int s = 0; s < D; ++s) p[s] = s < static_cast<int>(d) ? t[s] : 0u;
@@ -167,28 +157,23 @@ __device__ __forceinline__ void draw_tile(const Call& P, const Batch& B, int h, 
     }
   }
   __syncthreads();
-  const DivD div(d);
-  const uint32_t cnt = static_cast<uint32_t>(rows) * d;
-  const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
-  for (uint32_t base = threadIdx.x; base < cnt; base += NT * kDrawAhead) {
-    uint32_t g[kDrawAhead];
-    bool has[kDrawAhead];
+}
+
+// The neighbours of the destinations that draw_positions settled, kAhead of them per thread from the idx-th
+// padded position of the tile on, NT apart; kNoSample where there is none.
+template <int NT, int kAhead, int ROWS, int WORDS, typename Call>
+__device__ __forceinline__ void read_neighbours(const Call& P, const DivD& div, const DrawLds<ROWS, WORDS>& S,
+                                                uint32_t base, uint32_t cnt, uint32_t (&g)[kAhead]) {
+  const uint32_t d = div.d, ld = draw_stride(d);
 #pragma unroll
-    for (int u = 0; u < kDrawAhead; ++u) {
-      const uint32_t idx = base + u * NT;
-      uint32_t r = 0, s = 0;
-      if (idx < cnt) div.split(idx, r, s);
-      const uint32_t deg = S.deg[r];
-      has[u] = idx < cnt && s < deg;
-      const uint32_t p = deg > d ? S.draw[r * ld + s] : s;  // whole row in CSR order when deg <= d
-      // a neighbour id is read once per batch: keep it out of the way of data that is reused
-      g[u] = has[u] ? static_cast<uint32_t>(__builtin_nontemporal_load(P.indices + (S.start[r] + p))) : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < kDrawAhead; ++u) {
-      if (has[u]) on_sample(pos0 + base + u * NT, g[u]);
-      else if (ALL && base + u * NT < cnt) on_sample(pos0 + base + u * NT, kNoSample);
-    }
+  for (int u = 0; u < kAhead; ++u) {
+    const uint32_t idx = base + u * NT;
+    uint32_t r = 0, s = 0;
+    if (idx < cnt) div.split(idx, r, s);
+    const uint32_t deg = S.deg[r];
+    const uint32_t p = deg > d ? S.draw[r * ld + s] : s;  // whole row in CSR order when deg <= d
+    // a neighbour id is read once per batch: keep it out of the way of data that is reused
+    g[u] = idx < cnt && s < deg ? static_cast<uint32_t>(__builtin_nontemporal_load(P.indices + (S.start[r] + p))) : kNoSample;
   }
 }
 

@@ -2,17 +2,16 @@
 //
 // Procedure OneHopMFG keeps one map from global to local ids and gives a node its local id at the
 // first encounter.  Here the map never exists as one structure in memory.  Per hop:
-//   sample_hist   draws the neighbours (draw_tile) into gsrc and counts, per block
-//                 of destinations, how many records fall into each hash bucket; a record is
-//                 (node, value): one per known node (value = its local id) and one per sample
-//                 (value = tag | scan position);
-//   scan_hist     turns the counts of a bucket over the row blocks into offsets, bucket sizes;
-//   scatter       moves the records into their buckets (one contiguous range of `rec` each);
-//   split_buckets only for hops with more records than 1024 buckets of the target size hold (such
+//   sample_part   a block of destinations draws its neighbours into gsrc and sorts its records by hash bucket
+//                 in LDS; a record is (node, value): one per known node (value = its local id) and one per
+//                 sample (value = tag | scan position).  The sorted records, a segment, and where each
+//                 bucket begins within it go to memory side by side with the other blocks';
+//   split_buckets only for hops with more records than 2^kPartMaxLgB buckets of the target size hold (such
 //                 a hop starts with fewer, larger buckets, see part_levels): one block per bucket
-//                 orders the bucket's records by further hash bits into sub-buckets (`rec2`),
-//                 which then take the place of the buckets;
-//   dedup_buckets one block per bucket builds a hash table of the bucket's nodes in LDS, keeping
+//                 collects the bucket's records from all segments and orders them by further hash bits into
+//                 sub-buckets (`rec2`), which then take the place of the buckets;
+//   dedup_buckets one block per bucket collects the bucket's records from all segments and builds a hash table
+//                 of its nodes in LDS, keeping
 //                 the smallest value per node (a known node's local id always wins, else the
 //                 earliest scan position).  A sample that is its node's first appearance keeps
 //                 its gsrc entry (the node id, bit 31 clear); every other sample's entry is
@@ -26,16 +25,21 @@
 #ifndef SMFG_KERNELS_PART_H_
 #define SMFG_KERNELS_PART_H_
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels_fast.h"
 
 namespace smfg_dev {
 
-constexpr int kPartMaxLgB = 10;                     // at most 1024 buckets per hop and level ...
+constexpr int kPartMaxLgB = 11;                     // at most 2048 buckets per hop ...
 constexpr int kPartMaxLg2 = 10;                     // ... each split into at most 1024 sub-buckets
-constexpr int kPartTableLg = 12;                    // LDS table: 4096 slots of 8 bytes
-constexpr uint32_t kPartSlots = 1u << kPartTableLg;
-constexpr int kPartBucketRecords = 2048;            // buckets are sized for at most this many on average
+constexpr int kPartTableLg = 11;                    // LDS table: 2048 slots
+constexpr int kPartBucketRecords = 1024;            // buckets are sized for at most this many on average ...
+constexpr int kPartFewRecords = 256;                // ... in hops that leave the chip idle for half or a quarter of it,
+constexpr int kPartBuckets = 512;                   // as long as a launch has fewer buckets than this
+constexpr int kPartMostRecords = 1228;              // before a second level begins
+constexpr int64_t kPartOneLevel = int64_t(kPartMostRecords + 1) << kPartMaxLgB;  // one level of buckets holds fewer
 constexpr int64_t kPartMaxRecords = static_cast<int64_t>(kPartBucketRecords) << (kPartMaxLgB + kPartMaxLg2);
 constexpr uint32_t kPartHash = 0x9E3779B1u;         // odd: node -> node * kPartHash is a bijection on 32 bits
 constexpr uint32_t kResolved = 0x80000000u;         // gsrc entry: low 30 bits = final local id of a known node
@@ -45,25 +49,24 @@ __device__ __forceinline__ uint32_t part_bucket(uint32_t node, int lgB) {
   return lgB == 0 ? 0u : (node * kPartHash) >> (32 - lgB);
 }
 
-// Buckets (2^lgB) and sub-buckets per bucket (2^lg2) of the current hop.  Padded positions: as the
-// host planned them from the worst case.  Exact offsets (P.flat): the worst case of a hop that
-// takes whole neighbourhoods is far above what a batch draws, so the shape follows the hop's
-// actual record count (known nodes + samples, both final before the first kernel that asks) and
-// the host's figures only bound it; grids are sized for the bound and surplus blocks leave.
-constexpr int kFlatBlock = 8192;  // stream elements (known nodes, then samples) per block of the flat kernels
+// Buckets (2^lgB) and sub-buckets per bucket (2^lg2) of the current hop, settled on the device: the host's figures
+// come from the most destinations and samples a hop can have and only bound them (whole neighbourhoods: far
+// less than all edges of the graph).  Grids are sized for the bound and surplus blocks leave.
+// A block of k_dedup_buckets takes about as long for a bucket of 256 records as for one of 1024, some 7 us of dependent
+// reads and barriers, so a hop has as few buckets as fill the chip, and as large ones as the registers of a
+// block hold: 1.0 M records in each of eight batches 69 us with buckets of 1000, 77 with 500; 410 K records in
+// four batches 7 us with 512 buckets, 14 with 64.  One level ends where the parts of a bucket become so short, two
+// records of a segment of 4096, that beside another set's gather every one of them is a line from memory: 5.6 M
+// records per batch, pipelined, 326 us per batch with two levels and 400 with 4096 buckets (alone 113 and 124 us); for 2.4 M
+// it is 180 us with 2048 buckets and 177 with two levels, alone 115 and 168 per set of four.
 struct HopShape {
   int lgB, lg2;
 };
 // 2^lg buckets in all: one level up to 2^kPartMaxLgB of them; beyond that two levels, the first of
-// only 2^kPartSplitLgB buckets (more if the second would exceed 2^kPartMaxLg2), so that what a
-// block sends to a bucket per round is a run of a sector or more and the lines it is filling stay
-// in the L2 until they are full.  One or two batches take twice as many, because each first-level bucket
-// is one block of k_split_buckets: 128 of them leave half the chip idle (one batch of 29 M records: scatter +
-// split 414 -> 345 us), and 256 in all leave it waiting for the largest (two batches of 256 seeds with whole
-// neighbourhoods on the products-shaped graph 397 -> 391 us per batch; without such hubs it is even: (20,20,20) 2735
-// against 2744, (100,100) 256 against 257).  Four batches of 2.4 M records are 10 us better off with 128.
-constexpr int kPartSplitLgB = 7;
-constexpr int part_split_lg(int batches) { return batches <= 2 ? kPartSplitLgB + 1 : kPartSplitLgB; }
+// 2^kPartSplitLgB buckets (more if the second would exceed 2^kPartMaxLg2), of which a segment of 4096 records
+// has a part of 16, a line of 128 bytes, to be read by k_split_buckets.
+constexpr int kPartSplitLgB = 8;
+constexpr int part_split_lg(int) { return kPartSplitLgB; }  // whatever the number of batches
 __host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2, int batches = SMFG_MAX_BATCHES) {
   if (lg <= kPartMaxLgB) {
     lgB = lg;
@@ -74,20 +77,74 @@ __host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2, int batc
   lgB = lg - kPartMaxLg2 > least ? lg - kPartMaxLg2 : least;
   lg2 = lg - lgB;
 }
+// log2 of the buckets for that many records of a batch, `most` at most.
+__host__ __device__ inline int part_buckets_lg(long long records, int batches, int most) {
+  int lg = 0;
+  while (lg < most && ((records >> lg) > (lg < kPartMaxLgB ? kPartBucketRecords : kPartMostRecords) || ((records >> lg) > kPartFewRecords && (batches << lg) < kPartBuckets))) ++lg;
+  return lg;
+}
+// Records: known nodes and sample positions, or samples where their number is known (P.flat); both are
+// final before the first kernel that asks.
 __device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B) {
-  HopShape s{P.lgB, P.lg2};
+  const long long n = B.counts[P.h];
+  const long long records = P.flat ? n + B.counts[P.L + 1 + P.h] : n * (1 + P.d);
+  HopShape s;
+  part_levels(part_buckets_lg(records, P.G, P.lg), s.lgB, s.lg2, P.G);
+  if (s.lg2 == 0 && s.lgB > P.lgB) s.lgB = P.lgB;
+  return s;
+}
+
+// ---- segments ------------------------------------------------------------------------------------
+// The records of one block sorted by bucket: segment g is rec[g * cap ..), bucket b's part of it
+// [offs[b], offs[b + 1]) of its row of `hist`, offsets within the segment.  A bucket is the union of its parts
+// of all segments.  So no block has to know what the others hold before it writes.  With buckets of one
+// contiguous range each, the counts of all blocks had to be scanned between a kernel that counted and one that
+// read the samples back and moved the records: 1.0 M records in each of eight batches 179 us for
+// the three, 119 us for k_sample_part, which draws in 116 us of scattered reads and sorts beside them; its buckets'
+// many short parts cost k_dedup_buckets some us (59 -> 63).  29 M records of one batch (two levels): 575 -> 360 us.
+// Blocks are of 256 threads, whose places a gather beside them leaves free often enough (whole neighbourhoods,
+// pipelined: k_part_flat with 1024 threads 780 us, 56 alone).  Segments of 4096 records, 16 per thread, instead of 2048
+// where a hop has more than 512 of those: k_dedup_buckets 78 -> 67 us, k_sample_part the same; 8192 records gain
+// nothing more, and cost fanout 20 its occupancy (230 -> 293 us).
+constexpr int kSegPer = 16;                       // most records of a segment per thread of its block
+constexpr int kSegMax = kSegPer * kThreads;
+__host__ __device__ constexpr uint32_t offs_stride(int lgB) { return ((1u << lgB) + 3u) & ~1u; }  // whole 4-byte words
+// Most destinations of fanout d in a segment of `per` records per thread, and the least that a full one holds.
+__host__ __device__ constexpr int seg_rows(int per, int d) {
+  return per * kThreads / (1 + d) < per / 4 * kThreads ? per * kThreads / (1 + d) : per / 4 * kThreads;
+}
+__host__ __device__ constexpr int seg_least(int d) { return seg_rows(kSegPer, d) * (1 + d); }
+// Exact offsets: records per segment, a multiple of 1024 settled on the device from the hop's record count, so
+// that a launch has some 512 segments where it can.
+__device__ __forceinline__ uint32_t flat_seg(const Launch& P, uint32_t records) {
+  const uint32_t per = (records / 512u * static_cast<uint32_t>(P.G) + 1023u) & ~1023u;
+  return per < 1024u ? 1024u : per > static_cast<uint32_t>(kSegMax) ? static_cast<uint32_t>(kSegMax) : per;
+}
+struct Segments {
+  uint32_t count, cap;
+};
+__device__ __forceinline__ Segments hop_segments(const Launch& P, const BatchCtx& B) {
+  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
+  Segments s;
   if (P.flat) {
-    const long long records = B.counts[P.h] + B.counts[P.L + 1 + P.h];
-    int lg = 0;
-    while (lg < P.lgB + P.lg2 && (records >> lg) > kPartBucketRecords) ++lg;
-    part_levels(lg, s.lgB, s.lg2, P.G);
+    const uint32_t records = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
+    s.cap = flat_seg(P, records);
+    s.count = (records + s.cap - 1u) / s.cap;
+  } else {
+    s.cap = static_cast<uint32_t>(P.block_rows) * static_cast<uint32_t>(1 + P.d);
+    s.count = (n + static_cast<uint32_t>(P.block_rows) - 1u) / static_cast<uint32_t>(P.block_rows);
   }
   return s;
 }
-// Row blocks (padded positions) or flat blocks (exact offsets) of the current hop.
-__device__ __forceinline__ int hop_blocks(const Launch& P, const BatchCtx& B) {
-  if (P.flat) return static_cast<int>((B.counts[P.h] + B.counts[P.L + 1 + P.h] + kFlatBlock - 1) / kFlatBlock);
-  return static_cast<int>((B.counts[P.h] + P.block_rows - 1) / P.block_rows);
+
+// Buckets are dealt to blocks so that neighbouring buckets, whose parts share lines in every segment, run on
+// the same XCD (workgroups go to the XCDs in turn, a batch's to 8 / gcd(8, batches) of them).
+constexpr uint32_t kXcds = 8;
+__device__ __forceinline__ uint32_t bucket_of_block(const Launch& P, uint32_t i, uint32_t buckets) {
+  const uint32_t g = static_cast<uint32_t>(P.G);
+  const uint32_t ways = g % 8u == 0u ? 1u : g % 4u == 0u ? 2u : g % 2u == 0u ? 4u : kXcds;
+  if (buckets < ways) return i;
+  return (i % ways) * (buckets / ways) + i / ways;
 }
 
 // counts <- (n_0, 0, ..., status 0); node_ids[0, n_0) <- seeds; labels of the seeds.  Seeds are
@@ -117,485 +174,439 @@ __global__ void __launch_bounds__(kThreads) k_begin(const Launch P) {
   }
 }
 
-// Samples of the block's destinations -> gsrc, rowk; per-bucket record counts -> hist row.
-// D: the fanout rounded up to 8, 16 or 32.
-template <int D>
-__global__ void __launch_bounds__(kThreads) k_sample_hist(const Launch P) {
-  __shared__ DrawLds<kThreads, 4096> S;
-  __shared__ uint32_t hist[1 << kPartMaxLgB];
-  const BatchCtx& B = P.b[batch_of_block(P)];
-  const int blk = block_in_batch(P);
-  if (block_has_status(B, P.L)) return;
-  const int n = static_cast<int>(B.counts[P.h]);
-  const int r0 = blk * P.block_rows;
-  if (r0 >= n) return;
-  const int r1 = r0 + P.block_rows < n ? r0 + P.block_rows : n;
-  const int nB = 1 << P.lgB;
-  for (int b = threadIdx.x; b < nB; b += kThreads) hist[b] = 0u;
-  __syncthreads();
-  const int turn = S.turn(P.d, P.block_rows);
-  for (int i0 = r0; i0 < r1; i0 += turn) {
-    draw_tile<D, false>(
-        P, B, P.h, static_cast<uint32_t>(P.d), B.node_ids, S, i0, r1 - i0 < turn ? r1 - i0 : turn,
-        [&] { set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE); },
-        [&](int i, uint32_t v, uint32_t k) {
-          B.rowk[i] = static_cast<int32_t>(k);
-          atomicAdd(&hist[part_bucket(v, P.lgB)], 1u);  // the destination itself, a known node
-        },
-        [&](uint32_t pos, uint32_t g) {
-          B.gsrc[pos] = static_cast<int32_t>(g);
-          atomicAdd(&hist[part_bucket(g, P.lgB)], 1u);
-        });
-    __syncthreads();
-  }
-  uint32_t* out = B.hist + static_cast<size_t>(blk) * nB;
-  for (int b = threadIdx.x; b < nB; b += kThreads) out[b] = hist[b];
-}
-
-// Counts of a bucket over the row blocks -> exclusive offsets, and the bucket's size.  A thread
-// block takes kScanCols buckets; kScanSegs threads share a bucket, each a contiguous range of the
-// row blocks (sum, then the ranges' exclusive scan in LDS, then the offsets).
-constexpr int kScanCols = 32;
-constexpr int kScanSegs = kThreads / kScanCols;
-__global__ void __launch_bounds__(kThreads) k_scan_hist(const Launch P) {
-  __shared__ uint32_t part[kScanSegs][kScanCols];
-  const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const int blocks = hop_blocks(P, B);
-  const int nB = 1 << hop_shape(P, B).lgB;
-  const int c = threadIdx.x % kScanCols, seg = threadIdx.x / kScanCols;
-  const int b = block_in_batch(P) * kScanCols + c;
-  const int per = (blocks + kScanSegs - 1) / kScanSegs;
-  const int j0 = seg * per < blocks ? seg * per : blocks;
-  const int j1 = j0 + per < blocks ? j0 + per : blocks;
-  uint32_t* col = B.hist + (b < nB ? b : 0);
+// Exclusive scan of the counts cnt[0, nB) of a block's buckets in place, the total at cnt[nB], which is returned as
+// well.  All threads of the block call, and all find cnt complete on return.
+template <int NT>
+__device__ __forceinline__ uint32_t scan_counts(uint32_t* cnt, uint32_t nB, uint32_t* scan) {
+  const uint32_t per = nB > NT ? nB / NT : 1u;
   uint32_t sum = 0;
-  if (b < nB) {
-    int j = j0;
-    constexpr int U = 8;
-    for (; j + U <= j1; j += U) {
-      uint32_t t[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) t[u] = col[static_cast<size_t>(j + u) * nB];
-#pragma unroll
-      for (int u = 0; u < U; ++u) sum += t[u];
-    }
-    for (; j < j1; ++j) sum += col[static_cast<size_t>(j) * nB];
+  for (uint32_t u = 0; u < per; ++u) {
+    const uint32_t b = threadIdx.x * per + u;
+    if (b < nB) sum += cnt[b];
   }
-  part[seg][c] = sum;
+  uint32_t total;
+  uint32_t pre = block_exscan<NT>(sum, scan, total);
+  for (uint32_t u = 0; u < per; ++u) {
+    const uint32_t b = threadIdx.x * per + u;
+    if (b < nB) {
+      const uint32_t c = cnt[b];
+      cnt[b] = pre;
+      pre += c;
+    }
+  }
+  if (threadIdx.x == 0) cnt[nB] = total;
   __syncthreads();
-  if (b >= nB) return;
-  uint32_t run = 0, total = 0;
-#pragma unroll
-  for (int q = 0; q < kScanSegs; ++q) {
-    const uint32_t v = part[q][c];
-    if (q < seg) run += v;
-    total += v;
-  }
-  if (seg == 0) B.bstart[nB + 1 + b] = total;  // bucket size
-  int j = j0;
-  constexpr int U = 8;
-  for (; j + U <= j1; j += U) {
-    uint32_t t[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = col[static_cast<size_t>(j + u) * nB];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      col[static_cast<size_t>(j + u) * nB] = run;
-      run += t[u];
-    }
-  }
-  for (; j < j1; ++j) {
-    const uint32_t t = col[static_cast<size_t>(j) * nB];
-    col[static_cast<size_t>(j) * nB] = run;
-    run += t;
-  }
+  return total;
 }
-
-// ---- records to buckets, in rounds staged through LDS ------------------------------------------
-// A block that moves records to buckets takes them in rounds of kScatterPer per thread: the round's
-// records are counted per bucket (each gets its rank within its bucket by an LDS atomicAdd), the
-// counts are scanned, the records are put in bucket order into a staging array in LDS and written
-// out in that order, so that what a bucket receives from a round leaves as one run of consecutive
-// addresses.  gbase[b] is where the block's next record of bucket b goes.
-constexpr int kScatterPer = 8;
-constexpr int kStageBuckets = 1 << (kPartMaxLgB > kPartMaxLg2 ? kPartMaxLgB : kPartMaxLg2);
-
-template <int NT>  // threads of the block
-struct StageLds {
-  static constexpr int kRound = kScatterPer * NT;
-  static constexpr int kPer = kStageBuckets / NT;  // buckets per thread in the block scans
-  uint32_t gbase[kStageBuckets];
-  uint32_t cnt[kStageBuckets];
-  uint32_t lstart[kStageBuckets];
-  unsigned long long stage[kRound];
-  unsigned long long scan[NT / 64];
-};
-
-// gbase[b] <- first + exclusive scan of sizes[b] (+ offs[b] if given), b < nb; returns the total
-// of the sizes.  `write_starts`, if given, also receives first + the exclusive scan.
-template <int NT, typename SizeOf, typename OffOf, typename StartTo>
-__device__ __forceinline__ uint32_t stage_set_bases(StageLds<NT>& L, int nb, uint32_t first, SizeOf size_of, OffOf off_of,
-                                                     StartTo start_to) {
-  constexpr int kStagePer = StageLds<NT>::kPer;
-  uint32_t sz[kStagePer];
-  uint32_t mine = 0;
-#pragma unroll
-  for (int u = 0; u < kStagePer; ++u) {
-    const int b = threadIdx.x * kStagePer + u;
-    sz[u] = b < nb ? size_of(b) : 0u;
-    mine += sz[u];
-  }
-  unsigned long long total;
-  uint32_t pre = first + static_cast<uint32_t>(block_exscan<NT>(mine, L.scan, total));
-#pragma unroll
-  for (int u = 0; u < kStagePer; ++u) {
-    const int b = threadIdx.x * kStagePer + u;
-    if (b < nb) {
-      L.gbase[b] = pre + off_of(b);
-      start_to(b, pre);
-    }
-    pre += sz[u];
-  }
-  __syncthreads();
-  return static_cast<uint32_t>(total);
+// Counts of a segment's buckets, two to a word: a record's rank in its bucket, then where its bucket begins.
+__device__ __forceinline__ uint32_t count_packed(uint32_t* cnt, uint32_t b) {
+  const uint32_t shift = (b & 1u) * 16u;
+  return atomicAdd(&cnt[b >> 1], 1u << shift) >> shift & 0xFFFFu;
 }
-
-// One round: r[u] are this thread's records (kEmpty = none), bucket_of maps a node to its bucket
-// in [0, nb).  All threads of the block call.
-template <int NT, typename BucketOf>
-__device__ __forceinline__ void stage_round(StageLds<NT>& L, int nb, const unsigned long long (&r)[kScatterPer],
-                                            BucketOf bucket_of, uint64_t* __restrict__ dst) {
-  constexpr int kStagePer = StageLds<NT>::kPer;
-  __syncthreads();  // the previous round has been written out
-  for (int b = threadIdx.x; b < nb; b += NT) L.cnt[b] = 0u;
-  __syncthreads();
-  uint32_t bk[kScatterPer], rk[kScatterPer];
-#pragma unroll
-  for (int u = 0; u < kScatterPer; ++u) {
-    bk[u] = 0u;
-    rk[u] = 0u;
-    if (r[u] != kEmpty) {
-      bk[u] = bucket_of(static_cast<uint32_t>(r[u] >> 32));
-      rk[u] = atomicAdd(&L.cnt[bk[u]], 1u);
-    }
-  }
-  __syncthreads();
-  uint32_t c[kStagePer];
-  uint32_t mine = 0;
-#pragma unroll
-  for (int u = 0; u < kStagePer; ++u) {
-    const int b = threadIdx.x * kStagePer + u;
-    c[u] = b < nb ? L.cnt[b] : 0u;
-    mine += c[u];
-  }
-  unsigned long long total;
-  uint32_t pre = static_cast<uint32_t>(block_exscan<NT>(mine, L.scan, total));
-#pragma unroll
-  for (int u = 0; u < kStagePer; ++u) {
-    const int b = threadIdx.x * kStagePer + u;
-    if (b < nb) L.lstart[b] = pre;
-    pre += c[u];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kScatterPer; ++u)
-    if (r[u] != kEmpty) L.stage[L.lstart[bk[u]] + rk[u]] = r[u];
-  __syncthreads();
-  const uint32_t staged = static_cast<uint32_t>(total);
-  for (uint32_t t = threadIdx.x; t < staged; t += NT) {
-    const unsigned long long x = L.stage[t];
-    const uint32_t b = bucket_of(static_cast<uint32_t>(x >> 32));
-    dst[L.gbase[b] + (t - L.lstart[b])] = x;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kStagePer; ++u) {
-    const int b = threadIdx.x * kStagePer + u;
-    if (b < nb) L.gbase[b] += c[u];
-  }
-}
-
-// The first record of every bucket (exclusive scan of the bucket sizes k_scan_hist left) plus this
-// block's offset within each bucket; block 0 also stores the bucket starts for k_dedup_buckets.
+__device__ __forceinline__ uint32_t packed(const uint32_t* cnt, uint32_t b) { return cnt[b >> 1] >> ((b & 1u) * 16u) & 0xFFFFu; }
+// Exclusive scan of such counts in place, with the total behind them, and to the segment's row of hist.
 template <int NT>
-__device__ __forceinline__ void stage_bucket_bases(StageLds<NT>& L, const BatchCtx& B, int nB, int blk) {
-  const uint32_t* offs = B.hist + static_cast<size_t>(blk) * nB;
-  const uint32_t total = stage_set_bases(
-      L, nB, 0u, [&](int b) { return B.bstart[nB + 1 + b]; }, [&](int b) { return offs[b]; },
-      [&](int b, uint32_t start) {
-        if (blk == 0) B.bstart[b] = start;
-      });
-  if (blk == 0 && threadIdx.x == 0) B.bstart[nB] = total;
+__device__ __forceinline__ uint32_t segment_offsets(uint32_t* cnt, int lgB, uint16_t* __restrict__ row, uint32_t* scan) {
+  const uint32_t words = lgB == 0 ? 1u : 1u << (lgB - 1);
+  const uint32_t per = words > NT ? words / NT : 1u;
+  uint32_t sum = 0, total;
+  for (uint32_t u = 0; u < per; ++u) {
+    const uint32_t w = threadIdx.x * per + u;
+    if (w < words) sum += (cnt[w] & 0xFFFFu) + (cnt[w] >> 16);
+  }
+  uint32_t pre = block_exscan<NT>(sum, scan, total);
+  for (uint32_t u = 0; u < per; ++u) {
+    const uint32_t w = threadIdx.x * per + u;
+    if (w < words) {
+      const uint32_t c = cnt[w];
+      cnt[w] = pre | (pre + (c & 0xFFFFu)) << 16;
+      pre += (c & 0xFFFFu) + (c >> 16);
+    }
+  }
+  if (lgB > 0 && threadIdx.x == 0) cnt[words] = total;
+  __syncthreads();
+  for (uint32_t q = threadIdx.x; q < offs_stride(lgB) / 2u; q += NT) reinterpret_cast<uint32_t*>(row)[q] = cnt[q];
+  return total;
 }
 
-// Records of the block's destinations (its known nodes first, then its samples in position
-// order) -> their buckets.
-template <int NT>
-__global__ void __launch_bounds__(NT) k_scatter(const Launch P) {
-  __shared__ StageLds<NT> L;
+// Samples of the block's destinations -> gsrc, rowk; their records and the destinations' -> a segment.
+// D: the fanout rounded up to 8, 16 or 32.
+template <int D, int PER>
+__global__ void __launch_bounds__(kThreads) k_sample_part(const Launch P) {
+  constexpr int NT = kThreads, kRows = PER / 4;  // at most so many destinations per thread
+  __shared__ union {
+    DrawLds<kRows * NT, PER * NT> draw;
+    unsigned long long stage[PER * NT];
+  } S;
+  __shared__ uint32_t scan[NT / 64];
+  extern __shared__ uint32_t cnt[];  // offs_stride / 2 words
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
   const int blk = block_in_batch(P);
+  if (block_has_status(B, P.L)) return;
   const int n = static_cast<int>(B.counts[P.h]);
   const int r0 = blk * P.block_rows;
   if (r0 >= n) return;
-  const int r1 = r0 + P.block_rows < n ? r0 + P.block_rows : n;
-  const int nB = 1 << P.lgB;
-  stage_bucket_bases(L, B, nB, blk);
+  const int rows = n - r0 < P.block_rows ? n - r0 : P.block_rows;
   const uint32_t d = static_cast<uint32_t>(P.d);
-  const DivD div(d);
-  const uint32_t known = static_cast<uint32_t>(r1 - r0);
+  const int lgB = hop_shape(P, B).lgB;
+  for (uint32_t b = threadIdx.x; b < offs_stride(lgB) / 2u; b += NT) cnt[b] = 0u;
+  draw_positions<D, NT>(
+      P, B, P.h, d, B.node_ids, S.draw, r0, rows, [&] { set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE); },
+      [&](int i, uint32_t, uint32_t k) { B.rowk[i] = static_cast<int32_t>(k); });
+  const uint32_t samples = static_cast<uint32_t>(rows) * d;
   const uint32_t pos0 = static_cast<uint32_t>(r0) * d;
-  const uint32_t stream = known + known * d;  // known nodes, then the padded sample positions
-  for (uint32_t c0 = 0; c0 < stream; c0 += StageLds<NT>::kRound) {
-    unsigned long long rec[kScatterPer];
-    uint32_t k[kScatterPer], sl[kScatterPer], g[kScatterPer];
+  uint32_t g[PER], rk[PER], v[kRows], rv[kRows];
+  read_neighbours<NT>(P, DivD(d), S.draw, threadIdx.x, samples, g);
 #pragma unroll
-    for (int u = 0; u < kScatterPer; ++u) {
-      const uint32_t e = c0 + u * NT + threadIdx.x;
-      k[u] = 0u;
-      sl[u] = 0u;
-      g[u] = 0u;
-      if (e < known) {
-        g[u] = static_cast<uint32_t>(B.node_ids[r0 + static_cast<int>(e)]);
-        k[u] = 1u;
-      } else if (e < stream) {
-        uint32_t r;
-        div.split(e - known, r, sl[u]);
-        k[u] = static_cast<uint32_t>(B.rowk[r0 + static_cast<int>(r)]);
-        g[u] = static_cast<uint32_t>(B.gsrc[pos0 + (e - known)]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kScatterPer; ++u) {
-      const uint32_t e = c0 + u * NT + threadIdx.x;
-      rec[u] = kEmpty;
-      if (e < stream && sl[u] < k[u]) {
-        // a known node (destination i has local id i), or a sample: tag | position
-        const uint32_t val = e < known ? static_cast<uint32_t>(r0) + e : (kPend | (pos0 + (e - known)));
-        rec[u] = (static_cast<unsigned long long>(g[u]) << 32) | val;
-      }
-    }
-    stage_round(L, nB, rec, [&](uint32_t node) { return part_bucket(node, P.lgB); }, B.rec);
+  for (int u = 0; u < kRows; ++u) {
+    const int r = u * NT + static_cast<int>(threadIdx.x);
+    v[u] = r < rows ? S.draw.node[r] : kNoSample;
+    rv[u] = r < rows ? count_packed(cnt, part_bucket(v[u], lgB)) : 0u;
   }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    rk[u] = 0u;
+    if (g[u] != kNoSample) {
+      B.gsrc[pos0 + u * NT + threadIdx.x] = static_cast<int32_t>(g[u]);
+      rk[u] = count_packed(cnt, part_bucket(g[u], lgB));
+    }
+  }
+  __syncthreads();
+  const uint32_t total = segment_offsets<NT>(cnt, lgB, B.hist + static_cast<size_t>(blk) * offs_stride(lgB), scan);
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const uint32_t r = u * NT + threadIdx.x;
+    if (r < static_cast<uint32_t>(rows))
+      S.stage[packed(cnt, part_bucket(v[u], lgB)) + rv[u]] = (static_cast<unsigned long long>(v[u]) << 32) | (static_cast<uint32_t>(r0) + r);
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (g[u] != kNoSample)
+      S.stage[packed(cnt, part_bucket(g[u], lgB)) + rk[u]] =
+          (static_cast<unsigned long long>(g[u]) << 32) | (kPend | (pos0 + u * NT + threadIdx.x));
+  __syncthreads();
+  uint64_t* __restrict__ out = B.rec + static_cast<size_t>(blk) * (static_cast<uint32_t>(P.block_rows) * (1u + d));
+  for (uint32_t t = threadIdx.x; t < total; t += NT) out[t] = S.stage[t];
 }
 
-// Grid-stride over the buckets: a bucket's records, ordered by the lg2 hash bits below the
-// bucket's, go to the same range of rec2; the sub-buckets' first records go to bstart2.  A counting
-// pass over the bucket, then the staged rounds.  There are only 128 buckets or so, one block each, so
-// a block has to keep its compute unit busy alone: 16 waves, rounds of 8192 records (at 128 sub-buckets
-// a run of 512 bytes each), and a round's records are requested before the round before it is moved.
-// With 4 waves, 128 buckets and nothing requested ahead one batch's 29 M records took 449 us and 7.3 M 78
-// us; 241 and 41 us with 16 waves, 148 and 30 us with 256 buckets on top (part_split_lg).
-template <int NT>
-__global__ void __launch_bounds__(NT) k_split_buckets(const Launch P) {
-  constexpr uint32_t kRound = StageLds<NT>::kRound;
-  __shared__ StageLds<NT> L;
+// ---- second level ------------------------------------------------------------------------------
+// A block takes a bucket's parts of `range` consecutive segments and sorts their records by the lg2 hash bits below the
+// bucket's, so that a sub-bucket lies in parts as well, one per range: those of (range, bucket) go to the
+// place in rec2 that the records of lower buckets of the range leave free in front of it, and bstart2 keeps
+// where each of its sub-buckets begins.  range is such that a block's records fit its registers unless they are
+// far from evenly spread.
+// It reads every record once; a block per bucket, which counted the whole bucket before it moved anything, took 154 us
+// for 29 M records, and 129 us so.
+constexpr int kSplitThreads = kThreads;
+constexpr uint32_t kSplitMax = kSegPer * kSplitThreads;
+constexpr uint32_t kSplitAim = kSplitMax / 8u * 7u;  // some 8 standard deviations below
+__host__ __device__ inline uint32_t split_range(uint32_t cap, int lgB) {
+  const uint32_t per = static_cast<uint32_t>((static_cast<uint64_t>(kSplitAim) << lgB) / cap);
+  return per < 1u ? 1u : per;
+}
+
+__global__ void __launch_bounds__(kSplitThreads) k_split_buckets(const Launch P) {
+  constexpr int NT = kSplitThreads;
+  __shared__ union {
+    uint32_t list[kSplitMax];
+    unsigned long long stage[kSplitMax];
+  } S;
+  __shared__ uint32_t cnt[(1 << kPartMaxLg2) + 1], scan[NT / 64];
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const HopShape hs = hop_shape(P, B);
   if (hs.lg2 == 0) return;
-  const uint32_t nB1 = 1u << hs.lgB;
-  const int n2 = 1 << hs.lg2;
+  const Segments segs = hop_segments(P, B);
+  const uint32_t nB = 1u << hs.lgB, n2 = 1u << hs.lg2, stride = offs_stride(hs.lgB);
+  const uint32_t range = split_range(segs.cap, hs.lgB);
+  const uint32_t ranges = (segs.count + range - 1u) / range;
   const int shift = 32 - hs.lgB - hs.lg2;
-  const uint32_t mask = static_cast<uint32_t>(n2 - 1);
-  const auto sub_of = [&](uint32_t node) { return ((node * kPartHash) >> shift) & mask; };
-  for (uint32_t b1 = static_cast<uint32_t>(block_in_batch(P)); b1 < nB1;
-       b1 += static_cast<uint32_t>(blocks_per_batch(P))) {
-    const uint32_t rec0 = B.bstart[b1];
-    const uint32_t rec1 = rec0 + B.bstart[nB1 + 1 + b1];
-    const auto fetch = [&](uint32_t c0, unsigned long long (&r)[kScatterPer]) {
-#pragma unroll
-      for (int u = 0; u < kScatterPer; ++u) {
-        const uint32_t q = c0 + u * NT + threadIdx.x;
-        r[u] = q < rec1 ? B.rec[q] : kEmpty;
-      }
-    };
-    unsigned long long r[kScatterPer], ahead[kScatterPer];
-    __syncthreads();  // the previous bucket is done with the LDS arrays
-    for (int b = threadIdx.x; b < n2; b += NT) L.cnt[b] = 0u;
-    __syncthreads();
-    fetch(rec0, ahead);
-    for (uint32_t c0 = rec0; c0 < rec1; c0 += kRound) {
-#pragma unroll
-      for (int u = 0; u < kScatterPer; ++u) r[u] = ahead[u];
-      fetch(c0 + kRound, ahead);
-#pragma unroll
-      for (int u = 0; u < kScatterPer; ++u)
-        if (r[u] != kEmpty) atomicAdd(&L.cnt[sub_of(static_cast<uint32_t>(r[u] >> 32))], 1u);
+  const auto sub_of = [&](unsigned long long rec) { return ((static_cast<uint32_t>(rec >> 32) * kPartHash) >> shift) & (n2 - 1u); };
+  for (uint32_t i = static_cast<uint32_t>(block_in_batch(P)); i < ranges * nB; i += static_cast<uint32_t>(blocks_per_batch(P))) {
+    const uint32_t bucket = bucket_of_block(P, i % nB, nB);
+    const uint32_t s0 = i / nB * range, s1 = segs.count - s0 < range ? segs.count : s0 + range;
+    __syncthreads();  // the previous bucket is done with the LDS
+    for (uint32_t b = threadIdx.x; b < n2; b += NT) cnt[b] = 0u;
+    // how many records there are, how many of lower buckets, and where each is, while they fit
+    uint32_t total = 0, lower = 0, longest = 0;
+    for (uint32_t c0 = s0; c0 < s1; c0 += NT) {
+      const uint32_t s = c0 + threadIdx.x;
+      const uint16_t* at = B.hist + static_cast<size_t>(s) * stride + bucket;
+      const uint32_t start = s < s1 ? at[0] : 0u, size = s < s1 ? at[1] - start : 0u;
+      uint32_t turn, below;
+      const uint32_t to = total + block_exscan<NT>(size, scan, turn);
+      block_exscan<NT>(start, scan, below);
+      total += turn;
+      lower += below;
+      longest = longest > size ? longest : size;
+      if (total <= kSplitMax)
+        for (uint32_t j = 0; j < size; ++j) S.list[to + j] = s * segs.cap + start + j;
     }
-    fetch(rec0, ahead);
     __syncthreads();
-    stage_set_bases(
-        L, n2, rec0, [&](int b) { return L.cnt[b]; }, [](int) { return 0u; },
-        [&](int b, uint32_t start) { B.bstart2[(static_cast<size_t>(b1) << hs.lg2) + b] = start; });
-    if (b1 == nB1 - 1 && threadIdx.x == 0) B.bstart2[static_cast<size_t>(nB1) << hs.lg2] = rec1;
-    for (uint32_t c0 = rec0; c0 < rec1; c0 += kRound) {
+    const uint32_t rec0 = s0 * segs.cap + lower;
+    uint32_t* starts = B.bstart2 + static_cast<size_t>(i / nB * nB + bucket) * (n2 + 1u);
+    if (total <= kSplitMax) {
+      unsigned long long r[kSegPer];
+      uint32_t rk[kSegPer];
 #pragma unroll
-      for (int u = 0; u < kScatterPer; ++u) r[u] = ahead[u];
-      fetch(c0 + kRound, ahead);
-      stage_round(L, n2, r, sub_of, B.rec2);
+      for (int u = 0; u < kSegPer; ++u) {
+        const uint32_t q = u * NT + threadIdx.x;
+        r[u] = q < total ? B.rec[S.list[q]] : kEmpty;
+      }
+#pragma unroll
+      for (int u = 0; u < kSegPer; ++u) rk[u] = r[u] != kEmpty ? atomicAdd(&cnt[sub_of(r[u])], 1u) : 0u;
+      __syncthreads();
+      scan_counts<NT>(cnt, n2, scan);
+      for (uint32_t b = threadIdx.x; b <= n2; b += NT) starts[b] = rec0 + cnt[b];
+#pragma unroll
+      for (int u = 0; u < kSegPer; ++u)
+        if (r[u] != kEmpty) S.stage[cnt[sub_of(r[u])] + rk[u]] = r[u];
+      __syncthreads();
+      for (uint32_t t = threadIdx.x; t < total; t += NT) B.rec2[rec0 + t] = S.stage[t];
+    } else {  // read twice, written one by one
+      longest = block_max<NT>(longest, scan);
+      const auto each = [&](auto use) {
+        for (uint32_t q = threadIdx.x; q < (s1 - s0) * longest; q += NT) {
+          const uint32_t s = s0 + q / longest, j = q % longest;
+          const uint16_t* at = B.hist + static_cast<size_t>(s) * stride + bucket;
+          if (at[0] + j < at[1]) use(B.rec[static_cast<size_t>(s) * segs.cap + at[0] + j]);
+        }
+      };
+      each([&](unsigned long long rec) { atomicAdd(&cnt[sub_of(rec)], 1u); });
+      __syncthreads();
+      scan_counts<NT>(cnt, n2, scan);
+      for (uint32_t b = threadIdx.x; b <= n2; b += NT) starts[b] = rec0 + cnt[b];
+      __syncthreads();
+      each([&](unsigned long long rec) { B.rec2[rec0 + atomicAdd(&cnt[sub_of(rec)], 1u)] = rec; });
     }
   }
 }
 
-// Grid-stride over the (sub-)buckets, a block at a time.  All records of a node are in one bucket,
-// so the bucket's table in LDS sees every occurrence of its nodes.  A bucket with more records than the table takes is
-// handled in 2^lgR rounds, round r taking the nodes whose next lgR hash bits equal r; should a
-// round still overflow (skewed bits), the bucket starts over with one more bit.  With
-// 32 - lgB - lgR <= kPartTableLg bits left every node of a round has a slot of its own (the hash
-// is a bijection), so the retries end.
-// One record into the bucket's table: the slot of its node keeps the smallest value.  False if the
-// table has no slot left.
-template <uint32_t SLOTS>
-__device__ __forceinline__ bool dedup_insert(unsigned long long* tab, unsigned long long rec, uint32_t sl) {
+// ---- dedup -----------------------------------------------------------------------------------------
+// All records of a node are in one (sub-)bucket, so the bucket's table in LDS sees every occurrence of its nodes.
+// The table in LDS: a node and the smallest value of its records per slot, in arrays of their own, since LDS atomics on
+// 32 bits and reads of half the width make up for the second access (1.0 M records in eight batches 100 us with
+// 64-bit words, 88 so).
+template <int LG>
+struct DedupTable {
+  static constexpr uint32_t kSlots = 1u << LG;
+  uint32_t node[kSlots], least[kSlots];
+};
+constexpr uint32_t kNoNode = 0xFFFFFFFFu;
+
+template <int NT, int LG>
+__device__ __forceinline__ void dedup_clear(DedupTable<LG>& T) {
+  uint4* words = reinterpret_cast<uint4*>(&T);
+  for (uint32_t q = threadIdx.x; q < sizeof(T) / 16; q += NT) words[q] = make_uint4(kNoNode, kNoNode, kNoNode, kNoNode);
+}
+
+// One record into the bucket's table: the slot of its node keeps the smallest value.  False if none of
+// the first PROBES slots is free.
+template <uint32_t PROBES, int LG>
+__device__ __forceinline__ bool dedup_insert(DedupTable<LG>& T, unsigned long long rec, uint32_t& sl) {
   const uint32_t node = static_cast<uint32_t>(rec >> 32);
-  // A plain read first: a node sampled thousands of times (a hub) would otherwise queue
-  // thousands of atomics on one LDS word, while most of its records only need to see that
-  // a smaller value is there already.  Slots never lose their node, values only fall.
-  for (uint32_t probes = 0; probes < SLOTS; ++probes) {
-    unsigned long long old = tab[sl];
-    if (old == kEmpty) old = atomicCAS(&tab[sl], kEmpty, rec);
-    if (old == kEmpty) return true;
-    if (static_cast<uint32_t>(old >> 32) == node) {
-      if (old > rec) atomicMin(&tab[sl], rec);
+  // A plain read first: a node sampled thousands of times (a hub) would otherwise queue thousands of
+  // compare-and-swaps on one LDS word.  Slots never lose their node, values only fall.
+  for (uint32_t probes = 0; probes < PROBES; ++probes) {
+    uint32_t old = T.node[sl];
+    if (old == kNoNode) old = atomicCAS(&T.node[sl], kNoNode, node);
+    if (old == kNoNode || old == node) {
+      atomicMin(&T.least[sl], static_cast<uint32_t>(rec));
       return true;
     }
-    sl = (sl + 1u) & (SLOTS - 1u);
+    sl = (sl + 1u) & (T.kSlots - 1u);
   }
   return false;
 }
 
-// What the filled table says about one record: a known node must be alone with its id; a sample
-// that is not its node's smallest value learns the node's local id or the position of its first
-// appearance.
-template <uint32_t SLOTS, typename Call, typename Batch>
-__device__ __forceinline__ void dedup_settle(const Call& P, const Batch& B, const unsigned long long* tab,
-                                             unsigned long long rec, uint32_t sl) {
-  const uint32_t node = static_cast<uint32_t>(rec >> 32);
-  const uint32_t val = static_cast<uint32_t>(rec);
-  uint32_t least = 0u;
-  uint32_t probes = 0;
-  for (; probes < SLOTS; ++probes) {
-    const unsigned long long t = tab[sl];
-    if (static_cast<uint32_t>(t >> 32) == node) {
-      least = static_cast<uint32_t>(t);
-      break;
-    }
-    sl = (sl + 1u) & (SLOTS - 1u);
-  }
-  if (probes == SLOTS) {  // every inserted node is found again
-    set_status(B, P.L, SMFG_ST_INTERNAL);
-    return;
-  }
-  if (val < kPend) {
-    // a known node: two of them with one id can only be a repeated seed
-    if (least != val) set_status(B, P.L, SMFG_ST_DUPLICATE_SEED);
-  } else if (least != val) {
-    // least < kPend: the node's final local id; else least names the position of the first
-    // appearance (least == val: this sample is that first appearance, its entry stays)
+// What the smallest value of a record's node says about it: a sample that is not its node's smallest value learns the
+// node's local id or the position of its first appearance.  kRepeated for a known node that is not alone with its
+// id: two of them with one id can only be a repeated seed.
+constexpr uint32_t kRepeated = 1u, kLost = 2u;
+template <typename Batch>
+__device__ __forceinline__ uint32_t settle_record(const Batch& B, uint32_t val, uint32_t least) {
+  if (least == val) return 0u;  // a known node, or a first appearance, whose entry stays
+  // least < kPend: the node's final local id; else least names the position of the first appearance
+  if (val >= kPend)
     B.gsrc[val & ~kTagMask] =
         static_cast<int32_t>(least < kPend ? (kResolved | least) : (kPointer | (least & ~kTagMask)));
-  }
+  return val < kPend ? kRepeated : 0u;
+}
+template <typename Batch>
+__device__ __forceinline__ void report(const Batch& B, int L, uint32_t wrong) {
+  if (wrong != 0u) set_status(B, L, (wrong & kLost) != 0u ? SMFG_ST_INTERNAL : SMFG_ST_DUPLICATE_SEED);
 }
 
-// All records of a set that holds every record of its nodes: cnt of them, record(i) the i-th one or
-// kEmpty; `free_bits` hash bits are not yet spoken for.  tab: 2^LG slots of LDS, overflow: one LDS word.
-// All threads of the block (NT) call.
-template <int NT, int LG, typename Call, typename Batch, typename Record>
-__device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, unsigned long long* tab, int& overflow,
-                                              uint32_t cnt, int free_bits, Record record) {
-  constexpr uint32_t kSlots = 1u << LG;
-  constexpr int U = 8;  // records in flight per thread
-  const int max_lgR = free_bits > LG ? free_bits - LG : 0;
-  if (cnt <= NT * U && cnt <= kSlots / 2) {
-    // the usual bucket: its records stay in registers between the two passes, and a table at most
-    // half full cannot overflow
+// What the filled table says about one record.
+template <int LG, typename Batch>
+__device__ __forceinline__ uint32_t dedup_settle(const Batch& B, const DedupTable<LG>& T, unsigned long long rec, uint32_t sl) {
+  const uint32_t node = static_cast<uint32_t>(rec >> 32);
+  for (uint32_t probes = 0; probes < T.kSlots; ++probes) {
+    if (T.node[sl] == node) return settle_record(B, static_cast<uint32_t>(rec), T.least[sl]);
+    sl = (sl + 1u) & (T.kSlots - 1u);
+  }
+  return kLost;  // every inserted node is found again, unless the scratch is disturbed meanwhile
+}
+
+// All records of a set that holds every record of its nodes, which fit the registers of the block: U per
+// thread (kEmpty: none).  They stay there between the two passes, with the slot that the first one found; there
+// are no more than 2^LG of them, so that the table cannot overflow.  `free_bits` hash bits are not
+// yet spoken for.  All threads of the block (NT) call, none of which uses the table's LDS any more.
+template <int NT, int LG, int U, typename Call, typename Batch>
+__device__ __forceinline__ void dedup_in_registers(const Call& P, const Batch& B, DedupTable<LG>& T, int free_bits,
+                                                   const unsigned long long (&mine)[U]) {
+  const int down = free_bits > LG ? free_bits - LG : 0;
+  uint32_t sl[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) sl[u] = ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> down) & (T.kSlots - 1u);
+  dedup_clear<NT>(T);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (mine[u] != kEmpty) dedup_insert<(1u << LG)>(T, mine[u], sl[u]);
+  __syncthreads();
+  uint32_t wrong = 0u;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (mine[u] != kEmpty) wrong |= settle_record(B, static_cast<uint32_t>(mine[u]), T.least[sl[u]]);
+  report(B, P.L, wrong);
+  __syncthreads();
+}
+
+// The records of a (sub-)bucket that lies in parts: part_of(p, from, size) tells where the p-th of them is in recs and
+// how much it holds.  A thread per part, then a thread per record, which finds it through a list in the LDS:
+// that of the usual bucket then becomes its table, of a larger one (hubs among its nodes, as a rule, so few nodes for
+// its size) it stays in the upper half, a window of kList records at a time, and the records are read in both
+// passes.  Nodes that do not fit half the table are taken in 2^lgR rounds, round i those whose next lgR hash bits equal i; should a round still
+// overflow, the bucket starts over with one more bit.  With no more hash bits left than the slots have,
+// every node of a round has a slot of its own (the hash is a bijection), so the retries end.
+// U records per thread are kept in registers: 5 are what 64 of them hold, with which eight blocks share a compute unit
+// (with 8, and 88 registers, 1.0 M records in each of eight batches took 78 us instead of 69), and enough for
+// buckets of 1024 whatever their spread; 6 for those of 1228.
+template <int U, typename PartOf>
+__device__ __forceinline__ void dedup_parts(const Launch& P, const BatchCtx& B, DedupTable<kPartTableLg>& T, int& overflow,
+                                            uint32_t* scan, const uint64_t* __restrict__ recs, uint32_t parts, int free_bits,
+                                            PartOf part_of) {
+  constexpr int NT = kThreads;
+  constexpr int kPer = 4;  // parts per thread and turn
+  constexpr uint32_t kList = DedupTable<kPartTableLg>::kSlots;
+  static_assert(sizeof(T) == 2 * kList * sizeof(uint32_t), "the list takes the upper half");
+  uint32_t* list = reinterpret_cast<uint32_t*>(&T) + kList;
+  // few, longer parts: several threads to each, of which the first counts it
+  uint32_t lanes = 64u;
+  while (lanes > 1u && NT / lanes < parts) lanes /= 2u;
+  const uint32_t lane = threadIdx.x & (lanes - 1u);
+  // where the records w0 .. w0 + kList of the bucket are; returns how many it has in all
+  const auto find = [&](uint32_t w0) {
+    uint32_t cnt = 0;
+    for (uint32_t p0 = 0; p0 < parts; p0 += NT * kPer / lanes) {
+      uint32_t from[kPer], size[kPer], mine = 0, turn;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {  // every read on its way before the first is used
+        const uint32_t p = p0 + (u * NT + threadIdx.x) / lanes;
+        part_of(p < parts ? p : 0u, from[u], size[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        if (p0 + (u * NT + threadIdx.x) / lanes >= parts) size[u] = 0u;
+        mine += lane == 0u ? size[u] : 0u;
+      }
+      uint32_t to = cnt + block_exscan<NT>(mine, scan, turn) - w0;
+      if (lane != 0u) to -= size[0] + size[1] + size[2] + size[3];
+      cnt += turn;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        for (uint32_t j = lane; j < size[u]; j += lanes)
+          if (to + j < kList) list[to + j] = from[u] + j;
+        to += size[u];
+      }
+    }
+    __syncthreads();
+    return cnt;
+  };
+  const uint32_t cnt = find(0u);
+  if (cnt <= NT * U) {
     unsigned long long mine[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t r = u * NT + threadIdx.x;
-      mine[u] = r < cnt ? record(r) : kEmpty;
-    }
-    for (uint32_t q = threadIdx.x; q < kSlots; q += NT) tab[q] = kEmpty;
+    for (int u = 0; u < U; ++u) mine[u] = u * NT + threadIdx.x < cnt ? recs[list[u * NT + threadIdx.x]] : kEmpty;
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (mine[u] != kEmpty)
-        dedup_insert<kSlots>(tab, mine[u],
-                             ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> max_lgR) & (kSlots - 1u));
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (mine[u] != kEmpty)
-        dedup_settle<kSlots>(P, B, tab, mine[u],
-                             ((static_cast<uint32_t>(mine[u] >> 32) * kPartHash) >> max_lgR) & (kSlots - 1u));
-    __syncthreads();
+    if (cnt != 0u) dedup_in_registers<NT>(P, B, T, free_bits, mine);
     return;
   }
-  int lgR = 0;
-  while (lgR < max_lgR && (cnt >> lgR) > kSlots / 2) ++lgR;
-  for (;;) {
-    bool failed = false;
-    const int rem = free_bits - lgR;  // hash bits below the round's
-    const int down = rem > LG ? rem - LG : 0;
+  constexpr int kHalf = kPartTableLg - 1, kAhead = 4;
+  DedupTable<kHalf>& H = *reinterpret_cast<DedupTable<kHalf>*>(&T);
+  const int max_lgR = free_bits > kHalf ? free_bits - kHalf : 0;
+  uint32_t wrong = 0u;
+#pragma unroll 1
+  for (int lgR = 0; lgR <= max_lgR; ++lgR) {
+    const int rem = free_bits - lgR, down = rem > kHalf ? rem - kHalf : 0;
     const uint32_t rounds = 1u << lgR;
+    bool failed = false;
+#pragma unroll 1
     for (uint32_t round = 0; round < rounds && !failed; ++round) {
-      for (uint32_t q = threadIdx.x; q < kSlots; q += NT) tab[q] = kEmpty;
+      dedup_clear<NT>(H);
       if (threadIdx.x == 0) overflow = 0;
-      __syncthreads();
+#pragma unroll 1
       for (int pass = 0; pass < 2 && !failed; ++pass) {  // insert, then settle
-        for (uint32_t c0 = 0; c0 < cnt; c0 += NT * U) {
-          unsigned long long mine[U];
+#pragma unroll 1
+        for (uint32_t w0 = 0; w0 < cnt; w0 += kList) {
+          __syncthreads();
+          if (cnt > kList) find(w0);
+          const uint32_t here = cnt - w0 < kList ? cnt - w0 : kList;
+#pragma unroll 1
+          for (uint32_t r = threadIdx.x; r < here; r += NT * kAhead) {
+            unsigned long long mine[kAhead];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const uint32_t r = c0 + u * NT + threadIdx.x;
-            mine[u] = r < cnt ? record(r) : kEmpty;
-          }
+            for (int u = 0; u < kAhead; ++u) mine[u] = r + u * NT < here ? recs[list[r + u * NT]] : kEmpty;
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if (mine[u] == kEmpty) continue;
-            const uint32_t hsh = static_cast<uint32_t>(mine[u] >> 32) * kPartHash;
-            if (lgR != 0 && ((hsh >> rem) & (rounds - 1u)) != round) continue;
-            const uint32_t sl = (hsh >> down) & (kSlots - 1u);
-            if (pass == 0) {
-              if (!dedup_insert<kSlots>(tab, mine[u], sl)) overflow = 1;
-            } else {
-              dedup_settle<kSlots>(P, B, tab, mine[u], sl);
+            for (int u = 0; u < kAhead; ++u) {
+              const uint32_t hash = static_cast<uint32_t>(mine[u] >> 32) * kPartHash;
+              if (mine[u] == kEmpty || (lgR != 0 && ((hash >> rem) & (rounds - 1u)) != round)) continue;
+              uint32_t sl = (hash >> down) & (H.kSlots - 1u);
+              if (pass == 1) wrong |= dedup_settle(B, H, mine[u], sl);
+              else if (!dedup_insert<64>(H, mine[u], sl)) overflow = 1;
             }
           }
         }
         __syncthreads();
         failed = overflow != 0;
       }
+      __syncthreads();  // every thread has read the overflow word, and is done with the table
     }
     if (!failed) break;
-    if (lgR >= max_lgR) {  // cannot overflow with a slot per node
-      if (threadIdx.x == 0) set_status(B, P.L, SMFG_ST_INTERNAL);
-      break;
-    }
-    __syncthreads();  // every thread has read the overflow word before the next attempt clears it
-    ++lgR;
+    if (lgR == max_lgR) wrong |= kLost;  // cannot overflow with a slot per node
   }
+  report(B, P.L, wrong);
 }
 
-__global__ void __launch_bounds__(kThreads) k_dedup_buckets(const Launch P) {
-  __shared__ unsigned long long tab[kPartSlots];
+// LARGE: the hop may have two levels, or the largest buckets of one (the host's bound says so); then a block takes
+// several (sub-)buckets one after the other.
+template <bool LARGE>
+__global__ void __launch_bounds__(kThreads, LARGE ? 7 : 8) k_dedup_buckets(const Launch P) {
+  __shared__ __align__(16) DedupTable<kPartTableLg> T;
+  __shared__ uint32_t scan[kThreads / 64];
   __shared__ int overflow_lds;
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const HopShape hs = hop_shape(P, B);
-  const uint32_t nB = 1u << hs.lgB;
-  const uint64_t* __restrict__ recs = hs.lg2 == 0 ? B.rec : B.rec2;
-  for (uint32_t bucket = static_cast<uint32_t>(block_in_batch(P)); bucket < (nB << hs.lg2);
-       bucket += static_cast<uint32_t>(blocks_per_batch(P))) {
-    // the (sub-)bucket's records
-    const uint32_t rec0 = hs.lg2 == 0 ? B.bstart[bucket] : B.bstart2[bucket];
-    const uint32_t rec1 = hs.lg2 == 0 ? rec0 + B.bstart[nB + 1 + bucket] : B.bstart2[bucket + 1];
-    if (rec1 == rec0) continue;
-    dedup_records<kThreads, kPartTableLg>(P, B, tab, overflow_lds, rec1 - rec0, 32 - hs.lgB - hs.lg2,
-                                          [&](uint32_t i) { return recs[rec0 + i]; });
+  const Segments segs = hop_segments(P, B);
+  const bool two = LARGE && hs.lg2 != 0;
+  const uint32_t nB = 1u << hs.lgB, n2 = 1u << hs.lg2, all = nB << hs.lg2, stride = offs_stride(hs.lgB);
+  const uint32_t range = split_range(segs.cap, hs.lgB), parts = two ? (segs.count + range - 1u) / range : segs.count;
+  for (uint32_t i = static_cast<uint32_t>(block_in_batch(P)); i < all; i += static_cast<uint32_t>(blocks_per_batch(P))) {
+    const uint32_t bucket = bucket_of_block(P, i, all);
+    dedup_parts<LARGE ? 6 : 5>(P, B, T, overflow_lds, scan, two ? B.rec2 : B.rec, parts, 32 - hs.lgB - hs.lg2,
+                [&](uint32_t p, uint32_t& from, uint32_t& size) {
+                  if (two) {
+                    const uint32_t* at = B.bstart2 + static_cast<size_t>(p * nB + (bucket >> hs.lg2)) * (n2 + 1u) + (bucket & (n2 - 1u));
+                    from = at[0];
+                    size = at[1] - at[0];
+                  } else {
+                    const uint16_t* at = B.hist + static_cast<size_t>(p) * stride + bucket;
+                    from = p * segs.cap + at[0];
+                    size = static_cast<uint32_t>(at[1]) - at[0];
+                  }
+                });
     __syncthreads();
   }
 }

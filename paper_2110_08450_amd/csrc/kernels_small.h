@@ -78,24 +78,94 @@ __global__ void __launch_bounds__(kThreads) k_small_draw(const SmallLaunch P, in
   if (h == 0 && i0 == 0)
     for (int q = threadIdx.x; q < 2 * P.L + 2; q += kThreads) B.counts[q] = q == 0 ? n : 0;
   if (i0 >= n) return;
-  draw_tile<D, true>(
-      P, B, h, static_cast<uint32_t>(P.fanouts[h]), h == 0 ? B.seeds : B.node_ids, S, i0,
-      n - i0 < P.rows[h] ? n - i0 : P.rows[h], [] {},
+  const uint32_t d = static_cast<uint32_t>(P.fanouts[h]);
+  const int rows = n - i0 < P.rows[h] ? n - i0 : P.rows[h];
+  draw_positions<D, kThreads>(
+      P, B, h, d, h == 0 ? B.seeds : B.node_ids, S, i0, rows, [] {},
       [&](int i, uint32_t v, uint32_t k) {
         B.rowk[i] = static_cast<int32_t>(k);
         if (h == 0) {
           B.node_ids[i] = static_cast<int32_t>(v);
           if (B.labels && v < P.num_nodes) copy_label(P, B, i, static_cast<int32_t>(v));
         }
-      },
-      [&](uint32_t pos, uint32_t g) { B.gsrc[pos] = static_cast<int32_t>(g); });
+      });
+  const uint32_t cnt = static_cast<uint32_t>(rows) * d;
+  uint32_t g[1];  // a sample per thread
+  read_neighbours<kThreads>(P, DivD(d), S, threadIdx.x, cnt, g);
+  if (threadIdx.x < cnt) B.gsrc[static_cast<uint32_t>(i0) * d + threadIdx.x] = static_cast<int32_t>(g[0]);
+}
+
+// All records of a set that holds every record of its nodes: record(i) for i in [0, cnt) one of them or
+// kEmpty; `free_bits` hash bits are not yet spoken for.  More than half the table are handled in 2^lgR rounds, as
+// in dedup_parts.  overflow: one LDS word.  All threads of the block (NT) call.
+template <int NT, int LG, typename Call, typename Batch, typename Record>
+__device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, DedupTable<LG>& T, int& overflow,
+                                              uint32_t cnt, int free_bits, Record record) {
+  constexpr int U = 8;  // records in flight per thread
+  const int max_lgR = free_bits > LG ? free_bits - LG : 0;
+  if (cnt <= NT * U && cnt <= T.kSlots / 2) {
+    unsigned long long mine[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t r = u * NT + threadIdx.x;
+      mine[u] = r < cnt ? record(r) : kEmpty;
+    }
+    dedup_in_registers<NT>(P, B, T, free_bits, mine);
+    return;
+  }
+  uint32_t wrong = 0u;
+  int lgR = 0;
+  while (lgR < max_lgR && (cnt >> lgR) > T.kSlots / 2) ++lgR;
+  for (;;) {
+    bool failed = false;
+    const int rem = free_bits - lgR;  // hash bits below the round's
+    const int down = rem > LG ? rem - LG : 0;
+    const uint32_t rounds = 1u << lgR;
+    for (uint32_t round = 0; round < rounds && !failed; ++round) {
+      dedup_clear<NT>(T);
+      if (threadIdx.x == 0) overflow = 0;
+      __syncthreads();
+      for (int pass = 0; pass < 2 && !failed; ++pass) {  // insert, then settle
+        for (uint32_t c0 = 0; c0 < cnt; c0 += NT * U) {
+          unsigned long long mine[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const uint32_t r = c0 + u * NT + threadIdx.x;
+            mine[u] = r < cnt ? record(r) : kEmpty;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (mine[u] == kEmpty) continue;
+            const uint32_t hsh = static_cast<uint32_t>(mine[u] >> 32) * kPartHash;
+            if (lgR != 0 && ((hsh >> rem) & (rounds - 1u)) != round) continue;
+            uint32_t sl = (hsh >> down) & (T.kSlots - 1u);
+            if (pass == 0) {
+              if (!dedup_insert<(1u << LG)>(T, mine[u], sl)) overflow = 1;
+            } else {
+              wrong |= dedup_settle(B, T, mine[u], sl);
+            }
+          }
+        }
+        __syncthreads();
+        failed = overflow != 0;
+      }
+    }
+    if (!failed) break;
+    if (lgR >= max_lgR) {  // cannot overflow with a slot per node
+      wrong |= kLost;
+      break;
+    }
+    __syncthreads();  // every thread has read the overflow word before the next attempt clears it
+    ++lgR;
+  }
+  report(B, P.L, wrong);
 }
 
 // One block per (batch, bucket).  Blocks of other buckets rewrite entries while this one reads them; such
 // an entry is of no interest before (another bucket's node) nor after (bit 31 set).
 __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch P, int h) {
   constexpr int NT = kSmallThreads;
-  __shared__ unsigned long long tab[1 << kSmallTableLg];
+  __shared__ __align__(16) DedupTable<kSmallTableLg> T;
   __shared__ unsigned long long list[kSmallList];
   __shared__ uint32_t listed;
   __shared__ int overflow;
@@ -152,7 +222,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
   }
   __syncthreads();
   const bool fits = listed <= kSmallList;
-  dedup_records<NT, kSmallTableLg>(P, B, tab, overflow, fits ? listed : cnt, 32, [&](uint32_t i) {
+  dedup_records<NT>(P, B, T, overflow, fits ? listed : cnt, 32, [&](uint32_t i) {
     if (fits) return list[i];
     const uint32_t node = static_cast<uint32_t>(i < n ? B.node_ids[i] : B.gsrc[i - n]);
     return wanted(node) ? as_record(node, i) : kEmpty;

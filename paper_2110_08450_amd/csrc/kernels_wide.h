@@ -1,7 +1,7 @@
 // libsmfg wide path: fanouts above SMFG_MAX_FANOUT and SMFG_FANOUT_ALL, samples at exact block offsets.
 // count_rows / scan_count_tiles fix the offsets; then either the table strategy (sample_wide<true>,
-// flag_flat, scan_flat_tiles, assemble_flat) or the partition strategy (sample_wide<false>, hist_flat,
-// scan_hist, scatter_flat, [split_buckets], dedup_buckets, flag_flat_part, scan_flat_tiles,
+// flag_flat, scan_flat_tiles, assemble_flat) or the partition strategy (sample_wide<false>, part_flat,
+// [split_buckets], dedup_buckets, flag_flat_part, scan_flat_tiles,
 // assemble_flat_part) turns the samples into local ids.
 #ifndef SMFG_KERNELS_WIDE_H_
 #define SMFG_KERNELS_WIDE_H_
@@ -44,7 +44,7 @@ __global__ void __launch_bounds__(kThreads) k_count_rows(const Launch P) {
       B.rowk[i] = static_cast<int32_t>(k);
     }
     unsigned long long total;
-    const unsigned long long pre = block_exscan(k, lds, total);
+    const unsigned long long pre = block_exscan(static_cast<unsigned long long>(k), lds, total);
     if (i < n) B.rowoff[i] = static_cast<int32_t>(pre);
     if (threadIdx.x == 0) B.tile_sums[tile] = total;
     __syncthreads();
@@ -279,69 +279,48 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
 
 // ---- partition strategy over exact offsets ----------------------------------------------------
 // The records of a hop as one stream: element e < n is known node e, element n + pos the sample
-// at position pos.  A flat block owns kFlatBlock consecutive elements.
+// at position pos.
 __device__ __forceinline__ unsigned long long flat_record(const BatchCtx& B, uint32_t e, uint32_t n) {
   if (e < n) return (static_cast<unsigned long long>(static_cast<uint32_t>(B.node_ids[e])) << 32) | e;
   const uint32_t pos = e - n;
   return (static_cast<unsigned long long>(static_cast<uint32_t>(B.gsrc[pos])) << 32) | (kPend | pos);
 }
 
-// Per flat block: records per bucket -> hist row.
-__global__ void __launch_bounds__(kThreads) k_hist_flat(const Launch P) {
-  __shared__ uint32_t hist[1 << kPartMaxLgB];
-  const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
-  const uint32_t total = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-  const int lgB = hop_shape(P, B).lgB;
-  const int nB = 1 << lgB;
-  const int blocks = hop_blocks(P, B);
-  for (int blk = block_in_batch(P); blk < blocks; blk += blocks_per_batch(P)) {
-    __syncthreads();
-    for (int b = threadIdx.x; b < nB; b += kThreads) hist[b] = 0u;
-    __syncthreads();
-    const uint32_t e0 = static_cast<uint32_t>(blk) * kFlatBlock;
-    constexpr int U = 8;
-    for (uint32_t c0 = e0; c0 < e0 + kFlatBlock && c0 < total; c0 += kThreads * U) {
-      unsigned long long r[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t e = c0 + u * kThreads + threadIdx.x;
-        r[u] = e < total ? flat_record(B, e, n) : kEmpty;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (r[u] != kEmpty) atomicAdd(&hist[part_bucket(static_cast<uint32_t>(r[u] >> 32), lgB)], 1u);
-    }
-    __syncthreads();
-    uint32_t* out = B.hist + static_cast<size_t>(blk) * nB;
-    for (int b = threadIdx.x; b < nB; b += kThreads) out[b] = hist[b];
-  }
-}
-
-// Records of a flat block -> their buckets, in the staged rounds of k_scatter.
-__global__ void __launch_bounds__(kThreads) k_scatter_flat(const Launch P) {
-  __shared__ StageLds<kThreads> L;
+// The stream's segments, sorted by bucket.
+constexpr int kFlatThreads = kThreads;
+__global__ void __launch_bounds__(kFlatThreads) k_part_flat(const Launch P) {
+  constexpr int NT = kFlatThreads;
+  __shared__ unsigned long long stage[kSegMax];
+  __shared__ uint32_t scan[NT / 64];
+  extern __shared__ uint32_t cnt[];  // offs_stride / 2 words
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
   const uint32_t total_e = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
   const int lgB = hop_shape(P, B).lgB;
-  const int nB = 1 << lgB;
-  const int blocks = hop_blocks(P, B);
-  for (int blk = block_in_batch(P); blk < blocks; blk += blocks_per_batch(P)) {
-    __syncthreads();  // the previous flat block is done with the LDS arrays
-    stage_bucket_bases(L, B, nB, blk);
-    const uint32_t e0 = static_cast<uint32_t>(blk) * kFlatBlock;
-    for (uint32_t c0 = e0; c0 < e0 + kFlatBlock && c0 < total_e; c0 += StageLds<kThreads>::kRound) {
-      unsigned long long r[kScatterPer];
+  const Segments segs = hop_segments(P, B);
+  for (uint32_t seg = static_cast<uint32_t>(block_in_batch(P)); seg < segs.count; seg += static_cast<uint32_t>(blocks_per_batch(P))) {
+    const uint32_t e0 = seg * segs.cap;
+    const uint32_t e1 = total_e - e0 < segs.cap ? total_e : e0 + segs.cap;
+    unsigned long long r[kSegPer];
+    uint32_t rk[kSegPer];
 #pragma unroll
-      for (int u = 0; u < kScatterPer; ++u) {
-        const uint32_t e = c0 + u * kThreads + threadIdx.x;
-        r[u] = e < total_e ? flat_record(B, e, n) : kEmpty;
-      }
-      stage_round(L, nB, r, [&](uint32_t node) { return part_bucket(node, lgB); }, B.rec);
+    for (int u = 0; u < kSegPer; ++u) {
+      const uint32_t e = e0 + u * NT + threadIdx.x;
+      r[u] = e < e1 ? flat_record(B, e, n) : kEmpty;
     }
+    __syncthreads();  // the previous segment has been written out
+    for (uint32_t b = threadIdx.x; b < offs_stride(lgB) / 2u; b += NT) cnt[b] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSegPer; ++u) rk[u] = r[u] != kEmpty ? count_packed(cnt, part_bucket(static_cast<uint32_t>(r[u] >> 32), lgB)) : 0u;
+    __syncthreads();
+    segment_offsets<NT>(cnt, lgB, B.hist + static_cast<size_t>(seg) * offs_stride(lgB), scan);
+#pragma unroll
+    for (int u = 0; u < kSegPer; ++u)
+      if (r[u] != kEmpty) stage[packed(cnt, part_bucket(static_cast<uint32_t>(r[u] >> 32), lgB)) + rk[u]] = r[u];
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < e1 - e0; t += NT) B.rec[e0 + t] = stage[t];
   }
 }
 
@@ -366,7 +345,7 @@ __global__ void __launch_bounds__(kThreads) k_flag_flat_part(const Launch P) {
       if (pos < E && (static_cast<uint32_t>(B.gsrc[pos]) & kResolved) == 0u) nibble |= 1u << u;
     }
     unsigned long long total;
-    const uint32_t pre = static_cast<uint32_t>(block_exscan(__popc(nibble), lds, total));
+    const uint32_t pre = static_cast<uint32_t>(block_exscan(static_cast<unsigned long long>(__popc(nibble)), lds, total));
     // the 16 nibbles of a group, OR-ed over its lanes
     unsigned long long bits = static_cast<unsigned long long>(nibble) << (4 * sub);
 #pragma unroll
@@ -462,7 +441,7 @@ __global__ void __launch_bounds__(kThreads) k_flag_flat(const Launch P) {
       mine += first[u];
     }
     unsigned long long total;
-    uint32_t pre = static_cast<uint32_t>(block_exscan(mine, lds, total));
+    uint32_t pre = static_cast<uint32_t>(block_exscan(static_cast<unsigned long long>(mine), lds, total));
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (p0 + u < E) B.rank[p0 + u] = pre;

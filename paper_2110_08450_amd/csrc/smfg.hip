@@ -6,7 +6,7 @@
 // check of the input arrays).
 //
 // All batches of a call share each launch (the batch is the fastest-varying part of the block index).  A
-// hop is three launches where it is small, six or more under the partition strategy (their files describe
+// hop is three launches where it is small, four or five under the partition strategy (their files describe
 // both), and four under the table strategy:
 //   sample_insert  per destination: degree, Floyd/Philox row positions, neighbour ids, and an
 //                  insert of each neighbour into the batch's dedup table carrying the sample's
@@ -153,9 +153,9 @@ struct smfg_workspace {
   bool forced;           // the strategy was named by SMFG_DEDUP: small calls keep to it too
   bool flat;             // partition strategy also over exact offsets (wide fanouts): group records, row starts etc. present
   int64_t rec_entries;   // capacity of rec: known nodes + samples of a hop
-  int64_t hist_entries;  // capacity of hist: row blocks x buckets of a hop
+  int64_t hist_entries;  // capacity of hist: segments x offsets of a hop
   int split_lg;          // log2 of the most sub-buckets a hop needs (0: no hop splits its buckets)
-  int64_t b_table, b_slot, b_row, b_tiles, b_stiles, b_rec, b_hist, b_bstart, b_bstart2, b_grp;  // byte sizes of the slab's parts
+  int64_t b_table, b_slot, b_row, b_tiles, b_stiles, b_rec, b_hist, b_bstart2, b_grp;  // byte sizes of the slab's parts
   uint32_t table_log2;
   void* slab;
   uint64_t* table;
@@ -172,8 +172,7 @@ struct smfg_workspace {
   uint4* grp;
   uint64_t* stile_sums;
   uint64_t* rec;
-  uint32_t* hist;
-  uint32_t* bstart;
+  uint16_t* hist;
   uint64_t* rec2;
   uint32_t* bstart2;
 };
@@ -222,31 +221,58 @@ inline unsigned dedup_blocks(int lgB, int lg2, unsigned batches) {
 }
 inline int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 
-// Launch shape of one hop under the partition strategy: 2^lgB hash buckets (at most 1024) sized for
+// Launch shape of one hop under the partition strategy: 2^lgB hash buckets (at most 2^kPartMaxLgB) sized for
 // kPartBucketRecords records on average in the worst case; a hop that needs more buckets than that
-// takes two levels, 2^lgB buckets each split into 2^lg2 (part_levels); destinations cut into row blocks that are whole
-// multiples of what a thread block draws at once, at most 512 of them (128 in a launch of more than
-// 8 batches; more for hops beyond 256 K destinations, up to 4096).
+// takes two levels, 2^lgB buckets each split into 2^lg2 (part_levels); destinations cut into segments of
+// block_rows, at most kSegments of them unless those would be longer than a block sorts.
+constexpr int64_t kSegments = 512;
 struct HopPlan {
   int lgB, lg2;
+  int one_level;  // log2 of the most buckets the device may take in one level; lgB unless two are planned
+  int per;  // records per thread of k_sample_part, 8 or 16
   int block_rows;
   int64_t row_blocks;
 };
 
+int buckets_log2(int64_t records, int batches = 1) { return part_buckets_lg(records, batches, kPartMaxLgB + kPartMaxLg2); }
+
 HopPlan plan_hop(int64_t max_rows, int d, int batches) {
   HopPlan hp;
-  const int64_t records = max_rows * (1 + d);
-  int lg = 0;
-  while (lg < kPartMaxLgB + kPartMaxLg2 && (records >> lg) > kPartBucketRecords) ++lg;
-  part_levels(lg, hp.lgB, hp.lg2, batches);
-  int64_t cap = (max_rows + 511) / 512;
-  const int64_t least = batches > 8 ? 128 : 512;  // fewer, longer row blocks when many batches fill the chip anyway
-  cap = cap < least ? least : (cap > 4096 ? 4096 : cap);
-  hp.block_rows = (64 / d) * (kThreads / 64);
-  while ((max_rows + hp.block_rows - 1) / hp.block_rows > cap) hp.block_rows *= 2;
-  hp.row_blocks = (max_rows + hp.block_rows - 1) / hp.block_rows;
+  part_levels(buckets_log2(max_rows * (1 + d), batches), hp.lgB, hp.lg2, batches);
+  hp.one_level = hp.lg2 > 0 ? kPartMaxLgB : hp.lgB;
+  int64_t rows = (max_rows + kSegments - 1) / kSegments;
+  const int64_t least = (64 / d) * (kThreads / 64);
+  if (rows < least) rows = least;
+  if (rows > seg_rows(8, d)) rows = seg_rows(16, d);
+  hp.block_rows = static_cast<int>(rows);
+  hp.per = rows <= seg_rows(8, d) ? 8 : 16;
+  hp.row_blocks = (max_rows + rows - 1) / rows;
   if (hp.row_blocks < 1) hp.row_blocks = 1;
   return hp;
+}
+
+// The entries of hist for hops of up to `records` records: the offsets of the most buckets in kSegments segments, or
+// in such of at least `least` records.  (A call of other fanouts, whose segments are smaller, makes do with
+// fewer buckets, see plan_part_hop.)
+int64_t hist_entries_for(int64_t records, int64_t least) {
+  const auto segments = [](int64_t r, int64_t cap) { return r / cap + 2 > kSegments + 1 ? r / cap + 2 : kSegments + 1; };
+  int lgB, lg2;
+  part_levels(buckets_log2(records), lgB, lg2);
+  if (lg2 == 0) return segments(records, least) * offs_stride(lgB);
+  const int64_t one = segments(kPartOneLevel, least) * offs_stride(kPartMaxLgB), two = segments(records, seg_least(1)) * offs_stride(lgB);
+  return one > two ? one : two;
+}
+// Words of bstart2 for hops of up to `records` records that take two levels.  The segments of a range hold about
+// kSplitAim << lgB records, less what rounding the range down to whole segments takes off.
+int64_t split_entries_for(int64_t records) {
+  int64_t most = 0;
+  for (int lg = kPartMaxLgB + 1; lg <= buckets_log2(records); ++lg) {
+    int lgB, lg2;
+    part_levels(lg, lgB, lg2);
+    const int64_t n = ((records / ((int64_t(kSplitAim) - 64) << lgB) + 2) << lgB) * ((1 << lg2) + 1);
+    if (n > most) most = n;
+  }
+  return most;
 }
 
 // Destinations each hop can have at most: seeds, then everything known so far, capped by the node
@@ -280,7 +306,7 @@ bool part_forced() {
 
 // Workspaces whose largest hop stays below kPartMinRecords are planned for the table strategy.  Such calls take
 // the small path as a rule (the limits are the same); the table serves those it does not take, with four
-// launches per hop against the partition strategy's six, all of them launch-bound.
+// launches per hop, all of them launch-bound, like the partition strategy's.
 constexpr int64_t kPartMinRecords = 32768;
 static_assert(kPartMinRecords == kSmallRecords, "a table workspace's own calls are small");
 
@@ -293,35 +319,35 @@ bool part_needs(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t nu
   for (int h = 0; h < L; ++h)
     if (fanouts[h] < 1 || fanouts[h] > SMFG_MAX_FANOUT) return false;
   if (!hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows)) return false;
+  int64_t least = kSegMax;
   for (int h = 0; h < L; ++h) {
     const int64_t records = rows[h] * (1 + fanouts[h]);
     if (records > kPartMaxRecords) return false;
-    const HopPlan hp = plan_hop(rows[h], fanouts[h], 1);  // the most row blocks any launch will use
+    if (seg_least(fanouts[h]) < least) least = seg_least(fanouts[h]);
+    const HopPlan hp = plan_hop(rows[h], fanouts[h], 1);
     if (records > *rec_entries) *rec_entries = records;
-    // a call with fewer seeds may take one level of up to 2^kPartMaxLgB buckets where this bound takes two
-    const int lg1 = hp.lgB + hp.lg2 < kPartMaxLgB ? hp.lgB + hp.lg2 : kPartMaxLgB;
-    if ((hp.row_blocks << lg1) > *hist_entries) *hist_entries = hp.row_blocks << lg1;
     if (hp.lg2 > 0 && hp.lgB + hp.lg2 > *split_lg) *split_lg = hp.lgB + hp.lg2;
   }
+  *hist_entries = hist_entries_for(*rec_entries, least);
   if (*rec_entries < kPartMinRecords && !part_forced()) return false;
   return true;
 }
 
 // The shape of one hop of a call under the partition strategy; false if a workspace has no room for it.
-// The bucket counts of a workspace are sized for the row blocks of the most seeds.  Fewer rows can be
-// cut into more blocks (block_rows doubles once they exceed the cap: 600 seeds of fanouts (15, 10, 5) make 275
-// blocks in the last hop, 515 make 473), so a call with fewer seeds takes longer row blocks until they fit.
 bool plan_part_hop(const smfg_workspace* const* ws, int num_batches, int64_t max_rows, int d, HopPlan* hp) {
   *hp = plan_hop(max_rows, d, num_batches);
   for (int b = 0; b < num_batches; ++b) {
     if (max_rows * (1 + d) > ws[b]->rec_entries) return false;
     if (hp->lg2 > 0 && hp->lgB + hp->lg2 > ws[b]->split_lg) return false;
-    while ((hp->row_blocks << hp->lgB) > ws[b]->hist_entries) {
-      if (hp->row_blocks == 1) return false;
-      hp->block_rows *= 2;
-      hp->row_blocks = (max_rows + hp->block_rows - 1) / hp->block_rows;
+    if (hp->lg2 > 0 && hp->row_blocks * offs_stride(hp->lgB) > ws[b]->hist_entries) return false;
+    const int64_t most = kPartOneLevel / (1 + d);
+    const int64_t one_level = hp->lg2 > 0 && max_rows > most ? (most + hp->block_rows - 1) / hp->block_rows : hp->row_blocks;
+    while (one_level * offs_stride(hp->one_level) > ws[b]->hist_entries) {
+      if (hp->one_level == 0) return false;
+      --hp->one_level;
     }
   }
+  if (hp->lg2 == 0) hp->lgB = hp->one_level;
   return true;
 }
 
@@ -359,13 +385,9 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
     // slot_entries samples
     ws->part = ws->flat = true;
     ws->rec_entries = node_capacity + ws->slot_entries;
-    int lg = 0;
-    while (lg < kPartMaxLgB + kPartMaxLg2 && (ws->rec_entries >> lg) > kPartBucketRecords) ++lg;
-    const int lgB = lg < kPartMaxLgB ? lg : kPartMaxLgB;
-    ws->split_lg = lg > lgB ? lg : 0;
-    int64_t rows = (ws->rec_entries + kFlatBlock - 1) / kFlatBlock + 1;
-    if (rows < 520) rows = 520;  // a later call with fanouts up to SMFG_MAX_FANOUT uses row blocks instead
-    ws->hist_entries = rows << lgB;
+    const int lg = buckets_log2(ws->rec_entries);
+    ws->split_lg = lg > kPartMaxLgB ? lg : 0;
+    ws->hist_entries = hist_entries_for(ws->rec_entries, seg_least(SMFG_MAX_FANOUT));
   } else {
     ws->part = !table_forced() &&
                part_needs(max_seeds, L, fanouts, g->num_nodes, node_capacity, &ws->rec_entries, &ws->hist_entries,
@@ -379,11 +401,10 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
   ws->b_stiles = align256((ws->slot_entries / kWideTile + 2) * 8);
   if (ws->part) {
     ws->b_rec = align256(ws->rec_entries * 8);
-    ws->b_hist = align256(ws->hist_entries * 4);
-    ws->b_bstart = align256((2 * (int64_t(1) << kPartMaxLgB) + 2) * 4);
-    ws->b_bstart2 = ws->split_lg > 0 ? align256(((int64_t(1) << ws->split_lg) + 2) * 4) : 0;
+    ws->b_hist = align256(ws->hist_entries * 2);
+    ws->b_bstart2 = ws->split_lg > 0 ? align256(split_entries_for(ws->rec_entries) * 4) : 0;
     ws->bytes = ws->b_slot + 4 * ws->b_row + ws->b_tiles + (ws->split_lg > 0 ? 2 : 1) * ws->b_rec + ws->b_hist +
-                ws->b_bstart + ws->b_bstart2;
+                ws->b_bstart2;
     ws->b_grp = ws->flat ? align256((ws->slot_entries / 64 + 2) * 16) : 0;
     if (ws->flat) ws->bytes += ws->b_grp + 3 * ws->b_row + ws->b_stiles;
   } else {
@@ -391,6 +412,18 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
     ws->bytes = ws->b_table + 4 * ws->b_slot + 8 * ws->b_row + ws->b_tiles + ws->b_stiles;
   }
   return SMFG_OK;
+}
+
+// Makes a planned workspace fit `bytes` by giving up offsets, which costs buckets (plan_part_hop), but not more than
+// leave 64 of them in kSegments segments.  False if that is not enough.
+bool fit_workspace(smfg_workspace* ws, int64_t bytes) {
+  if (ws->bytes <= bytes) return true;
+  const int64_t b_hist = ws->b_hist - align256(ws->bytes - bytes);
+  if (!ws->part || b_hist < (kSegments + 1) * offs_stride(6) * 2) return false;
+  ws->bytes -= ws->b_hist - b_hist;
+  ws->b_hist = b_hist;
+  ws->hist_entries = b_hist / 2;
+  return true;
 }
 
 // Points the arrays of a planned workspace into `base` (ws->bytes bytes, 256-byte aligned).
@@ -403,8 +436,7 @@ void bind_workspace(smfg_workspace* ws, void* base) {
   ws->tile_sums = reinterpret_cast<uint64_t*>(p); p += ws->b_tiles;
   if (ws->part) {
     ws->rec = reinterpret_cast<uint64_t*>(p); p += ws->b_rec;
-    ws->hist = reinterpret_cast<uint32_t*>(p); p += ws->b_hist;
-    ws->bstart = reinterpret_cast<uint32_t*>(p); p += ws->b_bstart;
+    ws->hist = reinterpret_cast<uint16_t*>(p); p += ws->b_hist;
     if (ws->split_lg > 0) {
       ws->bstart2 = reinterpret_cast<uint32_t*>(p); p += ws->b_bstart2;
       ws->rec2 = reinterpret_cast<uint64_t*>(p); p += ws->b_rec;
@@ -448,8 +480,8 @@ int static_scratch_of(int device, void** out) {
 }
 
 // A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: hop
-// 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's six
-// launches, 21 to 29 us so.
+// 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's
+// launches (six then), 21 to 29 us so.
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 // How many of a call's hops, counted from the first one, take the small path; rows[b][h] bounds the
 // destinations of hop h of batch b.  Each batch is held against its own workspace: its samples sit at
@@ -544,21 +576,30 @@ void launch_small_hop(const SmallLaunch& S, int h, int64_t max_rows, hipStream_t
   k_small_finish<<<blocks_for(max_rows, S.tile[h], 0xFFFFFFu) * G, kSmallThreads, 0, st>>>(S, h);
 }
 
-// A block per first-level bucket of the bound (the kernel strides over more): while that is not more
-// blocks than compute units, of 16 waves each; 8 waves when two and more share one (2.4 M records in each of
-// four batches: 50 us with 16 waves, 40 with 8, 47 with 4).
-void launch_split(const Launch& P, hipStream_t st) {
-  const int lg = P.lgB < part_split_lg(P.G) ? P.lgB : part_split_lg(P.G);
-  const unsigned blocks = static_cast<unsigned>(P.G) << lg;
-  if (blocks <= 256) k_split_buckets<1024><<<blocks, 1024, 0, st>>>(P);
-  else k_split_buckets<512><<<blocks, 512, 0, st>>>(P);
+// A block per (range, bucket) of a hop with that many records at most, but no more than some that fill the chip: the
+// bound may be far above what the hop has, and the kernel strides over more.
+void launch_split(const Launch& P, int64_t records, hipStream_t st) {
+  const unsigned G = static_cast<unsigned>(P.G);
+  k_split_buckets<<<blocks_for(records, kSplitAim, 2048u / G + 1u) * G, kSplitThreads, 0, st>>>(P);
 }
 
-// A kernel that keeps the picks of a destination in registers: the variant for up to 8, 16 or 32 of them.
-using LaunchKernel = void (*)(const Launch);
-void launch_by_fanout(int d, unsigned blocks, hipStream_t st, const Launch& P, LaunchKernel to8, LaunchKernel to16,
-                      LaunchKernel to32) {
-  (d <= 8 ? to8 : d <= 16 ? to16 : to32)<<<blocks, kThreads, 0, st>>>(P);
+void launch_dedup(const Launch& P, unsigned G, hipStream_t st) {
+  const unsigned blocks = dedup_blocks(P.lgB, P.lg - P.lgB, G) * G;
+  if (P.lg >= kPartMaxLgB) k_dedup_buckets<true><<<blocks, kThreads, 0, st>>>(P);
+  else k_dedup_buckets<false><<<blocks, kThreads, 0, st>>>(P);
+}
+
+template <int PER>
+void launch_sample_part_of(const Launch& P, unsigned blocks, hipStream_t st) {
+  const size_t lds = offs_stride(P.lgB) * sizeof(uint16_t);
+  if (P.d <= 8) k_sample_part<8, PER><<<blocks, kThreads, lds, st>>>(P);
+  else if (P.d <= 16) k_sample_part<16, PER><<<blocks, kThreads, lds, st>>>(P);
+  else k_sample_part<32, PER><<<blocks, kThreads, lds, st>>>(P);
+}
+void launch_sample_part(const Launch& P, const HopPlan& hp, unsigned G, hipStream_t st) {
+  const unsigned blocks = static_cast<unsigned>(hp.row_blocks) * G;
+  if (hp.per == 8) launch_sample_part_of<8>(P, blocks, st);
+  else launch_sample_part_of<16>(P, blocks, st);
 }
 
 // The gather launch shared by smfg_sample_mfg_many and smfg_gather_many.  Vectors of 4 bytes and less only
@@ -870,7 +911,6 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     B.stile_sums = w->stile_sums;
     B.rec = w->rec;
     B.hist = w->hist;
-    B.bstart = w->bstart;
     B.rec2 = w->rec2;
     B.bstart2 = w->bstart2;
     B.features = static_cast<uint8_t*>(o.features);
@@ -910,7 +950,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
   }
   if (!part && !table) return SMFG_ERR_INVALID_ARG;  // workspaces of one call must be planned alike
   HopPlan plan[SMFG_MAX_LAYERS];
-  HopPlan flat_plan = {0, 0, 0, 1};
+  int flat_lg = 0, flat_one_level = kPartMaxLgB;
   if (part && wide) {
     // exact offsets: every workspace must have been planned for wide fanouts; the shape of a hop
     // is settled on the device, the host only bounds it by the roomiest workspace
@@ -919,11 +959,12 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       if (!ws[b]->flat) return SMFG_ERR_CAPACITY;
       if (ws[b]->rec_entries > records) records = ws[b]->rec_entries;
     }
-    int lg = 0;
-    while (lg < kPartMaxLgB + kPartMaxLg2 && (records >> lg) > kPartBucketRecords) ++lg;
-    flat_plan.lgB = lg < kPartMaxLgB ? lg : kPartMaxLgB;
-    flat_plan.lg2 = lg - flat_plan.lgB;
-    flat_plan.row_blocks = (records + kFlatBlock - 1) / kFlatBlock;
+    flat_lg = buckets_log2(records, num_batches);
+    for (int b = 0; b < num_batches; ++b) {
+      const int64_t most = ws[b]->rec_entries < kPartOneLevel ? ws[b]->rec_entries : kPartOneLevel;
+      const int64_t segs = most / kSegMax + 2 > kSegments + 1 ? most / kSegMax + 2 : kSegments + 1;
+      while (segs * offs_stride(flat_one_level) > ws[b]->hist_entries) --flat_one_level;
+    }
   } else if (part) {
     for (int h = 0; h < L; ++h)
       if (!plan_part_hop(ws, num_batches, max_n[h], fanouts[h], &plan[h])) return SMFG_ERR_CAPACITY;
@@ -967,27 +1008,17 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     const int64_t rows = max_n[h];
     const unsigned tile_blocks = blocks_for(rows, kTileRows, kCap);
     if (part && !wide) {
-      P.lgB = plan[h].lgB;
-      P.lg2 = plan[h].lg2;
+      P.lgB = plan[h].one_level;
+      P.lg = plan[h].lgB + plan[h].lg2;
       P.block_rows = plan[h].block_rows;
-      const unsigned row_blocks = static_cast<unsigned>(plan[h].row_blocks);
-      const unsigned buckets = 1u << P.lgB;
-      {
-        StageTimer t_(SMFG_STAGE_SAMPLE, st);
-        launch_by_fanout(P.d, row_blocks * G, st, P, k_sample_hist<8>, k_sample_hist<16>, k_sample_hist<32>);
-      }
       {
         StageTimer t_(SMFG_STAGE_PARTITION, st);
-        k_scan_hist<<<((buckets + kScanCols - 1) / kScanCols) * G, kThreads, 0, st>>>(P);
-        // with two levels a block has some 16 K records for its 128 or 256 buckets: rounds of 8192 instead of
-        // 2048 make the runs four times as long (29 M records 197 -> 173 us); with one level it has 2304
-        if (P.lg2 > 0) k_scatter<1024><<<row_blocks * G, 1024, 0, st>>>(P);
-        else k_scatter<kThreads><<<row_blocks * G, kThreads, 0, st>>>(P);
-        if (P.lg2 > 0) launch_split(P, st);
+        launch_sample_part(P, plan[h], G, st);
+        if (P.lg > kPartMaxLgB) launch_split(P, rows * (1 + P.d), st);
       }
       {
         StageTimer t_(SMFG_STAGE_DEDUP, st);
-        k_dedup_buckets<<<dedup_blocks(P.lgB, P.lg2, G) * G, kThreads, 0, st>>>(P);
+        launch_dedup(P, G, st);
       }
       {
         StageTimer t_(SMFG_STAGE_FLAG, st);
@@ -1018,26 +1049,26 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       }
       if (part) {
         P.flat = 1;
-        P.lgB = flat_plan.lgB;
-        P.lg2 = flat_plan.lg2;
-        int64_t stream_bound = rows + samples;  // known nodes + samples of this hop, at most
-        // the bound is loose when whole neighbourhoods are taken; blocks of 8192 elements each stride over more
-        const unsigned stream_blocks = blocks_for(stream_bound, kFlatBlock, 1024);
-        const unsigned buckets = 1u << P.lgB;
+        const int64_t stream_bound = rows + samples;  // known nodes + samples of this hop, at most
+        const int hop_lg = buckets_log2(stream_bound, num_batches), lg = hop_lg < flat_lg ? hop_lg : flat_lg;
+        P.lgB = lg < flat_one_level ? lg : flat_one_level;
+        P.lg = lg;
+        // the bound is loose when whole neighbourhoods are taken; blocks stride over more
+        const unsigned stream_blocks = blocks_for(stream_bound, kFlatThreads, 1024);
+        // 2^lgB buckets is the most the device can settle on in one level
+        const size_t lds = offs_stride(P.lgB) * sizeof(uint16_t);
         {
           StageTimer t_(SMFG_STAGE_SAMPLE, st);
           k_sample_wide<false><<<wave_blocks * G, kThreads, wide_lds_bytes(P.d), st>>>(P);
         }
         {
           StageTimer t_(SMFG_STAGE_PARTITION, st);
-          k_hist_flat<<<stream_blocks * G, kThreads, 0, st>>>(P);
-          k_scan_hist<<<((buckets + kScanCols - 1) / kScanCols) * G, kThreads, 0, st>>>(P);
-          k_scatter_flat<<<stream_blocks * G, kThreads, 0, st>>>(P);
-          if (P.lg2 > 0) launch_split(P, st);
+          k_part_flat<<<stream_blocks * G, kFlatThreads, lds, st>>>(P);
+          if (P.lg > kPartMaxLgB) launch_split(P, stream_bound, st);
         }
         {
           StageTimer t_(SMFG_STAGE_DEDUP, st);
-          k_dedup_buckets<<<dedup_blocks(P.lgB, P.lg2, G) * G, kThreads, 0, st>>>(P);
+          launch_dedup(P, G, st);
         }
         {
           StageTimer t_(SMFG_STAGE_FLAG, st);
@@ -1117,7 +1148,7 @@ int smfg_sample_mfg_static(const smfg_graph_t* g, const int32_t* d_seeds, int32_
   smfg_workspace ws;
   int rc = plan_workspace(&ws, g, num_seeds, L, fanouts, out->node_capacity, 0);
   if (rc != SMFG_OK) return rc;
-  if (ws.bytes > static_cast<int64_t>(SMFG_STATIC_SCRATCH_BYTES)) return SMFG_ERR_CAPACITY;
+  if (!fit_workspace(&ws, SMFG_STATIC_SCRATCH_BYTES)) return SMFG_ERR_CAPACITY;
   int cur = 0;
   hipError_t e = hipGetDevice(&cur);
   if (e != hipSuccess) return hip_err(e);

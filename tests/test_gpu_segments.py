@@ -1,0 +1,64 @@
+"""Hops of the partition strategy at the sizes where their segments, buckets and sub-buckets change, against the
+CPU oracle (needs an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2110_08450_amd import binding as smfg
+from test_gpu_parity import DEV, GpuGraph, assert_same, fetch
+from test_gpu_variants import random_graph, sample
+
+pytestmark = pytest.mark.gpu
+
+
+def segment_rows(d):
+    """Destinations of a full segment of 8 records per thread of a block of 256."""
+    return min(2048 // (1 + d), 512)
+
+
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("d", [1, 2, 3, 7, 16, 20, 32])
+def test_segments_of_either_size(d, more, monkeypatch):
+    """512 full segments of 8 records per thread, and one destination more, which makes them segments of 16 with a
+    short last one; each with another batch of a few rows, down to one."""
+    monkeypatch.setenv("SMFG_DEDUP", "partition")
+    n = 270_000
+    gg = random_graph(n, 2 * d, d)
+    perm = np.random.default_rng(d).permutation(n).astype(np.int32)
+    batches = [perm[:512 * segment_rows(d) + more], perm[-1 - 40 * more:]]
+    ws = [smfg.workspace_create(gg.g, len(batches[0]), (d,)) for _ in batches]
+    outs = [smfg.alloc_output(gg.g, len(b), (d,)) for b in batches]
+    smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(b).to(DEV) for b in batches], (d,), [5, 6], outs)
+    for b, key, out in zip(batches, (5, 6), outs):
+        assert_same(fetch(out, 1), gg.oracle.sample_mfg(b, (d,), key), 1)
+
+
+@pytest.mark.parametrize("fanout", [4, 3, -1])
+@pytest.mark.parametrize("hubs", [0, 3])
+def test_two_levels_with_and_without_hubs(hubs, fanout):
+    """More records than one level takes; with the neighbours of half the destinations among three nodes, whose
+    buckets hold far more than a block of the second level keeps in registers."""
+    n = 2_000_000
+    rng = np.random.default_rng(hubs)
+    rows = rng.integers(0, n, size=(n, 4)).astype(np.int32)
+    if hubs:
+        rows[::2] = rng.integers(0, hubs, size=(n // 2, 4)) * 600_001 + 17
+    gg = GpuGraph(np.arange(n + 1, dtype=np.int64) * 4, rows.ravel(), None)
+    s = rng.permutation(n)[:1_950_000].astype(np.int32)
+    ws = smfg.workspace_create(gg.g, len(s), (fanout,), 0, 4 * n if fanout < 0 else 0)
+    out = smfg.alloc_output(gg.g, len(s), (fanout,), edge_capacity=[4 * n])
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), (fanout,), 9, out)
+    assert_same(fetch(out, 1), gg.oracle.sample_mfg(s, (fanout,), 9), 1)
+
+
+def test_segments_of_other_fanouts_than_planned(monkeypatch):
+    """A workspace made for fanout 20 and used with 1 and 2, whose segments are smaller and so more."""
+    monkeypatch.setenv("SMFG_DEDUP", "partition")
+    n = 1_500_000
+    gg = random_graph(n, 4, 2)
+    perm = np.random.default_rng(0).permutation(n).astype(np.int32)
+    ws = smfg.workspace_create(gg.g, 140_000, (20,))
+    for d, seeds in [(1, 140_000), (2, 139_999)]:
+        out = smfg.alloc_output(gg.g, seeds, (d,))
+        smfg.sample_mfg(gg.g, ws, torch.from_numpy(perm[:seeds]).to(DEV), (d,), 3, out)
+        assert_same(fetch(out, 1), gg.oracle.sample_mfg(perm[:seeds], (d,), 3), 1)

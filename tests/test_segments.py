@@ -1,0 +1,115 @@
+"""Room for the segments of a hop: whatever number of destinations and samples a batch turns out to have, the
+offsets of its segments and sub-buckets fit what its workspace was made for.  The library's source is
+compiled together with a few exports, so this runs without a GPU."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2110_08450_amd import build
+
+EXPORTS = r"""
+#include "smfg.hip"
+extern "C" {
+void* plan(int64_t num_nodes, int32_t max_seeds, int32_t L, const int32_t* fanouts, int64_t samples) {
+  smfg_graph g;
+  std::memset(&g, 0, sizeof(g));
+  g.num_nodes = num_nodes;
+  smfg_workspace* ws = new smfg_workspace;
+  if (plan_workspace(ws, &g, max_seeds, L, fanouts, 0, samples) == SMFG_OK && ws->part) return ws;
+  delete ws;
+  return nullptr;
+}
+void drop(void* ws) { delete static_cast<smfg_workspace*>(ws); }
+int64_t records(const void* ws) { return static_cast<const smfg_workspace*>(ws)->rec_entries; }
+static int64_t room(const smfg_workspace* w, int64_t count, int64_t cap, int64_t records, int batches, int one_level, int lg) {
+  int lgB, lg2;
+  part_levels(part_buckets_lg(records, batches, lg), lgB, lg2, batches);
+  if (lg2 == 0 && lgB > one_level) lgB = one_level;
+  if (count * offs_stride(lgB) * 2 > w->b_hist) return -1;
+  if (lg2 == 0) return 1;
+  if (lgB > kPartMaxLgB || lg2 > kPartMaxLg2) return -2;
+  const int64_t range = split_range(static_cast<uint32_t>(cap), lgB);
+  if (((count + range - 1) / range << lgB) * ((1 << lg2) + 1) * 4 > w->b_bstart2) return -3;
+  return 2;
+}
+// rows of a hop that were bounded by max_rows: 1 or 2 levels, or negative where something does not fit
+int64_t drawn(void* ws, int32_t batches, int64_t max_rows, int32_t d, int64_t rows) {
+  const smfg_workspace* w = static_cast<const smfg_workspace*>(ws);
+  const smfg_workspace* all[SMFG_MAX_BATCHES];
+  for (int b = 0; b < batches; ++b) all[b] = w;
+  HopPlan hp;
+  if (!plan_part_hop(all, batches, max_rows, d, &hp)) return -10;
+  if (hp.block_rows > seg_rows(hp.per, d) || hp.block_rows * (1 + d) > hp.per * kThreads || hp.block_rows > hp.per / 4 * kThreads) return -11;
+  if (hp.block_rows * static_cast<int64_t>(draw_stride(d)) > hp.per * kThreads) return -12;
+  if (hp.row_blocks * hp.block_rows < max_rows) return -13;
+  const int64_t cap = static_cast<int64_t>(hp.block_rows) * (1 + d);
+  if ((rows + hp.block_rows - 1) / hp.block_rows * cap > w->rec_entries + cap) return -14;
+  return room(w, (rows + hp.block_rows - 1) / hp.block_rows, cap, rows * (1 + d), batches, hp.one_level, hp.lgB + hp.lg2);
+}
+int64_t flat(void* ws, int32_t batches, int64_t records) {
+  const smfg_workspace* w = static_cast<const smfg_workspace*>(ws);
+  const int lg = buckets_log2(w->rec_entries, batches);
+  int64_t cap = (records / 512 * batches + 1023) & ~int64_t(1023);
+  cap = cap < 1024 ? 1024 : cap > kSegMax ? kSegMax : cap;
+  return room(w, (records + cap - 1) / cap, cap, records, batches, kPartMaxLgB, lg);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    d = tmp_path_factory.mktemp("segments")
+    src, lib = d / "host.hip", d / "host.so"
+    src.write_text(EXPORTS)
+    subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC", "-shared",
+                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-I", os.path.dirname(build.SRC), "-I", build.INCLUDE, str(src), "-o", str(lib)],
+                   check=True, capture_output=True, timeout=300)
+    h = ctypes.CDLL(str(lib))
+    i32, i64, vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
+    h.plan.argtypes, h.plan.restype = [i64, i32, i32, ctypes.POINTER(i32), i64], vp
+    h.drop.argtypes, h.drop.restype = [vp], None
+    h.records.argtypes, h.records.restype = [vp], i64
+    h.drawn.argtypes, h.drawn.restype = [vp, i32, i64, i32, i64], i64
+    h.flat.argtypes, h.flat.restype = [vp, i32, i64], i64
+    return h
+
+
+def _sizes(rnd, most):
+    return {most, most - 1, most // 2 + 1, 1, *(int(most ** rnd.random()) for _ in range(30)), *(rnd.randint(1, most) for _ in range(20))}
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_offsets_of_every_hop_fit_the_workspace(host, wide):
+    """Own fanouts or others, fewer seeds, fewer rows than the bound, any number of batches."""
+    rnd = random.Random(4)
+    levels = set()
+    for _ in range(250):
+        nodes = int(10 ** rnd.uniform(4, 8.6))
+        fan = [rnd.choice([1, 2, 3, 5, 10, 20, 32, rnd.randint(1, 32)]) for _ in range(rnd.randint(1, 3))]
+        if wide:
+            fan.append(rnd.choice([40, 100, 1000]))
+        seeds = int(10 ** rnd.uniform(2, 6.3))
+        w = host.plan(nodes, seeds, len(fan), (ctypes.c_int32 * len(fan))(*fan), 0)
+        if not w:
+            continue
+        most = host.records(w)
+        for batches in (1, 2, 4, 8, 16):
+            if wide:
+                for r in _sizes(rnd, most):
+                    levels.add(("flat", host.flat(w, batches, r)))
+            for d in {1, 2, 3, 5, 20, 32, *[x for x in fan if x <= 32]}:
+                top = min(most // (1 + d), nodes)
+                if top < 1:
+                    continue
+                for bound in {top, rnd.randint(1, top)}:
+                    for rows in _sizes(rnd, bound):
+                        got = host.drawn(w, batches, bound, d, rows)
+                        assert got > 0, (got, nodes, fan, seeds, batches, d, bound, rows)
+                        levels.add(("drawn", got))
+        host.drop(w)
+    assert levels == {("drawn", 1), ("drawn", 2)} | ({("flat", 1), ("flat", 2)} if wide else set())
