@@ -423,12 +423,11 @@ __device__ __forceinline__ bool dedup_insert(DedupTable<LG>& T, unsigned long lo
 // node's local id or the position of its first appearance.  kRepeated for a known node that is not alone with its
 // id: two of them with one id can only be a repeated seed.
 constexpr uint32_t kRepeated = 1u, kLost = 2u;
-template <typename Batch>
-__device__ __forceinline__ uint32_t settle_record(const Batch& B, uint32_t val, uint32_t least) {
+__device__ __forceinline__ uint32_t settle_record(int32_t* gsrc, uint32_t val, uint32_t least) {
   if (least == val) return 0u;  // a known node, or a first appearance, whose entry stays
   // least < kPend: the node's final local id; else least names the position of the first appearance
   if (val >= kPend)
-    B.gsrc[val & ~kTagMask] =
+    gsrc[val & ~kTagMask] =
         static_cast<int32_t>(least < kPend ? (kResolved | least) : (kPointer | (least & ~kTagMask)));
   return val < kPend ? kRepeated : 0u;
 }
@@ -438,11 +437,11 @@ __device__ __forceinline__ void report(const Batch& B, int L, uint32_t wrong) {
 }
 
 // What the filled table says about one record.
-template <int LG, typename Batch>
-__device__ __forceinline__ uint32_t dedup_settle(const Batch& B, const DedupTable<LG>& T, unsigned long long rec, uint32_t sl) {
+template <int LG>
+__device__ __forceinline__ uint32_t dedup_settle(int32_t* gsrc, const DedupTable<LG>& T, unsigned long long rec, uint32_t sl) {
   const uint32_t node = static_cast<uint32_t>(rec >> 32);
   for (uint32_t probes = 0; probes < T.kSlots; ++probes) {
-    if (T.node[sl] == node) return settle_record(B, static_cast<uint32_t>(rec), T.least[sl]);
+    if (T.node[sl] == node) return settle_record(gsrc, static_cast<uint32_t>(rec), T.least[sl]);
     sl = (sl + 1u) & (T.kSlots - 1u);
   }
   return kLost;  // every inserted node is found again, unless the scratch is disturbed meanwhile
@@ -452,9 +451,9 @@ __device__ __forceinline__ uint32_t dedup_settle(const Batch& B, const DedupTabl
 // thread (kEmpty: none).  They stay there between the two passes, with the slot that the first one found; there
 // are no more than 2^LG of them, so that the table cannot overflow.  `free_bits` hash bits are not
 // yet spoken for.  All threads of the block (NT) call, none of which uses the table's LDS any more.
-template <int NT, int LG, int U, typename Call, typename Batch>
-__device__ __forceinline__ void dedup_in_registers(const Call& P, const Batch& B, DedupTable<LG>& T, int free_bits,
-                                                   const unsigned long long (&mine)[U]) {
+template <int NT, int LG, int U>
+__device__ __forceinline__ uint32_t dedup_in_registers(int32_t* gsrc, DedupTable<LG>& T, int free_bits,
+                                                       const unsigned long long (&mine)[U]) {
   const int down = free_bits > LG ? free_bits - LG : 0;
   uint32_t sl[U];
 #pragma unroll
@@ -468,9 +467,9 @@ __device__ __forceinline__ void dedup_in_registers(const Call& P, const Batch& B
   uint32_t wrong = 0u;
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (mine[u] != kEmpty) wrong |= settle_record(B, static_cast<uint32_t>(mine[u]), T.least[sl[u]]);
-  report(B, P.L, wrong);
+    if (mine[u] != kEmpty) wrong |= settle_record(gsrc, static_cast<uint32_t>(mine[u]), T.least[sl[u]]);
   __syncthreads();
+  return wrong;
 }
 
 // The records of a (sub-)bucket that lies in parts: part_of(p, from, size) tells where the p-th of them is in recs and
@@ -530,7 +529,7 @@ __device__ __forceinline__ void dedup_parts(const Launch& P, const BatchCtx& B, 
 #pragma unroll
     for (int u = 0; u < U; ++u) mine[u] = u * NT + threadIdx.x < cnt ? recs[list[u * NT + threadIdx.x]] : kEmpty;
     __syncthreads();
-    if (cnt != 0u) dedup_in_registers<NT>(P, B, T, free_bits, mine);
+    if (cnt != 0u) report(B, P.L, dedup_in_registers<NT>(B.gsrc, T, free_bits, mine));
     return;
   }
   constexpr int kHalf = kPartTableLg - 1, kAhead = 4;
@@ -563,7 +562,7 @@ __device__ __forceinline__ void dedup_parts(const Launch& P, const BatchCtx& B, 
               const uint32_t hash = static_cast<uint32_t>(mine[u] >> 32) * kPartHash;
               if (mine[u] == kEmpty || (lgR != 0 && ((hash >> rem) & (rounds - 1u)) != round)) continue;
               uint32_t sl = (hash >> down) & (H.kSlots - 1u);
-              if (pass == 1) wrong |= dedup_settle(B, H, mine[u], sl);
+              if (pass == 1) wrong |= dedup_settle(B.gsrc, H, mine[u], sl);
               else if (!dedup_insert<64>(H, mine[u], sl)) overflow = 1;
             }
           }

@@ -1,17 +1,19 @@
-// libsmfg small hops: three launches per hop, whatever is in it.
+// libsmfg small hops: two launches per hop, whatever is in it, and one before the first.
 //
 // A hop of fewer than kSmallRecords records keeps no kernel busy for much longer than its launch and a
 // chain of dependent reads take (about 5 us together), so what counts is how many there are:
-//   draw    many blocks, since its scattered reads need many compute units to be in flight at once;
+//   draw    of the first hop: many blocks, since its scattered reads need many compute units to be in flight at once;
 //   dedup   2^kSmallLgB blocks per batch, each reads all records, keeps those of its hash bucket and
 //           settles them in an LDS table: no histogram, no scatter;
 //   finish  blocks of consecutive destinations; each reads all entries of the hop, which gives it the
 //           first-appearance bits and their prefix sums in its own LDS, and then writes the final ids of
-//           its own destinations: no flags, no scan of tiles in between, no block waits for another.
+//           its own destinations: no flags, no scan of tiles in between, no block waits for another.  It then
+//           knows the ids and local ids of its destinations and of the new nodes among their samples, and goes on
+//           with these: the draw of the next small hop, or, after the last hop of a call, their feature rows.
 // Reading everything in every block costs up to 128 KB from the L2, a few us at most.  Measured, one batch
 // per call, whole call with its gather, against the table strategy's four launches per hop: (10, 5) with
-// 256 seeds 62 -> 44 us, (15, 10, 5) with 2 / 16 / 31 seeds 64 -> 58, 78 -> 68, 89 -> 81 us, (15) with
-// 1024 seeds (57 us, partition strategy) 31 us; seven batches of 31 seeds 124 -> 102 us.  One block for a
+// 256 seeds 62 -> 38 us, (15, 10, 5) with 16 seeds 78 -> 60 us; with the draw and the gather in launches of their
+// own 41 and 65 us.  One block for a
 // whole batch was slower (16 seeds: 172 us): a single compute unit has too few reads in flight.
 #ifndef SMFG_KERNELS_SMALL_H_
 #define SMFG_KERNELS_SMALL_H_
@@ -27,12 +29,25 @@ constexpr int64_t kSmallRecords = 32768;  // known nodes + positions of a hop: f
 constexpr int kSmallLgB = 4;              // 16 buckets
 constexpr int kSmallTableLg = 13;         // of 8192 slots
 constexpr uint32_t kSmallList = 1u << (kSmallTableLg - 1);
+// Destinations per block of finish for a hop of at most max_rows: some 32 blocks per batch, fewer where there are
+// many batches, since a block takes a compute unit for itself.
+constexpr int kSmallMinBlocks = 256 / SMFG_MAX_BATCHES, kSmallMaxBlocks = 32, kSmallMinTile = 8;
+constexpr int small_tile(int64_t max_rows, int batches) {
+  const int most = 256 / batches, blocks = most > kSmallMaxBlocks ? kSmallMaxBlocks : most;
+  const int64_t tile = (max_rows + blocks - 1) / blocks;
+  return static_cast<int>(tile < kSmallMinTile ? kSmallMinTile : tile);
+}
+// The most destinations and new nodes of a block.
+constexpr int kSmallNodes = static_cast<int>(kSmallRecords) / kSmallMinBlocks + kSmallMinTile * (1 + SMFG_MAX_FANOUT);
+static_assert(kSmallRecords / 2 / kSmallMinBlocks <= kSmallThreads, "a thread per destination");
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(1)));  // a vector at any byte address
 
 struct SmallBatch {
   const int32_t* seeds;
   int64_t* counts;
   int32_t* node_ids;
   uint8_t* labels;
+  uint8_t* features;
   int32_t* gsrc;  // per (destination, slot): node id, settled state, or kNoSample
   int32_t* rowk;  // samples per destination
   int32_t* blk_indptr[SMFG_MAX_LAYERS];
@@ -41,6 +56,9 @@ struct SmallBatch {
   int32_t node_capacity;
   int32_t num_seeds;
   uint32_t key0, key1;
+  // Odd hops have arrays of their own, so many times 256 bytes behind these: finish writes what the next hop starts with
+  // while other blocks of it still read the present one's.
+  uint32_t gsrc_odd, rowk_odd;
 };
 
 struct SmallLaunch {
@@ -52,11 +70,19 @@ struct SmallLaunch {
   int32_t L;
   int32_t G;
   int32_t fanouts[SMFG_MAX_LAYERS];
-  int32_t rows[SMFG_MAX_LAYERS];   // destinations per block of the draw
+  int32_t rows;                    // destinations per block of the draw
   int32_t tile[SMFG_MAX_LAYERS];   // destinations per block of finish, at most kSmallThreads
+  const uint8_t* feat;             // rows to be gathered by the last hop, or null
+  int64_t row_bytes, row_stride;
   SmallBatch b[SMFG_MAX_BATCHES];
 };
 static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments are limited to 4 KB");
+
+__device__ __forceinline__ int32_t* small_array(int32_t* even, uint32_t odd, int h) {
+  return (h & 1) == 0 ? even : even + static_cast<size_t>(odd) * 64u;
+}
+__device__ __forceinline__ int32_t* small_gsrc(const SmallBatch& B, int h) { return small_array(B.gsrc, B.gsrc_odd, h); }
+__device__ __forceinline__ int32_t* small_rowk(const SmallBatch& B, int h) { return small_array(B.rowk, B.rowk_odd, h); }
 
 __device__ __forceinline__ int small_batch(const SmallLaunch& P) { return static_cast<int>(blockIdx.x % static_cast<unsigned>(P.G)); }
 __device__ __forceinline__ int small_block(const SmallLaunch& P) { return static_cast<int>(blockIdx.x / static_cast<unsigned>(P.G)); }
@@ -67,27 +93,25 @@ __device__ __forceinline__ int small_rows(const SmallLaunch& P, const SmallBatch
   return block_has_status(B, P.L) ? -1 : n;
 }
 
-// Every position of the hop gets a node id or kNoSample.  Hop 0 reads the seeds, copies them to the
-// node ids and starts the counts; k_small_dedup looks for seeds that are no nodes.
+// Hop 0: every position gets a node id or kNoSample.  Reads the seeds, copies them to the node ids and starts the
+// counts; k_small_dedup looks for seeds that are no nodes.
 template <int D>
-__global__ void __launch_bounds__(kThreads) k_small_draw(const SmallLaunch P, int h) {
+__global__ void __launch_bounds__(kThreads) k_small_draw(const SmallLaunch P) {
   __shared__ DrawLds<kThreads, 512> S;  // kThreads / d rows of at most d + 1 words
   const SmallBatch& B = P.b[small_batch(P)];
-  const int n = h == 0 ? B.num_seeds : small_rows(P, B, h);
-  const int i0 = small_block(P) * P.rows[h];
-  if (h == 0 && i0 == 0)
+  const int n = B.num_seeds;
+  const int i0 = small_block(P) * P.rows;
+  if (i0 == 0)
     for (int q = threadIdx.x; q < 2 * P.L + 2; q += kThreads) B.counts[q] = q == 0 ? n : 0;
   if (i0 >= n) return;
-  const uint32_t d = static_cast<uint32_t>(P.fanouts[h]);
-  const int rows = n - i0 < P.rows[h] ? n - i0 : P.rows[h];
+  const uint32_t d = static_cast<uint32_t>(P.fanouts[0]);
+  const int rows = n - i0 < P.rows ? n - i0 : P.rows;
   draw_positions<D, kThreads>(
-      P, B, h, d, h == 0 ? B.seeds : B.node_ids, S, i0, rows, [] {},
+      P, B, 0, d, B.seeds, S, i0, rows, [] {},
       [&](int i, uint32_t v, uint32_t k) {
         B.rowk[i] = static_cast<int32_t>(k);
-        if (h == 0) {
-          B.node_ids[i] = static_cast<int32_t>(v);
-          if (B.labels && v < P.num_nodes) copy_label(P, B, i, static_cast<int32_t>(v));
-        }
+        B.node_ids[i] = static_cast<int32_t>(v);
+        if (B.labels && v < P.num_nodes) copy_label(P, B, i, static_cast<int32_t>(v));
       });
   const uint32_t cnt = static_cast<uint32_t>(rows) * d;
   uint32_t g[1];  // a sample per thread
@@ -97,10 +121,10 @@ __global__ void __launch_bounds__(kThreads) k_small_draw(const SmallLaunch P, in
 
 // All records of a set that holds every record of its nodes: record(i) for i in [0, cnt) one of them or
 // kEmpty; `free_bits` hash bits are not yet spoken for.  More than half the table are handled in 2^lgR rounds, as
-// in dedup_parts.  overflow: one LDS word.  All threads of the block (NT) call.
-template <int NT, int LG, typename Call, typename Batch, typename Record>
-__device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, DedupTable<LG>& T, int& overflow,
-                                              uint32_t cnt, int free_bits, Record record) {
+// in dedup_parts.  overflow: one LDS word.  What was wrong, if anything.  All threads of the block (NT) call.
+template <int NT, int LG, typename Record>
+__device__ __forceinline__ uint32_t dedup_records(int32_t* gsrc, DedupTable<LG>& T, int& overflow, uint32_t cnt, int free_bits,
+                                                  Record record) {
   constexpr int U = 8;  // records in flight per thread
   const int max_lgR = free_bits > LG ? free_bits - LG : 0;
   if (cnt <= NT * U && cnt <= T.kSlots / 2) {
@@ -110,8 +134,7 @@ __device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, Ded
       const uint32_t r = u * NT + threadIdx.x;
       mine[u] = r < cnt ? record(r) : kEmpty;
     }
-    dedup_in_registers<NT>(P, B, T, free_bits, mine);
-    return;
+    return dedup_in_registers<NT>(gsrc, T, free_bits, mine);
   }
   uint32_t wrong = 0u;
   int lgR = 0;
@@ -142,7 +165,7 @@ __device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, Ded
             if (pass == 0) {
               if (!dedup_insert<(1u << LG)>(T, mine[u], sl)) overflow = 1;
             } else {
-              wrong |= dedup_settle(B, T, mine[u], sl);
+              wrong |= dedup_settle(gsrc, T, mine[u], sl);
             }
           }
         }
@@ -158,7 +181,7 @@ __device__ __forceinline__ void dedup_records(const Call& P, const Batch& B, Ded
     __syncthreads();  // every thread has read the overflow word before the next attempt clears it
     ++lgR;
   }
-  report(B, P.L, wrong);
+  return wrong;
 }
 
 // One block per (batch, bucket).  Blocks of other buckets rewrite entries while this one reads them; such
@@ -190,6 +213,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
     for (uint32_t i = threadIdx.x; i < n; i += NT)
       if (static_cast<uint32_t>(B.node_ids[i]) >= P.num_nodes) set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
   const uint32_t positions = cnt - n;
+  int32_t* gsrc = small_gsrc(B, h);
   // a turn: K known nodes and 4 U positions per thread, every read on its way before the first is used
   // (the entries are padded to whole 256 bytes); a thread reserves room for all it found at once
   constexpr int K = 4, U = 4;
@@ -201,7 +225,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t q = q0 + u * NT * 4u;
-      const uint4 x = q < positions ? *reinterpret_cast<const uint4*>(B.gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
+      const uint4 x = q < positions ? *reinterpret_cast<const uint4*>(gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
       e[K + 4 * u] = x.x; e[K + 4 * u + 1] = x.y; e[K + 4 * u + 2] = x.z; e[K + 4 * u + 3] = x.w;
     }
     uint32_t found = 0;
@@ -222,22 +246,28 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
   }
   __syncthreads();
   const bool fits = listed <= kSmallList;
-  dedup_records<NT>(P, B, T, overflow, fits ? listed : cnt, 32, [&](uint32_t i) {
+  const uint32_t wrong = dedup_records<NT>(gsrc, T, overflow, fits ? listed : cnt, 32, [&](uint32_t i) {
     if (fits) return list[i];
-    const uint32_t node = static_cast<uint32_t>(i < n ? B.node_ids[i] : B.gsrc[i - n]);
+    const uint32_t node = static_cast<uint32_t>(i < n ? B.node_ids[i] : gsrc[i - n]);
     return wanted(node) ? as_record(node, i) : kEmpty;
   });
+  report(B, P.L, wrong);
 }
 
-// Blocks of P.tile[h] destinations.
+// Blocks of P.tile[h] destinations.  What follows goes on in the same block, which has the nodes in its LDS: its own
+// destinations and the new nodes among their samples.  D > 0: the draw of the next hop for them, D its fanout rounded
+// up to 8, 16 or 32.  GATHER: the last hop; their feature rows.
+template <int D, bool GATHER>
 __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunch P, int h) {
   constexpr int NT = kSmallThreads;
+  constexpr bool kGoesOn = D > 0 || GATHER;
   constexpr int kWords = static_cast<int>(kSmallRecords / 64);
   static_assert(kWords <= NT, "a thread per word of the scan");
   __shared__ unsigned long long first[kWords];  // bit q % 64 of word q / 64: position q is a first appearance
   __shared__ uint32_t before[kWords];           // first appearances before the word
   __shared__ uint32_t off[NT];                  // block offsets of the own destinations
   __shared__ unsigned long long scan[NT / 64];
+  __shared__ int32_t ids[kGoesOn ? kSmallNodes : 1];  // the own destinations, then the new nodes
   const SmallBatch& B = P.b[small_batch(P)];
   const int n = small_rows(P, B, h);
   const int i0 = small_block(P) * P.tile[h];
@@ -246,11 +276,14 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   const uint32_t d = static_cast<uint32_t>(P.fanouts[h]);
   const uint32_t positions = static_cast<uint32_t>(n) * d;
   const int tid = threadIdx.x;
-  const uint32_t k = tid < rows ? static_cast<uint32_t>(B.rowk[i0 + tid]) : 0u;
+  const int32_t* rowk = small_rowk(B, h);
+  const int32_t* gsrc = small_gsrc(B, h);
+  const uint32_t k = tid < rows ? static_cast<uint32_t>(rowk[i0 + tid]) : 0u;
+  if (kGoesOn && tid < rows) ids[tid] = B.node_ids[i0 + tid];
   // samples of the destinations before the own ones, and of all
   unsigned long long sums = 0;
   for (int i = tid; i < n; i += NT) {
-    const unsigned long long x = static_cast<uint32_t>(B.rowk[i]);
+    const unsigned long long x = static_cast<uint32_t>(rowk[i]);
     sums += i < i0 ? (x << 32 | x) : x;
   }
   constexpr int U = 4;
@@ -259,7 +292,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t q = q0 + u * NT * 4u;
-      e[u] = q < positions ? *reinterpret_cast<const uint4*>(B.gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
+      e[u] = q < positions ? *reinterpret_cast<const uint4*>(gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -299,20 +332,77 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
   const uint32_t own_cnt = static_cast<uint32_t>(rows) * d;
   const auto id_of = [&](uint32_t q) { return before[q >> 6] + static_cast<uint32_t>(__popcll(first[q >> 6] & ((1ull << (q & 63u)) - 1ull))); };
+  const uint32_t first_new = own_cnt > 0u ? id_of(pos0) : 0u;
   for (uint32_t idx = tid; idx < own_cnt; idx += NT) {
-    const uint32_t e = static_cast<uint32_t>(B.gsrc[pos0 + idx]);
+    const uint32_t e = static_cast<uint32_t>(gsrc[pos0 + idx]);
     if (e == kNoSample) continue;
     uint32_t r, s, local;
     div.split(idx, r, s);
     if ((e & kResolved) == 0u) {
       local = id_of(pos0 + idx);
       B.node_ids[local] = static_cast<int32_t>(e);
+      if (kGoesOn) ids[static_cast<uint32_t>(rows) + local - first_new] = static_cast<int32_t>(e);
     } else if ((e & kPointer) == kPointer) {
       local = id_of(e & ~kPointer);  // a pointer always names a first appearance
     } else {
       local = e & ~kPointer;
     }
     B.blk_indices[h][off[r] + s] = static_cast<int32_t>(local);
+  }
+  if constexpr (kGoesOn) {
+    __syncthreads();
+    // id_of counts the bits below a position, so the end of the own positions tells how many new nodes they have
+    const uint32_t end = pos0 + own_cnt;
+    const uint32_t after = own_cnt == 0u ? first_new : end < positions ? id_of(end) : nodes;
+    const int known = rows, count = rows + static_cast<int>(after - first_new);
+    const auto index_of = [&](int j) { return j < known ? i0 + j : static_cast<int>(first_new) + j - known; };
+    if constexpr (D > 0) {
+      __shared__ DrawLds<NT, 4 * NT> S;
+      const uint32_t next_d = static_cast<uint32_t>(P.fanouts[h + 1]);
+      int32_t* next_gsrc = small_gsrc(B, h + 1);
+      int32_t* next_rowk = small_rowk(B, h + 1);
+      const int most = 4 * NT / static_cast<int>(draw_stride(next_d)), turn = most < NT ? most : NT;
+      const DivD next_div(next_d);
+      for (int j0 = 0; j0 < count; j0 += turn) {
+        const int here = count - j0 < turn ? count - j0 : turn;
+        draw_positions<D, NT>(P, B, h + 1, next_d, ids, S, j0, here, [] {},
+                              [&](int j, uint32_t, uint32_t samples) { next_rowk[index_of(j)] = static_cast<int32_t>(samples); });
+        const uint32_t cnt = static_cast<uint32_t>(here) * next_d;
+        for (uint32_t base = tid; base < cnt; base += 2u * NT) {
+          uint32_t g[2];
+          read_neighbours<NT>(P, next_div, S, base, cnt, g);
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            if (base + u * NT < cnt) {
+              uint32_t r, s;
+              next_div.split(base + u * NT, r, s);
+              next_gsrc[static_cast<uint32_t>(index_of(j0 + static_cast<int>(r))) * next_d + s] = static_cast<int32_t>(g[u]);
+            }
+        }
+        __syncthreads();  // the next turn's rows replace these
+      }
+    }
+    if constexpr (GATHER) {
+      const uint32_t vecs = static_cast<uint32_t>((P.row_bytes + 15) / 16), all = static_cast<uint32_t>(count) * vecs;
+      for (uint32_t base = tid; base < all; base += 4u * NT) {
+        u32x4u v[4];
+        uint8_t* to[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t q = base + u * NT < all ? base + u * NT : all - 1u;
+          const uint32_t j = q / vecs;
+          int64_t id = ids[j];
+          if (id < 0 || id >= P.num_nodes) id = 0;  // no id can cause a read outside x
+          // a row's last vector ends with it and may overlap the one before (see AnyRow)
+          const int64_t byte = q - j * vecs == vecs - 1u ? P.row_bytes - 16 : static_cast<int64_t>(q - j * vecs) * 16;
+          v[u] = *reinterpret_cast<const u32x4u*>(P.feat + id * P.row_stride + byte);
+          to[u] = B.features + static_cast<int64_t>(index_of(static_cast<int>(j))) * P.row_bytes + byte;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (base + u * NT < all) *reinterpret_cast<u32x4u*>(to[u]) = v[u];
+      }
+    }
   }
 }
 

@@ -91,8 +91,12 @@ struct Profiler {
 struct StageTimer {
   int rec = -1;
   hipStream_t st;
-  StageTimer(int stage, hipStream_t s) : st(s) {
+  // also: another stage that the launch does the work of; it is counted there as well, and its time only in `stage`
+  StageTimer(int stage, hipStream_t s, int also = -1) : st(s) {
     if (g_prof.level == 0) return;
+    if (also >= 0) {
+      StageTimer counted(also, s);
+    }
     if (g_prof.level == 1 && stage != SMFG_STAGE_GATHER) return;
     const int r = g_prof.used.fetch_add(1, std::memory_order_relaxed);
     if (r >= g_prof.max_records) return;
@@ -522,22 +526,24 @@ constexpr int kCrowdedBatches = 4;
 bool crowded_by_a_gather(const smfg_graph* g, bool gathers, int num_batches) {
   return g->feat && !gathers && num_batches > kCrowdedBatches;
 }
-SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32_t* fanouts, const int64_t* max_rows) {
+SmallLaunch small_launch(const Launch& P, const smfg_workspace* const* ws, const smfg_output_t* outs, const int32_t* fanouts,
+                         const int64_t* max_rows) {
   SmallLaunch S;
   std::memset(&S, 0, sizeof(S));
   S.indptr = P.indptr;
   S.indices = P.indices;
   S.labels = P.labels;
+  S.feat = P.feat;
+  S.row_bytes = P.row_bytes;
+  S.row_stride = P.row_stride;
   S.num_nodes = P.num_nodes;
   S.label_bytes = P.label_bytes;
   S.L = P.L;
   S.G = P.G;
+  S.rows = kThreads / fanouts[0];  // a sample per thread
   for (int h = 0; h < P.L; ++h) {
-    if (!hop_is_small(fanouts[h], max_rows[h])) continue;
     S.fanouts[h] = fanouts[h];
-    S.rows[h] = kThreads / fanouts[h];  // a sample per thread
-    const int64_t tile = (max_rows[h] + 7) / 8;  // about eight blocks
-    S.tile[h] = static_cast<int32_t>(tile < 32 ? 32 : tile > kSmallThreads ? kSmallThreads : tile);
+    S.tile[h] = hop_is_small(fanouts[h], max_rows[h]) ? small_tile(max_rows[h], P.G) : 0;
   }
   for (int b = 0; b < P.G; ++b) {
     const BatchCtx& B = P.b[b];
@@ -546,8 +552,13 @@ SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32
     T.counts = B.counts;
     T.node_ids = B.node_ids;
     T.labels = B.labels;
+    T.features = B.features;
     T.gsrc = B.gsrc;
     T.rowk = B.rowk;
+    // arrays that the other paths write before they read them; the records hold a position's entry and more
+    const void* gsrc_odd = ws[b]->part ? static_cast<const void*>(ws[b]->rec) : ws[b]->ent;
+    T.gsrc_odd = static_cast<uint32_t>((static_cast<const uint8_t*>(gsrc_odd) - reinterpret_cast<const uint8_t*>(B.gsrc)) / 256);
+    T.rowk_odd = static_cast<uint32_t>((B.rowoff - B.rowk) / 64);
     for (int h = 0; h < P.L; ++h) {
       T.blk_indptr[h] = outs[b].indptr[h];
       T.blk_indices[h] = outs[b].indices[h];
@@ -560,20 +571,29 @@ SmallLaunch small_launch(const Launch& P, const smfg_output_t* outs, const int32
   }
   return S;
 }
-void launch_small_hop(const SmallLaunch& S, int h, int64_t max_rows, hipStream_t st) {
+// Feature rows that the last hop's finish copies itself: up to kSmallGather bytes in a batch at most, by some 32
+// blocks where a launch of its own has hundreds, and in vectors of 16 bytes.
+constexpr int64_t kSmallGather = 4 << 20;
+bool small_gather(int64_t row_bytes, int64_t max_nodes) { return row_bytes >= 16 && max_nodes * row_bytes <= kSmallGather; }
+// The first `hops` hops; `gather`: the last of them, which is the call's, copies the feature rows.
+void launch_small_hops(const SmallLaunch& S, int hops, const int64_t* max_rows, bool gather, hipStream_t st) {
   const unsigned G = static_cast<unsigned>(S.G);
   {
     StageTimer t_(SMFG_STAGE_SAMPLE, st);
-    const unsigned blocks = blocks_for(max_rows, S.rows[h], 0xFFFFFFu) * G;
-    const int d = S.fanouts[h];
-    (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks, kThreads, 0, st>>>(S, h);
+    const int d = S.fanouts[0];
+    (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks_for(max_rows[0], S.rows, 0xFFFFFFu) * G, kThreads, 0, st>>>(S);
   }
-  {
-    StageTimer t_(SMFG_STAGE_DEDUP, st);
-    k_small_dedup<<<G << kSmallLgB, kSmallThreads, 0, st>>>(S, h);
+  for (int h = 0; h < hops; ++h) {
+    {
+      StageTimer t_(SMFG_STAGE_DEDUP, st);
+      k_small_dedup<<<G << kSmallLgB, kSmallThreads, 0, st>>>(S, h);
+    }
+    StageTimer t_(SMFG_STAGE_ASSEMBLE, st, h + 1 < hops ? SMFG_STAGE_SAMPLE : gather ? SMFG_STAGE_GATHER : -1);
+    const unsigned blocks = blocks_for(max_rows[h], S.tile[h], 0xFFFFFFu) * G;
+    const int d = h + 1 < hops ? S.fanouts[h + 1] : 0;
+    (d > 16 ? k_small_finish<32, false> : d > 8 ? k_small_finish<16, false> : d > 0 ? k_small_finish<8, false>
+     : gather ? k_small_finish<0, true> : k_small_finish<0, false>)<<<blocks, kSmallThreads, 0, st>>>(S, h);
   }
-  StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
-  k_small_finish<<<blocks_for(max_rows, S.tile[h], 0xFFFFFFu) * G, kSmallThreads, 0, st>>>(S, h);
 }
 
 // A block per (range, bucket) of a hop with that many records at most, but no more than some that fill the chip: the
@@ -979,9 +999,10 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
 
   const int small_hops = small_hops_of(ws, num_seeds, g->num_nodes, bound, fanouts, L, num_batches,
                                        crowded_by_a_gather(g, want_feat, num_batches));
-  SmallLaunch S;
+  // a call of small hops only may gather in the last of them
+  const bool gathered = want_feat && small_hops == L && small_gather(g->row_bytes, max_n[L]);
   if (small_hops > 0) {
-    S = small_launch(P, outs, fanouts, max_n);
+    launch_small_hops(small_launch(P, ws, outs, fanouts, max_n), small_hops, max_n, gathered, st);
   } else if (part) {
     StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_begin<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P);
@@ -993,11 +1014,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     { StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_insert_seeds<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P); }
   }
-  for (int h = 0; h < L; ++h) {
-    if (h < small_hops) {
-      launch_small_hop(S, h, max_n[h], st);
-      continue;
-    }
+  for (int h = small_hops; h < L; ++h) {
     P.h = h;
     P.d = fanouts[h];
     for (int b = 0; b < num_batches; ++b) {
@@ -1121,7 +1138,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       else k_assemble<true><<<tile_blocks * G, kThreads, 0, st>>>(P);
     }
   }
-  if (want_feat) launch_gather(P, max_n[L], vb, G, st);
+  if (want_feat && !gathered) launch_gather(P, max_n[L], vb, G, st);
   hipError_t e = hipGetLastError();
   if (cur != g->device) (void)hipSetDevice(cur);
   return hip_err(e);

@@ -62,3 +62,24 @@ def test_segments_of_other_fanouts_than_planned(monkeypatch):
         out = smfg.alloc_output(gg.g, seeds, (d,))
         smfg.sample_mfg(gg.g, ws, torch.from_numpy(perm[:seeds]).to(DEV), (d,), 3, out)
         assert_same(fetch(out, 1), gg.oracle.sample_mfg(perm[:seeds], (d,), 3), 1)
+
+
+@pytest.mark.parametrize("batches", [1, 3, 16])
+@pytest.mark.parametrize("fanouts,seeds,dim,dtype", [
+    ((10, 5), 256, 32, np.float32), ((1, 32), 300, 9, np.float16), ((31, 3), 200, 8, np.float16), ((32, 1), 990, 4, np.float32),
+    ((15, 10, 5), 16, 100, np.float16), ((2, 2, 2, 17), 30, 101, np.float16), ((1,), 16383, 7, np.float32), ((3,), 0, 16, np.float32),
+    ((10, 5), 290, 700, np.float32)])
+def test_small_hops_that_go_on(fanouts, seeds, dim, dtype, batches):
+    """Small calls whose blocks draw for the next hop, in one turn or several, and copy the feature rows, of 16 bytes
+    and more and up to the size that is left to the gather; the odd hops' arrays of table and partition workspaces."""
+    gg = random_graph(40_000, 40, 13, dim=dim, dtype=dtype)
+    rng = np.random.default_rng(seeds)
+    sizes = [seeds] + [int(x) for x in rng.integers(0, seeds + 1, size=batches - 1)]
+    s = [rng.permutation(40_000)[:k].astype(np.int32) for k in sizes]
+    ws = [smfg.workspace_create(gg.g, seeds, fanouts) for _ in s]
+    outs = [smfg.alloc_output(gg.g, seeds, fanouts) for _ in s]
+    for turn in range(2):
+        keys = [100 * turn + b for b in range(batches)]
+        smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(x).to(DEV) for x in s], fanouts, keys, outs)
+        for x, key, out in zip(s, keys, outs):
+            assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(x, fanouts, key), len(fanouts))
