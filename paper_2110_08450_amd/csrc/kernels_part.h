@@ -612,49 +612,48 @@ __global__ void __launch_bounds__(kThreads, LARGE ? 7 : 8) k_dedup_buckets(const
 
 // flag_rows for the entries dedup_buckets leaves: a valid sample whose entry still is a node id
 // (bit 31 clear) is a first appearance.  Per destination: bit mask of its first appearances; in-tile
-// exclusive scan of (samples, new nodes); per-tile totals.
+// exclusive scan of (samples, new nodes); per-tile totals.  Streaming: a wave's ballot is the bits of 64 positions,
+// from which each destination then takes its own.  With an LDS atomicOr per first appearance, 20 consecutive
+// ones of which hit one word, 29 M positions took 54 us; 43 so, 2.8 TB/s of entries.
 __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
   __shared__ unsigned long long lds[kThreads / 64];
-  __shared__ int k_lds[kTileRows];
-  __shared__ unsigned int mask_lds[kTileRows];
+  __shared__ unsigned long long bits[kTileRows * SMFG_MAX_FANOUT / 64 + 1];  // of the tile's positions
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const int nblocks = blocks_per_batch(P);
   const int n = static_cast<int>(B.counts[P.h]);
   const uint32_t d = static_cast<uint32_t>(P.d);
-  const DivD div(d);
   const int tiles = (n + kTileRows - 1) / kTileRows;
   for (int tile = block_in_batch(P); tile < tiles; tile += nblocks) {
     const int i0 = tile * kTileRows;
     const int nrows = n - i0 < kTileRows ? n - i0 : kTileRows;
     const int tr = threadIdx.x;
-    __syncthreads();
-    k_lds[tr] = tr < nrows ? B.rowk[i0 + tr] : 0;
-    mask_lds[tr] = 0u;
-    __syncthreads();
+    const int k = tr < nrows ? B.rowk[i0 + tr] : 0;
     const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
     const uint32_t cnt = static_cast<uint32_t>(nrows) * d;
+    __syncthreads();  // the previous tile's bits have been read
     constexpr int U = 4;
-    for (uint32_t base = threadIdx.x; base < cnt; base += kThreads * U) {
+    for (uint32_t base = tr & ~63; base < cnt; base += kThreads * U) {  // whole waves
       uint32_t e[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint32_t idx = base + u * kThreads;
+        const uint32_t idx = base + u * kThreads + (tr & 63);
         e[u] = idx < cnt ? static_cast<uint32_t>(B.gsrc[pos0 + idx]) : kResolved;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint32_t idx = base + u * kThreads;
-        if (idx < cnt && (e[u] & kResolved) == 0u) {
-          uint32_t r, sl;
-          div.split(idx, r, sl);
-          if (sl < static_cast<uint32_t>(k_lds[r])) atomicOr(&mask_lds[r], 1u << sl);
-        }
+        const unsigned long long b = __ballot((e[u] & kResolved) == 0u);
+        if ((tr & 63) == 0 && base + u * kThreads < cnt) bits[(base + u * kThreads) >> 6] = b;
       }
     }
     __syncthreads();
-    const int k = k_lds[tr];
-    const uint32_t m = mask_lds[tr];
+    uint32_t m = 0u;
+    if (k > 0) {
+      const uint32_t at = static_cast<uint32_t>(tr) * d, sh = at & 63u;
+      unsigned long long own = bits[at >> 6] >> sh;
+      if (sh + d > 64u) own |= bits[(at >> 6) + 1u] << (64u - sh);
+      m = static_cast<uint32_t>(own & ((1ull << k) - 1ull));
+    }
     const unsigned long long x = (static_cast<unsigned long long>(k) << 32) | static_cast<unsigned long long>(__popc(m));
     unsigned long long total;
     const unsigned long long pre = block_exscan(x, lds, total);
@@ -677,15 +676,14 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
   constexpr int kPer = kAssembleTiles / kThreads;
   __shared__ uint32_t tile_new[SCAN ? kAssembleTiles : 1];  // new nodes before each tile
   __shared__ unsigned long long own_lds, scan_lds[kThreads / 64];
-  __shared__ int k_lds[kTileRows];
-  __shared__ unsigned int mask_lds[kTileRows];
-  __shared__ unsigned int off_lds[kTileRows];   // global edge offset of the destination
-  __shared__ unsigned int rank_lds[kTileRows];  // local id of the destination's first new node
+  // per destination: samples, first-appearance bits, block offset, local id of the first new node
+  __shared__ uint4 row_lds[kTileRows];
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const int n = static_cast<int>(B.counts[P.h]);
   const uint32_t d = static_cast<uint32_t>(P.d);
   const DivD div(d);
+  const double inv_d = 1.0 / static_cast<double>(d);
   const int tiles = (n + kTileRows - 1) / kTileRows;
   const int nblocks = blocks_per_batch(P);
   if (SCAN) {
@@ -718,13 +716,9 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
     if (tr < nrows) {
       const uint32_t off = static_cast<uint32_t>(tpre >> 32) + static_cast<uint32_t>(B.rowoff[i0 + tr]);
       const uint2 mn = B.rowmn[i0 + tr];
-      k_lds[tr] = B.rowk[i0 + tr];
-      mask_lds[tr] = mn.x;
-      off_lds[tr] = off;
-      rank_lds[tr] = static_cast<uint32_t>(n) + static_cast<uint32_t>(tpre & 0xFFFFFFFFull) + mn.y;
+      row_lds[tr] = make_uint4(static_cast<uint32_t>(B.rowk[i0 + tr]), mn.x, off,
+                               static_cast<uint32_t>(n) + static_cast<uint32_t>(tpre & 0xFFFFFFFFull) + mn.y);
       B.blk_indptr[i0 + tr] = static_cast<int32_t>(off);
-    } else {
-      k_lds[tr] = 0;
     }
     __syncthreads();
     const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
@@ -740,18 +734,21 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
       // the records of the destinations that pointers name are fetched for all U samples of the
       // thread before any is used (other samples fetch the tile's first record), so the scattered
       // reads of a thread overlap
-      uint32_t r[U], sl[U], q[U], qi[U];
+      uint32_t sl[U], q[U], qi[U];
+      uint4 row[U];
       bool live[U], dup[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const uint32_t idx = base + u * kThreads;
-        r[u] = 0u;
+        uint32_t r = 0u;
         sl[u] = 0u;
-        if (idx < cnt) div.split(idx, r[u], sl[u]);
-        live[u] = idx < cnt && sl[u] < static_cast<uint32_t>(k_lds[r[u]]);
+        if (idx < cnt) div.split(idx, r, sl[u]);
+        row[u] = row_lds[r];
+        live[u] = idx < cnt && sl[u] < row[u].x;
         dup[u] = live[u] && (e[u] & kPointer) == kPointer;
         q[u] = dup[u] ? (e[u] & ~kPointer) : pos0;
-        qi[u] = q[u] / d;
+        // q / d: positions have 30 bits, so half of 1 / d is far more than what the product is off
+        qi[u] = static_cast<uint32_t>((static_cast<double>(q[u]) + 0.5) * inv_d);
       }
       uint2 mn[U];
       uint32_t ts[U];
@@ -765,7 +762,7 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
         if (!live[u]) continue;
         uint32_t local;
         if ((e[u] & kResolved) == 0u) {  // first appearance: rank among the new nodes of this hop
-          local = rank_lds[r[u]] + __popc(mask_lds[r[u]] & ((1u << sl[u]) - 1u));
+          local = row[u].w + __popc(row[u].y & ((1u << sl[u]) - 1u));
           B.node_ids[local] = static_cast<int32_t>(e[u]);
         } else if (dup[u]) {
           const uint32_t qs = q[u] - qi[u] * d;
@@ -777,7 +774,7 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
         } else {
           local = e[u] & ~kPointer;
         }
-        B.blk_indices[off_lds[r[u]] + sl[u]] = static_cast<int32_t>(local);
+        B.blk_indices[row[u].z + sl[u]] = static_cast<int32_t>(local);
       }
     }
   }
