@@ -148,7 +148,7 @@ __device__ __forceinline__ uint32_t bucket_of_block(const Launch& P, uint32_t i,
 }
 
 // counts <- (n_0, 0, ..., status 0); node_ids[0, n_0) <- seeds; labels of the seeds.  Seeds are
-// range-checked by the first hop's k_sample_hist, which runs after the status word is zero.  A batch of more
+// range-checked by the first hop's k_sample_part or k_count_rows, which run after the status word is zero.  A batch of more
 // seeds than the graph has nodes holds a stray or a repeated one; it ends here, since grids, rows and
 // positions of a hop are bounded by the number of nodes.
 __global__ void __launch_bounds__(kThreads) k_begin(const Launch P) {
