@@ -329,31 +329,47 @@ __global__ void __launch_bounds__(kFlatThreads) k_part_flat(const Launch P) {
 // 16-byte record: the 64 first-appearance bits and the number of new nodes of the tile before the
 // group.  For a hop of millions of samples that is about a megabyte, which stays in the L2, so the
 // lookups of the samples that repeat a node (scattered over the hop) do not go to memory.
+// A wave takes four groups one after the other, a sample per lane, so that its reads are consecutive and a ballot is
+// a group's bits.
 __global__ void __launch_bounds__(kThreads) k_flag_flat_part(const Launch P) {
-  __shared__ unsigned long long lds[kThreads / 64];
+  constexpr int kWaves = kThreads / 64;
+  __shared__ uint32_t lds[2][kWaves];
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
   const uint32_t tiles = (E + kWideTile - 1) / kWideTile;
-  const int sub = threadIdx.x & 15;  // 16 threads x 4 samples = one group of 64
-  for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P)) {
-    const uint32_t p0 = tile * kWideTile + threadIdx.x * 4;
-    uint32_t nibble = 0;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int turn = 0;  // a wave writes the sums of the next tile while others may still read the present one's
+  for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P), turn ^= 1) {
+    const uint32_t p0 = tile * kWideTile + static_cast<uint32_t>(wave) * 256u;
+    uint32_t e[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t pos = p0 + u;
-      if (pos < E && (static_cast<uint32_t>(B.gsrc[pos]) & kResolved) == 0u) nibble |= 1u << u;
+      const uint32_t pos = p0 + u * 64 + lane;
+      e[u] = pos < E ? static_cast<uint32_t>(B.gsrc[pos]) : kResolved;
     }
-    unsigned long long total;
-    const uint32_t pre = static_cast<uint32_t>(block_exscan(static_cast<unsigned long long>(__popc(nibble)), lds, total));
-    // the 16 nibbles of a group, OR-ed over its lanes
-    unsigned long long bits = static_cast<unsigned long long>(nibble) << (4 * sub);
+    unsigned long long own = 0;  // lane u < 4: the bits of group u, and the new nodes of the wave before it
+    uint32_t before = 0, sum = 0;
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, 64);
-    if (sub == 0 && p0 < E)
-      B.grp[p0 >> 6] = make_uint4(static_cast<uint32_t>(bits), static_cast<uint32_t>(bits >> 32), pre, 0u);
-    if (threadIdx.x == 0) B.stile_sums[tile] = total;
+    for (int u = 0; u < 4; ++u) {
+      const unsigned long long bits = __ballot((e[u] & kResolved) == 0u);
+      if (lane == u) {
+        own = bits;
+        before = sum;
+      }
+      sum += static_cast<uint32_t>(__popcll(bits));
+    }
+    if (lane == 0) lds[turn][wave] = sum;
     __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) before += lds[turn][w];
+      total += lds[turn][w];
+    }
+    if (lane < 4 && p0 + static_cast<uint32_t>(lane) * 64u < E)
+      B.grp[(p0 >> 6) + lane] = make_uint4(static_cast<uint32_t>(own), static_cast<uint32_t>(own >> 32), before, 0u);
+    if (threadIdx.x == 0) B.stile_sums[tile] = total;
   }
 }
 
@@ -363,7 +379,7 @@ __device__ __forceinline__ uint32_t flat_rank(const uint4 g, uint32_t tile_befor
   return tile_before + g.z + __popcll(bits & ((1ull << (q & 63u)) - 1ull));
 }
 
-// assemble_flat for those entries.
+// assemble_flat for those entries, a wave's samples as in flag_flat_part: its reads and writes are consecutive.
 __global__ void __launch_bounds__(kThreads) k_assemble_flat_part(const Launch P) {
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (status_of(B, P.L) != 0) return;
@@ -372,16 +388,17 @@ __global__ void __launch_bounds__(kThreads) k_assemble_flat_part(const Launch P)
   const uint32_t tiles = (E + kWideTile - 1) / kWideTile;
   for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P)) {
     const uint32_t tpre = static_cast<uint32_t>(B.stile_sums[tile]);
-    const uint32_t p0 = tile * kWideTile + threadIdx.x * 4;
-    if (p0 >= E) continue;
-    const uint4 own = B.grp[p0 >> 6];  // the thread's four samples share a group
+    const uint32_t p0 = tile * kWideTile + (threadIdx.x >> 6) * 256u + (threadIdx.x & 63u);
+    uint4 own[4];
     uint32_t e[4], q[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t pos = p0 + u;
+      const uint32_t pos = p0 + u * 64;
       e[u] = pos < E ? static_cast<uint32_t>(B.gsrc[pos]) : kResolved;
-      q[u] = (e[u] & kPointer) == kPointer ? (e[u] & ~kPointer) : p0;
+      own[u] = B.grp[(pos < E ? pos : tile * kWideTile) >> 6];
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = (e[u] & kPointer) == kPointer ? (e[u] & ~kPointer) : tile * kWideTile;
     // what the pointers name is fetched for all four samples before any is used
     uint4 qg[4];
     uint32_t qtile[4];
@@ -392,11 +409,11 @@ __global__ void __launch_bounds__(kThreads) k_assemble_flat_part(const Launch P)
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t pos = p0 + u;
+      const uint32_t pos = p0 + u * 64;
       if (pos >= E) continue;
       uint32_t local;
       if ((e[u] & kResolved) == 0u) {  // first appearance
-        local = n + flat_rank(own, tpre, pos);
+        local = n + flat_rank(own[u], tpre, pos);
         B.node_ids[local] = static_cast<int32_t>(e[u]);
       } else if ((e[u] & kPointer) == kPointer) {
         local = n + flat_rank(qg[u], qtile[u], q[u]);  // a pointer always names a first appearance

@@ -83,3 +83,22 @@ def test_small_hops_that_go_on(fanouts, seeds, dim, dtype, batches):
         smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(x).to(DEV) for x in s], fanouts, keys, outs)
         for x, key, out in zip(s, keys, outs):
             assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(x, fanouts, key), len(fanouts))
+
+
+@pytest.mark.parametrize("samples", [1, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 4097])
+def test_flat_groups_and_tiles(samples, monkeypatch):
+    """Whole neighbourhoods of two destinations at the edges of groups of 64 samples, of a wave's 256 and of tiles of
+    1024; a third of the samples repeat nodes, the destinations among them."""
+    monkeypatch.setenv("SMFG_DEDUP", "partition")
+    n = 6000
+    rng = np.random.default_rng(samples)
+    first = rng.permutation(n)[:samples - samples // 3]
+    indices = np.concatenate([first, rng.choice(np.append(first, [0, 1]), samples // 3)]).astype(np.int32)
+    indptr = np.full(n + 1, samples, dtype=np.int64)
+    indptr[:2] = [0, len(first)]
+    gg = GpuGraph(indptr, indices, None)
+    s = np.array([0, 1], dtype=np.int32)
+    ws = smfg.workspace_create(gg.g, 2, (-1,), 0, samples)
+    out = smfg.alloc_output(gg.g, 2, (-1,), edge_capacity=[samples])
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), (-1,), 3, out)
+    assert_same(fetch(out, 1), gg.oracle.sample_mfg(s, (-1,), 3), 1)
