@@ -116,8 +116,8 @@ __host__ __device__ constexpr int seg_rows(int per, int d) {
 __host__ __device__ constexpr int seg_least(int d) { return seg_rows(kSegPer, d) * (1 + d); }
 // Exact offsets: records per segment, a multiple of 1024 settled on the device from the hop's record count, so
 // that a launch has some 512 segments where it can.
-__device__ __forceinline__ uint32_t flat_seg(const Launch& P, uint32_t records) {
-  const uint32_t per = (records / 512u * static_cast<uint32_t>(P.G) + 1023u) & ~1023u;
+__host__ __device__ inline uint32_t flat_seg(uint32_t batches, uint32_t records) {
+  const uint32_t per = (records / 512u * batches + 1023u) & ~1023u;
   return per < 1024u ? 1024u : per > static_cast<uint32_t>(kSegMax) ? static_cast<uint32_t>(kSegMax) : per;
 }
 struct Segments {
@@ -128,7 +128,7 @@ __device__ __forceinline__ Segments hop_segments(const Launch& P, const BatchCtx
   Segments s;
   if (P.flat) {
     const uint32_t records = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-    s.cap = flat_seg(P, records);
+    s.cap = flat_seg(static_cast<uint32_t>(P.G), records);
     s.count = (records + s.cap - 1u) / s.cap;
   } else {
     s.cap = static_cast<uint32_t>(P.block_rows) * static_cast<uint32_t>(1 + P.d);

@@ -255,15 +255,21 @@ HopPlan plan_hop(int64_t max_rows, int d, int batches) {
   return hp;
 }
 
+// The most segments that such many records make where a full one of a hop of more than kSegments holds at least `least`.
+int64_t most_segments(int64_t records, int64_t least) {
+  const int64_t count = records / least + 2;
+  return count > kSegments + 1 ? count : kSegments + 1;
+}
+
 // The entries of hist for hops of up to `records` records: the offsets of the most buckets in kSegments segments, or
 // in such of at least `least` records.  (A call of other fanouts, whose segments are smaller, makes do with
 // fewer buckets, see plan_part_hop.)
 int64_t hist_entries_for(int64_t records, int64_t least) {
-  const auto segments = [](int64_t r, int64_t cap) { return r / cap + 2 > kSegments + 1 ? r / cap + 2 : kSegments + 1; };
   int lgB, lg2;
   part_levels(buckets_log2(records), lgB, lg2);
-  if (lg2 == 0) return segments(records, least) * offs_stride(lgB);
-  const int64_t one = segments(kPartOneLevel, least) * offs_stride(kPartMaxLgB), two = segments(records, seg_least(1)) * offs_stride(lgB);
+  if (lg2 == 0) return most_segments(records, least) * offs_stride(lgB);
+  const int64_t one = most_segments(kPartOneLevel, least) * offs_stride(kPartMaxLgB);
+  const int64_t two = most_segments(records, seg_least(1)) * offs_stride(lgB);
   return one > two ? one : two;
 }
 // Words of bstart2 for hops of up to `records` records that take two levels.  The segments of a range hold about
@@ -355,6 +361,31 @@ bool plan_part_hop(const smfg_workspace* const* ws, int num_batches, int64_t max
   return true;
 }
 
+// The same for a hop over exact offsets of at most `bound` known nodes and samples in any batch.  The shape of a batch's hop
+// is settled on the device, from its own numbers; the host only bounds it, by what the roomiest workspace holds.
+bool plan_flat_hop(const smfg_workspace* const* ws, int num_batches, int64_t bound, HopPlan* hp) {
+  int64_t most = 1;
+  int cap = kPartMaxLgB;
+  for (int b = 0; b < num_batches; ++b) {
+    if (!ws[b]->flat) return false;  // every workspace must have been planned for wide fanouts
+    const int64_t records = bound < ws[b]->rec_entries ? bound : ws[b]->rec_entries;
+    if (records > most) most = records;
+    // a batch takes two levels by its number of records alone, so it has to have all the offsets that takes; in one
+    // level it makes do with fewer buckets
+    part_levels(buckets_log2(records, num_batches), hp->lgB, hp->lg2, num_batches);
+    if (hp->lg2 > 0 && most_segments(records, kSegMax) * offs_stride(hp->lgB) > ws[b]->hist_entries) return false;
+    const int64_t one_level = most_segments(records < kPartOneLevel ? records : kPartOneLevel, kSegMax);
+    while (one_level * offs_stride(cap) > ws[b]->hist_entries) {
+      if (cap == 0) return false;
+      --cap;
+    }
+  }
+  part_levels(buckets_log2(most, num_batches), hp->lgB, hp->lg2, num_batches);
+  const int lg = hp->lgB + hp->lg2;
+  hp->one_level = lg < cap ? lg : cap;
+  return true;
+}
+
 // Sizes of a workspace for up to max_seeds seeds, the given fanouts and capacities: fills every
 // field of *ws but the pointers (slab stays null).  Host only.
 int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, int32_t L, const int32_t* fanouts,
@@ -418,8 +449,9 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
   return SMFG_OK;
 }
 
-// Makes a planned workspace fit `bytes` by giving up offsets, which costs buckets (plan_part_hop), but not more than
-// leave 64 of them in kSegments segments.  False if that is not enough.
+// Makes a planned workspace fit `bytes` by giving up offsets, which costs buckets in hops of one level, but not more than
+// leave 64 of them in kSegments segments.  False if that is not enough.  Hops of two levels may then have no room, which
+// plan_part_hop and plan_flat_hop find out.
 bool fit_workspace(smfg_workspace* ws, int64_t bytes) {
   if (ws->bytes <= bytes) return true;
   const int64_t b_hist = ws->b_hist - align256(ws->bytes - bytes);
@@ -970,25 +1002,13 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
   }
   if (!part && !table) return SMFG_ERR_INVALID_ARG;  // workspaces of one call must be planned alike
   HopPlan plan[SMFG_MAX_LAYERS];
-  int flat_lg = 0, flat_one_level = kPartMaxLgB;
-  if (part && wide) {
-    // exact offsets: every workspace must have been planned for wide fanouts; the shape of a hop
-    // is settled on the device, the host only bounds it by the roomiest workspace
-    int64_t records = 1;
-    for (int b = 0; b < num_batches; ++b) {
-      if (!ws[b]->flat) return SMFG_ERR_CAPACITY;
-      if (ws[b]->rec_entries > records) records = ws[b]->rec_entries;
-    }
-    flat_lg = buckets_log2(records, num_batches);
-    for (int b = 0; b < num_batches; ++b) {
-      const int64_t most = ws[b]->rec_entries < kPartOneLevel ? ws[b]->rec_entries : kPartOneLevel;
-      const int64_t segs = most / kSegMax + 2 > kSegments + 1 ? most / kSegMax + 2 : kSegments + 1;
-      while (segs * offs_stride(flat_one_level) > ws[b]->hist_entries) --flat_one_level;
-    }
-  } else if (part) {
+  int64_t samples[SMFG_MAX_LAYERS];  // wide path: upper bound of E_h
+  for (int h = 0; h < L; ++h) samples[h] = fanouts[h] < 0 || max_n[h] * fanouts[h] > max_entries ? max_entries : max_n[h] * fanouts[h];
+  if (part)
     for (int h = 0; h < L; ++h)
-      if (!plan_part_hop(ws, num_batches, max_n[h], fanouts[h], &plan[h])) return SMFG_ERR_CAPACITY;
-  }
+      if (!(wide ? plan_flat_hop(ws, num_batches, max_n[h] + samples[h], &plan[h])
+                 : plan_part_hop(ws, num_batches, max_n[h], fanouts[h], &plan[h])))
+        return SMFG_ERR_CAPACITY;
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   int cur = 0;
@@ -1054,9 +1074,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       continue;
     }
     if (wide) {
-      int64_t samples = P.d < 0 ? max_entries : rows * P.d;  // upper bound of E_h
-      if (samples > max_entries) samples = max_entries;
-      const unsigned flat_blocks = blocks_for(samples, kWideTile, kCap);
+      const unsigned flat_blocks = blocks_for(samples[h], kWideTile, kCap);
       // a wave per destination while the grid allows; beyond that a wave takes several (see k_sample_wide)
       const unsigned wave_blocks = blocks_for(rows, kThreads / 64, 2 * kCap);
       {
@@ -1066,10 +1084,9 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       }
       if (part) {
         P.flat = 1;
-        const int64_t stream_bound = rows + samples;  // known nodes + samples of this hop, at most
-        const int hop_lg = buckets_log2(stream_bound, num_batches), lg = hop_lg < flat_lg ? hop_lg : flat_lg;
-        P.lgB = lg < flat_one_level ? lg : flat_one_level;
-        P.lg = lg;
+        const int64_t stream_bound = rows + samples[h];  // known nodes + samples of this hop, at most
+        P.lgB = plan[h].one_level;
+        P.lg = plan[h].lgB + plan[h].lg2;
         // the bound is loose when whole neighbourhoods are taken; blocks stride over more
         const unsigned stream_blocks = blocks_for(stream_bound, kFlatThreads, 1024);
         // 2^lgB buckets is the most the device can settle on in one level

@@ -102,3 +102,21 @@ def test_flat_groups_and_tiles(samples, monkeypatch):
     out = smfg.alloc_output(gg.g, 2, (-1,), edge_capacity=[samples])
     smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), (-1,), 3, out)
     assert_same(fetch(out, 1), gg.oracle.sample_mfg(s, (-1,), 3), 1)
+
+
+def test_static_calls_with_few_offsets_left():
+    """Wide fanouts whose scratch is made to fit 64 MiB by giving up offsets: the same results with all of them left, as few
+    as hops of two levels take (3.1 M records), and a refusal below."""
+    n, fan = 100_000, (100,)
+    rng = np.random.default_rng(3)
+    gg = GpuGraph(np.arange(n + 1, dtype=np.int64) * 110, rng.integers(0, n, size=110 * n).astype(np.int32), None)
+    perm = rng.permutation(n).astype(np.int32)
+    out = smfg.alloc_output(gg.g, 30_877, fan)
+    dev = torch.from_numpy(perm).to(DEV)
+    for seeds in (24_000, 29_900, 30_716):
+        smfg.sample_mfg_static(gg.g, dev[:seeds], fan, 11, out)
+        assert_same(fetch(out, 1), gg.oracle.sample_mfg(perm[:seeds], fan, 11), 1)
+    for seeds in (30_717, 30_800, 30_876, 30_877):
+        with pytest.raises(smfg.SmfgError) as e:
+            smfg.sample_mfg_static(gg.g, dev[:seeds], fan, 11, out)
+        assert e.value.code == smfg.ERR_CAPACITY

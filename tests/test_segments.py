@@ -49,12 +49,21 @@ int64_t drawn(void* ws, int32_t batches, int64_t max_rows, int32_t d, int64_t ro
   if ((rows + hp.block_rows - 1) / hp.block_rows * cap > w->rec_entries + cap) return -14;
   return room(w, (rows + hp.block_rows - 1) / hp.block_rows, cap, rows * (1 + d), batches, hp.one_level, hp.lgB + hp.lg2);
 }
-int64_t flat(void* ws, int32_t batches, int64_t records) {
+// gives up offsets until the workspace takes `bytes`
+int32_t cut(void* ws, int64_t bytes) { return fit_workspace(static_cast<smfg_workspace*>(ws), bytes) ? 1 : 0; }
+int64_t size(const void* ws, int64_t* offsets) {
+  *offsets = static_cast<const smfg_workspace*>(ws)->b_hist;
+  return static_cast<const smfg_workspace*>(ws)->bytes;
+}
+// `records` of a hop over exact offsets that was bounded by `bound`: 1 or 2 levels, 0 if the call is refused
+int64_t flat(void* ws, int32_t batches, int64_t bound, int64_t records) {
   const smfg_workspace* w = static_cast<const smfg_workspace*>(ws);
-  const int lg = buckets_log2(w->rec_entries, batches);
-  int64_t cap = (records / 512 * batches + 1023) & ~int64_t(1023);
-  cap = cap < 1024 ? 1024 : cap > kSegMax ? kSegMax : cap;
-  return room(w, (records + cap - 1) / cap, cap, records, batches, kPartMaxLgB, lg);
+  const smfg_workspace* all[SMFG_MAX_BATCHES];
+  for (int b = 0; b < batches; ++b) all[b] = w;
+  HopPlan hp;
+  if (!plan_flat_hop(all, batches, bound, &hp)) return 0;
+  const int64_t cap = flat_seg(batches, static_cast<uint32_t>(records));
+  return room(w, (records + cap - 1) / cap, cap, records, batches, hp.one_level, hp.lgB + hp.lg2);
 }
 }
 """
@@ -75,7 +84,9 @@ def host(tmp_path_factory):
     h.drop.argtypes, h.drop.restype = [vp], None
     h.records.argtypes, h.records.restype = [vp], i64
     h.drawn.argtypes, h.drawn.restype = [vp, i32, i64, i32, i64], i64
-    h.flat.argtypes, h.flat.restype = [vp, i32, i64], i64
+    h.flat.argtypes, h.flat.restype = [vp, i32, i64, i64], i64
+    h.cut.argtypes = [vp, i64]
+    h.size.argtypes, h.size.restype = [vp, ctypes.POINTER(i64)], i64
     return h
 
 
@@ -100,8 +111,11 @@ def test_offsets_of_every_hop_fit_the_workspace(host, wide):
         most = host.records(w)
         for batches in (1, 2, 4, 8, 16):
             if wide:
-                for r in _sizes(rnd, most):
-                    levels.add(("flat", host.flat(w, batches, r)))
+                for bound in {most, rnd.randint(1, most)}:
+                    for r in _sizes(rnd, bound):
+                        got = host.flat(w, batches, bound, r)
+                        assert got > 0, (got, nodes, fan, seeds, batches, bound, r)
+                        levels.add(("flat", got))
             for d in {1, 2, 3, 5, 20, 32, *[x for x in fan if x <= 32]}:
                 top = min(most // (1 + d), nodes)
                 if top < 1:
@@ -113,3 +127,29 @@ def test_offsets_of_every_hop_fit_the_workspace(host, wide):
                         levels.add(("drawn", got))
         host.drop(w)
     assert levels == {("drawn", 1), ("drawn", 2)} | ({("flat", 1), ("flat", 2)} if wide else set())
+
+
+def test_workspaces_cut_to_fit_hold_the_offsets_or_refuse(host):
+    """Calls over exact offsets whose scratch was made to fit by giving up offsets, at limits from all of them to none: what is
+    still accepted has room for whatever a batch turns out to have, in one level or two; 100 000 nodes of
+    degree 100, 30 876 seeds of fanout 100 and the 64 MiB of a static call among them."""
+    rnd = random.Random(7)
+    seen = set()
+    cases = [(100_000, [100], 30_876, 64 << 20), (100_000, [100], 30_718, 64 << 20), (50_000, [100], 31_950, 64 << 20)]
+    for _ in range(400):
+        fan = [rnd.choice([1, 3, 10, 32, 40, 100, 300, 1000]) for _ in range(rnd.randint(0, 2))] + [rnd.choice([33, 100, 1000])]
+        cases.append((int(10 ** rnd.uniform(4, 7.5)), fan, int(10 ** rnd.uniform(0, 5.5)), 0))
+    for nodes, fan, seeds, limit in cases:
+        w = host.plan(nodes, seeds, len(fan), (ctypes.c_int32 * len(fan))(*fan), 0)
+        if not w:
+            continue
+        offsets = ctypes.c_int64()
+        total, most = host.size(w, offsets), host.records(w)
+        if host.cut(w, limit or total - rnd.randint(0, offsets.value)):
+            for bound in {most, rnd.randint(1, most)}:
+                for r in _sizes(rnd, bound):
+                    got = host.flat(w, 1, bound, r)
+                    assert got >= 0, (got, nodes, fan, seeds, bound, r)
+                    seen.add(got)
+        host.drop(w)
+    assert seen == {0, 1, 2}
