@@ -52,6 +52,7 @@ struct BatchCtx {
   uint16_t* hist;        // per segment, the first record of each bucket within it and the end of the last
   uint64_t* rec2;        // the records once more, each bucket's of a range of segments sorted by sub-bucket (hops with lg2 > 0)
   uint32_t* bstart2;     // [ranges][buckets][sub-buckets + 1] where each begins in rec2, and the end of the last
+  int32_t one_level;     // log2 of the most buckets of the current hop that hist has room for in one level
 };
 
 struct Launch {
@@ -67,7 +68,7 @@ struct Launch {
   int32_t h;       // current hop
   int32_t d;       // its fanout
   int32_t G;       // batches
-  int32_t lgB;     // partition path: log2 of the most hash buckets of this hop in one level
+  int32_t lgB;     // partition path: log2 of the most hash buckets that any batch starts this hop with
   int32_t lg;      // partition path: log2 of the most buckets, or sub-buckets in all (see hop_shape)
   int32_t block_rows;  // partition path: destinations per segment of this hop
   int32_t flat;    // partition path over exact offsets: the hop's number of samples is known

@@ -83,15 +83,19 @@ __host__ __device__ inline int part_buckets_lg(long long records, int batches, i
   while (lg < most && ((records >> lg) > (lg < kPartMaxLgB ? kPartBucketRecords : kPartMostRecords) || ((records >> lg) > kPartFewRecords && (batches << lg) < kPartBuckets))) ++lg;
   return lg;
 }
+// The shape for that many records of a batch: 2^lg buckets at most in all, and in one level 2^one_level, what the batch's
+// workspace has offsets for.
+__host__ __device__ inline HopShape hop_levels(long long records, int batches, int lg, int one_level) {
+  HopShape s;
+  part_levels(part_buckets_lg(records, batches, lg), s.lgB, s.lg2, batches);
+  if (s.lg2 == 0 && s.lgB > one_level) s.lgB = one_level;
+  return s;
+}
 // Records: known nodes and sample positions, or samples where their number is known (P.flat); both are
 // final before the first kernel that asks.
 __device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B) {
   const long long n = B.counts[P.h];
-  const long long records = P.flat ? n + B.counts[P.L + 1 + P.h] : n * (1 + P.d);
-  HopShape s;
-  part_levels(part_buckets_lg(records, P.G, P.lg), s.lgB, s.lg2, P.G);
-  if (s.lg2 == 0 && s.lgB > P.lgB) s.lgB = P.lgB;
-  return s;
+  return hop_levels(P.flat ? n + B.counts[P.L + 1 + P.h] : n * (1 + P.d), P.G, P.lg, B.one_level);
 }
 
 // ---- segments ------------------------------------------------------------------------------------

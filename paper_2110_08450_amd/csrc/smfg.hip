@@ -231,8 +231,9 @@ inline int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 // block_rows, at most kSegments of them unless those would be longer than a block sorts.
 constexpr int64_t kSegments = 512;
 struct HopPlan {
-  int lgB, lg2;
-  int one_level;  // log2 of the most buckets the device may take in one level; lgB unless two are planned
+  int lgB, lg2;                     // levels of the most records that a batch may have
+  int one_level[SMFG_MAX_BATCHES];  // log2 of the most buckets that a batch may take in one level
+  int most_lgB;                     // log2 of the most buckets that any batch may start with, in one level or two
   int per;  // records per thread of k_sample_part, 8 or 16
   int block_rows;
   int64_t row_blocks;
@@ -243,7 +244,6 @@ int buckets_log2(int64_t records, int batches = 1) { return part_buckets_lg(reco
 HopPlan plan_hop(int64_t max_rows, int d, int batches) {
   HopPlan hp;
   part_levels(buckets_log2(max_rows * (1 + d), batches), hp.lgB, hp.lg2, batches);
-  hp.one_level = hp.lg2 > 0 ? kPartMaxLgB : hp.lgB;
   int64_t rows = (max_rows + kSegments - 1) / kSegments;
   const int64_t least = (64 / d) * (kThreads / 64);
   if (rows < least) rows = least;
@@ -343,46 +343,54 @@ bool part_needs(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t nu
   return true;
 }
 
+// A batch takes two levels by its number of records alone, so its workspace has to have all the offsets that takes, 2^lgB
+// buckets in `two` segments; in one level, of `one` segments, it makes do with fewer buckets.  False if that does not help.
+bool fit_hop(const smfg_workspace* ws, int lgB, int lg2, int64_t two, int64_t one, int* one_level) {
+  if (lg2 > 0 && two * offs_stride(lgB) > ws->hist_entries) return false;
+  *one_level = lg2 > 0 ? kPartMaxLgB : lgB;
+  while (one * offs_stride(*one_level) > ws->hist_entries) {
+    if (*one_level == 0) return false;
+    --*one_level;
+  }
+  return true;
+}
+void settle_levels(int num_batches, HopPlan* hp) {
+  hp->most_lgB = hp->lg2 > 0 ? hp->lgB : 0;
+  for (int b = 0; b < num_batches; ++b)
+    if (hp->one_level[b] > hp->most_lgB) hp->most_lgB = hp->one_level[b];
+  if (hp->lg2 == 0) hp->lgB = hp->most_lgB;
+}
+
 // The shape of one hop of a call under the partition strategy; false if a workspace has no room for it.
 bool plan_part_hop(const smfg_workspace* const* ws, int num_batches, int64_t max_rows, int d, HopPlan* hp) {
   *hp = plan_hop(max_rows, d, num_batches);
+  const int64_t most = kPartOneLevel / (1 + d);
+  const int64_t one_level = hp->lg2 > 0 && max_rows > most ? (most + hp->block_rows - 1) / hp->block_rows : hp->row_blocks;
   for (int b = 0; b < num_batches; ++b) {
     if (max_rows * (1 + d) > ws[b]->rec_entries) return false;
     if (hp->lg2 > 0 && hp->lgB + hp->lg2 > ws[b]->split_lg) return false;
-    if (hp->lg2 > 0 && hp->row_blocks * offs_stride(hp->lgB) > ws[b]->hist_entries) return false;
-    const int64_t most = kPartOneLevel / (1 + d);
-    const int64_t one_level = hp->lg2 > 0 && max_rows > most ? (most + hp->block_rows - 1) / hp->block_rows : hp->row_blocks;
-    while (one_level * offs_stride(hp->one_level) > ws[b]->hist_entries) {
-      if (hp->one_level == 0) return false;
-      --hp->one_level;
-    }
+    if (!fit_hop(ws[b], hp->lgB, hp->lg2, hp->row_blocks, one_level, &hp->one_level[b])) return false;
   }
-  if (hp->lg2 == 0) hp->lgB = hp->one_level;
+  settle_levels(num_batches, hp);
   return true;
 }
 
 // The same for a hop over exact offsets of at most `bound` known nodes and samples in any batch.  The shape of a batch's hop
-// is settled on the device, from its own numbers; the host only bounds it, by what the roomiest workspace holds.
+// is settled on the device, from its own numbers and for its own workspace; the host only bounds it.
 bool plan_flat_hop(const smfg_workspace* const* ws, int num_batches, int64_t bound, HopPlan* hp) {
   int64_t most = 1;
-  int cap = kPartMaxLgB;
   for (int b = 0; b < num_batches; ++b) {
     if (!ws[b]->flat) return false;  // every workspace must have been planned for wide fanouts
     const int64_t records = bound < ws[b]->rec_entries ? bound : ws[b]->rec_entries;
     if (records > most) most = records;
-    // a batch takes two levels by its number of records alone, so it has to have all the offsets that takes; in one
-    // level it makes do with fewer buckets
-    part_levels(buckets_log2(records, num_batches), hp->lgB, hp->lg2, num_batches);
-    if (hp->lg2 > 0 && most_segments(records, kSegMax) * offs_stride(hp->lgB) > ws[b]->hist_entries) return false;
-    const int64_t one_level = most_segments(records < kPartOneLevel ? records : kPartOneLevel, kSegMax);
-    while (one_level * offs_stride(cap) > ws[b]->hist_entries) {
-      if (cap == 0) return false;
-      --cap;
-    }
+    int lgB, lg2;
+    part_levels(buckets_log2(records, num_batches), lgB, lg2, num_batches);
+    if (!fit_hop(ws[b], lgB, lg2, most_segments(records, kSegMax),
+                 most_segments(records < kPartOneLevel ? records : kPartOneLevel, kSegMax), &hp->one_level[b]))
+      return false;
   }
   part_levels(buckets_log2(most, num_batches), hp->lgB, hp->lg2, num_batches);
-  const int lg = hp->lgB + hp->lg2;
-  hp->one_level = lg < cap ? lg : cap;
+  settle_levels(num_batches, hp);
   return true;
 }
 
@@ -641,9 +649,12 @@ void launch_dedup(const Launch& P, unsigned G, hipStream_t st) {
   else k_dedup_buckets<false><<<blocks, kThreads, 0, st>>>(P);
 }
 
+// LDS for the bucket counts and offsets of a segment.
+size_t offsets_lds_bytes(int lgB) { return offs_stride(lgB) * sizeof(uint16_t); }
+
 template <int PER>
 void launch_sample_part_of(const Launch& P, unsigned blocks, hipStream_t st) {
-  const size_t lds = offs_stride(P.lgB) * sizeof(uint16_t);
+  const size_t lds = offsets_lds_bytes(P.lgB);
   if (P.d <= 8) k_sample_part<8, PER><<<blocks, kThreads, lds, st>>>(P);
   else if (P.d <= 16) k_sample_part<16, PER><<<blocks, kThreads, lds, st>>>(P);
   else k_sample_part<32, PER><<<blocks, kThreads, lds, st>>>(P);
@@ -1041,12 +1052,15 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       P.b[b].blk_indptr = outs[b].indptr[h];
       P.b[b].blk_indices = outs[b].indices[h];
       P.b[b].edge_capacity = outs[b].edge_capacity[h];
+      if (part) P.b[b].one_level = plan[h].one_level[b];
+    }
+    if (part) {
+      P.lgB = plan[h].most_lgB;
+      P.lg = plan[h].lgB + plan[h].lg2;
     }
     const int64_t rows = max_n[h];
     const unsigned tile_blocks = blocks_for(rows, kTileRows, kCap);
     if (part && !wide) {
-      P.lgB = plan[h].one_level;
-      P.lg = plan[h].lgB + plan[h].lg2;
       P.block_rows = plan[h].block_rows;
       {
         StageTimer t_(SMFG_STAGE_PARTITION, st);
@@ -1085,19 +1099,15 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       if (part) {
         P.flat = 1;
         const int64_t stream_bound = rows + samples[h];  // known nodes + samples of this hop, at most
-        P.lgB = plan[h].one_level;
-        P.lg = plan[h].lgB + plan[h].lg2;
         // the bound is loose when whole neighbourhoods are taken; blocks stride over more
         const unsigned stream_blocks = blocks_for(stream_bound, kFlatThreads, 1024);
-        // 2^lgB buckets is the most the device can settle on in one level
-        const size_t lds = offs_stride(P.lgB) * sizeof(uint16_t);
         {
           StageTimer t_(SMFG_STAGE_SAMPLE, st);
           k_sample_wide<false><<<wave_blocks * G, kThreads, wide_lds_bytes(P.d), st>>>(P);
         }
         {
           StageTimer t_(SMFG_STAGE_PARTITION, st);
-          k_part_flat<<<stream_blocks * G, kFlatThreads, lds, st>>>(P);
+          k_part_flat<<<stream_blocks * G, kFlatThreads, offsets_lds_bytes(P.lgB), st>>>(P);
           if (P.lg > kPartMaxLgB) launch_split(P, stream_bound, st);
         }
         {

@@ -120,3 +120,21 @@ def test_static_calls_with_few_offsets_left():
         with pytest.raises(smfg.SmfgError) as e:
             smfg.sample_mfg_static(gg.g, dev[:seeds], fan, 11, out)
         assert e.value.code == smfg.ERR_CAPACITY
+
+
+@pytest.mark.parametrize("fanouts,sizes", [((100,), (26_000, 16)), ((100,), (20_000, 1)), ((100,), (1, 26_000, 300, 12_000)),
+                                           ((40, 40), (2000, 1)), ((-1,), (3, 24_000))])
+def test_wide_set_of_one_large_and_one_small_workspace(fanouts, sizes):
+    """A workspace made for each batch: the small one has offsets for a few buckets only, the large batch takes 2048, or two
+    levels beyond 2.5 M records, beside it."""
+    n = 150_000
+    rng = np.random.default_rng(5)
+    gg = GpuGraph(np.arange(n + 1, dtype=np.int64) * 110, rng.integers(0, n, size=110 * n).astype(np.int32), None)
+    s = [rng.permutation(n)[:k].astype(np.int32) for k in sizes]
+    samples = [110 * k if fanouts[0] < 0 else 0 for k in sizes]
+    ws = [smfg.workspace_create(gg.g, k, fanouts, 0, e) for k, e in zip(sizes, samples)]
+    outs = [smfg.alloc_output(gg.g, k, fanouts, edge_capacity=[e] if e else None) for k, e in zip(sizes, samples)]
+    for turn in range(2):
+        smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(x).to(DEV) for x in s], fanouts, [turn + 10 * b for b in range(len(s))], outs)
+        for b, (x, out) in enumerate(zip(s, outs)):
+            assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(x, fanouts, turn + 10 * b), len(fanouts))

@@ -24,11 +24,12 @@ void* plan(int64_t num_nodes, int32_t max_seeds, int32_t L, const int32_t* fanou
 }
 void drop(void* ws) { delete static_cast<smfg_workspace*>(ws); }
 int64_t records(const void* ws) { return static_cast<const smfg_workspace*>(ws)->rec_entries; }
-static int64_t room(const smfg_workspace* w, int64_t count, int64_t cap, int64_t records, int batches, int one_level, int lg) {
-  int lgB, lg2;
-  part_levels(part_buckets_lg(records, batches, lg), lgB, lg2, batches);
-  if (lg2 == 0 && lgB > one_level) lgB = one_level;
+// the levels that `records` of a hop's batch b take, if they have room in its workspace and in the LDS of the hop's blocks
+static int64_t room(const smfg_workspace* w, int64_t count, int64_t cap, int64_t records, int batches, const HopPlan& hp, int b) {
+  const HopShape hs = hop_levels(records, batches, hp.lgB + hp.lg2, hp.one_level[b]);
+  const int lgB = hs.lgB, lg2 = hs.lg2;
   if (count * offs_stride(lgB) * 2 > w->b_hist) return -1;
+  if (offs_stride(lgB) * 2 > offsets_lds_bytes(hp.most_lgB)) return -4;
   if (lg2 == 0) return 1;
   if (lgB > kPartMaxLgB || lg2 > kPartMaxLg2) return -2;
   const int64_t range = split_range(static_cast<uint32_t>(cap), lgB);
@@ -47,7 +48,7 @@ int64_t drawn(void* ws, int32_t batches, int64_t max_rows, int32_t d, int64_t ro
   if (hp.row_blocks * hp.block_rows < max_rows) return -13;
   const int64_t cap = static_cast<int64_t>(hp.block_rows) * (1 + d);
   if ((rows + hp.block_rows - 1) / hp.block_rows * cap > w->rec_entries + cap) return -14;
-  return room(w, (rows + hp.block_rows - 1) / hp.block_rows, cap, rows * (1 + d), batches, hp.one_level, hp.lgB + hp.lg2);
+  return room(w, (rows + hp.block_rows - 1) / hp.block_rows, cap, rows * (1 + d), batches, hp, 0);
 }
 // gives up offsets until the workspace takes `bytes`
 int32_t cut(void* ws, int64_t bytes) { return fit_workspace(static_cast<smfg_workspace*>(ws), bytes) ? 1 : 0; }
@@ -63,7 +64,23 @@ int64_t flat(void* ws, int32_t batches, int64_t bound, int64_t records) {
   HopPlan hp;
   if (!plan_flat_hop(all, batches, bound, &hp)) return 0;
   const int64_t cap = flat_seg(batches, static_cast<uint32_t>(records));
-  return room(w, (records + cap - 1) / cap, cap, records, batches, hp.one_level, hp.lgB + hp.lg2);
+  return room(w, (records + cap - 1) / cap, cap, records, batches, hp, 0);
+}
+// The same for every batch of a set whose workspaces differ, records[b] of each; `share`: the most records to a bucket in a
+// batch whose workspace was not cut.
+int64_t flat_set(void** ws, int32_t batches, int64_t bound, const int64_t* records, int64_t* share) {
+  const smfg_workspace* const* w = reinterpret_cast<const smfg_workspace* const*>(ws);
+  HopPlan hp;
+  if (!plan_flat_hop(w, batches, bound, &hp)) return 0;
+  *share = 0;
+  for (int b = 0; b < batches; ++b) {
+    const int64_t cap = flat_seg(batches, static_cast<uint32_t>(records[b]));
+    const int64_t got = room(w[b], (records[b] + cap - 1) / cap, cap, records[b], batches, hp, b);
+    if (got < 0) return got;
+    const HopShape hs = hop_levels(records[b], batches, hp.lgB + hp.lg2, hp.one_level[b]);
+    if (records[b] >> (hs.lgB + hs.lg2) > *share) *share = records[b] >> (hs.lgB + hs.lg2);
+  }
+  return 1;
 }
 }
 """
@@ -85,6 +102,7 @@ def host(tmp_path_factory):
     h.records.argtypes, h.records.restype = [vp], i64
     h.drawn.argtypes, h.drawn.restype = [vp, i32, i64, i32, i64], i64
     h.flat.argtypes, h.flat.restype = [vp, i32, i64, i64], i64
+    h.flat_set.argtypes, h.flat_set.restype = [ctypes.POINTER(vp), i32, i64, ctypes.POINTER(i64), ctypes.POINTER(i64)], i64
     h.cut.argtypes = [vp, i64]
     h.size.argtypes, h.size.restype = [vp, ctypes.POINTER(i64)], i64
     return h
@@ -153,3 +171,28 @@ def test_workspaces_cut_to_fit_hold_the_offsets_or_refuse(host):
                     seen.add(got)
         host.drop(w)
     assert seen == {0, 1, 2}
+
+
+def test_wide_sets_of_workspaces_of_any_size(host):
+    """A launch set over exact offsets: every batch has the buckets that its own records take, 1228 of them to a bucket at
+    most, whatever the workspaces beside its own were made for, and a block has LDS for them."""
+    rnd = random.Random(11)
+    fan = (ctypes.c_int32 * 2)(100, 100)
+    seen = set()
+    for turn in range(300):
+        nodes = 2_450_000 if turn < 20 else int(10 ** rnd.uniform(3, 7))
+        tops = [2048, 1] if turn < 20 else [int(10 ** rnd.uniform(0, 3.6)) for _ in range(rnd.randint(2, 16))]
+        ws = [host.plan(nodes, top, 2, fan, 0) for top in tops]
+        if all(ws):
+            most = [host.records(w) for w in ws]
+            bound = max(most) if turn < 20 else rnd.randint(1, max(most))
+            share = ctypes.c_int64()
+            for _ in range(40):
+                recs = [rnd.choice([min(bound, m), int(min(bound, m) ** rnd.random()), rnd.randint(1, min(bound, m))]) for m in most]
+                got = host.flat_set((ctypes.c_void_p * len(ws))(*ws), len(ws), bound, (ctypes.c_int64 * len(ws))(*recs), share)
+                assert got == 1 and share.value <= 1228, (got, share.value, nodes, tops, bound, recs)
+                seen.add(max(recs) >= 1229 << 11)
+        for w in ws:
+            if w:
+                host.drop(w)
+    assert seen == {False, True}
