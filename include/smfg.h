@@ -307,7 +307,9 @@ int smfg_read_counts(const smfg_output_t *out, int32_t L, int64_t *h_counts, voi
  * level 1 = only the feature gather launch, level 2 = every launch.  At most max_records
  * launches are recorded, later ones run untimed.  smfg_profile_end synchronises the device,
  * adds up the event-to-event milliseconds and the launch count per stage, and frees the events.
- * A launch that does the work of two stages is counted in both; its time goes to one of them.
+ * A launch that does the work of two stages is counted in both; its time goes to the first: one that
+ * draws and partitions a hop's samples (SAMPLE, PARTITION), one that assembles a hop and draws for the
+ * next or copies the feature rows (ASSEMBLE, and SAMPLE or GATHER).
  */
 #define SMFG_STAGE_CLEAR 0
 #define SMFG_STAGE_SEEDS 1

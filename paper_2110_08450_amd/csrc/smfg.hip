@@ -1063,9 +1063,12 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     if (part && !wide) {
       P.block_rows = plan[h].block_rows;
       {
-        StageTimer t_(SMFG_STAGE_PARTITION, st);
+        StageTimer t_(SMFG_STAGE_SAMPLE, st, SMFG_STAGE_PARTITION);
         launch_sample_part(P, plan[h], G, st);
-        if (P.lg > kPartMaxLgB) launch_split(P, rows * (1 + P.d), st);
+      }
+      if (P.lg > kPartMaxLgB) {
+        StageTimer t_(SMFG_STAGE_PARTITION, st);
+        launch_split(P, rows * (1 + P.d), st);
       }
       {
         StageTimer t_(SMFG_STAGE_DEDUP, st);

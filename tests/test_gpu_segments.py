@@ -138,3 +138,20 @@ def test_wide_set_of_one_large_and_one_small_workspace(fanouts, sizes):
         smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(x).to(DEV) for x in s], fanouts, [turn + 10 * b for b in range(len(s))], outs)
         for b, (x, out) in enumerate(zip(s, outs)):
             assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(x, fanouts, turn + 10 * b), len(fanouts))
+
+
+def test_stages_of_launches_that_do_two():
+    """A hop of the partition strategy draws and partitions in one launch, counted in both stages, with its time in the
+    sampling; one of two levels is split in another."""
+    gg = random_graph(400_000, 40, 21)
+    for seeds, fan, splits in [(20_000, (10,), 0), (150_000, (20,), 1)]:
+        s = torch.arange(seeds, dtype=torch.int32, device=DEV)
+        ws = smfg.workspace_create(gg.g, seeds, fan)
+        out = smfg.alloc_output(gg.g, seeds, fan)
+        smfg.profile_begin(2, 100)
+        try:
+            smfg.sample_mfg(gg.g, ws, s, fan, 1, out)
+        finally:
+            prof = smfg.profile_end()
+        assert prof["sample_insert"][1] == 1 and prof["sample_insert"][0] > 0
+        assert prof["partition"][1] == 1 + splits
