@@ -383,7 +383,8 @@ def main():
     dt = pass_s[len(pass_s) // 2] if len(pass_s) % 2 else 0.5 * (pass_s[len(pass_s) // 2 - 1] + pass_s[len(pass_s) // 2])
     gather_ms, gather_launches = stages["gather"]
     gather_bytes = 2 * row_bytes * n_final * passes
-    gather_gbs = gather_bytes / (gather_ms * 1e-3) / 1e9 if gather_ms > 0 else 0.0
+    # none of its own where the sampling launches copy the rows (small calls that gather themselves)
+    gather_gbs = gather_bytes / (gather_ms * 1e-3) / 1e9 if gather_ms > 0 else None
     cnt_of_slot = {}
     for q, (c, k, slot) in last_call.items():
         cnt_of_slot[q] = [cnt[(c + b) % K] for b in range(k)]
@@ -500,10 +501,10 @@ def main():
         "path_algorithmic_GBps": alg / dt / 1e9,
         "path_frac_of_hbm_peak": alg / dt / 1e9 / HBM_PEAK_GBS,
         "roofline": {"bound": "hbm", "kernel": "k_gather", "achieved": gather_gbs, "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": gather_gbs / HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": gather_gbs / HBM_PEAK_GBS if gather_gbs else None,
                      "traffic": traffic_row * n_final * passes / max(1, gather_launches) if traffic_row else None,
                      "traffic_unit": "bytes per launch", "traffic_note": traffic_note,
-                     "avg_launch_ms": gather_ms / max(1, gather_launches), "launches": gather_launches,
+                     "avg_launch_ms": gather_ms / gather_launches if gather_gbs else None, "launches": gather_launches,
                      "note": "achieved = algorithmic bytes of all gather launches of the timed region / their summed "
                              "durations (HIP events on the launch's own stream).  With --pipeline 1 every one of them "
                              "but the very last shares the chip with the sampling kernels of the next launch set; "
@@ -513,7 +514,7 @@ def main():
                      "algorithmic_bytes_per_launch": gather_bytes / max(1, gather_launches),
                      "device_copy_GBps": copy_gbs,
                      "alone_frac_of_device_copy": alone_gbs / copy_gbs if copy_gbs > 0 else None,
-                     "read_only_half_GBps": gather_gbs / 2},
+                     "read_only_half_GBps": gather_gbs / 2 if gather_gbs else None},
     }
 
     if consumer is not None:

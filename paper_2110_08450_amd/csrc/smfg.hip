@@ -86,17 +86,16 @@ struct Profiler {
   std::atomic<int> used{0};  // launches may be issued from several threads while a profile is open
   hipEvent_t* ev = nullptr;  // 2 per record
   int* stage = nullptr;
+  std::atomic<int64_t> also[SMFG_NUM_STAGES] = {};  // launches that did a stage's work besides that of their own
 } g_prof;
 
 struct StageTimer {
   int rec = -1;
   hipStream_t st;
-  // also: another stage that the launch does the work of; it is counted there as well, and its time only in `stage`
+  // also: another stage that the launch does the work of; it is counted there, without a time
   StageTimer(int stage, hipStream_t s, int also = -1) : st(s) {
     if (g_prof.level == 0) return;
-    if (also >= 0) {
-      StageTimer counted(also, s);
-    }
+    if (also >= 0 && (g_prof.level == 2 || also == SMFG_STAGE_GATHER)) g_prof.also[also].fetch_add(1, std::memory_order_relaxed);
     if (g_prof.level == 1 && stage != SMFG_STAGE_GATHER) return;
     const int r = g_prof.used.fetch_add(1, std::memory_order_relaxed);
     if (r >= g_prof.max_records) return;
@@ -117,6 +116,7 @@ void profiler_free() {
   g_prof.level = 0;
   g_prof.max_records = 0;
   g_prof.used.store(0);
+  for (auto& n : g_prof.also) n.store(0);
   g_prof.ev = nullptr;
   g_prof.stage = nullptr;
 }
@@ -1419,6 +1419,7 @@ int smfg_profile_end(double* stage_ms, int64_t* stage_launches) {
     stage_ms[g_prof.stage[r]] += ms;
     stage_launches[g_prof.stage[r]] += 1;
   }
+  for (int s = 0; s < SMFG_NUM_STAGES; ++s) stage_launches[s] += g_prof.also[s].load();
   profiler_free();
   return SMFG_OK;
 }

@@ -155,3 +155,23 @@ def test_stages_of_launches_that_do_two():
             prof = smfg.profile_end()
         assert prof["sample_insert"][1] == 1 and prof["sample_insert"][0] > 0
         assert prof["partition"][1] == 1 + splits
+
+
+@pytest.mark.parametrize("level", [1, 2])
+@pytest.mark.parametrize("dim,folded", [(32, True), (3, False)])
+def test_a_gather_without_a_launch_has_no_time(dim, folded, level):
+    """Rows that the last hop's launch copies itself are counted as a gather; its time is that launch's."""
+    gg = random_graph(20_000, 30, 17, dim=dim, dtype=np.float32)
+    s = torch.arange(100, dtype=torch.int32, device=DEV)
+    ws = smfg.workspace_create(gg.g, 100, (10, 5))
+    out = smfg.alloc_output(gg.g, 100, (10, 5))
+    smfg.profile_begin(level, 100)
+    try:
+        for key in range(3):
+            smfg.sample_mfg(gg.g, ws, s, (10, 5), key, out)
+    finally:
+        prof = smfg.profile_end()
+    assert prof["gather"][1] == 3 and (prof["gather"][0] == 0) == folded
+    assert prof["assemble"][1] == (6 if level == 2 else 0) == prof["sample_insert"][1]
+    again = smfg.profile_end()
+    assert all(n == 0 for _, n in again.values())
