@@ -66,15 +66,13 @@ struct HopShape {
 // 2^kPartSplitLgB buckets (more if the second would exceed 2^kPartMaxLg2), of which a segment of 4096 records
 // has a part of 16, a line of 128 bytes, to be read by k_split_buckets.
 constexpr int kPartSplitLgB = 8;
-constexpr int part_split_lg(int) { return kPartSplitLgB; }  // whatever the number of batches
-__host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2, int batches = SMFG_MAX_BATCHES) {
+__host__ __device__ inline void part_levels(int lg, int& lgB, int& lg2) {
   if (lg <= kPartMaxLgB) {
     lgB = lg;
     lg2 = 0;
     return;
   }
-  const int least = part_split_lg(batches);
-  lgB = lg - kPartMaxLg2 > least ? lg - kPartMaxLg2 : least;
+  lgB = lg - kPartMaxLg2 > kPartSplitLgB ? lg - kPartMaxLg2 : kPartSplitLgB;
   lg2 = lg - lgB;
 }
 // log2 of the buckets for that many records of a batch, `most` at most.
@@ -87,7 +85,7 @@ __host__ __device__ inline int part_buckets_lg(long long records, int batches, i
 // workspace has offsets for.
 __host__ __device__ inline HopShape hop_levels(long long records, int batches, int lg, int one_level) {
   HopShape s;
-  part_levels(part_buckets_lg(records, batches, lg), s.lgB, s.lg2, batches);
+  part_levels(part_buckets_lg(records, batches, lg), s.lgB, s.lg2);
   if (s.lg2 == 0 && s.lgB > one_level) s.lgB = one_level;
   return s;
 }

@@ -243,7 +243,7 @@ int buckets_log2(int64_t records, int batches = 1) { return part_buckets_lg(reco
 
 HopPlan plan_hop(int64_t max_rows, int d, int batches) {
   HopPlan hp;
-  part_levels(buckets_log2(max_rows * (1 + d), batches), hp.lgB, hp.lg2, batches);
+  part_levels(buckets_log2(max_rows * (1 + d), batches), hp.lgB, hp.lg2);
   int64_t rows = (max_rows + kSegments - 1) / kSegments;
   const int64_t least = (64 / d) * (kThreads / 64);
   if (rows < least) rows = least;
@@ -384,12 +384,12 @@ bool plan_flat_hop(const smfg_workspace* const* ws, int num_batches, int64_t bou
     const int64_t records = bound < ws[b]->rec_entries ? bound : ws[b]->rec_entries;
     if (records > most) most = records;
     int lgB, lg2;
-    part_levels(buckets_log2(records, num_batches), lgB, lg2, num_batches);
+    part_levels(buckets_log2(records, num_batches), lgB, lg2);
     if (!fit_hop(ws[b], lgB, lg2, most_segments(records, kSegMax),
                  most_segments(records < kPartOneLevel ? records : kPartOneLevel, kSegMax), &hp->one_level[b]))
       return false;
   }
-  part_levels(buckets_log2(most, num_batches), hp->lgB, hp->lg2, num_batches);
+  part_levels(buckets_log2(most, num_batches), hp->lgB, hp->lg2);
   settle_levels(num_batches, hp);
   return true;
 }

@@ -32,10 +32,12 @@ int32_t row_bounds(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t
   return hop_row_bounds(num_seeds, L, fanouts, num_nodes, node_capacity, rows) ? 1 : 0;
 }
 // lgB, lg2 and the least lgB of a hop of two levels
-void levels(int32_t lg, int32_t batches, int32_t* out) {
-  part_levels(lg, out[0], out[1], batches);
-  out[2] = part_split_lg(batches);
+void levels(int32_t lg, int32_t* out) {
+  part_levels(lg, out[0], out[1]);
+  out[2] = kPartSplitLgB;
 }
+int32_t buckets(int64_t records, int32_t batches) { return buckets_log2(records, batches); }
+int64_t one_level_records() { return kPartOneLevel; }
 int32_t max_levels(int32_t which) { return which == 0 ? kPartMaxLgB : kPartMaxLg2; }
 int32_t gather_block(int64_t row_bytes) { return gather_rows_per_block(row_bytes); }
 int32_t gather_vector(int64_t address, int64_t row_bytes) {
@@ -81,7 +83,9 @@ def host(tmp_path_factory):
     h.drop.argtypes = h.is_part.argtypes = h.slots.argtypes = [vp]
     h.slots.restype = i64
     h.crowded.argtypes = [i64, i32, i32]
-    h.levels.argtypes = [i32, i32, I32P]
+    h.levels.argtypes = [i32, I32P]
+    h.buckets.argtypes = [i64, i32]
+    h.one_level_records.restype = i64
     h.gather_block.argtypes, h.gather_vector.argtypes = [i64], [i64, i64]
     h.hist_entries.argtypes, h.hist_entries.restype = [vp], i64
     h.part_hop.argtypes, h.part_hop.restype = [ctypes.POINTER(vp), i32, i64, i32, I64P], i64
@@ -200,14 +204,27 @@ def test_gather_blocks_stay_within_their_indices(host):
                 assert vec >= 8
 
 
-def test_bucket_levels_for_every_number_of_batches(host):
-    """How 2^lg hash buckets are laid out in one or two levels: within what the kernels' LDS arrays hold;
-    together always 2^lg, so that the capacity of a workspace does not depend on the launch set; a hop of two
-    levels starts with at least as many buckets as its number of batches asks for."""
+def test_bucket_levels(host):
+    """How 2^lg hash buckets are laid out in one or two levels: within what the kernels' LDS arrays hold, together
+    always 2^lg; a hop of two levels starts with 256 buckets or more."""
     most_b, most_2 = host.max_levels(0), host.max_levels(1)
     out = (ctypes.c_int32 * 3)()
-    for batches in range(1, 17):
-        for lg in range(most_b + most_2 + 1):
-            host.levels(lg, batches, out)
-            assert out[0] + out[1] == lg and 0 <= out[0] <= most_b and 0 <= out[1] <= most_2
-            assert out[1] == 0 if lg <= most_b else (out[1] > 0 and out[0] >= out[2])
+    for lg in range(most_b + most_2 + 1):
+        host.levels(lg, out)
+        assert out[0] + out[1] == lg and 0 <= out[0] <= most_b and 0 <= out[1] <= most_2
+        assert out[1] == 0 if lg <= most_b else (out[1] > 0 and out[0] >= out[2] == 8)
+
+
+def test_bucket_levels_for_every_number_of_batches(host):
+    """Two levels begin at the same number of records however many batches share a launch, so that the capacity of a
+    workspace does not depend on the launch set; a batch never has more buckets for being one of several, and has the
+    same ones from 512 in all."""
+    most_b, one_level = host.max_levels(0), host.one_level_records()
+    rnd = random.Random(3)
+    for records in [1, one_level - 1, one_level] + [int(10 ** rnd.uniform(0, 9)) for _ in range(2000)]:
+        alone = host.buckets(records, 1)
+        assert (alone > most_b) == (records >= one_level)
+        for batches in range(2, 17):
+            lg = host.buckets(records, batches)
+            assert lg <= alone and (lg == alone or batches << lg >= 512)
+            assert lg == alone or alone <= most_b
