@@ -202,10 +202,9 @@ int smfg_sample_mfg(const smfg_graph_t *g, smfg_workspace_t *ws, const int32_t *
  * outputs and results as smfg_sample_mfg, but the scratch lives in a fixed array inside the
  * library (SMFG_STATIC_SCRATCH_BYTES per GPU, held from the library's load until the process
  * ends) and the call allocates and frees nothing.  The scratch needed grows with
- * out->node_capacity and the fanouts as smfg_workspace_bytes reports for a workspace
- * created with (num_seeds, fanouts, out->node_capacity); where that is a few MiB more than the
- * array holds, the call makes do with fewer hash buckets, if its hops allow it.  A call that needs
- * more than that returns SMFG_ERR_CAPACITY and launches nothing (pass a smaller out->node_capacity - a
+ * out->node_capacity and the fanouts exactly as smfg_workspace_bytes reports for a workspace
+ * created with (num_seeds, fanouts, out->node_capacity); a call that needs more than the array
+ * holds returns SMFG_ERR_CAPACITY and launches nothing (pass a smaller out->node_capacity - a
  * batch that outgrows it ends with SMFG_ST_NODE_CAPACITY - or use a workspace).  Fanouts must be
  * in [1, SMFG_MAX_WIDE_FANOUT] (SMFG_FANOUT_ALL has no size bound without a workspace:
  * SMFG_ERR_INVALID_ARG).  All calls on one GPU share the array: two calls that overlap in time

@@ -49,7 +49,8 @@ struct BatchCtx {
   uint32_t table_mask;
   // partition path (no table): records of a hop grouped by hash bucket
   uint64_t* rec;         // (node << 32 | value) per known node and per sample, in segments sorted by bucket
-  uint16_t* hist;        // per segment, the first record of each bucket within it and the end of the last
+  uint16_t* hist;        // per segment, the first record of each bucket within it and the end of the last; takes turns
+                         // with rowmn, and in hops of one level with bstart2 and rec2
   uint64_t* rec2;        // the records once more, each bucket's of a range of segments sorted by sub-bucket (hops with lg2 > 0)
   uint32_t* bstart2;     // [ranges][buckets][sub-buckets + 1] where each begins in rec2, and the end of the last
   int32_t one_level;     // log2 of the most buckets of the current hop that hist has room for in one level

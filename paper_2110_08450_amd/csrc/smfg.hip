@@ -157,9 +157,10 @@ struct smfg_workspace {
   bool forced;           // the strategy was named by SMFG_DEDUP: small calls keep to it too
   bool flat;             // partition strategy also over exact offsets (wide fanouts): group records, row starts etc. present
   int64_t rec_entries;   // capacity of rec: known nodes + samples of a hop
-  int64_t hist_entries;  // capacity of hist: segments x offsets of a hop
+  int64_t hist_entries;  // capacity of hist, segments x offsets, in hops of one level
+  int64_t hist_two;      // ... and in hops of two, which use what follows it
   int split_lg;          // log2 of the most sub-buckets a hop needs (0: no hop splits its buckets)
-  int64_t b_table, b_slot, b_row, b_tiles, b_stiles, b_rec, b_hist, b_bstart2, b_grp;  // byte sizes of the slab's parts
+  int64_t b_table, b_slot, b_row, b_rowmn, b_tiles, b_stiles, b_rec, b_bstart2, b_grp;  // byte sizes of the slab's parts
   uint32_t table_log2;
   void* slab;
   uint64_t* table;
@@ -261,16 +262,17 @@ int64_t most_segments(int64_t records, int64_t least) {
   return count > kSegments + 1 ? count : kSegments + 1;
 }
 
-// The entries of hist for hops of up to `records` records: the offsets of the most buckets in kSegments segments, or
-// in such of at least `least` records.  (A call of other fanouts, whose segments are smaller, makes do with
-// fewer buckets, see plan_part_hop.)
-int64_t hist_entries_for(int64_t records, int64_t least) {
+// The entries of hist for hops of up to `records` records: in one level, of up to kPartOneLevel, the offsets of the most
+// buckets in kSegments segments, or in such of at least `least` records (a call of other fanouts, whose segments are
+// smaller, makes do with fewer buckets, see fit_hop); in two levels those of any fanouts, 0 if there are none.
+int64_t one_level_entries(int64_t records, int64_t least) {
+  if (records >= kPartOneLevel) return most_segments(kPartOneLevel, least) * offs_stride(kPartMaxLgB);
+  return most_segments(records, least) * offs_stride(buckets_log2(records));
+}
+int64_t two_level_entries(int64_t records) {
   int lgB, lg2;
   part_levels(buckets_log2(records), lgB, lg2);
-  if (lg2 == 0) return most_segments(records, least) * offs_stride(lgB);
-  const int64_t one = most_segments(kPartOneLevel, least) * offs_stride(kPartMaxLgB);
-  const int64_t two = most_segments(records, seg_least(1)) * offs_stride(lgB);
-  return one > two ? one : two;
+  return lg2 > 0 ? most_segments(records, seg_least(1)) * offs_stride(lgB) : 0;
 }
 // Words of bstart2 for hops of up to `records` records that take two levels.  The segments of a range hold about
 // kSplitAim << lgB records, less what rounding the range down to whole segments takes off.
@@ -338,7 +340,7 @@ bool part_needs(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t nu
     if (records > *rec_entries) *rec_entries = records;
     if (hp.lg2 > 0 && hp.lgB + hp.lg2 > *split_lg) *split_lg = hp.lgB + hp.lg2;
   }
-  *hist_entries = hist_entries_for(*rec_entries, least);
+  *hist_entries = one_level_entries(*rec_entries, least);
   if (*rec_entries < kPartMinRecords && !part_forced()) return false;
   return true;
 }
@@ -346,7 +348,7 @@ bool part_needs(int32_t num_seeds, int32_t L, const int32_t* fanouts, int64_t nu
 // A batch takes two levels by its number of records alone, so its workspace has to have all the offsets that takes, 2^lgB
 // buckets in `two` segments; in one level, of `one` segments, it makes do with fewer buckets.  False if that does not help.
 bool fit_hop(const smfg_workspace* ws, int lgB, int lg2, int64_t two, int64_t one, int* one_level) {
-  if (lg2 > 0 && two * offs_stride(lgB) > ws->hist_entries) return false;
+  if (lg2 > 0 && two * offs_stride(lgB) > ws->hist_two) return false;
   *one_level = lg2 > 0 ? kPartMaxLgB : lgB;
   while (one * offs_stride(*one_level) > ws->hist_entries) {
     if (*one_level == 0) return false;
@@ -430,7 +432,7 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
     ws->rec_entries = node_capacity + ws->slot_entries;
     const int lg = buckets_log2(ws->rec_entries);
     ws->split_lg = lg > kPartMaxLgB ? lg : 0;
-    ws->hist_entries = hist_entries_for(ws->rec_entries, seg_least(SMFG_MAX_FANOUT));
+    ws->hist_entries = one_level_entries(ws->rec_entries, seg_least(SMFG_MAX_FANOUT));
   } else {
     ws->part = !table_forced() &&
                part_needs(max_seeds, L, fanouts, g->num_nodes, node_capacity, &ws->rec_entries, &ws->hist_entries,
@@ -440,34 +442,27 @@ int plan_workspace(smfg_workspace* ws, const smfg_graph* g, int32_t max_seeds, i
   const int64_t tiles = (node_capacity + kTileRows - 1) / kTileRows + 1;
   ws->b_slot = align256(ws->slot_entries * 4);
   ws->b_row = align256((node_capacity + 4) * 4);
+  ws->b_rowmn = 2 * ws->b_row;
   ws->b_tiles = align256(tiles * 8);
   ws->b_stiles = align256((ws->slot_entries / kWideTile + 2) * 8);
   if (ws->part) {
     ws->b_rec = align256(ws->rec_entries * 8);
-    ws->b_hist = align256(ws->hist_entries * 2);
+    // hist and rowmn take turns: flag_rows writes the one when dedup_buckets has read the other.  A hop of one level
+    // uses neither bstart2 nor rec2, so its offsets may run on over them.
+    const int64_t hist = 2 * (ws->split_lg > 0 ? two_level_entries(ws->rec_entries) : ws->hist_entries);
+    if (ws->b_rowmn < hist) ws->b_rowmn = align256(hist);
     ws->b_bstart2 = ws->split_lg > 0 ? align256(split_entries_for(ws->rec_entries) * 4) : 0;
-    ws->bytes = ws->b_slot + 4 * ws->b_row + ws->b_tiles + (ws->split_lg > 0 ? 2 : 1) * ws->b_rec + ws->b_hist +
-                ws->b_bstart2;
+    const int64_t second = ws->split_lg > 0 ? ws->b_bstart2 + ws->b_rec : 0;
+    ws->hist_two = ws->b_rowmn / 2;
+    ws->hist_entries = (ws->b_rowmn + second) / 2;
+    ws->bytes = ws->b_slot + 2 * ws->b_row + ws->b_rowmn + ws->b_tiles + ws->b_rec + second;
     ws->b_grp = ws->flat ? align256((ws->slot_entries / 64 + 2) * 16) : 0;
     if (ws->flat) ws->bytes += ws->b_grp + 3 * ws->b_row + ws->b_stiles;
   } else {
     ws->b_table = align256((int64_t(1) << lg) * 8);
-    ws->bytes = ws->b_table + 4 * ws->b_slot + 8 * ws->b_row + ws->b_tiles + ws->b_stiles;
+    ws->bytes = ws->b_table + 4 * ws->b_slot + 6 * ws->b_row + ws->b_rowmn + ws->b_tiles + ws->b_stiles;
   }
   return SMFG_OK;
-}
-
-// Makes a planned workspace fit `bytes` by giving up offsets, which costs buckets in hops of one level, but not more than
-// leave 64 of them in kSegments segments.  False if that is not enough.  Hops of two levels may then have no room, which
-// plan_part_hop and plan_flat_hop find out.
-bool fit_workspace(smfg_workspace* ws, int64_t bytes) {
-  if (ws->bytes <= bytes) return true;
-  const int64_t b_hist = ws->b_hist - align256(ws->bytes - bytes);
-  if (!ws->part || b_hist < (kSegments + 1) * offs_stride(6) * 2) return false;
-  ws->bytes -= ws->b_hist - b_hist;
-  ws->b_hist = b_hist;
-  ws->hist_entries = b_hist / 2;
-  return true;
 }
 
 // Points the arrays of a planned workspace into `base` (ws->bytes bytes, 256-byte aligned).
@@ -475,16 +470,17 @@ void bind_workspace(smfg_workspace* ws, void* base) {
   uint8_t* p = static_cast<uint8_t*>(base);
   ws->gsrc = reinterpret_cast<int32_t*>(p); p += ws->b_slot;
   ws->rowk = reinterpret_cast<int32_t*>(p); p += ws->b_row;
-  ws->rowmn = reinterpret_cast<uint2*>(p); p += 2 * ws->b_row;
   ws->rowoff = reinterpret_cast<int32_t*>(p); p += ws->b_row;
   ws->tile_sums = reinterpret_cast<uint64_t*>(p); p += ws->b_tiles;
+  ws->rowmn = reinterpret_cast<uint2*>(p);
+  if (ws->part) ws->hist = reinterpret_cast<uint16_t*>(p);
+  p += ws->b_rowmn;
   if (ws->part) {
-    ws->rec = reinterpret_cast<uint64_t*>(p); p += ws->b_rec;
-    ws->hist = reinterpret_cast<uint16_t*>(p); p += ws->b_hist;
     if (ws->split_lg > 0) {
       ws->bstart2 = reinterpret_cast<uint32_t*>(p); p += ws->b_bstart2;
       ws->rec2 = reinterpret_cast<uint64_t*>(p); p += ws->b_rec;
     }
+    ws->rec = reinterpret_cast<uint64_t*>(p); p += ws->b_rec;
     if (ws->flat) {
       ws->grp = reinterpret_cast<uint4*>(p); p += ws->b_grp;
       ws->rowstart = reinterpret_cast<int64_t*>(p); p += 2 * ws->b_row;
@@ -1195,7 +1191,7 @@ int smfg_sample_mfg_static(const smfg_graph_t* g, const int32_t* d_seeds, int32_
   smfg_workspace ws;
   int rc = plan_workspace(&ws, g, num_seeds, L, fanouts, out->node_capacity, 0);
   if (rc != SMFG_OK) return rc;
-  if (!fit_workspace(&ws, SMFG_STATIC_SCRATCH_BYTES)) return SMFG_ERR_CAPACITY;
+  if (ws.bytes > static_cast<int64_t>(SMFG_STATIC_SCRATCH_BYTES)) return SMFG_ERR_CAPACITY;
   int cur = 0;
   hipError_t e = hipGetDevice(&cur);
   if (e != hipSuccess) return hip_err(e);

@@ -104,22 +104,24 @@ def test_flat_groups_and_tiles(samples, monkeypatch):
     assert_same(fetch(out, 1), gg.oracle.sample_mfg(s, (-1,), 3), 1)
 
 
-def test_static_calls_with_few_offsets_left():
-    """Wide fanouts whose scratch is made to fit 64 MiB by giving up offsets: the same results with all of them left, as few
-    as hops of two levels take (3.1 M records), and a refusal below."""
-    n, fan = 100_000, (100,)
+@pytest.mark.parametrize("n,fan,most,others", [(100_000, (100,), 30_907, (24_000, 29_894, 30_717, 30_876)), (300_000, (32,), 94_834, (75_000, 94_238))])
+def test_static_calls_up_to_the_limit_of_their_scratch(n, fan, most, others):
+    """Hops of one level and of two whose scratch takes nearly all of the 64 MiB, up to the last that a workspace of that
+    size would serve; the next one is refused."""
     rng = np.random.default_rng(3)
-    gg = GpuGraph(np.arange(n + 1, dtype=np.int64) * 110, rng.integers(0, n, size=110 * n).astype(np.int32), None)
+    deg = fan[0] + 10
+    gg = GpuGraph(np.arange(n + 1, dtype=np.int64) * deg, rng.integers(0, n, size=deg * n).astype(np.int32), None)
     perm = rng.permutation(n).astype(np.int32)
-    out = smfg.alloc_output(gg.g, 30_877, fan)
+    out = smfg.alloc_output(gg.g, most + 1, fan)
     dev = torch.from_numpy(perm).to(DEV)
-    for seeds in (24_000, 29_900, 30_716):
+    for seeds in (*others, most):
+        assert smfg.workspace_create(gg.g, seeds, fan).nbytes <= smfg.STATIC_SCRATCH_BYTES
         smfg.sample_mfg_static(gg.g, dev[:seeds], fan, 11, out)
         assert_same(fetch(out, 1), gg.oracle.sample_mfg(perm[:seeds], fan, 11), 1)
-    for seeds in (30_717, 30_800, 30_876, 30_877):
-        with pytest.raises(smfg.SmfgError) as e:
-            smfg.sample_mfg_static(gg.g, dev[:seeds], fan, 11, out)
-        assert e.value.code == smfg.ERR_CAPACITY
+    assert smfg.workspace_create(gg.g, most + 1, fan).nbytes > smfg.STATIC_SCRATCH_BYTES
+    with pytest.raises(smfg.SmfgError) as e:
+        smfg.sample_mfg_static(gg.g, dev[:most + 1], fan, 11, out)
+    assert e.value.code == smfg.ERR_CAPACITY
 
 
 @pytest.mark.parametrize("fanouts,sizes", [((100,), (26_000, 16)), ((100,), (20_000, 1)), ((100,), (1, 26_000, 300, 12_000)),

@@ -28,7 +28,7 @@ int64_t records(const void* ws) { return static_cast<const smfg_workspace*>(ws)-
 static int64_t room(const smfg_workspace* w, int64_t count, int64_t cap, int64_t records, int batches, const HopPlan& hp, int b) {
   const HopShape hs = hop_levels(records, batches, hp.lgB + hp.lg2, hp.one_level[b]);
   const int lgB = hs.lgB, lg2 = hs.lg2;
-  if (count * offs_stride(lgB) * 2 > w->b_hist) return -1;
+  if (count * offs_stride(lgB) > (lg2 > 0 ? w->hist_two : w->hist_entries)) return -1;
   if (offs_stride(lgB) * 2 > offsets_lds_bytes(hp.most_lgB)) return -4;
   if (lg2 == 0) return 1;
   if (lgB > kPartMaxLgB || lg2 > kPartMaxLg2) return -2;
@@ -48,13 +48,37 @@ int64_t drawn(void* ws, int32_t batches, int64_t max_rows, int32_t d, int64_t ro
   if (hp.row_blocks * hp.block_rows < max_rows) return -13;
   const int64_t cap = static_cast<int64_t>(hp.block_rows) * (1 + d);
   if ((rows + hp.block_rows - 1) / hp.block_rows * cap > w->rec_entries + cap) return -14;
+  const HopShape hs = hop_levels(rows * (1 + d), batches, hp.lgB + hp.lg2, hp.one_level[0]);
+  if (rows * (1 + d) >> (hs.lgB + hs.lg2) > kPartMostRecords) return -15;
   return room(w, (rows + hp.block_rows - 1) / hp.block_rows, cap, rows * (1 + d), batches, hp, 0);
 }
-// gives up offsets until the workspace takes `bytes`
-int32_t cut(void* ws, int64_t bytes) { return fit_workspace(static_cast<smfg_workspace*>(ws), bytes) ? 1 : 0; }
-int64_t size(const void* ws, int64_t* offsets) {
-  *offsets = static_cast<const smfg_workspace*>(ws)->b_hist;
-  return static_cast<const smfg_workspace*>(ws)->bytes;
+// Whether the arrays of a workspace, with hist as long as hops of one and of two levels may take it, lie one behind the
+// other, but for those that take turns; its size.
+int64_t layout(void* ws) {
+  smfg_workspace* w = static_cast<smfg_workspace*>(ws);
+  const uint64_t base = 1ull << 32;
+  bind_workspace(w, reinterpret_cast<void*>(base));
+  const int64_t n = w->node_capacity;
+  const auto end = [&](const void* p, int64_t bytes) { return reinterpret_cast<uint64_t>(p) + static_cast<uint64_t>(bytes); };
+  const auto at = [&](const void* p) { return reinterpret_cast<uint64_t>(p); };
+  const int64_t tiles = (n + kTileRows - 1) / kTileRows;
+  if (end(w->gsrc, w->slot_entries * 4) > at(w->rowk) || end(w->rowk, n * 4) > at(w->rowoff)) return -1;
+  if (end(w->rowoff, n * 4) > at(w->tile_sums) || end(w->tile_sums, tiles * 8) > at(w->rowmn) || at(w->hist) != at(w->rowmn)) return -2;
+  if (end(w->rowmn, n * 8) > at(w->split_lg > 0 ? static_cast<void*>(w->bstart2) : w->rec)) return -3;
+  if (end(w->hist, w->hist_two * 2) > at(w->split_lg > 0 ? static_cast<void*>(w->bstart2) : w->rec)) return -4;
+  if (end(w->hist, w->hist_entries * 2) > at(w->rec)) return -5;
+  if (w->split_lg > 0 && (end(w->bstart2, split_entries_for(w->rec_entries) * 4) > at(w->rec2) || end(w->rec2, w->rec_entries * 8) > at(w->rec))) return -6;
+  uint64_t last = end(w->rec, w->rec_entries * 8);
+  if (w->flat) {
+    if (last > at(w->grp) || end(w->grp, (w->slot_entries / 64 + 1) * 16) > at(w->rowstart) || end(w->rowstart, n * 8) > at(w->rowdeg) ||
+        end(w->rowdeg, n * 4) > at(w->stile_sums))
+      return -7;
+    last = end(w->stile_sums, (w->slot_entries / kWideTile + 1) * 8);
+  }
+  for (const void* p : {static_cast<void*>(w->gsrc), static_cast<void*>(w->rowk), static_cast<void*>(w->rowoff), static_cast<void*>(w->tile_sums),
+                        static_cast<void*>(w->rowmn), static_cast<void*>(w->bstart2), static_cast<void*>(w->rec2), static_cast<void*>(w->rec)})
+    if (at(p) % 256 != 0) return -8;
+  return last <= base + static_cast<uint64_t>(w->bytes) ? w->bytes : -9;
 }
 // `records` of a hop over exact offsets that was bounded by `bound`: 1 or 2 levels, 0 if the call is refused
 int64_t flat(void* ws, int32_t batches, int64_t bound, int64_t records) {
@@ -103,8 +127,7 @@ def host(tmp_path_factory):
     h.drawn.argtypes, h.drawn.restype = [vp, i32, i64, i32, i64], i64
     h.flat.argtypes, h.flat.restype = [vp, i32, i64, i64], i64
     h.flat_set.argtypes, h.flat_set.restype = [ctypes.POINTER(vp), i32, i64, ctypes.POINTER(i64), ctypes.POINTER(i64)], i64
-    h.cut.argtypes = [vp, i64]
-    h.size.argtypes, h.size.restype = [vp, ctypes.POINTER(i64)], i64
+    h.layout.argtypes, h.layout.restype = [vp], i64
     return h
 
 
@@ -127,6 +150,7 @@ def test_offsets_of_every_hop_fit_the_workspace(host, wide):
         if not w:
             continue
         most = host.records(w)
+        assert host.layout(w) > 0, (host.layout(w), nodes, fan, seeds)
         for batches in (1, 2, 4, 8, 16):
             if wide:
                 for bound in {most, rnd.randint(1, most)}:
@@ -147,30 +171,18 @@ def test_offsets_of_every_hop_fit_the_workspace(host, wide):
     assert levels == {("drawn", 1), ("drawn", 2)} | ({("flat", 1), ("flat", 2)} if wide else set())
 
 
-def test_workspaces_cut_to_fit_hold_the_offsets_or_refuse(host):
-    """Calls over exact offsets whose scratch was made to fit by giving up offsets, at limits from all of them to none: what is
-    still accepted has room for whatever a batch turns out to have, in one level or two; 100 000 nodes of
-    degree 100, 30 876 seeds of fanout 100 and the 64 MiB of a static call among them."""
-    rnd = random.Random(7)
-    seen = set()
-    cases = [(100_000, [100], 30_876, 64 << 20), (100_000, [100], 30_718, 64 << 20), (50_000, [100], 31_950, 64 << 20)]
-    for _ in range(400):
-        fan = [rnd.choice([1, 3, 10, 32, 40, 100, 300, 1000]) for _ in range(rnd.randint(0, 2))] + [rnd.choice([33, 100, 1000])]
-        cases.append((int(10 ** rnd.uniform(4, 7.5)), fan, int(10 ** rnd.uniform(0, 5.5)), 0))
-    for nodes, fan, seeds, limit in cases:
+def test_static_calls_near_the_limit_of_their_scratch(host):
+    """Calls that once took nearly all of the 64 MiB fit them with all the buckets that their records take."""
+    share = ctypes.c_int64()
+    for nodes, fan, seeds in [(100_000, [100], 29_893), (95_101, [327, 3, 3], 9_174), (717_948, [32], 82_705), (481_513, [32, 1000], 65),
+                              (524_879, [1000], 2_044), (311_627, [32], 92_402), (242_211, [5, 32, 10], 15_676), (35_837, [806, 40, 40], 3_874)]:
         w = host.plan(nodes, seeds, len(fan), (ctypes.c_int32 * len(fan))(*fan), 0)
-        if not w:
-            continue
-        offsets = ctypes.c_int64()
-        total, most = host.size(w, offsets), host.records(w)
-        if host.cut(w, limit or total - rnd.randint(0, offsets.value)):
-            for bound in {most, rnd.randint(1, most)}:
-                for r in _sizes(rnd, bound):
-                    got = host.flat(w, 1, bound, r)
-                    assert got >= 0, (got, nodes, fan, seeds, bound, r)
-                    seen.add(got)
+        assert 0 < host.layout(w) <= 64 << 20, (nodes, fan, seeds)
+        most = host.records(w)
+        if max(fan) > 32:
+            for r in {most, min(most, (1229 << 11) - 1), min(most, 1229 << 11)}:
+                assert host.flat_set((ctypes.c_void_p * 1)(w), 1, most, (ctypes.c_int64 * 1)(r), share) == 1 and share.value <= 1228
         host.drop(w)
-    assert seen == {0, 1, 2}
 
 
 def test_wide_sets_of_workspaces_of_any_size(host):
