@@ -1,6 +1,6 @@
 // libsmfg fast path (fanouts up to SMFG_MAX_FANOUT), samples at padded positions pos = i * d + s.
-// This file: the draw (draw_tile of the partition strategy and the small hops, draw_neighbour of the table
-// strategy), the table strategy's clear / seed insert / sample_insert, its flag_rows and assemble passes that
+// This file: the draw (draw_positions and read_neighbours of the partition strategy and the small hops,
+// draw_neighbour of the table strategy), the table strategy's clear / seed insert / sample_insert, its flag_rows and assemble passes that
 // turn first-appearance information into local ids, and scan_tiles, which both strategies use.
 #ifndef SMFG_KERNELS_FAST_H_
 #define SMFG_KERNELS_FAST_H_

@@ -101,9 +101,10 @@ __device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B
 // [offs[b], offs[b + 1]) of its row of `hist`, offsets within the segment.  A bucket is the union of its parts
 // of all segments.  So no block has to know what the others hold before it writes.  With buckets of one
 // contiguous range each, the counts of all blocks had to be scanned between a kernel that counted and one that
-// read the samples back and moved the records: 1.0 M records in each of eight batches 179 us for
-// the three, 119 us for k_sample_part, which draws in 116 us of scattered reads and sorts beside them; its buckets'
-// many short parts cost k_dedup_buckets some us (59 -> 63).  29 M records of one batch (two levels): 575 -> 360 us.
+// read the samples back and moved the records: 1.0 M records in each of eight batches 168 us for
+// the three, 107 of them for the one that drew, 114 us for k_sample_part, which sorts beside its scattered reads; its buckets'
+// many short parts cost k_dedup_buckets some us (59 -> 68).  29 M records of one batch (two levels, with the split):
+// 549 -> 339 us, k_dedup_buckets 164 -> 210.
 // Blocks are of 256 threads, whose places a gather beside them leaves free often enough (whole neighbourhoods,
 // pipelined: k_part_flat with 1024 threads 780 us, 56 alone).  Segments of 4096 records, 16 per thread, instead of 2048
 // where a hop has more than 512 of those: k_dedup_buckets 78 -> 67 us, k_sample_part the same; 8192 records gain
@@ -298,7 +299,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_part(const Launch P) {
 // where each of its sub-buckets begins.  range is such that a block's records fit its registers unless they are
 // far from evenly spread.
 // It reads every record once; a block per bucket, which counted the whole bucket before it moved anything, took 154 us
-// for 29 M records, and 129 us so.
+// for 29 M records, and 130 us so.
 constexpr int kSplitThreads = kThreads;
 constexpr uint32_t kSplitMax = kSegPer * kSplitThreads;
 constexpr uint32_t kSplitAim = kSplitMax / 8u * 7u;  // some 8 standard deviations below

@@ -6,8 +6,8 @@
 // check of the input arrays).
 //
 // All batches of a call share each launch (the batch is the fastest-varying part of the block index).  A
-// hop is three launches where it is small, four or five under the partition strategy (their files describe
-// both), and four under the table strategy:
+// hop is two launches where it is small (and one before the first), four to six under the partition strategy (their
+// files describe both), and four under the table strategy:
 //   sample_insert  per destination: degree, Floyd/Philox row positions, neighbour ids, and an
 //                  insert of each neighbour into the batch's dedup table carrying the sample's
 //                  scan position (section 4.1 "fusing sampling and MFG construction": the edge
@@ -519,9 +519,9 @@ int static_scratch_of(int device, void** out) {
   return SMFG_OK;
 }
 
-// A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: hop
-// 0 of a batch of 1024 seeds x 15 (16 K records) 53 to 67 us with the partition strategy's
-// launches (six then), 21 to 29 us so.
+// A hop below kSmallRecords records in every batch takes k_small_*, also before larger hops: with hop 0 of
+// 1024 seeds x 15 (16 K records) under the partition strategy a whole call of one batch takes 131, 180 and 206 us
+// (the three graphs below, the smallest first), and 119, 168 and 199 us so.
 bool hop_is_small(int d, int64_t max_rows) { return d >= 1 && d <= SMFG_MAX_FANOUT && max_rows * (1 + d) < kSmallRecords; }
 // How many of a call's hops, counted from the first one, take the small path; rows[b][h] bounds the
 // destinations of hop h of batch b.  Each batch is held against its own workspace: its samples sit at
@@ -549,15 +549,16 @@ int small_hops_of(const smfg_workspace* const* ws, const int32_t* num_seeds, int
 }
 // A call that leaves the gather to another one is prepared beside the gather of another set, whose many short
 // blocks keep taking the places that a block of 16 waves waits for.  How much that costs depends on what else
-// runs: with a model behind the pipeline (a layer per hop) sets of up to four batches still gain from fewer
-// launches, larger ones hardly; with nothing behind it the largest graph loses from two batches on, all from
-// five.  Time per batch without / with small first hops, fanouts (15, 10, 5), 1024 seeds; graphs and tables as
-// papers100M (28 GB), products (490 MB) and arxiv (87 MB) have, and an eighth of papers100M with the model:
+// runs.  Time per batch without / with small first hops, fanouts (15, 10, 5), 1024 seeds; graphs and tables as
+// papers100M (28 GB), products (490 MB) and arxiv (87 MB) have, and an eighth of papers100M with a model behind the
+// pipeline (a layer per hop):
 //                        1 batch                  2 batches             4 batches              8 batches
-//   the call gathers     256/228 243/204 171/150  189/171 163/142 98/86 152/141 121/113 62/55  131/124 99/96 42/39 us
-//   beside a gather      243/237 154/141 146/127  163/171 109/107 62/56 129/142  90/92  42/41  111/122 83/84 34/33 us
-//   ... and a model      3, 4, 6, 7, 8 and 16 batches: 238/231, 234/228, 225/227, 228/226, 245/242, 230/228 us
-// The arxiv shape in long passes, sets of 5, 6, 8 and 16 beside a gather: 35.4/36.0, 33.0/33.5, 28.7/29.2, 25.2/26.5 us.
+//   the call gathers     206/199 180/168 131/119  154/151 128/122 78/71 131/125 104/101 50/47  119/112 91/90 37/36 us
+//   beside a gather      184/194 113/115  87/77   127/146  90/93  48/45 107/124  81/82  32/33  104/117 80/81 27/28 us
+//   ... and a model      1, 2, 3, 4, 6, 8 and 16 batches: 249/263, 228/240, 222/220, 247/245, 219/218, 232/231, 227/224 us
+// The line was drawn where sets of up to four batches gained on all three graphs, with the partition strategy's
+// six launches per hop and eight blocks of k_small_finish per batch; with its four launches and some 32 blocks only
+// sets of one and two on the smallest graph still do, and sets of three and more with a model behind them, a little.
 constexpr int kCrowdedBatches = 4;
 bool crowded_by_a_gather(const smfg_graph* g, bool gathers, int num_batches) {
   return g->feat && !gathers && num_batches > kCrowdedBatches;
@@ -608,7 +609,13 @@ SmallLaunch small_launch(const Launch& P, const smfg_workspace* const* ws, const
   return S;
 }
 // Feature rows that the last hop's finish copies itself: up to kSmallGather bytes in a batch at most, by some 32
-// blocks where a launch of its own has hundreds, and in vectors of 16 bytes.
+// blocks (16 in a set of 16 batches) where a launch of its own has hundreds, and in vectors of 16 bytes.  Calls of fanouts (10, 5)
+// and 256 seeds, at most 16.9 K rows a batch, in a launch of its own / in finish:
+//   MB in a batch   0.3      1.1        2.2        4.3        8.7        17         35
+//    1 batch     42.5/40.2  42.8/40.4  43.3/41.2  44.2/43.0  45.6/46.5  48.4/53.6  54.8/70.9 us
+//    8 batches   44.5/41.4  45.9/42.8  47.9/44.9  53.8/50.0  65.1/64.0  88.5/83.7   140/148 us
+//   16 batches   49.4/45.6  52.2/48.2  55.7/50.9  66.4/63.9  89.4/85.4   137/147    241/254 us
+// One hop of 900 x 20 and three of (15, 10, 5) change sides at the same size; the bound counts the most rows a call can have.
 constexpr int64_t kSmallGather = 4 << 20;
 bool small_gather(int64_t row_bytes, int64_t max_nodes) { return row_bytes >= 16 && max_nodes * row_bytes <= kSmallGather; }
 // The first `hops` hops; `gather`: the last of them, which is the call's, copies the feature rows.

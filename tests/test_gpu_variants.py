@@ -28,8 +28,9 @@ def sample(gg, seeds, fanouts, key):
 
 
 def launches(call):
-    """Launches per stage of a call.  Three per hop (sample_insert, dedup_buckets, assemble) and none
-    before the first one: the call took the small path."""
+    """Launches per stage of a call.  On the small path a hop counts once as sample_insert (a launch of its own for the
+    first, done by the hop before for the others), dedup_buckets and assemble, the last of which may do the gather, and
+    nothing comes before the first one."""
     smfg.profile_begin(2, 200)
     try:
         call()
