@@ -11,7 +11,8 @@ namespace smfg_dev {
 // contiguous range of the block's indices array; a lane owns V consecutive columns per round of
 // 16 * V columns.  kAggDepth source rows are requested before the first is used, whichever
 // destination they belong to, so a short destination (fanout 5) does not limit the loads in
-// flight.  Each destination's rows are added in float, in slot order, then divided once.
+// flight; their ids come in one read of the group, an id per lane, those of the next ten while these are added (96 K
+// destinations x 5 of 200 bytes 27.8 -> 27.2 us).  Each destination's rows are added in float, in slot order, then divided once.
 // Offsets are clamped to [0, max_edges] and source ids outside [0, max_src) read row 0, so the
 // arrays of a batch that ended with a status (contents unspecified) cannot cause a stray read.
 constexpr int kAggLanes = 16;
@@ -33,44 +34,48 @@ struct alignas(ALIGNED ? sizeof(T) * V : sizeof(T)) RowVec {
 __device__ __forceinline__ float to_float(_Float16 h) { return static_cast<float>(h); }
 __device__ __forceinline__ float to_float(float f) { return f; }
 
-// Offsets of the SPAN + 1 boundaries of a group's destinations i0 .. i0 + SPAN into off[] (LDS);
-// a destination past the end n repeats the last boundary.  Call with all lanes of the group, then
-// synchronise before walk_group_means reads them.
-template <int SPAN>
-__device__ __forceinline__ void load_group_offsets(int* off, const int32_t* __restrict__ indptr, int64_t i0,
-                                                   int64_t n, int64_t max_edges, int lane) {
-  if (lane <= SPAN) {
-    int64_t i = i0 + lane;
-    if (i > n) i = n;
-    int o = i0 <= n ? indptr[i] : 0;
-    if (o < 0) o = 0;
-    if (o > max_edges) o = static_cast<int>(max_edges);
-    off[lane] = o;
+// Offset of a destination.  The array has max_dst + 1 of them, so they can be on their way together with the number of
+// destinations; what lies past its end is not used.
+__device__ __forceinline__ int load_offset(const int32_t* __restrict__ indptr, int64_t i, int64_t max_dst, int64_t max_edges) {
+  const int o = indptr[i < max_dst ? i : max_dst];
+  return o < 0 ? 0 : o > max_edges ? static_cast<int>(max_edges) : o;
+}
+
+// The boundaries of a group's destinations from its lanes (lane q <= SPAN that of destination q), never decreasing, those
+// past its last destination the end of it.
+template <int LANES, int SPAN>
+__device__ __forceinline__ void group_offsets(int mine, int rows_here, int (&off)[SPAN + 1]) {
+#pragma unroll
+  for (int q = 0; q <= SPAN; ++q) {
+    const int o = __shfl(mine, q, LANES);
+    off[q] = q == 0 || (q <= rows_here && o > off[q - 1]) ? o : off[q - 1];
   }
 }
 
-// Means of the group's rows_here (<= SPAN) destinations; emit(r, c, mean) receives, once per
-// destination r and column round, the V means of columns c .. c + V (zeros for an empty row).
-template <typename T, int V, bool ALIGNED, typename Emit>
-__device__ __forceinline__ void walk_group_means(const int* off, int rows_here,
-                                                 const int32_t* __restrict__ indices, const T* __restrict__ x,
-                                                 uint32_t nsrc, int dim, int lane, Emit emit) {
+// Source ids of the group's samples from e on, one per lane; the last one again past e_end.
+__device__ __forceinline__ uint32_t load_id(const int32_t* __restrict__ indices, int e, int e_end, int lane) {
+  return e < e_end ? static_cast<uint32_t>(indices[e + lane < e_end ? e + lane : e_end - 1]) : 0u;
+}
+
+// Means of the group's rows_here (<= SPAN) destinations, off[0 .. rows_here] their boundaries.  emit(r, c, mean) receives, once
+// per destination r and column round, the V means of columns c .. c + V (zeros for an empty row).  All lanes of the
+// group call, and stay together: they hold each other's ids.
+template <typename T, int V, bool ALIGNED, int LANES, int DEPTH, int SPAN, typename Emit>
+__device__ __forceinline__ void walk_group_means(const int (&off)[SPAN + 1], int rows_here, const int32_t* __restrict__ indices,
+                                                 const T* __restrict__ x, uint32_t nsrc, int dim, int lane, Emit emit) {
   typedef RowVec<T, V, ALIGNED> Vec;
-  const int e_begin = off[0];
-  for (int c0 = lane * V; c0 < dim; c0 += kAggLanes * V) {
-    const int c = ALIGNED || c0 + V <= dim ? c0 : dim - V;
+  static_assert(DEPTH <= LANES, "a lane per id");
+  const int e_begin = off[0], e_end = off[SPAN];
+  const uint32_t first = load_id(indices, e_begin, e_end, lane);
+  for (int cb = 0; cb < dim; cb += LANES * V) {
+    const int c0 = cb + lane * V;
+    const int c = c0 + V <= dim ? c0 : dim - V;
     float acc[V];
 #pragma unroll
     for (int t = 0; t < V; ++t) acc[t] = 0.f;
     int r = 0;               // destination being summed
     int r_begin = e_begin;   // its first sample
     int r_end = off[1];
-    if (r_end < r_begin) r_end = r_begin;
-    int e_end = r_end;       // end of the group's range, kept non-decreasing
-    for (int q = 2; q <= rows_here; ++q) {
-      const int o = off[q];
-      if (o > e_end) e_end = o;
-    }
     // closes destination r (mean or zeros) and moves to the next one
     auto close_row = [&]() {
       const float k = static_cast<float>(r_end - r_begin);
@@ -80,29 +85,23 @@ __device__ __forceinline__ void walk_group_means(const int* off, int rows_here,
         mean[t] = r_end > r_begin ? acc[t] / k : 0.f;
         acc[t] = 0.f;
       }
-      emit(r, c, mean);
+      if (c0 < dim) emit(r, c, mean);
       ++r;
       r_begin = r_end;
-      if (r < rows_here) {
-        const int o2 = off[r + 1];
-        r_end = o2 > r_begin ? o2 : r_begin;
-      }
+#pragma unroll
+      for (int q = 2; q <= SPAN; ++q)
+        if (q == r + 1) r_end = off[q];
     };
-    for (int e = e_begin; e < e_end; e += kAggDepth) {
-      Vec rows[kAggDepth];
-      uint32_t ids[kAggDepth];
+    uint32_t ids = first;
+    for (int e = e_begin; e < e_end; e += DEPTH) {
+      Vec rows[DEPTH];
+      ids = ids < nsrc ? ids : 0u;
 #pragma unroll
-      for (int u = 0; u < kAggDepth; ++u) {
-        const int ee = e + u < e_end ? e + u : e_end - 1;
-        ids[u] = static_cast<uint32_t>(indices[ee]);
-      }
+      for (int u = 0; u < DEPTH; ++u)
+        rows[u] = *reinterpret_cast<const Vec*>(x + static_cast<int64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(ids), u, LANES))) * dim + c);
+      ids = load_id(indices, e + DEPTH, e_end, lane);
 #pragma unroll
-      for (int u = 0; u < kAggDepth; ++u) {
-        const uint32_t sidx = ids[u] < nsrc ? ids[u] : 0u;
-        rows[u] = *reinterpret_cast<const Vec*>(x + static_cast<int64_t>(sidx) * dim + c);
-      }
-#pragma unroll
-      for (int u = 0; u < kAggDepth; ++u) {
+      for (int u = 0; u < DEPTH; ++u) {
         if (e + u < e_end) {
           while (e + u >= r_end && r < rows_here) close_row();
 #pragma unroll
@@ -121,38 +120,64 @@ __global__ void __launch_bounds__(kThreads) k_mean_aggregate(const int32_t* __re
                                                              const int64_t* __restrict__ num_dst, int64_t max_dst,
                                                              const T* __restrict__ x, int64_t max_src, int dim,
                                                              float* __restrict__ out) {
-  __shared__ int s_off[kAggGroups][kAggSpan + 1];
-  int64_t n = *num_dst;
-  if (n > max_dst) n = max_dst;
   const int grp = threadIdx.x / kAggLanes, lane = threadIdx.x & (kAggLanes - 1);
   const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kAggRows + static_cast<int64_t>(grp) * kAggSpan;
-  if (static_cast<int64_t>(blockIdx.x) * kAggRows >= n) return;  // whole block past the end
-  load_group_offsets<kAggSpan>(s_off[grp], indptr, i0, n, max_edges, lane);
-  __syncthreads();
+  const int mine = load_offset(indptr, i0 + (lane < kAggSpan ? lane : kAggSpan), max_dst, max_edges);
+  int64_t n = *num_dst;
+  if (n > max_dst) n = max_dst;
   if (i0 >= n) return;
   const int rows_here = static_cast<int>(n - i0 < kAggSpan ? n - i0 : kAggSpan);
-  walk_group_means<T, V, ALIGNED>(s_off[grp], rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
-                         [&](int r, int c, const float* mean) {
-                           float* o = out + (i0 + r) * dim + c;
+  int off[kAggSpan + 1];
+  group_offsets<kAggLanes, kAggSpan>(mine, rows_here, off);
+  walk_group_means<T, V, ALIGNED, kAggLanes, kAggDepth, kAggSpan>(off, rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
+                                                                  [&](int r, int c, const float* mean) {
+                                                                    float* o = out + (i0 + r) * dim + c;
 #pragma unroll
-                           for (int t = 0; t < V; ++t) o[t] = mean[t];
-                         });
+                                                                    for (int t = 0; t < V; ++t) o[t] = mean[t];
+                                                                  });
 }
 
 // ---- one GraphSAGE layer: out = act([x_dst | mean] W^T + b) -------------------------------------
 //
-// A block owns ROWS consecutive destinations.  It first builds the layer input of its rows
-// in LDS as halfs: columns [0, dim) the destination's own row (destination i is source i, so
-// these are contiguous rows of x), columns [dim, 2 dim) the neighbour means from the walk above,
-// rounded to half.  Then each wave multiplies the tile by 32-column slices of W^T with
-// v_mfma_f32_32x32x16_f16 (one 32 x 32 accumulator per 32 rows), adds the bias, applies the ReLU
-// and stores.  W comes pre-arranged in the lanes' operand order (k_sage_pack_weights).
-// ROWS is 64 for dim <= 128 and 32 above, which keeps the tile within 64 KB of LDS.
+// A persistent block takes a range of consecutive destinations, a tile of them after the other.  A lane group of
+// 8, 16 or 32 lanes fetches the rows of a destination's samples, a vector of 8 columns per lane; their mean,
+// rounded to half, and the destination's own row (destination i is source i) make a row of the tile in LDS, which eight
+// waves then multiply, each by its 32 columns of W^T, with v_mfma_f32_32x32x16_f16.  A wave keeps its part of W in
+// registers for all tiles of the block: read for every tile of 64 rows it was 0.3 GB from the L2 for 154 K destinations of
+// 128 -> 256, as much as the rows, and took half as long again.
+//
+// dim <= 128 (k_sage_layer): eight more waves do the fetching, two tiles ahead of the one that is being multiplied, so that
+// rows are on their way all the time; what is left is the HBM's.  154 K destinations x 5, 128 -> 256, half: 80 -> 67 us, 4.3 TB/s of what
+// the layer cannot do without; 96 K x 5 of 104 columns 51 -> 40, 47 K of 96 26 -> 19, 150 K x 10, 64 -> 128 63 -> 54.  With
+// all waves doing both, a tile ahead, 78 us for the first.  Where a block has a tile or less, a chain of dependent reads
+// remains: 12.5 K x 10, 128 -> 256 20 -> 12 us, 1 K x 15 19 -> 10.
+// dim > 128 (k_sage_layer_wide): W takes 128 registers of a wave, which leaves room for eight waves in a compute unit, and all
+// of them fetch, a tile ahead.  300 K x 5, 256 -> 256 283 -> 226 us, 60 K x 15 113 -> 107, 13 K x 10 24 -> 21.5, 1 K x 15 20 -> 10;
+// with four waves that only fetch and eight that only multiply 244, 123, 22 and 15.
+// Such a block takes a compute unit for itself, so beside another stream's gather it waits for one: a layer of an epoch's
+// consumer can stand still for as long as the gather of the next set takes, which then is that much faster (16 batches
+// with three layers each 3.60 -> 3.46 ms; with blocks of 256 threads that read W for every tile 3.52, for the second layer only 3.68).
 constexpr int kLayerPad = 8;  // halfs of padding per LDS row
 constexpr int kLayerMaxDim = 256;
-constexpr int kLayerAhead = 8;  // vectors of W requested ahead of their use
+constexpr int kLayerMaxCols = 256;  // of W in the registers of kLayerWaves waves
+constexpr int kLayerWaves = 8;   // that multiply
+constexpr int kLayerLoaders = 8;
+constexpr int kLayerThreads = (kLayerWaves + kLayerLoaders) * 64, kLayerWideThreads = kLayerWaves * 64;
+constexpr int kLayerWideRows = 32;
+constexpr int kLayerBlocks = 256;   // one to a compute unit
+constexpr int kLayerMinRows = 16;   // of a block
+constexpr int layer_rows(int lanes) { return kLayerLoaders * 64 / lanes; }
+constexpr int layer_lda(int dim) { return 2 * dim + kLayerPad; }
+// a wave's results, 32 x 32 of them, on their way through the LDS to consecutive memory
+template <typename OutT>
+constexpr int layer_ldo() { return 32 + 16 / static_cast<int>(sizeof(OutT)); }
+template <typename OutT>
+constexpr size_t layer_lds_bytes(int rows, int dim) { return sizeof(_Float16) * 2 * rows * layer_lda(dim) + sizeof(OutT) * kLayerWaves * 32 * layer_ldo<OutT>(); }
+static_assert(layer_lds_bytes<float>(layer_rows(8), 64) <= 160 * 1024 && layer_lds_bytes<float>(layer_rows(16), 128) <= 160 * 1024 &&
+              layer_lds_bytes<float>(kLayerWideRows, kLayerMaxDim) <= 160 * 1024, "LDS of a compute unit");
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
 // Weights in the order the layer kernel's lanes consume them: for column slice sl (32 output
@@ -174,23 +199,336 @@ __global__ void __launch_bounds__(kThreads) k_sage_pack_weights(const _Float16* 
   }
 }
 
+struct LayerArgs {
+  const int32_t* indptr;
+  const int32_t* indices;
+  int64_t max_edges;
+  const int64_t* num_dst;
+  int64_t max_dst;
+  const _Float16* x;
+  int64_t max_src;
+  int dim;
+  const _Float16* w;
+  const float* bias;
+  int out_dim, relu;
+  void* out;
+};
+
+// The block's destinations: an even share, so that no block has a tile more than the others to do.
+__device__ __forceinline__ void layer_range(const LayerArgs& P, int& b0, int& b1) {
+  int64_t n = *P.num_dst;
+  if (n > P.max_dst) n = P.max_dst;
+  if (n > P.max_src) n = P.max_src;  // a destination's own row is row i of x
+  if (n < 0) n = 0;
+  b0 = static_cast<int>(n * blockIdx.x / gridDim.x);
+  b1 = static_cast<int>(n * (blockIdx.x + 1) / gridDim.x);
+}
+
+// What a lane reads: vectors of 8 columns of rows of x; lanes past the last column read it once more.
+struct LayerColumns {
+  const char* at;
+  uint32_t row_bytes, nsrc;
+  bool own;  // the lane has columns
+  __device__ __forceinline__ LayerColumns(const LayerArgs& P, int lane)
+      : at(reinterpret_cast<const char*>(P.x) + (lane * 8 < P.dim ? lane * 8 : P.dim - 8) * sizeof(_Float16)),
+        row_bytes(static_cast<uint32_t>(P.dim) * sizeof(_Float16)), nsrc(static_cast<uint32_t>(P.max_src)), own(lane * 8 < P.dim) {}
+  __device__ __forceinline__ half8_t row(uint32_t i) const {
+    return *reinterpret_cast<const half8_t*>(at + static_cast<uint64_t>(i) * row_bytes);
+  }
+  // the rows that DEPTH lanes of the group name, from the first-th on
+  template <int LANES, int DEPTH>
+  __device__ __forceinline__ void rows(uint32_t ids, half8_t (&v)[DEPTH], int first = 0) const {
+    ids = ids < nsrc ? ids : 0u;
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) v[u] = row(static_cast<uint32_t>(__shfl(static_cast<int>(ids), first + u, LANES)));
+  }
+};
+
+__device__ __forceinline__ void layer_add(float (&acc)[8], const half8_t v) {
+#pragma unroll
+  for (int t = 0; t < 8; ++t) acc[t] += to_float(v[t]);
+}
+// Sums / k, zeros if k is 0.  The quotient, rounded once, is that of the sum and the rounded reciprocal, corrected by its remainder
+// (Markstein): for k < 2^20 what a division gives, in 4 instructions instead of 10 (2 of the 80 us above).
+__device__ __forceinline__ half8_t layer_mean(const float (&acc)[8], int samples) {
+  const float k = static_cast<float>(samples > 0 ? samples : 1), inv = 1.f / k;
+  half8_t h;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const float q = acc[t] * inv;
+    h[t] = static_cast<_Float16>(__builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, k, acc[t]), inv, q), k, acc[t]));
+  }
+  return h;
+}
+
+// A wave's part of the multiplication: columns 32 wave .. + 32.
+template <typename OutT, int STEPS>  // STEPS: of 16 reduction indices, at most
+struct LayerProduct {
+  const LayerArgs& P;
+  const int wave, lane, col, hi, nq, lda;
+  const bool vectors;
+  OutT* const res;  // [32][layer_ldo], the wave's own
+  half8_t w[STEPS];
+
+  __device__ __forceinline__ half8_t weights(int slice, int q) const {
+    return reinterpret_cast<const half8_t*>(P.w)[(static_cast<int64_t>(slice) * nq + (q < nq ? q : 0)) * 64 + lane];
+  }
+  __device__ __forceinline__ LayerProduct(const LayerArgs& p, int wv, OutT* all_res)
+      : P(p), wave(wv), lane(threadIdx.x & 63), col(lane & 31), hi(lane >> 5), nq(p.dim / 8), lda(layer_lda(p.dim)),
+        vectors(p.out_dim % (16 / static_cast<int>(sizeof(OutT))) == 0 && reinterpret_cast<uintptr_t>(p.out) % 16 == 0),
+        res(all_res + wv * 32 * layer_ldo<OutT>()) {
+    if (wave * 32 < P.out_dim) {
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q) w[q] = weights(wave, q);
+    }
+  }
+  // destinations tile0 .. tile0 + here, their inputs in a
+  __device__ __forceinline__ void tile(const _Float16* a, int tile0, int here) const {
+    constexpr int kVec = 16 / static_cast<int>(sizeof(OutT)), kRowLanes = 32 / kVec, ldo = layer_ldo<OutT>();
+    if (wave * 32 >= P.out_dim) return;
+    const int j = wave * 32 + col;
+    const float bias = P.bias && j < P.out_dim ? P.bias[j] : 0.f;
+    for (int rb = 0; rb < here; rb += 32) {
+      const _Float16* ap = a + (rb + col) * lda + hi * 8;
+      float16_t acc;
+#pragma unroll
+      for (int t = 0; t < 16; ++t) acc[t] = 0.f;
+      // lane half hi supplies reduction indices 16 q + 8 hi .. + 8 of both operands (any assignment works as
+      // long as it is the same on both sides); rows past the tile's last only reach results that are not stored
+      const auto step = [&](int q, const half8_t b) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8_t*>(ap + q * 16), b, acc, 0, 0, 0);
+      };
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q)
+        if (q < nq) step(q, w[q]);
+      // element t of a lane's accumulator: row 8 (t / 4) + 4 hi + t % 4, column col
+      OutT* o = res + 4 * hi * ldo + col;
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        float v = acc[t] + bias;
+        if (P.relu) v = v > 0.f ? v : 0.f;
+        o[(8 * (t / 4) + t % 4) * ldo] = static_cast<OutT>(v);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      OutT* to = static_cast<OutT*>(P.out) + static_cast<int64_t>(tile0 + rb) * P.out_dim + wave * 32;
+      const int rows = here - rb < 32 ? here - rb : 32, cols = P.out_dim - wave * 32 < 32 ? P.out_dim - wave * 32 : 32;
+      if (vectors) {
+        const int c = lane % kRowLanes * kVec;
+#pragma unroll
+        for (int r0 = 0; r0 < 32; r0 += 64 / kRowLanes) {
+          const int r = r0 + lane / kRowLanes;
+          if (r < rows && c < cols) *reinterpret_cast<float4_t*>(to + static_cast<int64_t>(r) * P.out_dim + c) = *reinterpret_cast<const float4_t*>(res + r * ldo + c);
+        }
+      } else if (col < cols) {
+        for (int r = hi; r < rows; r += 2) to[static_cast<int64_t>(r) * P.out_dim + col] = res[r * ldo + col];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+};
+
+// dim <= 8 * LANES <= 128.  A lane group of the fetching waves has a destination per tile; the rows of two tiles, the ids of
+// a third and the offsets of a fourth are on their way.  Of a destination with more than kDepth samples the first kDepth are
+// fetched ahead, the others as many at a time when these are added (8 of them ahead: 1 % more for a fanout of 5, 2 % less for 64).
+template <typename OutT, int LANES>
+__global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P) {
+  constexpr int ROWS = layer_rows(LANES), kDepth = 5, kAhead = 2;
+  static_assert(ROWS % 32 == 0, "whole accumulators");
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int lda = layer_lda(P.dim);
+  _Float16* buf = reinterpret_cast<_Float16*>(lds_raw);  // [2][ROWS][lda]
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int b0, b1;
+  layer_range(P, b0, b1);
+  const int tiles = (b1 - b0 + ROWS - 1) / ROWS;
+  if (tiles == 0) return;
+  if (wv < kLayerLoaders) {
+    const int grp = threadIdx.x / LANES, lane = threadIdx.x & (LANES - 1);
+    const LayerColumns x(P, lane);
+    struct Ahead {
+      half8_t rows[kDepth], own;
+      uint32_t ids;  // of the samples from begin on, as many as the group has lanes
+      int begin, end;
+    } s[kAhead];
+    const auto row_of = [&](int tile) {  // the last one again past the end
+      const uint32_t i = static_cast<uint32_t>(b0) + static_cast<uint32_t>(tile) * ROWS + static_cast<uint32_t>(grp), last = static_cast<uint32_t>(b1 - 1);
+      return i < last ? i : last;
+    };
+    int begin, end, next_begin, next_end;
+    uint32_t id;
+    const auto read_offsets = [&](int tile) {
+      next_begin = load_offset(P.indptr, row_of(tile), P.max_dst, P.max_edges);
+      next_end = load_offset(P.indptr, row_of(tile) + 1u, P.max_dst, P.max_edges);
+    };
+    const auto read_ids = [&]() {
+      begin = next_begin;
+      end = next_end > begin ? next_end : begin;
+      id = load_id(P.indices, begin, end, lane);
+    };
+    // rows of a tile; ids and offsets of those behind it first, since waiting for them must not be waiting for the rows
+    const auto issue = [&](Ahead& t, int tile) {
+      t.ids = id;
+      t.begin = begin;
+      t.end = end;
+      read_ids();
+      read_offsets(tile + 2);
+      x.rows<LANES>(t.ids, t.rows);
+      t.own = x.row(row_of(tile));
+    };
+    const auto finish = [&](Ahead& t, _Float16* a) {
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      int base = t.begin;  // t.ids are those from here on
+      uint32_t more = base + 2 * kDepth > base + LANES ? load_id(P.indices, base + kDepth, t.end, lane) : 0u;
+      for (int e = t.begin; e < t.end; e += kDepth) {
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u)
+          if (e + u < t.end) layer_add(acc, t.rows[u]);
+        const int next = e + kDepth;
+        if (next < t.end) {
+          if (next + kDepth > base + LANES) {
+            t.ids = more;
+            base = next;
+          }
+          x.rows<LANES>(t.ids, t.rows, next - base);
+          if (next + 2 * kDepth > base + LANES) more = load_id(P.indices, next + kDepth, t.end, lane);
+        }
+      }
+      const half8_t mean = layer_mean(acc, t.end - t.begin);
+      if (x.own) {
+        *reinterpret_cast<half8_t*>(a + grp * lda + lane * 8) = t.own;
+        *reinterpret_cast<half8_t*>(a + grp * lda + P.dim + lane * 8) = mean;
+      }
+    };
+    read_offsets(0);
+    read_ids();
+    read_offsets(1);
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) issue(s[k], k);
+    for (int t = 0; t < tiles; t += 2) {
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        if (t + half < tiles) {
+          finish(s[half % kAhead], buf + half * ROWS * lda);
+          issue(s[half % kAhead], t + half + kAhead);
+          __syncthreads();
+        }
+      }
+    }
+    __syncthreads();
+    return;
+  }
+  const LayerProduct<OutT, LANES> product(P, wv - kLayerLoaders, reinterpret_cast<OutT*>(buf + 2 * ROWS * lda));
+  __syncthreads();
+  for (int t = 0; t < tiles; ++t) {
+    const int tile0 = b0 + t * ROWS;
+    product.tile(buf + (t & 1) * ROWS * lda, tile0, b1 - tile0 < ROWS ? b1 - tile0 : ROWS);
+    __syncthreads();
+  }
+}
+
+// 128 < dim <= 256.  A lane group has up to kSpan consecutive destinations per tile, fewer where the block has few; the first rows of
+// the next tile are on their way while the present one is multiplied.
+template <typename OutT>
+__global__ void __launch_bounds__(kLayerWideThreads, 2) k_sage_layer_wide(const LayerArgs P) {
+  constexpr int LANES = 32, kGroups = kLayerWideThreads / LANES, kSpan = kLayerWideRows / kGroups, kDepth = 10;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int lda = layer_lda(P.dim);
+  _Float16* buf = reinterpret_cast<_Float16*>(lds_raw);  // [2][kLayerWideRows][lda]
+  const LayerProduct<OutT, LANES> product(P, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), reinterpret_cast<OutT*>(buf + 2 * kLayerWideRows * lda));
+  int b0, b1;
+  layer_range(P, b0, b1);
+  if (b0 == b1) return;
+  const int want = (b1 - b0 + kGroups - 1) / kGroups, per = want < kSpan ? want : kSpan, rows_tile = kGroups * per;
+  const int grp = threadIdx.x / LANES, lane = threadIdx.x & (LANES - 1);
+  const LayerColumns x(P, lane);
+  const uint32_t past = static_cast<uint32_t>(b1);
+  const auto rows_of = [&](uint32_t i0) { return i0 < past ? (past - i0 < static_cast<uint32_t>(per) ? static_cast<int>(past - i0) : per) : 0; };
+  const auto offset_of = [&](uint32_t i0) { return load_offset(P.indptr, static_cast<int64_t>(i0) + (lane < kSpan ? lane : kSpan), P.max_dst, P.max_edges); };
+  half8_t rows[kDepth], own[kSpan];
+  const auto read_own = [&](uint32_t i0) {
+#pragma unroll
+    for (uint32_t r = 0; r < kSpan; ++r) own[r] = x.row(i0 + r < past ? i0 + r : past - 1u);
+  };
+  uint32_t i0 = static_cast<uint32_t>(b0 + grp * per);
+  int off[kSpan + 1], mine = offset_of(i0);
+  group_offsets<LANES, kSpan>(mine, rows_of(i0), off);
+  uint32_t id = load_id(P.indices, off[0], off[kSpan], lane);
+  mine = offset_of(i0 + static_cast<uint32_t>(rows_tile));
+  x.rows<LANES>(id, rows);
+  read_own(i0);
+  _Float16* a = buf;
+  for (int tile0 = b0; tile0 < b1; tile0 += rows_tile) {
+    int next[kSpan + 1];
+    group_offsets<LANES, kSpan>(mine, rows_of(i0 + static_cast<uint32_t>(rows_tile)), next);
+    id = load_id(P.indices, next[0], next[kSpan], lane);
+    mine = offset_of(i0 + 2u * static_cast<uint32_t>(rows_tile));
+    const int rows_here = rows_of(i0), e_end = off[kSpan];
+    _Float16* ag = a + grp * per * lda + lane * 8;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int r = 0, r_begin = off[0], r_end = off[1];
+    const auto close_row = [&]() {
+      const half8_t mean = layer_mean(acc, r_end - r_begin);
+      if (x.own) *reinterpret_cast<half8_t*>(ag + r * lda + P.dim) = mean;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) acc[t] = 0.f;
+      ++r;
+      r_begin = r_end;
+#pragma unroll
+      for (int q = 2; q <= kSpan; ++q)
+        if (q == r + 1) r_end = off[q];
+    };
+    uint32_t ids = load_id(P.indices, off[0] + kDepth, e_end, lane);
+    for (int e = off[0]; e < e_end; e += kDepth) {
+#pragma unroll
+      for (int u = 0; u < kDepth; ++u) {
+        if (e + u < e_end) {
+          while (e + u >= r_end && r < rows_here) close_row();
+          layer_add(acc, rows[u]);
+        }
+      }
+      if (e + kDepth < e_end) {
+        x.rows<LANES>(ids, rows);
+        ids = load_id(P.indices, e + 2 * kDepth, e_end, lane);
+      }
+    }
+    while (r < rows_here) close_row();
+#pragma unroll
+    for (int q = 0; q < kSpan; ++q)
+      if (x.own && q < rows_here) *reinterpret_cast<half8_t*>(ag + q * lda) = own[q];
+#pragma unroll
+    for (int q = 0; q <= kSpan; ++q) off[q] = next[q];
+    i0 += static_cast<uint32_t>(rows_tile);
+    if (tile0 + rows_tile < b1) {
+      x.rows<LANES>(id, rows);
+      read_own(i0);
+    }
+    // the other half of buf is written next, by waves that may be a tile ahead of those still multiplying this one
+    __syncthreads();
+    product.tile(a, tile0, b1 - tile0 < rows_tile ? b1 - tile0 : rows_tile);
+    a = a == buf ? buf + kLayerWideRows * lda : buf;
+  }
+}
+
+// More than kLayerMaxCols output columns: W does not fit the registers of a block, and every tile reads it from the L2.  A block
+// of four waves builds the inputs of ROWS destinations and multiplies them, a wave the column slices 4 apart.  100 K destinations x 5, 200 -> 300, half: 102 us
+// (150 by k_sage_layer_wide with the columns from 256 on read for every tile); 64 -> 300 47 us (63 by k_sage_layer).
+constexpr int layer_cols_rows(int dim) { return dim <= 128 ? 64 : 32; }  // at most 34 KB of LDS, four blocks to a compute unit
+constexpr int kLayerColsAhead = 8;  // vectors of W requested ahead of their use
 template <typename OutT, int ROWS>
-__global__ void __launch_bounds__(kThreads, 4) k_sage_layer(const int32_t* __restrict__ indptr,
-                                                         const int32_t* __restrict__ indices, int64_t max_edges,
-                                                         const int64_t* __restrict__ num_dst, int64_t max_dst,
-                                                         const _Float16* __restrict__ x, int64_t max_src, int dim,
-                                                         const _Float16* __restrict__ w,
-                                                         const float* __restrict__ bias, int out_dim, int relu,
-                                                         OutT* __restrict__ out) {
+__global__ void __launch_bounds__(kThreads, 4) k_sage_layer_cols(const LayerArgs P) {
   static_assert(ROWS == 32 || ROWS == 64, "one or two 32-row accumulators");
   constexpr int kLayerRows = ROWS;
   constexpr int kLayerSpan = ROWS / kAggGroups;  // destinations per lane group
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  __shared__ int s_off[kAggGroups][kLayerSpan + 1];
   _Float16* a_lds = reinterpret_cast<_Float16*>(lds_raw);  // [ROWS][2 dim + kLayerPad]
-  int64_t n = *num_dst;
-  if (n > max_dst) n = max_dst;
-  if (n > max_src) n = max_src;  // a destination's own row is row i of x
+  const _Float16* x = P.x;
+  const int dim = P.dim, out_dim = P.out_dim;
+  OutT* out = static_cast<OutT*>(P.out);
+  int64_t n = *P.num_dst;
+  if (n > P.max_dst) n = P.max_dst;
+  if (n > P.max_src) n = P.max_src;  // a destination's own row is row i of x
   const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kLayerRows;
   if (tile0 >= n) return;
   const int rows_tile = static_cast<int>(n - tile0 < kLayerRows ? n - tile0 : kLayerRows);
@@ -198,7 +536,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_sage_layer(const int32_t* __res
   const int lda = K + kLayerPad;
   const int grp = threadIdx.x / kAggLanes, lane = threadIdx.x & (kAggLanes - 1);
   const int64_t i0 = tile0 + static_cast<int64_t>(grp) * kLayerSpan;
-  load_group_offsets<kLayerSpan>(s_off[grp], indptr, i0, n, max_edges, lane);
+  const int mine = load_offset(P.indptr, i0 + (lane < kLayerSpan ? lane : kLayerSpan), P.max_dst, P.max_edges);
 
   // own rows -> columns [0, dim); rows past the end of the block become zeros (both halves)
   {
@@ -215,26 +553,28 @@ __global__ void __launch_bounds__(kThreads, 4) k_sage_layer(const int32_t* __res
   __syncthreads();
   if (i0 < n) {
     const int rows_here = static_cast<int>(n - i0 < kLayerSpan ? n - i0 : kLayerSpan);
+    int off[kLayerSpan + 1];
+    group_offsets<kAggLanes, kLayerSpan>(mine, rows_here, off);
     _Float16* a_grp = a_lds + (grp * kLayerSpan) * lda + dim;
-    walk_group_means<_Float16, 8, true>(s_off[grp], rows_here, indices, x, static_cast<uint32_t>(max_src), dim, lane,
-                                  [&](int r, int c, const float* mean) {
-                                    half8_t h;
+    walk_group_means<_Float16, 8, true, kAggLanes, kAggDepth, kLayerSpan>(off, rows_here, P.indices, x, static_cast<uint32_t>(P.max_src), dim, lane,
+                                                                          [&](int r, int c, const float* mean) {
+                                                                            half8_t h;
 #pragma unroll
-                                    for (int t = 0; t < 8; ++t) h[t] = static_cast<_Float16>(mean[t]);
-                                    *reinterpret_cast<half8_t*>(a_grp + r * lda + c) = h;
-                                  });
+                                                                            for (int t = 0; t < 8; ++t) h[t] = static_cast<_Float16>(mean[t]);
+                                                                            *reinterpret_cast<half8_t*>(a_grp + r * lda + c) = h;
+                                                                          });
   }
   __syncthreads();
 
   // tile [ROWS x K] times W^T: wave wv takes the column slices wv, wv + 4, ...  The packed
   // weights hold, for every slice and every 16 reduction indices, the 64 lanes' operands side by
   // side, so one load instruction of the wave reads 1 KB of consecutive memory (W stays in the L2);
-  // kLayerAhead such vectors are always on their way.
+  // kLayerColsAhead such vectors are always on their way.
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int col = l & 31, hi = l >> 5;
   const int nq = K / 16;
   for (int n0 = wv * 32; n0 < out_dim; n0 += 4 * 32) {
-    const half8_t* wp = reinterpret_cast<const half8_t*>(w) + static_cast<int64_t>(n0 / 32) * nq * 64 + l;
+    const half8_t* wp = reinterpret_cast<const half8_t*>(P.w) + static_cast<int64_t>(n0 / 32) * nq * 64 + l;
     const _Float16* ap0 = a_lds + col * lda + hi * 8;
     const _Float16* ap1 = ap0 + 32 * lda;
     float16_t acc0, acc1;
@@ -243,20 +583,20 @@ __global__ void __launch_bounds__(kThreads, 4) k_sage_layer(const int32_t* __res
       acc0[t] = 0.f;
       acc1[t] = 0.f;
     }
-    half8_t bq[kLayerAhead];
+    half8_t bq[kLayerColsAhead];
 #pragma unroll
-    for (int u = 0; u < kLayerAhead; ++u) bq[u] = wp[(u < nq ? u : 0) * 64];
+    for (int u = 0; u < kLayerColsAhead; ++u) bq[u] = wp[(u < nq ? u : 0) * 64];
     // one v_mfma_f32_32x32x16_f16 per vector: lane half hi supplies reduction indices 16 q + 8 hi .. + 8
     // of both operands (any assignment works as long as it is the same on both sides)
     // The body is free of branches (a vector past the end multiplies zeros), so the LDS reads of
     // the unrolled steps can be issued ahead of the MFMAs that use them.
-    for (int qb = 0; qb < nq; qb += kLayerAhead) {
+    for (int qb = 0; qb < nq; qb += kLayerColsAhead) {
 #pragma unroll
-      for (int u = 0; u < kLayerAhead; ++u) {
+      for (int u = 0; u < kLayerColsAhead; ++u) {
         const int q = qb + u;
         const half8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
         const half8_t b = q < nq ? bq[u] : zero;
-        const int qn = q + kLayerAhead;
+        const int qn = q + kLayerColsAhead;
         bq[u] = wp[(qn < nq ? qn : 0) * 64];
         const int k0 = (q < nq ? q : 0) * 16;
         const half8_t a0 = *reinterpret_cast<const half8_t*>(ap0 + k0);
@@ -271,14 +611,14 @@ __global__ void __launch_bounds__(kThreads, 4) k_sage_layer(const int32_t* __res
     // that depends on t is the same for all lanes, so a store is one lane pointer plus a uniform
     // offset.
     if (n0 + col < out_dim) {
-      const float bj = bias ? bias[n0 + col] : 0.f;
+      const float bj = P.bias ? P.bias[n0 + col] : 0.f;
       OutT* o0 = out + (tile0 + 4 * hi) * out_dim + n0 + col;
       const int rows_left = rows_tile - 4 * hi;  // rows of the tile at or after the lane's first
       OutT r0[16], r1[16];
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
         float v0 = acc0[t] + bj, v1 = acc1[t] + bj;
-        if (relu) {
+        if (P.relu) {
           v0 = v0 > 0.f ? v0 : 0.f;
           v1 = v1 > 0.f ? v1 : 0.f;
         }

@@ -722,6 +722,23 @@ void launch_gather_plain(const smfg_graph* g, int vb, const int32_t* ids, const 
   }
 }
 
+// Up to kLayerMaxCols output columns a block keeps W in its registers, and there is one to a compute unit where there are destinations enough.
+template <typename OutT>
+void launch_layer(const LayerArgs& P, hipStream_t st) {
+  if (P.out_dim > kLayerMaxCols) {
+    const int rows = layer_cols_rows(P.dim);
+    const size_t lds = sizeof(_Float16) * rows * layer_lda(P.dim);
+    const unsigned blocks = blocks_for(P.max_dst, rows, 0x7FFFFFFFu);
+    if (rows == 64) k_sage_layer_cols<OutT, 64><<<blocks, kThreads, lds, st>>>(P);
+    else k_sage_layer_cols<OutT, 32><<<blocks, kThreads, lds, st>>>(P);
+    return;
+  }
+  const unsigned blocks = blocks_for(P.max_dst, kLayerMinRows, kLayerBlocks);
+  if (P.dim <= 64) k_sage_layer<OutT, 8><<<blocks, kLayerThreads, layer_lds_bytes<OutT>(layer_rows(8), P.dim), st>>>(P);
+  else if (P.dim <= 128) k_sage_layer<OutT, 16><<<blocks, kLayerThreads, layer_lds_bytes<OutT>(layer_rows(16), P.dim), st>>>(P);
+  else k_sage_layer_wide<OutT><<<blocks, kLayerWideThreads, layer_lds_bytes<OutT>(kLayerWideRows, P.dim), st>>>(P);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1342,26 +1359,12 @@ int smfg_sage_layer(const int32_t* d_indptr, const int32_t* d_indices, int64_t m
     return SMFG_ERR_INVALID_ARG;
   if (max_dst == 0) return SMFG_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const _Float16* x = static_cast<const _Float16*>(d_x);
-  const _Float16* w = static_cast<const _Float16*>(d_w_packed);
-  const int rows = dim <= 128 ? 64 : 32;
-  const unsigned gb = blocks_for(max_dst, rows, 0x7FFFFFFFu);
-  const size_t lds = static_cast<size_t>(rows) * static_cast<size_t>(2 * dim + kLayerPad) * sizeof(_Float16);
+  const LayerArgs P = {d_indptr, d_indices, max_edges, d_num_dst, max_dst, static_cast<const _Float16*>(d_x), max_src, dim,
+                       static_cast<const _Float16*>(d_w_packed), d_bias, out_dim, relu, d_out};
   {
     StageTimer t_(SMFG_STAGE_LAYER, st);
-    if (out_elem_bytes == 2) {
-      _Float16* o = static_cast<_Float16*>(d_out);
-      if (rows == 64)
-        k_sage_layer<_Float16, 64><<<gb, kThreads, lds, st>>>(d_indptr, d_indices, max_edges, d_num_dst, max_dst, x, max_src, dim, w, d_bias, out_dim, relu, o);
-      else
-        k_sage_layer<_Float16, 32><<<gb, kThreads, lds, st>>>(d_indptr, d_indices, max_edges, d_num_dst, max_dst, x, max_src, dim, w, d_bias, out_dim, relu, o);
-    } else {
-      float* o = static_cast<float*>(d_out);
-      if (rows == 64)
-        k_sage_layer<float, 64><<<gb, kThreads, lds, st>>>(d_indptr, d_indices, max_edges, d_num_dst, max_dst, x, max_src, dim, w, d_bias, out_dim, relu, o);
-      else
-        k_sage_layer<float, 32><<<gb, kThreads, lds, st>>>(d_indptr, d_indices, max_edges, d_num_dst, max_dst, x, max_src, dim, w, d_bias, out_dim, relu, o);
-    }
+    if (out_elem_bytes == 2) launch_layer<_Float16>(P, st);
+    else launch_layer<float>(P, st);
   }
   return hip_err(hipGetLastError());
 }

@@ -1,0 +1,76 @@
+"""The layer kernels at the edges of their tiles, lane groups and column slices."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2110_08450_amd import binding as smfg
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def block_of(rng, n_dst, fanout, n_src):
+    k = rng.integers(0, fanout + 1, n_dst)
+    k[rng.integers(0, n_dst)] = 0
+    indptr = np.zeros(n_dst + 1, np.int32)
+    indptr[1:] = np.cumsum(k)
+    return indptr, rng.integers(0, n_src, max(1, int(indptr[-1])), dtype=np.int32)[:int(indptr[-1])]
+
+
+def layer(indptr, indices, x, w, b, relu, out_dtype, spare=3):
+    """The first n of n + spare rows of the block's arrays are destinations; the others' offsets are garbage."""
+    n = len(indptr) - 1
+    ip = torch.from_numpy(np.concatenate([indptr, np.full(spare, 2 ** 31 - 1, np.int32)])).to(DEV)
+    ix = torch.from_numpy(indices if len(indices) else np.zeros(1, np.int32)).to(DEV)  # never without an address
+    y = torch.full((n + spare, w.shape[0]), float("nan"), dtype=out_dtype, device=DEV)
+    smfg.sage_layer(ip, ix, torch.tensor([n], device=DEV), n + spare, torch.from_numpy(x).to(DEV),
+                    smfg.sage_pack_weights(torch.from_numpy(w).to(DEV)), torch.from_numpy(b).to(DEV), relu, y)
+    assert torch.isnan(y[n:]).all()  # nothing written past the destinations
+    return y[:n].float().cpu().numpy().astype(np.float64)
+
+
+# tiles are of 64 (dim <= 64), 32 and up to 32 destinations; a block has 16 or more of them, 256 blocks
+@pytest.mark.parametrize("n_dst,fanout,dim,out_dim,dtype", [
+    (1, 1, 8, 1, torch.float32), (15, 4, 8, 31, torch.float16), (17, 5, 56, 33, torch.float16), (65, 6, 64, 256, torch.float16),
+    (33, 5, 72, 32, torch.float32), (600, 11, 128, 255, torch.float16), (257, 16, 120, 256, torch.float32), (9001, 17, 128, 8, torch.float16),
+    (16, 10, 136, 40, torch.float16), (4111, 21, 136, 256, torch.float32), (8229, 4, 256, 172, torch.float16), (300, 33, 248, 17, torch.float16),
+    (130, 7, 16, 257, torch.float16), (70, 40, 128, 300, torch.float32), (33, 12, 256, 512, torch.float16), (20000, 3, 24, 24, torch.float16)])
+def test_layer_edges(n_dst, fanout, dim, out_dim, dtype):
+    """Bound: S (2^-11 + (2 dim + k + 2) 2^-24), S = sum of |w| |input| + |bias|: the mean rounded to half, then
+    float sums; half an ulp of a half result."""
+    rng = np.random.default_rng(n_dst + dim)
+    n_src = n_dst + 50
+    indptr, indices = block_of(rng, n_dst, fanout, n_src)
+    x = rng.standard_normal((n_src, dim)).astype(np.float16)
+    w = (rng.standard_normal((out_dim, 2 * dim)) / np.sqrt(dim)).astype(np.float16)
+    b = rng.standard_normal(out_dim).astype(np.float32)
+    relu = n_dst % 2 == 0
+    got = layer(indptr, indices, x, w, b, relu, dtype)
+    want, mag = oracle.sage_layer(indptr, indices, x, w.astype(np.float64), b.astype(np.float64), relu)
+    tol = mag * (2.0 ** -11 + (2 * dim + np.diff(indptr)[:, None] + 2) * 2.0 ** -24)
+    if dtype == torch.float16:
+        tol = tol + np.abs(want) * 2.0 ** -11 + 2.0 ** -24
+    assert (np.abs(got - want) <= tol).all()
+
+
+@pytest.mark.parametrize("dim", [8, 128, 136])
+def test_layer_means_are_rounded_quotients(dim):
+    """W picks one column of the mean, so the float result is the mean itself: the float sum in slot order,
+    divided, rounded to half, bit for bit; an infinite sum stays infinite."""
+    rng = np.random.default_rng(dim)
+    n_dst, n_src = 2000, 3000
+    indptr, indices = block_of(rng, n_dst, 70, n_src)
+    x = (rng.standard_normal((n_src, dim)) * 10.0 ** rng.uniform(-6, 3, (n_src, 1))).astype(np.float16)
+    w = np.zeros((dim, 2 * dim), np.float16)
+    w[np.arange(dim), dim + np.arange(dim)] = 1
+    got = layer(indptr, indices, x, w, np.zeros(dim, np.float32), False, torch.float32)
+    for i in range(n_dst):
+        s = np.zeros(dim, np.float32)
+        for e in range(indptr[i], indptr[i + 1]):
+            s = s + x[indices[e]].astype(np.float32)
+        k = np.float32(max(1, indptr[i + 1] - indptr[i]))
+        assert np.array_equal(got[i], (s / k).astype(np.float16).astype(np.float64))
+    x[:] = np.inf
+    got = layer(indptr, indices, x, np.ones((3, 2 * dim), np.float16), np.zeros(3, np.float32), False, torch.float32)
+    assert np.isposinf(got).all()
