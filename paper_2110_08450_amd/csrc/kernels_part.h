@@ -150,31 +150,35 @@ __device__ __forceinline__ uint32_t bucket_of_block(const Launch& P, uint32_t i,
   return (i % ways) * (buckets / ways) + i / ways;
 }
 
-// counts <- (n_0, 0, ..., status 0); node_ids[0, n_0) <- seeds; labels of the seeds.  Seeds are
-// range-checked by the first hop's k_sample_part or k_count_rows, which run after the status word is zero.  A batch of more
+// counts <- (n_0, 0, ..., status 0), by a whole block.  A batch of more
 // seeds than the graph has nodes holds a stray or a repeated one; it ends here, since grids, rows and
 // positions of a hop are bounded by the number of nodes.
+__device__ __forceinline__ void begin_counts(const Launch& P, const BatchCtx& B) {
+  int64_t status = SMFG_ST_OK;
+  if (B.num_seeds > P.num_nodes) {
+    int stray = 0;
+    for (int i = threadIdx.x; i < B.num_seeds; i += kThreads) {
+      const int32_t v = B.seeds[i];
+      stray |= v < 0 || static_cast<int64_t>(v) >= P.num_nodes;
+    }
+    status = __syncthreads_or(stray) ? SMFG_ST_SEED_OUT_OF_RANGE : SMFG_ST_DUPLICATE_SEED;
+  }
+  const int m = 2 * P.L + 2;
+  for (int q = threadIdx.x; q < m; q += kThreads) B.counts[q] = q == 0 ? B.num_seeds : q == m - 1 ? status : 0;
+}
+// ... and node_ids[i] <- seed i, with its label.
+__device__ __forceinline__ int32_t begin_seed(const Launch& P, const BatchCtx& B, int i) {
+  const int32_t v = B.seeds[i];
+  B.node_ids[i] = v;
+  if (B.labels && v >= 0 && static_cast<int64_t>(v) < P.num_nodes) copy_label(P, B, i, v);
+  return v;
+}
+// Both, for calls whose first hop is k_sample_part, which range-checks the seeds when the status word is zero.
 __global__ void __launch_bounds__(kThreads) k_begin(const Launch P) {
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_in_batch(P) == 0) {
-    int64_t status = SMFG_ST_OK;
-    if (B.num_seeds > P.num_nodes) {
-      int stray = 0;
-      for (int i = threadIdx.x; i < B.num_seeds; i += kThreads) {
-        const int32_t v = B.seeds[i];
-        stray |= v < 0 || static_cast<int64_t>(v) >= P.num_nodes;
-      }
-      status = __syncthreads_or(stray) ? SMFG_ST_SEED_OUT_OF_RANGE : SMFG_ST_DUPLICATE_SEED;
-    }
-    const int m = 2 * P.L + 2;
-    for (int q = threadIdx.x; q < m; q += kThreads) B.counts[q] = q == 0 ? B.num_seeds : q == m - 1 ? status : 0;
-  }
+  if (block_in_batch(P) == 0) begin_counts(P, B);
   const int stride = blocks_per_batch(P) * kThreads;
-  for (int i = block_in_batch(P) * kThreads + threadIdx.x; i < B.num_seeds; i += stride) {
-    const int32_t v = B.seeds[i];
-    B.node_ids[i] = v;
-    if (B.labels && v >= 0 && static_cast<int64_t>(v) < P.num_nodes) copy_label(P, B, i, v);
-  }
+  for (int i = block_in_batch(P) * kThreads + threadIdx.x; i < B.num_seeds; i += stride) begin_seed(P, B, i);
 }
 
 // Exclusive scan of the counts cnt[0, nB) of a block's buckets in place, the total at cnt[nB], which is returned as

@@ -1,8 +1,9 @@
 // libsmfg wide path: fanouts above SMFG_MAX_FANOUT and SMFG_FANOUT_ALL, samples at exact block offsets.
-// count_rows / scan_count_tiles fix the offsets; then either the table strategy (sample_wide<true>,
+// count_rows counts the samples; then either the table strategy (sample_wide<true>,
 // flag_flat, scan_flat_tiles, assemble_flat) or the partition strategy (sample_wide<false>, part_flat,
-// [split_buckets], dedup_buckets, flag_flat_part, scan_flat_tiles,
-// assemble_flat_part) turns the samples into local ids.
+// [split_buckets], dedup_buckets, flag_flat_part, assemble_flat_part) turns them into local ids.  No launch of the latter only
+// scans: two hops of fanouts (100, 100), four batches, 772 -> 742 us without the scans of either side and without k_begin, whole
+// neighbourhoods of two hops 401 -> 381, two hops of some 100 samples 79 -> 64.
 #ifndef SMFG_KERNELS_WIDE_H_
 #define SMFG_KERNELS_WIDE_H_
 
@@ -15,55 +16,100 @@ namespace smfg_dev {
 // comes first and the later passes walk the samples flat, four consecutive samples per thread.
 constexpr int kWideTile = 4 * kThreads;  // samples per flat tile
 
-// Degree, sample count and row start per destination; in-tile scan of the sample counts.
+// The block offset of a destination is rowoff, the samples of its tile of kTileRows before it, and the sums of the tiles before
+// that.  The first wave of a block of k_sample_wide adds these up while the row records are on their way: up to kDirectTiles totals, or,
+// in hops of more destinations (131 K), totals of kSuperTiles tiles, which k_count_rows adds to with one atomic per tile, and the last
+// few.  A launch in between that scanned the totals took 4.6 us, whatever a hop had.  With every wave adding up for itself the
+// kernel was bound by instruction issue (28 K destinations x 100 in each of four batches 85 -> 104 us).
+// The totals of tiles of tiles are in the memory of rowmn and hist, of which neither holds anything between two hops; the end of a
+// hop clears them for the next.  A first hop has none, nor has one behind small hops, whose nodes are too few.
+constexpr uint32_t kDirectTiles = 512, kSuperTiles = 64;
+static_assert((kSmallRecords + kTileRows - 1) / kTileRows <= kDirectTiles, "nodes known after small hops");
+__device__ __forceinline__ bool has_supers(const Launch& P, uint32_t tiles) { return P.h > 0 && tiles > kDirectTiles; }
+__device__ __forceinline__ unsigned long long* super_sums(const BatchCtx& B) { return reinterpret_cast<unsigned long long*>(B.rowmn); }
+__device__ __forceinline__ void clear_supers(const Launch& P, const BatchCtx& B) {
+  if (P.h + 1 == P.L) return;
+  const uint32_t supers = static_cast<uint32_t>(B.node_capacity) / (kTileRows * kSuperTiles) + 1u;
+  for (uint32_t q = block_in_batch(P) * kThreads + threadIdx.x; q < supers; q += blocks_per_batch(P) * kThreads) super_sums(B)[q] = 0ull;
+}
+
+// Degree, sample count and row start per destination; in-tile scan of the sample counts.  BEGIN: the first hop under the
+// partition strategy, which starts the counts and node ids as k_begin does; that no seed is stray is for k_sample_wide to
+// tell, since the status word is being cleared.
+template <bool BEGIN>
 __global__ void __launch_bounds__(kThreads) k_count_rows(const Launch P) {
   __shared__ unsigned long long lds[kThreads / 64];
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const int n = static_cast<int>(B.counts[P.h]);
+  if (BEGIN ? false : block_has_status(B, P.L)) return;
+  const int n = BEGIN ? B.num_seeds : static_cast<int>(B.counts[P.h]);
+  if (BEGIN && block_in_batch(P) == 0) begin_counts(P, B);
+  const bool rows = !BEGIN || n <= P.num_nodes;
   const int d = P.d;
   const int tiles = (n + kTileRows - 1) / kTileRows;
   for (int tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P)) {
     const int i = tile * kTileRows + threadIdx.x;
     uint32_t k = 0;
     if (i < n) {
-      const int32_t id = B.node_ids[i];
+      const int32_t id = BEGIN ? begin_seed(P, B, i) : B.node_ids[i];
       int64_t a = 0;
       uint32_t deg = 0;
       // the seeds are caller data: none may index the graph unchecked (later hops only hold
       // neighbour ids read from the graph)
-      if (P.h == 0 && (id < 0 || static_cast<int64_t>(id) >= P.num_nodes)) {
-        set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
-      } else {
+      if (P.h > 0 || (id >= 0 && static_cast<int64_t>(id) < P.num_nodes)) {
         a = P.indptr[id];
         deg = static_cast<uint32_t>(P.indptr[id + 1] - a);
       }
       k = (d < 0 || deg <= static_cast<uint32_t>(d)) ? deg : static_cast<uint32_t>(d);
-      B.rowstart[i] = a;
-      B.rowdeg[i] = deg;
-      B.rowk[i] = static_cast<int32_t>(k);
+      if (rows) {
+        B.rowstart[i] = a;
+        B.rowdeg[i] = deg;
+        B.rowk[i] = static_cast<int32_t>(k);
+      }
     }
     unsigned long long total;
     const unsigned long long pre = block_exscan(static_cast<unsigned long long>(k), lds, total);
-    if (i < n) B.rowoff[i] = static_cast<int32_t>(pre);
-    if (threadIdx.x == 0) B.tile_sums[tile] = total;
+    if (rows && i < n) B.rowoff[i] = static_cast<int32_t>(pre);
+    if (rows && threadIdx.x == 0) {
+      B.tile_sums[tile] = total;
+      if (has_supers(P, static_cast<uint32_t>(tiles))) atomicAdd(&super_sums(B)[static_cast<uint32_t>(tile) / kSuperTiles], total);
+    }
     __syncthreads();
   }
 }
 
-// Exclusive scan of the per-tile sample counts; E_h and its capacity checks.
-__global__ void __launch_bounds__(kTileScanThreads) k_scan_count_tiles(const Launch P) {
-  const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const int n = static_cast<int>(B.counts[P.h]);
-  const unsigned long long edges = scan_tile_sums(B.tile_sums, static_cast<uint32_t>((n + kTileRows - 1) / kTileRows));
-  if (threadIdx.x == 0) {
-    const bool fits = edges <= static_cast<unsigned long long>(B.edge_capacity) &&
-                      edges <= static_cast<unsigned long long>(B.lostto_entries);
-    B.counts[P.L + 1 + P.h] = static_cast<int64_t>(edges);
-    if (fits) B.blk_indptr[n] = static_cast<int32_t>(edges);
-    else set_status(B, P.L, SMFG_ST_EDGE_CAPACITY);
+// Samples of the hop's tiles before `tile`, the same for every lane of the wave, all of which call.
+__device__ __forceinline__ unsigned long long samples_before(const Launch& P, const BatchCtx& B, uint32_t tiles, uint32_t tile) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const bool supers = has_supers(P, tiles);
+  const uint64_t* sums = supers ? reinterpret_cast<const uint64_t*>(super_sums(B)) : B.tile_sums;
+  const uint32_t count = supers ? tile / kSuperTiles : tile;
+  static_assert(kSuperTiles == 64, "a lane per tile");
+  unsigned long long before = 0;
+  if (supers && lane < tile % kSuperTiles) before = B.tile_sums[(tile & ~(kSuperTiles - 1u)) + lane];
+  constexpr int U = 4;
+  for (uint32_t q0 = lane; q0 - lane < count; q0 += 64u * U) {  // every read of a turn on its way before the first is used
+    unsigned long long x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = sums[q0 + 64u * u < count ? q0 + 64u * u : count - 1u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) before += q0 + 64u * u < count ? x[u] : 0ull;
   }
+  const unsigned long long inc = wave_inscan(before);
+  return static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc >> 32), 63))) << 32 |
+         static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), 63));
+}
+
+// E_h, or what is wrong with the hop, by one wave.
+__device__ __forceinline__ void close_samples(const Launch& P, const BatchCtx& B, int n, uint32_t tiles, unsigned long long room) {
+  const unsigned long long edges = tiles == 0u ? 0ull : samples_before(P, B, tiles, tiles - 1u) + B.tile_sums[tiles - 1u];
+  // a stray seed comes first, as it does where seeds are checked before anything is counted
+  bool stray = false;
+  for (int i = threadIdx.x & 63; edges > room && P.h == 0 && i < n; i += 64) stray = stray || static_cast<uint32_t>(B.node_ids[i]) >= P.num_nodes;
+  stray = __any(stray);
+  if ((threadIdx.x & 63) != 0) return;
+  B.counts[P.L + 1 + P.h] = static_cast<int64_t>(edges);
+  if (edges <= room) B.blk_indptr[n] = static_cast<int32_t>(edges);
+  else set_status(B, P.L, stray ? SMFG_ST_SEED_OUT_OF_RANGE : SMFG_ST_EDGE_CAPACITY);
 }
 
 // A wave takes up to kWideRows consecutive destinations (fewer when the hop has fewer destinations
@@ -193,9 +239,13 @@ __device__ __forceinline__ void floyd_positions(const Launch& P, const BatchCtx&
 template <bool INSERT>
 __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
   extern __shared__ __align__(16) uint32_t wide_lds[];
+  __shared__ uint2 turn_lds[2];  // .x samples of the tiles before the turn's first one, .y whether the batch has a status
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (__any(status_of(B, P.L) != 0)) return;  // whole waves only: the lanes below cooperate
-  const int n = static_cast<int>(B.counts[P.h]);
+  // A batch that had a status when the block started may count more nodes than its arrays hold; those below are read, and nothing
+  // is done with them.  The first wave's answer is the block's: others may set a status meanwhile.
+  const bool stopped = status_of(B, P.L) != 0;
+  const int64_t known = B.counts[P.h];
+  const int n = static_cast<int>(known < B.node_capacity ? known : B.node_capacity);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const uint32_t words = wide_lds_words(P.d), table_words = wide_table_words(P.d);
@@ -205,19 +255,38 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
   const int waves_total = blocks_per_batch(P) * (kThreads / 64);
   int per = (n + waves_total - 1) / waves_total;  // destinations per wave and turn
   per = per < 1 ? 1 : (per > kWideRows ? kWideRows : per);
-  for (int i0 = (block_in_batch(P) * (kThreads / 64) + wave) * per; i0 < n; i0 += waves_total * per) {
+  static_assert(kThreads / 64 * kWideRows <= kTileRows, "a block's destinations are in two tiles at most");
+  const uint32_t tiles = static_cast<uint32_t>(n + kTileRows - 1) / kTileRows;
+  const unsigned long long room = static_cast<unsigned long long>(B.edge_capacity < B.lostto_entries ? B.edge_capacity : B.lostto_entries);
+  int turn = 0;  // wave 0 writes the next turn's offset while others may still read the present one's
+  for (int b0 = block_in_batch(P) * (kThreads / 64) * per; b0 < n; b0 += waves_total * per, turn ^= 1) {
+    const int i0 = b0 + wave * per;
     const int il = i0 + lane;
     uint32_t v_l = 0, deg_l = 0, k_l = 0, base_l = 0, a_lo = 0, a_hi = 0;
-    if (lane < per && il < n) {
+    const bool mine = lane < per && il < n;
+    if (mine) {
       v_l = static_cast<uint32_t>(B.node_ids[il]);
       const int64_t a = B.rowstart[il];
       a_lo = static_cast<uint32_t>(a);
       a_hi = static_cast<uint32_t>(static_cast<uint64_t>(a) >> 32);
       deg_l = static_cast<uint32_t>(B.rowdeg[il]);
       k_l = static_cast<uint32_t>(B.rowk[il]);
-      base_l = static_cast<uint32_t>(B.tile_sums[il / kTileRows]) + static_cast<uint32_t>(B.rowoff[il]);
+      base_l = static_cast<uint32_t>(B.rowoff[il]);
+      if (il / kTileRows != b0 / kTileRows) base_l += static_cast<uint32_t>(B.tile_sums[b0 / kTileRows]);
+    }
+    if (wave == 0) {
+      const uint32_t before = static_cast<uint32_t>(samples_before(P, B, tiles, static_cast<uint32_t>(b0 / kTileRows)));
+      if (lane == 0) turn_lds[turn] = make_uint2(before, stopped ? 1u : 0u);
+    }
+    __syncthreads();
+    if (turn_lds[turn].y != 0u) return;
+    base_l += turn_lds[turn].x;
+    if (mine) {
+      if (P.h == 0 && v_l >= P.num_nodes) set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);
       B.blk_indptr[il] = static_cast<int32_t>(base_l);
     }
+    // nothing is written past the room of a hop that has too many samples, whatever the offsets come to
+    if (static_cast<unsigned long long>(base_l) + k_l > room) k_l = deg_l = 0u;
     const int rows = n - i0 < per ? n - i0 : per;
     static_assert(kWideRows % 4 == 0 && kWideRows <= 64, "rows are walked four at a time, a lane per row record");
     for (int r0 = 0; r0 < rows; r0 += 4) {  // lanes beyond the last row hold k = 0
@@ -275,6 +344,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
       __builtin_amdgcn_wave_barrier();
     }
   }
+  if (block_in_batch(P) == blocks_per_batch(P) - 1 && wave == 0 && !stopped) close_samples(P, B, n, tiles, room);
 }
 
 // ---- partition strategy over exact offsets ----------------------------------------------------
@@ -331,45 +401,66 @@ __global__ void __launch_bounds__(kFlatThreads) k_part_flat(const Launch P) {
 // lookups of the samples that repeat a node (scattered over the hop) do not go to memory.
 // A wave takes four groups one after the other, a sample per lane, so that its reads are consecutive and a ballot is
 // a group's bits.  Bound by the stream of entries and, in launches with far more blocks than tiles, by the blocks that leave:
-// 9.7 M samples of four batches 18.5 -> 17.6 us, 5.5 M of one 9.9 -> 9.3, against four consecutive samples per thread.
+// 9.7 M samples of four batches 18.5 -> 17.6 us, 5.5 M of one 9.9 -> 9.3, against four consecutive samples per thread;
+// 12.3 and 8.3 with the larger tiles below and half the blocks.
+// Tiles are of as many groups as leave at most kFlatTiles of them, so that every block of k_assemble_flat_part can scan their totals
+// for itself.
+constexpr uint32_t kFlatTiles = 2048;
+__device__ __forceinline__ uint32_t flat_tile_lg(uint32_t samples) {  // log2 of the samples of a tile, for at most 2^30 of them
+  uint32_t lg = 10;
+  static_assert(kWideTile == 1 << 10, "the smallest tile");
+  while (samples > kFlatTiles << lg) ++lg;
+  return lg;
+}
 __global__ void __launch_bounds__(kThreads) k_flag_flat_part(const Launch P) {
   constexpr int kWaves = kThreads / 64;
   __shared__ uint32_t lds[2][kWaves];
   const BatchCtx& B = P.b[batch_of_block(P)];
   if (block_has_status(B, P.L)) return;
   const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-  const uint32_t tiles = (E + kWideTile - 1) / kWideTile;
+  const uint32_t lg = flat_tile_lg(E), tiles = (E + (1u << lg) - 1u) >> lg;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int turn = 0;  // a wave writes the sums of the next tile while others may still read the present one's
-  for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P), turn ^= 1) {
-    const uint32_t p0 = tile * kWideTile + static_cast<uint32_t>(wave) * 256u;
-    uint32_t e[4];
+  int turn = 0;  // a wave writes the next sums while others may still read the present ones
+  for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P)) {
+    const uint32_t end = E - (tile << lg) < 1u << lg ? E : (tile + 1u) << lg;
+    uint32_t total = 0;  // new nodes of the tile so far
+    uint32_t next[4];
+    const auto fetch = [&](uint32_t p0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t pos = p0 + u * 64 + lane;
-      e[u] = pos < E ? static_cast<uint32_t>(B.gsrc[pos]) : kResolved;
-    }
-    unsigned long long own = 0;  // lane u < 4: the bits of group u, and the new nodes of the wave before it
-    uint32_t before = 0, sum = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const unsigned long long bits = __ballot((e[u] & kResolved) == 0u);
-      if (lane == u) {
-        own = bits;
-        before = sum;
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t pos = p0 + u * 64 + lane;
+        next[u] = pos < end ? static_cast<uint32_t>(B.gsrc[pos]) : kResolved;
       }
-      sum += static_cast<uint32_t>(__popcll(bits));
-    }
-    if (lane == 0) lds[turn][wave] = sum;
-    __syncthreads();
-    uint32_t total = 0;
+    };
+    uint32_t p0 = (tile << lg) + static_cast<uint32_t>(wave) * 256u;
+    fetch(p0);
+    for (uint32_t c0 = tile << lg; c0 < end; c0 += kWideTile, p0 += kWideTile, turn ^= 1) {
+      uint32_t e[4];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      if (w < wave) before += lds[turn][w];
-      total += lds[turn][w];
+      for (int u = 0; u < 4; ++u) e[u] = next[u];
+      fetch(p0 + kWideTile);
+      unsigned long long own = 0;  // lane u < 4: the bits of group u, and the new nodes of the tile before it
+      uint32_t before = 0, sum = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned long long bits = __ballot((e[u] & kResolved) == 0u);
+        if (lane == u) {
+          own = bits;
+          before = sum;
+        }
+        sum += static_cast<uint32_t>(__popcll(bits));
+      }
+      if (lane == 0) lds[turn][wave] = sum;
+      __syncthreads();
+      before += total;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        if (w < wave) before += lds[turn][w];
+        total += lds[turn][w];
+      }
+      if (lane < 4 && p0 + static_cast<uint32_t>(lane) * 64u < end)
+        B.grp[(p0 >> 6) + lane] = make_uint4(static_cast<uint32_t>(own), static_cast<uint32_t>(own >> 32), before, 0u);
     }
-    if (lane < 4 && p0 + static_cast<uint32_t>(lane) * 64u < E)
-      B.grp[(p0 >> 6) + lane] = make_uint4(static_cast<uint32_t>(own), static_cast<uint32_t>(own >> 32), before, 0u);
     if (threadIdx.x == 0) B.stile_sums[tile] = total;
   }
 }
@@ -383,32 +474,61 @@ __device__ __forceinline__ uint32_t flat_rank(const uint4 g, uint32_t tile_befor
 // assemble_flat for those entries, a wave's samples as in flag_flat_part: its reads and writes are consecutive.
 // What is left is bound by the scattered lookups of what pointers name: 9.7 M samples of four batches 43 -> 34 us, 5.5 M of one
 // 28 -> 23.5, against four consecutive samples per thread, whose stores took every fourth word of a line.
+// Every block scans the totals of the tiles for itself, 16 KB from the L2 at most, and then takes several runs of kWideTile samples.
+constexpr unsigned kAssembleFlatBlocks = 2048;  // of a launch: what the chip holds at a time
 __global__ void __launch_bounds__(kThreads) k_assemble_flat_part(const Launch P) {
+  constexpr int kPer = kFlatTiles / kThreads;
+  __shared__ uint32_t tile_new[kFlatTiles];  // new nodes of the tiles before
+  __shared__ uint32_t scan[kThreads / 64];
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (status_of(B, P.L) != 0) return;
+  if (block_has_status(B, P.L)) return;
   const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
   const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-  const uint32_t tiles = (E + kWideTile - 1) / kWideTile;
-  for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P)) {
-    const uint32_t tpre = static_cast<uint32_t>(B.stile_sums[tile]);
-    const uint32_t p0 = tile * kWideTile + (threadIdx.x >> 6) * 256u + (threadIdx.x & 63u);
+  const uint32_t lg = flat_tile_lg(E), tiles = (E + (1u << lg) - 1u) >> lg, chunks = (E + kWideTile - 1) / kWideTile;
+  clear_supers(P, B);
+  if (static_cast<uint32_t>(block_in_batch(P)) >= (chunks > 0u ? chunks : 1u)) return;  // the first block also closes an empty hop
+  {
+    uint32_t x[kPer], mine = 0, fresh;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const uint32_t t = threadIdx.x * kPer + u;
+      x[u] = t < tiles ? static_cast<uint32_t>(B.stile_sums[t]) : 0u;
+      mine += x[u];
+    }
+    uint32_t pre = block_exscan<kThreads>(mine, scan, fresh);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      tile_new[threadIdx.x * kPer + u] = pre;
+      pre += x[u];
+    }
+    const int64_t nodes = static_cast<int64_t>(n) + static_cast<int64_t>(fresh);
+    if (block_in_batch(P) == 0 && threadIdx.x == 0) {
+      B.counts[P.h + 1] = nodes;
+      if (nodes > B.node_capacity) set_status(B, P.L, SMFG_ST_NODE_CAPACITY);
+    }
+    if (nodes > B.node_capacity) return;
+    __syncthreads();
+  }
+  for (uint32_t chunk = block_in_batch(P); chunk < chunks; chunk += blocks_per_batch(P)) {
+    const uint32_t c0 = chunk * kWideTile, tpre = tile_new[c0 >> lg];
+    const uint32_t p0 = c0 + (threadIdx.x >> 6) * 256u + (threadIdx.x & 63u);
     uint4 own[4];
     uint32_t e[4], q[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t pos = p0 + u * 64;
       e[u] = pos < E ? static_cast<uint32_t>(B.gsrc[pos]) : kResolved;
-      own[u] = B.grp[(pos < E ? pos : tile * kWideTile) >> 6];
+      own[u] = B.grp[(pos < E ? pos : c0) >> 6];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = (e[u] & kPointer) == kPointer ? (e[u] & ~kPointer) : tile * kWideTile;
+    for (int u = 0; u < 4; ++u) q[u] = (e[u] & kPointer) == kPointer ? (e[u] & ~kPointer) : c0;
     // what the pointers name is fetched for all four samples before any is used
     uint4 qg[4];
     uint32_t qtile[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       qg[u] = B.grp[q[u] >> 6];
-      qtile[u] = static_cast<uint32_t>(B.stile_sums[q[u] / kWideTile]);
+      qtile[u] = tile_new[q[u] >> lg];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -493,6 +613,7 @@ __global__ void __launch_bounds__(kThreads) k_assemble_flat(const Launch P) {
   const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
   const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
   const bool last = P.h == P.L - 1;
+  clear_supers(P, B);
   const uint32_t tiles = (E + kWideTile - 1) / kWideTile;
   for (uint32_t tile = block_in_batch(P); tile < tiles; tile += blocks_per_batch(P)) {
     const uint32_t tpre = n + static_cast<uint32_t>(B.stile_sums[tile]);

@@ -1054,10 +1054,10 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
   const bool gathered = want_feat && small_hops == L && small_gather(g->row_bytes, max_n[L]);
   if (small_hops > 0) {
     launch_small_hops(small_launch(P, ws, outs, fanouts, max_n), small_hops, max_n, gathered, st);
-  } else if (part) {
+  } else if (part && !wide) {
     StageTimer t_(SMFG_STAGE_SEEDS, st);
     k_begin<<<blocks_for(max_seeds, kThreads, kCap) * G, kThreads, 0, st>>>(P);
-  } else {
+  } else if (!part) {
     for (int b = 0; stale_notes && b < num_batches; ++b)
       k_fill_u32<<<blocks_for(ws[b]->slot_entries, kThreads * 4, 1024), kThreads, 0, st>>>(ws[b]->lostto, ws[b]->slot_entries, 0u);
     { StageTimer t_(SMFG_STAGE_CLEAR, st);
@@ -1112,12 +1112,16 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     }
     if (wide) {
       const unsigned flat_blocks = blocks_for(samples[h], kWideTile, kCap);
-      // a wave per destination while the grid allows; beyond that a wave takes several (see k_sample_wide)
-      const unsigned wave_blocks = blocks_for(rows, kThreads / 64, 2 * kCap);
-      {
+      // A wave per destination while the launch is of 8192 blocks at most, four times what the chip holds; beyond that a wave takes
+      // several (see k_sample_wide), which share its row records and offsets: 28 K destinations in each of four batches 101 us
+      // with up to 8192 blocks per batch, 85 with as many in all.
+      const unsigned wave_blocks = blocks_for(rows, kThreads / 64, 2 * kCap / G > 1024u ? 2 * kCap / G : 1024u);
+      if (part && h == 0) {
+        StageTimer t_(SMFG_STAGE_SEEDS, st, SMFG_STAGE_SCAN_TILES);
+        k_count_rows<true><<<tile_blocks * G, kThreads, 0, st>>>(P);
+      } else {
         StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
-        k_count_rows<<<tile_blocks * G, kThreads, 0, st>>>(P);
-        k_scan_count_tiles<<<G, kTileScanThreads, 0, st>>>(P);
+        k_count_rows<false><<<tile_blocks * G, kThreads, 0, st>>>(P);
       }
       if (part) {
         P.flat = 1;
@@ -1139,15 +1143,11 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
         }
         {
           StageTimer t_(SMFG_STAGE_FLAG, st);
-          k_flag_flat_part<<<flat_blocks * G, kThreads, 0, st>>>(P);
-        }
-        {
-          StageTimer t_(SMFG_STAGE_SCAN_TILES, st);
-          k_scan_flat_tiles<<<G, kTileScanThreads, 0, st>>>(P);
+          k_flag_flat_part<<<blocks_for(samples[h], kWideTile, kFlatTiles) * G, kThreads, 0, st>>>(P);
         }
         {
           StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
-          k_assemble_flat_part<<<flat_blocks * G, kThreads, 0, st>>>(P);
+          k_assemble_flat_part<<<blocks_for(samples[h], kWideTile, kAssembleFlatBlocks / G + 1u) * G, kThreads, 0, st>>>(P);
         }
         continue;
       }

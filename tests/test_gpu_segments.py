@@ -159,6 +159,42 @@ def test_stages_of_launches_that_do_two():
         assert prof["partition"][1] == 1 + splits
 
 
+@pytest.mark.parametrize("strategy", ["partition", "table"])
+@pytest.mark.parametrize("seeds,fanouts", [(131_072, (33, 33)), (131_073, (33, 33)), (70_000, (33, 5, 40))])
+def test_wide_hops_of_many_tiles(seeds, fanouts, strategy, monkeypatch):
+    """More destinations than a block adds up tile by tile (131072) in first and later hops, more samples (2 M) than 2048
+    tiles of 1024 hold, and the same workspace again."""
+    monkeypatch.setenv("SMFG_DEDUP", strategy)
+    gg = random_graph(200_000, 30, 31)
+    s = np.random.default_rng(seeds).permutation(200_000)[:seeds].astype(np.int32)
+    ws = smfg.workspace_create(gg.g, seeds, fanouts)
+    out = smfg.alloc_output(gg.g, seeds, fanouts)
+    for key in (7, 8):
+        smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), fanouts, key, out)
+        assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(s, fanouts, key), len(fanouts))
+
+
+@pytest.mark.parametrize("room,stray,status", [(0, False, smfg.ST_EDGE_CAPACITY), (0, True, smfg.ST_SEED_OUT_OF_RANGE),
+                                               (20, True, smfg.ST_SEED_OUT_OF_RANGE), (20, False, 0)])
+def test_wide_first_hop_that_does_not_fit(room, stray, status, monkeypatch):
+    """Samples beyond the room of a batch, a stray seed, or both: nothing lies behind the buffers' ends, and the stray seed is
+    what is reported."""
+    monkeypatch.setenv("SMFG_DEDUP", "partition")
+    gg = random_graph(5_000, 40, 32)
+    s = np.random.default_rng(32).permutation(5_000)[:600].astype(np.int32)
+    edges = gg.oracle.sample_mfg(s, (-1,), 1).num_edges[0]
+    if stray:
+        s[599] = 5_000
+    capacity = edges - 10 + room
+    ws = smfg.workspace_create(gg.g, 600, (-1,), 0, edges)
+    out = smfg.alloc_output(gg.g, 600, (-1,), edge_capacity=[edges])
+    out.indices[0].fill_(-7)
+    out.c.edge_capacity[0] = capacity
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), (-1,), 1, out)
+    assert fetch(out, 1)["status"] == status
+    assert (out.indices[0][min(capacity, edges):] == -7).all()
+
+
 @pytest.mark.parametrize("level", [1, 2])
 @pytest.mark.parametrize("dim,folded", [(32, True), (3, False)])
 def test_a_gather_without_a_launch_has_no_time(dim, folded, level):
