@@ -306,9 +306,10 @@ int smfg_read_counts(const smfg_output_t *out, int32_t L, int64_t *h_counts, voi
  * level 1 = only the feature gather launch, level 2 = every launch.  At most max_records
  * launches are timed, later ones run untimed.  smfg_profile_end synchronises the device,
  * adds up the event-to-event milliseconds and the launch count per stage, and frees the events.
- * A launch that does the work of two stages is counted in both; its time goes to the first: one that
- * draws and partitions a hop's samples (SAMPLE, PARTITION), one that assembles a hop and draws for the
- * next or copies the feature rows (ASSEMBLE, and SAMPLE or GATHER).  So the gather of a call that has
+ * A launch that does the work of several stages is counted in each; its time goes to the first: one that
+ * draws and partitions a hop's samples (SAMPLE, PARTITION), one that starts the counts and counts the samples
+ * of wide fanouts (SEEDS, SCAN_TILES), one that assembles a hop and, in small hops, drew or deduplicated its
+ * samples, draws for the next or copies the feature rows (ASSEMBLE, and SAMPLE, DEDUP or GATHER).  So the gather of a call that has
  * no launch of its own is counted, on either level, with no time.
  */
 #define SMFG_STAGE_CLEAR 0

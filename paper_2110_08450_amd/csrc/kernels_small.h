@@ -1,9 +1,9 @@
-// libsmfg small hops: two launches per hop, whatever is in it, and one before the first.
+// libsmfg small hops: two launches per hop, or one, whatever is in it, and at most one before the first.
 //
 // A hop of fewer than kSmallRecords records keeps no kernel busy for much longer than its launch and a
 // chain of dependent reads take (about 5 us together), so what counts is how many there are:
-//   draw    of the first hop: many blocks, since its scattered reads need many compute units to be in flight at once;
-//   dedup   2^kSmallLgB blocks per batch, each reads all records, keeps those of its hash bucket and
+//   draw    of the first hop, unless finish does it: many blocks, since its scattered reads need many compute units to be in flight at once;
+//   dedup   unless finish does it: 2^kSmallLgB blocks per batch, each reads all records, keeps those of its hash bucket and
 //           settles them in an LDS table: no histogram, no scatter;
 //   finish  blocks of consecutive destinations; each reads all entries of the hop, which gives it the
 //           first-appearance bits and their prefix sums in its own LDS, and then writes the final ids of
@@ -12,11 +12,13 @@
 //           with these: the draw of the next small hop, or, after the last hop of a call, their feature rows.
 // Reading everything in every block costs up to 128 KB from the L2, a few us at most.  Measured, one batch
 // per call, whole call with its gather, against the table strategy's four launches per hop: (10, 5) with
-// 256 seeds 62 -> 38 us, (15, 10, 5) with 16 seeds 78 -> 60 us; with the draw and the gather in launches of their
-// own 41 and 65 us.  One block for a
+// 256 seeds 62 -> 34 us, (15, 10, 5) with 16 seeds 78 -> 52 us; with a dedup for every hop 38 and 60, and with the draw and the
+// gather in launches of their own 41 and 65 us.  One block for a
 // whole batch was slower (16 seeds: 172 us): a single compute unit has too few reads in flight.
 #ifndef SMFG_KERNELS_SMALL_H_
 #define SMFG_KERNELS_SMALL_H_
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "kernels_fast.h"
@@ -31,7 +33,7 @@ constexpr int kSmallTableLg = 13;         // of 8192 slots
 constexpr uint32_t kSmallList = 1u << (kSmallTableLg - 1);
 // Destinations per block of finish for a hop of at most max_rows: some 32 blocks per batch, fewer where there are
 // many batches, since a block takes a compute unit for itself.
-constexpr int kSmallMinBlocks = 256 / SMFG_MAX_BATCHES, kSmallMaxBlocks = 32, kSmallMinTile = 8;
+constexpr int kSmallMinBlocks = 256 / SMFG_MAX_BATCHES, kSmallMaxBlocks = 32, kSmallMinTile = 1;
 constexpr int small_tile(int64_t max_rows, int batches) {
   const int most = 256 / batches, blocks = most > kSmallMaxBlocks ? kSmallMaxBlocks : most;
   const int64_t tile = (max_rows + blocks - 1) / blocks;
@@ -93,8 +95,8 @@ __device__ __forceinline__ int small_rows(const SmallLaunch& P, const SmallBatch
   return block_has_status(B, P.L) ? -1 : n;
 }
 
-// Hop 0: every position gets a node id or kNoSample.  Reads the seeds, copies them to the node ids and starts the
-// counts; k_small_dedup looks for seeds that are no nodes.
+// Hop 0 of more than finish draws: every position gets a node id or kNoSample.  Reads the seeds, copies them to the node ids and starts the
+// counts; k_small_dedup, or finish, looks for seeds that are no nodes.
 template <int D>
 __global__ void __launch_bounds__(kThreads) k_small_draw(const SmallLaunch P) {
   __shared__ DrawLds<kThreads, 512> S;  // kThreads / d rows of at most d + 1 words
@@ -254,10 +256,69 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
   report(B, P.L, wrong);
 }
 
+// Where finish finds the entries of its hop: settled by k_small_dedup, drawn by the launch before, or nowhere yet.
+enum { kSettled, kDrawn, kSeeds };
+// A hop of at most kOneRecords records is settled in the blocks of finish themselves, each of which has a table of all its nodes,
+// and a first hop of at most kOneDraw records and kOneSamples samples, one per thread, is drawn there as well: every block does all of it
+// again, but there is a launch less.  Only the first block tells what is wrong.  Calls of one hop with each in a launch of its own /
+// settled in finish / drawn there too, 1 batch and 16 batches, microseconds:
+//   16 seeds x 15      17.1 13.8 12.7   22.4 15.0 12.8        128 x 31 (4096 records)   24.9 23.2    26.6 26.3
+//   68 x 15            17.8 14.9 13.4   22.8 15.2 14.3        512 x 7 (4096)            19.2 18.8    22.6 21.3
+//   128 x 7            16.5 13.4 12.5   22.7 14.7 13.3        1024 x 3 (4096)           19.0 19.0    22.7 22.2
+//   1024 x 1 (2048)    17.5 15.0 17.2   22.7 17.2 18.8
+constexpr int64_t kOneRecords = 4096, kOneDraw = 1280, kOneSamples = 1024;
+template <int FROM>
+struct SmallTable {
+  DedupTable<kSmallTableLg> T;
+  uint32_t entry[kOneRecords];  // per position what k_small_dedup leaves in gsrc
+};
+template <>
+struct SmallTable<kSettled> {};
+
+// The entries of a batch's hop -> A.entry; e: those of positions 4 tid .. 4 tid + 3, drawn(i): known node i.  All
+// threads call; true if a known node is there twice.
+template <int NT, typename Known, typename Table>
+__device__ __forceinline__ bool settle_in_block(Table& A, uint32_t n, uint32_t positions, const uint32_t (&e)[4], Known known) {
+  constexpr int K = static_cast<int>(kOneRecords / 2 / NT);
+  static_assert(kOneRecords <= 4 * NT && kOneRecords <= 1 << (kSmallTableLg - 1), "positions of a thread, half the table");
+  const int tid = threadIdx.x;
+  const auto home = [](uint32_t node) { return (node * kPartHash) >> (32 - kSmallTableLg); };
+  uint32_t known_slot[K], slot[4];
+  dedup_clear<NT>(A.T);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    const uint32_t i = u * NT + tid;
+    const uint32_t v = i < n ? known(i) : 0u;
+    known_slot[u] = home(v);
+    if (i < n) dedup_insert<(1u << kSmallTableLg)>(A.T, static_cast<unsigned long long>(v) << 32 | i, known_slot[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    slot[u] = home(e[u]);
+    if (e[u] != kNoSample) dedup_insert<(1u << kSmallTableLg)>(A.T, static_cast<unsigned long long>(e[u]) << 32 | (kPend | (4u * tid + u)), slot[u]);
+  }
+  __syncthreads();
+  bool twice = false;
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    const uint32_t i = u * NT + tid;
+    twice = twice || (i < n && A.T.least[known_slot[u]] != i);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const uint32_t q = 4u * tid + u;
+    if (q >= positions) continue;
+    const uint32_t least = e[u] != kNoSample ? A.T.least[slot[u]] : 0u;
+    A.entry[q] = e[u] == kNoSample || least == (kPend | q) ? e[u] : least < kPend ? (kResolved | least) : (kPointer | (least & ~kTagMask));
+  }
+  return __syncthreads_or(twice ? 1 : 0) != 0;
+}
+
 // Blocks of P.tile[h] destinations.  What follows goes on in the same block, which has the nodes in its LDS: its own
 // destinations and the new nodes among their samples.  D > 0: the draw of the next hop for them, D its fanout rounded
 // up to 8, 16 or 32.  GATHER: the last hop; their feature rows.
-template <int D, bool GATHER>
+template <int D, bool GATHER, int FROM>
 __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunch P, int h) {
   constexpr int NT = kSmallThreads;
   constexpr bool kGoesOn = D > 0 || GATHER;
@@ -268,8 +329,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   __shared__ uint32_t off[NT];                  // block offsets of the own destinations
   __shared__ unsigned long long scan[NT / 64];
   __shared__ int32_t ids[kGoesOn ? kSmallNodes : 1];  // the own destinations, then the new nodes
+  __shared__ __align__(16) SmallTable<FROM> A;
+  __shared__ typename std::conditional<(D > 0 || FROM == kSeeds), DrawLds<NT, 4 * NT>, int>::type S;
   const SmallBatch& B = P.b[small_batch(P)];
-  const int n = small_rows(P, B, h);
+  const int n = FROM == kSeeds ? B.num_seeds : small_rows(P, B, h);
   const int i0 = small_block(P) * P.tile[h];
   if (n < 0 || (i0 >= n && i0 > 0)) return;  // the first block also closes an empty hop
   const int rows = n - i0 < P.tile[h] ? n - i0 : P.tile[h];
@@ -278,33 +341,69 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   const int tid = threadIdx.x;
   const int32_t* rowk = small_rowk(B, h);
   const int32_t* gsrc = small_gsrc(B, h);
-  const uint32_t k = tid < rows ? static_cast<uint32_t>(rowk[i0 + tid]) : 0u;
-  if (kGoesOn && tid < rows) ids[tid] = B.node_ids[i0 + tid];
+  int64_t wrong = SMFG_ST_OK;
+  if constexpr (FROM == kSeeds) {
+    int stray = 0;
+    draw_positions<32, NT>(
+        P, B, 0, d, B.seeds, S, 0, n, [&] { stray = 1; },
+        [&](int i, uint32_t v, uint32_t) {
+          if (i < i0 || i >= i0 + rows) return;
+          B.node_ids[i] = static_cast<int32_t>(v);
+          if (B.labels && v < P.num_nodes) copy_label(P, B, i, static_cast<int32_t>(v));
+        });
+    uint32_t g[1];  // a sample per thread
+    read_neighbours<NT>(P, DivD(d), S, tid, positions, g);
+    A.entry[tid] = g[0];
+    if (__syncthreads_or(stray)) wrong = SMFG_ST_SEED_OUT_OF_RANGE;
+  }
+  const auto samples_of = [&](int i) {
+    if constexpr (FROM == kSeeds) return S.deg[i] < d ? S.deg[i] : d;
+    else return static_cast<uint32_t>(rowk[i]);
+  };
+  const uint32_t k = tid < rows ? samples_of(i0 + tid) : 0u;
+  if (kGoesOn && tid < rows) ids[tid] = FROM == kSeeds ? B.seeds[i0 + tid] : B.node_ids[i0 + tid];
   // samples of the destinations before the own ones, and of all
   unsigned long long sums = 0;
   for (int i = tid; i < n; i += NT) {
-    const unsigned long long x = static_cast<uint32_t>(rowk[i]);
+    const unsigned long long x = samples_of(i);
     sums += i < i0 ? (x << 32 | x) : x;
   }
-  constexpr int U = 4;
-  for (uint32_t q0 = tid * 4u; q0 < ((positions + 63u) & ~63u); q0 += NT * 4u * U) {
-    uint4 e[U];
+  // bit 31 clear: a first appearance; the four bits of 16 threads make a word
+  const auto flag = [&](uint32_t q, const uint4 e) {
+    uint32_t nibble = (~e.x >> 31) | (~e.y >> 31) << 1 | (~e.z >> 31) << 2 | (~e.w >> 31) << 3;
+    if (q + 4u > positions) nibble &= q < positions ? (1u << (positions - q)) - 1u : 0u;
+    unsigned long long bits = static_cast<unsigned long long>(nibble) << (4 * (tid & 15));
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t q = q0 + u * NT * 4u;
-      e[u] = q < positions ? *reinterpret_cast<const uint4*>(gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
+    for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, 64);
+    if ((tid & 15) == 0 && q < positions) first[q >> 6] = bits;
+  };
+  if constexpr (FROM == kSettled) {
+    constexpr int U = 4;
+    for (uint32_t q0 = tid * 4u; q0 < ((positions + 63u) & ~63u); q0 += NT * 4u * U) {
+      uint4 e[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t q = q0 + u * NT * 4u;
+        e[u] = q < positions ? *reinterpret_cast<const uint4*>(gsrc + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) flag(q0 + u * NT * 4u, e[u]);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t q = q0 + u * NT * 4u;
-      // bit 31 clear: a first appearance; the four bits of 16 threads make a word
-      uint32_t nibble = (~e[u].x >> 31) | (~e[u].y >> 31) << 1 | (~e[u].z >> 31) << 2 | (~e[u].w >> 31) << 3;
-      if (q + 4u > positions) nibble &= q < positions ? (1u << (positions - q)) - 1u : 0u;
-      unsigned long long bits = static_cast<unsigned long long>(nibble) << (4 * (tid & 15));
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, 64);
-      if ((tid & 15) == 0 && q < positions) first[q >> 6] = bits;
-    }
+  } else {
+    const uint32_t q = 4u * tid;
+    const uint4 x = q >= positions ? make_uint4(kNoSample, kNoSample, kNoSample, kNoSample)
+                    : *reinterpret_cast<const uint4*>(FROM == kSeeds ? reinterpret_cast<const int32_t*>(A.entry) + q : gsrc + q);
+    const uint32_t e[4] = {x.x, q + 1u < positions ? x.y : kNoSample, q + 2u < positions ? x.z : kNoSample, q + 3u < positions ? x.w : kNoSample};
+    int stray = 0;
+    const bool twice = settle_in_block<NT>(A, static_cast<uint32_t>(n), positions, e, [&](uint32_t i) {
+      if constexpr (FROM == kSeeds) return S.node[i];
+      const uint32_t v = static_cast<uint32_t>(B.node_ids[i]);
+      if (h == 0 && v >= P.num_nodes) stray = 1;
+      return v;
+    });
+    if (FROM == kDrawn && h == 0 && __syncthreads_or(stray)) wrong = SMFG_ST_SEED_OUT_OF_RANGE;
+    if (twice && wrong == SMFG_ST_OK) wrong = SMFG_ST_DUPLICATE_SEED;
+    flag(q, q < positions ? *reinterpret_cast<const uint4*>(A.entry + q) : make_uint4(kNoSample, kNoSample, kNoSample, kNoSample));
   }
   unsigned long long total, all;
   block_exscan<NT>(sums, scan, all);
@@ -318,14 +417,18 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   off[tid] = own;
   const bool nodes_fit = nodes <= static_cast<uint32_t>(B.node_capacity);
   const bool edges_fit = edges <= static_cast<uint32_t>(B.edge_capacity[h]);
+  if (wrong == SMFG_ST_OK) wrong = !nodes_fit ? SMFG_ST_NODE_CAPACITY : !edges_fit ? SMFG_ST_EDGE_CAPACITY : SMFG_ST_OK;
   if (tid == 0 && i0 == 0) {
-    B.counts[P.L + 1 + h] = edges;
-    B.counts[h + 1] = nodes;
-    if (!nodes_fit) set_status(B, P.L, SMFG_ST_NODE_CAPACITY);
-    else if (!edges_fit) set_status(B, P.L, SMFG_ST_EDGE_CAPACITY);
-    else B.blk_indptr[h][n] = static_cast<int32_t>(edges);
+    if constexpr (FROM == kSeeds) {  // starts the counts
+      for (int q = 0; q < 2 * P.L + 2; ++q) B.counts[q] = q == 0 ? n : q == 1 ? nodes : q == P.L + 1 ? edges : q == 2 * P.L + 1 ? wrong : 0;
+    } else {
+      B.counts[P.L + 1 + h] = edges;
+      B.counts[h + 1] = nodes;
+      if (wrong != SMFG_ST_OK) set_status(B, P.L, wrong);
+    }
+    if (wrong == SMFG_ST_OK) B.blk_indptr[h][n] = static_cast<int32_t>(edges);
   }
-  if (!nodes_fit || !edges_fit) return;
+  if (wrong != SMFG_ST_OK) return;
   if (tid < rows) B.blk_indptr[h][i0 + tid] = static_cast<int32_t>(own);
   __syncthreads();
   const DivD div(d);
@@ -334,7 +437,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   const auto id_of = [&](uint32_t q) { return before[q >> 6] + static_cast<uint32_t>(__popcll(first[q >> 6] & ((1ull << (q & 63u)) - 1ull))); };
   const uint32_t first_new = own_cnt > 0u ? id_of(pos0) : 0u;
   for (uint32_t idx = tid; idx < own_cnt; idx += NT) {
-    const uint32_t e = static_cast<uint32_t>(gsrc[pos0 + idx]);
+    uint32_t e;
+    if constexpr (FROM == kSettled) e = static_cast<uint32_t>(gsrc[pos0 + idx]);
+    else e = A.entry[pos0 + idx];
     if (e == kNoSample) continue;
     uint32_t r, s, local;
     div.split(idx, r, s);
@@ -357,7 +462,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
     const int known = rows, count = rows + static_cast<int>(after - first_new);
     const auto index_of = [&](int j) { return j < known ? i0 + j : static_cast<int>(first_new) + j - known; };
     if constexpr (D > 0) {
-      __shared__ DrawLds<NT, 4 * NT> S;
       const uint32_t next_d = static_cast<uint32_t>(P.fanouts[h + 1]);
       int32_t* next_gsrc = small_gsrc(B, h + 1);
       int32_t* next_rowk = small_rowk(B, h + 1);

@@ -39,6 +39,7 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 
@@ -92,10 +93,11 @@ struct Profiler {
 struct StageTimer {
   int rec = -1;
   hipStream_t st;
-  // also: another stage that the launch does the work of; it is counted there, without a time
-  StageTimer(int stage, hipStream_t s, int also = -1) : st(s) {
+  // also: other stages that the launch does the work of; it is counted there, without a time
+  StageTimer(int stage, hipStream_t s, std::initializer_list<int> also = {}) : st(s) {
     if (g_prof.level == 0) return;
-    if (also >= 0 && (g_prof.level == 2 || also == SMFG_STAGE_GATHER)) g_prof.also[also].fetch_add(1, std::memory_order_relaxed);
+    for (const int a : also)
+      if (a >= 0 && (g_prof.level == 2 || a == SMFG_STAGE_GATHER)) g_prof.also[a].fetch_add(1, std::memory_order_relaxed);
     if (g_prof.level == 1 && stage != SMFG_STAGE_GATHER) return;
     const int r = g_prof.used.fetch_add(1, std::memory_order_relaxed);
     if (r >= g_prof.max_records) return;
@@ -619,23 +621,30 @@ SmallLaunch small_launch(const Launch& P, const smfg_workspace* const* ws, const
 constexpr int64_t kSmallGather = 4 << 20;
 bool small_gather(int64_t row_bytes, int64_t max_nodes) { return row_bytes >= 16 && max_nodes * row_bytes <= kSmallGather; }
 // The first `hops` hops; `gather`: the last of them, which is the call's, copies the feature rows.
+template <int FROM>
+void launch_small_finish(const SmallLaunch& S, int h, int next_d, bool gather, unsigned blocks, hipStream_t st) {
+  (next_d > 16 ? k_small_finish<32, false, FROM> : next_d > 8 ? k_small_finish<16, false, FROM> : next_d > 0 ? k_small_finish<8, false, FROM>
+   : gather ? k_small_finish<0, true, FROM> : k_small_finish<0, false, FROM>)<<<blocks, kSmallThreads, 0, st>>>(S, h);
+}
 void launch_small_hops(const SmallLaunch& S, int hops, const int64_t* max_rows, bool gather, hipStream_t st) {
   const unsigned G = static_cast<unsigned>(S.G);
-  {
-    StageTimer t_(SMFG_STAGE_SAMPLE, st);
-    const int d = S.fanouts[0];
-    (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks_for(max_rows[0], S.rows, 0xFFFFFFu) * G, kThreads, 0, st>>>(S);
-  }
   for (int h = 0; h < hops; ++h) {
-    {
+    const int d = S.fanouts[h], next_d = h + 1 < hops ? S.fanouts[h + 1] : 0;
+    const bool one = max_rows[h] * (1 + d) <= kOneRecords, draws = h == 0 && max_rows[h] * (1 + d) <= kOneDraw && max_rows[h] * d <= kOneSamples;
+    if (h == 0 && !draws) {
+      StageTimer t_(SMFG_STAGE_SAMPLE, st);
+      (d <= 8 ? k_small_draw<8> : d <= 16 ? k_small_draw<16> : k_small_draw<32>)<<<blocks_for(max_rows[0], S.rows, 0xFFFFFFu) * G, kThreads, 0, st>>>(S);
+    }
+    if (!one) {
       StageTimer t_(SMFG_STAGE_DEDUP, st);
       k_small_dedup<<<G << kSmallLgB, kSmallThreads, 0, st>>>(S, h);
     }
-    StageTimer t_(SMFG_STAGE_ASSEMBLE, st, h + 1 < hops ? SMFG_STAGE_SAMPLE : gather ? SMFG_STAGE_GATHER : -1);
+    StageTimer t_(SMFG_STAGE_ASSEMBLE, st,
+                  {draws ? SMFG_STAGE_SAMPLE : -1, one ? SMFG_STAGE_DEDUP : -1, next_d > 0 ? SMFG_STAGE_SAMPLE : gather && h + 1 == hops ? SMFG_STAGE_GATHER : -1});
     const unsigned blocks = blocks_for(max_rows[h], S.tile[h], 0xFFFFFFu) * G;
-    const int d = h + 1 < hops ? S.fanouts[h + 1] : 0;
-    (d > 16 ? k_small_finish<32, false> : d > 8 ? k_small_finish<16, false> : d > 0 ? k_small_finish<8, false>
-     : gather ? k_small_finish<0, true> : k_small_finish<0, false>)<<<blocks, kSmallThreads, 0, st>>>(S, h);
+    if (draws) launch_small_finish<kSeeds>(S, h, next_d, gather, blocks, st);
+    else if (one) launch_small_finish<kDrawn>(S, h, next_d, gather, blocks, st);
+    else launch_small_finish<kSettled>(S, h, next_d, gather, blocks, st);
   }
 }
 
@@ -1083,7 +1092,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
     if (part && !wide) {
       P.block_rows = plan[h].block_rows;
       {
-        StageTimer t_(SMFG_STAGE_SAMPLE, st, SMFG_STAGE_PARTITION);
+        StageTimer t_(SMFG_STAGE_SAMPLE, st, {SMFG_STAGE_PARTITION});
         launch_sample_part(P, plan[h], G, st);
       }
       if (P.lg > kPartMaxLgB) {
@@ -1117,7 +1126,7 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       // with up to 8192 blocks per batch, 85 with as many in all.
       const unsigned wave_blocks = blocks_for(rows, kThreads / 64, 2 * kCap / G > 1024u ? 2 * kCap / G : 1024u);
       if (part && h == 0) {
-        StageTimer t_(SMFG_STAGE_SEEDS, st, SMFG_STAGE_SCAN_TILES);
+        StageTimer t_(SMFG_STAGE_SEEDS, st, {SMFG_STAGE_SCAN_TILES});
         k_count_rows<true><<<tile_blocks * G, kThreads, 0, st>>>(P);
       } else {
         StageTimer t_(SMFG_STAGE_SCAN_TILES, st);

@@ -195,6 +195,41 @@ def test_wide_first_hop_that_does_not_fit(room, stray, status, monkeypatch):
     assert (out.indices[0][min(capacity, edges):] == -7).all()
 
 
+@pytest.mark.parametrize("fanouts,seeds", [((15,), 68), ((15,), 69), ((1,), 640), ((1,), 641), ((4, 2), 256), ((4, 2), 257), ((31,), 33), ((31,), 34),
+                                           ((1,), 2048), ((1,), 2049), ((31, 1), 128), ((31, 1), 129), ((3,), 1024), ((32, 3, 1), 1), ((7, 7), 0)])
+def test_small_hops_settled_in_one_launch(fanouts, seeds):
+    """First hops on both sides of 1280 records, 1024 samples and 4096 records, and hops behind them, one batch and several."""
+    gg = random_graph(3_000, 40, 5, dim=9)
+    keys = [3, 4, 5]
+    s = [np.random.default_rng(k).permutation(3_000)[:n].astype(np.int32) for k, n in zip(keys, [seeds, (seeds + 1) // 2, min(seeds, 1)])]
+    ws = [smfg.workspace_create(gg.g, len(x), fanouts) for x in s]
+    outs = [smfg.alloc_output(gg.g, max(len(x), 1), fanouts) for x in s]
+    for count in (1, 3):
+        smfg.sample_mfg_many(gg.g, ws[:count], [torch.from_numpy(x).to(DEV) for x in s[:count]], fanouts, keys[:count], outs[:count])
+        for x, key, out in list(zip(s, keys, outs))[:count]:
+            assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(x, fanouts, key), len(fanouts))
+
+
+@pytest.mark.parametrize("seeds", [40, 200])
+def test_small_hops_settled_in_one_launch_that_fail(seeds):
+    """Repeated and stray seeds and outputs too small, of first hops drawn in the same launch or before; the batches beside them and
+    the next call do not notice."""
+    gg = random_graph(5_000, 30, 8, dim=5)
+    fan, perm = (10, 5), np.random.default_rng(4).permutation(5_000).astype(np.int32)
+    s = [perm[i * 200:i * 200 + seeds].copy() for i in range(6)]
+    s[1][seeds - 1] = s[1][0]
+    s[2][seeds // 2], s[3][0] = 5_000, -1
+    outs = [smfg.alloc_output(gg.g, seeds, fan) for _ in s]
+    outs[4] = smfg.alloc_output(gg.g, seeds, fan, node_capacity=seeds + 1)
+    outs[5] = smfg.alloc_output(gg.g, seeds, fan, edge_capacity=[seeds, 100_000])
+    ws = [smfg.workspace_create(gg.g, seeds, fan) for _ in s]
+    for _ in range(2):
+        smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(x).to(DEV) for x in s], fan, range(6), outs)
+        assert_same(fetch(outs[0], 2), gg.oracle.sample_mfg(s[0], fan, 0), 2)
+        assert [fetch(o, 2)["status"] for o in outs[1:]] == [smfg.ST_DUPLICATE_SEED, smfg.ST_SEED_OUT_OF_RANGE, smfg.ST_SEED_OUT_OF_RANGE,
+                                                            smfg.ST_NODE_CAPACITY, smfg.ST_EDGE_CAPACITY]
+
+
 @pytest.mark.parametrize("level", [1, 2])
 @pytest.mark.parametrize("dim,folded", [(32, True), (3, False)])
 def test_a_gather_without_a_launch_has_no_time(dim, folded, level):
