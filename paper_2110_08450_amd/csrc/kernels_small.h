@@ -217,7 +217,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
   const uint32_t positions = cnt - n;
   int32_t* gsrc = small_gsrc(B, h);
   // a turn: K known nodes and 4 U positions per thread, every read on its way before the first is used
-  // (the entries are padded to whole 256 bytes); a thread reserves room for all it found at once
+  // (the entries are padded to whole 256 bytes); a wave reserves room for all it found at once (a thread each, 16 waves of 64 atomics
+  // on one word: 256 seeds x 10 and then x 5 8.5 -> 7.0 us, 1024 x 15 9.8 -> 7.7)
   constexpr int K = 4, U = 4;
   for (uint32_t c = 0; c * NT * K < n || c * NT * 4u * U < positions; ++c) {
     uint32_t e[K + 4 * U];
@@ -236,8 +237,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dedup(const SmallLaunch
       const bool there = t < K || q0 + static_cast<uint32_t>((t - K) / 4) * NT * 4u + static_cast<uint32_t>((t - K) % 4) < positions;
       found |= (there && wanted(e[t]) ? 1u : 0u) << t;
     }
-    if (found == 0u) continue;
-    uint32_t at = atomicAdd(&listed, static_cast<uint32_t>(__popc(found)));
+    const uint32_t own = static_cast<uint32_t>(__popc(found)), upto = wave_inscan(own);
+    uint32_t at = 0;
+    if ((threadIdx.x & 63u) == 63u) at = atomicAdd(&listed, upto);
+    at = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(at), 63)) + upto - own;
 #pragma unroll
     for (int t = 0; t < K + 4 * U; ++t)
       if (found >> t & 1u) {
