@@ -664,17 +664,18 @@ void launch_dedup(const Launch& P, unsigned G, hipStream_t st) {
 // LDS for the bucket counts and offsets of a segment.
 size_t offsets_lds_bytes(int lgB) { return offs_stride(lgB) * sizeof(uint16_t); }
 
-template <int PER>
+template <int PER, int NT>
 void launch_sample_part_of(const Launch& P, unsigned blocks, hipStream_t st) {
   const size_t lds = offsets_lds_bytes(P.lgB);
-  if (P.d <= 8) k_sample_part<8, PER><<<blocks, kThreads, lds, st>>>(P);
-  else if (P.d <= 16) k_sample_part<16, PER><<<blocks, kThreads, lds, st>>>(P);
-  else k_sample_part<32, PER><<<blocks, kThreads, lds, st>>>(P);
+  if (P.d <= 8) k_sample_part<8, PER, NT><<<blocks, NT, lds, st>>>(P);
+  else if (P.d <= 16) k_sample_part<16, PER, NT><<<blocks, NT, lds, st>>>(P);
+  else k_sample_part<32, PER, NT><<<blocks, NT, lds, st>>>(P);
 }
 void launch_sample_part(const Launch& P, const HopPlan& hp, unsigned G, hipStream_t st) {
   const unsigned blocks = static_cast<unsigned>(hp.row_blocks) * G;
-  if (hp.per == 8) launch_sample_part_of<8>(P, blocks, st);
-  else launch_sample_part_of<16>(P, blocks, st);
+  if (hp.per == 8) launch_sample_part_of<8, kThreads>(P, blocks, st);
+  else if (blocks <= kPartWideBlocks) launch_sample_part_of<8, kPartWideThreads>(P, blocks, st);
+  else launch_sample_part_of<16, kThreads>(P, blocks, st);
 }
 
 // The gather launch shared by smfg_sample_mfg_many and smfg_gather_many.  Vectors of 4 bytes and less only
