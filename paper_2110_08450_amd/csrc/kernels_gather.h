@@ -101,12 +101,18 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // row and the beginning of the next instead of overlapping took 109 us for the 602-byte rows.
 struct AnyRow {};
 
+// The id of the thread's row of the block, if the array has as many.
+template <int ROWS>
+__device__ __forceinline__ int32_t row_id(const int32_t* __restrict__ ids, int64_t size) {
+  const int64_t r = static_cast<int64_t>(blockIdx.x) * ROWS + threadIdx.x;
+  return threadIdx.x < ROWS && r < size ? ids[r] : 0;
+}
 template <typename V, int ROWS>
 __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, int64_t row_stride,
                                             int64_t row_bytes, int64_t num_nodes,
-                                            const int32_t* __restrict__ ids, int64_t n,
+                                            int32_t own, int64_t n,
                                             uint8_t* __restrict__ out) {
-  static_assert(ROWS <= kThreads, "a thread per row fetches its id");
+  static_assert(ROWS <= kThreads, "a thread per row has its id");
   constexpr bool kAny = __is_same(V, AnyRow);
   using W = typename std::conditional<kAny, u32x4, V>::type;
   using Index = typename std::conditional<ROWS == 1, uint64_t, uint32_t>::type;
@@ -117,7 +123,7 @@ __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, in
   const uint32_t rows = static_cast<uint32_t>(n - r0 < ROWS ? n - r0 : ROWS);
   const Index cnt = rows * vec_per_row;
   if (threadIdx.x < ROWS) {
-    int64_t id = threadIdx.x < rows ? ids[r0 + threadIdx.x] : 0;
+    int64_t id = threadIdx.x < rows ? own : 0;
     if (id < 0 || id >= num_nodes) id = 0;
     row_byte[threadIdx.x] = id * row_stride;
   }
@@ -156,10 +162,13 @@ __device__ __forceinline__ void gather_rows(const uint8_t* __restrict__ feat, in
 template <typename V, int ROWS>
 __global__ void __launch_bounds__(kThreads) k_gather(const Launch P) {
   const BatchCtx& B = P.b[blockIdx.y];
-  if (B.features == nullptr || status_of(B, P.L) != 0) return;
+  // The number of rows, the status and the ids, as far as the array goes, on their way together: a block is four reads that
+  // wait for each other otherwise, and two so.
   int64_t n = B.counts[P.L];
+  const int32_t own = row_id<ROWS>(B.node_ids, B.node_capacity);
+  if (B.features == nullptr || status_of(B, P.L) != 0) return;
   if (n > B.node_capacity) n = B.node_capacity;
-  gather_rows<V, ROWS>(P.feat, P.row_stride, P.row_bytes, P.num_nodes, B.node_ids, n, B.features);
+  gather_rows<V, ROWS>(P.feat, P.row_stride, P.row_bytes, P.num_nodes, own, n, B.features);
 }
 
 template <typename V, int ROWS>
@@ -170,7 +179,8 @@ __global__ void __launch_bounds__(kThreads) k_gather_plain(const uint8_t* feat, 
   int64_t n = *num_rows;
   if (n > max_rows) n = max_rows;
   if (n < 0) n = 0;
-  gather_rows<V, ROWS>(feat, row_stride, row_bytes, num_nodes, ids, n, out);
+  const int32_t own = row_id<ROWS>(ids, n);  // there need not be more
+  gather_rows<V, ROWS>(feat, row_stride, row_bytes, num_nodes, own, n, out);
 }
 
 }  // namespace smfg_dev

@@ -91,8 +91,7 @@ __host__ __device__ inline HopShape hop_levels(long long records, int batches, i
 }
 // Records: known nodes and sample positions, or samples where their number is known (P.flat); both are
 // final before the first kernel that asks.
-__device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B) {
-  const long long n = B.counts[P.h];
+__device__ __forceinline__ HopShape hop_shape(const Launch& P, const BatchCtx& B, long long n) {
   return hop_levels(P.flat ? n + B.counts[P.L + 1 + P.h] : n * (1 + P.d), P.G, P.lg, B.one_level);
 }
 
@@ -126,8 +125,7 @@ __host__ __device__ inline uint32_t flat_seg(uint32_t batches, uint32_t records)
 struct Segments {
   uint32_t count, cap;
 };
-__device__ __forceinline__ Segments hop_segments(const Launch& P, const BatchCtx& B) {
-  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
+__device__ __forceinline__ Segments hop_segments(const Launch& P, const BatchCtx& B, uint32_t n) {
   Segments s;
   if (P.flat) {
     const uint32_t records = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
@@ -252,13 +250,13 @@ __global__ void __launch_bounds__(NT) k_sample_part(const Launch P) {
   extern __shared__ uint32_t cnt[];  // offs_stride / 2 words
   const BatchCtx& B = P.b[batch_of_block(P)];
   const int blk = block_in_batch(P);
+  const int n = static_cast<int>(B.counts[P.h]);  // on its way with the status
   if (block_has_status(B, P.L)) return;
-  const int n = static_cast<int>(B.counts[P.h]);
   const int r0 = blk * P.block_rows;
   if (r0 >= n) return;
   const int rows = n - r0 < P.block_rows ? n - r0 : P.block_rows;
   const uint32_t d = static_cast<uint32_t>(P.d);
-  const int lgB = hop_shape(P, B).lgB;
+  const int lgB = hop_shape(P, B, n).lgB;
   for (uint32_t b = threadIdx.x; b < offs_stride(lgB) / 2u; b += NT) cnt[b] = 0u;
   draw_positions<D, NT>(
       P, B, P.h, d, B.node_ids, S.draw, r0, rows, [&] { set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE); },
@@ -323,10 +321,11 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_buckets(const Launch P)
   } S;
   __shared__ uint32_t cnt[(1 << kPartMaxLg2) + 1], scan[NT / 64];
   const BatchCtx& B = P.b[batch_of_block(P)];
+  const int64_t n = B.counts[P.h];  // on its way with the status
   if (block_has_status(B, P.L)) return;
-  const HopShape hs = hop_shape(P, B);
+  const HopShape hs = hop_shape(P, B, n);
   if (hs.lg2 == 0) return;
-  const Segments segs = hop_segments(P, B);
+  const Segments segs = hop_segments(P, B, static_cast<uint32_t>(n));
   const uint32_t nB = 1u << hs.lgB, n2 = 1u << hs.lg2, stride = offs_stride(hs.lgB);
   const uint32_t range = split_range(segs.cap, hs.lgB);
   const uint32_t ranges = (segs.count + range - 1u) / range;
@@ -596,9 +595,10 @@ __global__ void __launch_bounds__(kThreads, LARGE ? 7 : 8) k_dedup_buckets(const
   __shared__ uint32_t scan[kThreads / 64];
   __shared__ int overflow_lds;
   const BatchCtx& B = P.b[batch_of_block(P)];
+  const int64_t n = B.counts[P.h];  // on its way with the status
   if (block_has_status(B, P.L)) return;
-  const HopShape hs = hop_shape(P, B);
-  const Segments segs = hop_segments(P, B);
+  const HopShape hs = hop_shape(P, B, n);
+  const Segments segs = hop_segments(P, B, static_cast<uint32_t>(n));
   const bool two = LARGE && hs.lg2 != 0;
   const uint32_t nB = 1u << hs.lgB, n2 = 1u << hs.lg2, all = nB << hs.lg2, stride = offs_stride(hs.lgB);
   const uint32_t range = split_range(segs.cap, hs.lgB), parts = two ? (segs.count + range - 1u) / range : segs.count;
@@ -629,9 +629,9 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
   __shared__ unsigned long long lds[kThreads / 64];
   __shared__ unsigned long long bits[kTileRows * SMFG_MAX_FANOUT / 64 + 1];  // of the tile's positions
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
   const int nblocks = blocks_per_batch(P);
-  const int n = static_cast<int>(B.counts[P.h]);
+  const int n = static_cast<int>(B.counts[P.h]);  // on its way with the status
+  if (block_has_status(B, P.L)) return;
   const uint32_t d = static_cast<uint32_t>(P.d);
   const int tiles = (n + kTileRows - 1) / kTileRows;
   for (int tile = block_in_batch(P); tile < tiles; tile += nblocks) {
@@ -689,8 +689,8 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
   // per destination: samples, first-appearance bits, block offset, local id of the first new node
   __shared__ uint4 row_lds[kTileRows];
   const BatchCtx& B = P.b[batch_of_block(P)];
+  const int n = static_cast<int>(B.counts[P.h]);  // on its way with the status
   if (block_has_status(B, P.L)) return;
-  const int n = static_cast<int>(B.counts[P.h]);
   const uint32_t d = static_cast<uint32_t>(P.d);
   const DivD div(d);
   const double inv_d = 1.0 / static_cast<double>(d);

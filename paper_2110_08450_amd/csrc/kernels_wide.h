@@ -40,8 +40,8 @@ template <bool BEGIN>
 __global__ void __launch_bounds__(kThreads) k_count_rows(const Launch P) {
   __shared__ unsigned long long lds[kThreads / 64];
   const BatchCtx& B = P.b[batch_of_block(P)];
+  const int n = BEGIN ? B.num_seeds : static_cast<int>(B.counts[P.h]);  // on its way with the status
   if (BEGIN ? false : block_has_status(B, P.L)) return;
-  const int n = BEGIN ? B.num_seeds : static_cast<int>(B.counts[P.h]);
   if (BEGIN && block_in_batch(P) == 0) begin_counts(P, B);
   const bool rows = !BEGIN || n <= P.num_nodes;
   const int d = P.d;
@@ -364,11 +364,11 @@ __global__ void __launch_bounds__(kFlatThreads) k_part_flat(const Launch P) {
   __shared__ uint32_t scan[NT / 64];
   extern __shared__ uint32_t cnt[];  // offs_stride / 2 words
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
+  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);  // both on their way with the status
   const uint32_t total_e = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-  const int lgB = hop_shape(P, B).lgB;
-  const Segments segs = hop_segments(P, B);
+  if (block_has_status(B, P.L)) return;
+  const int lgB = hop_shape(P, B, n).lgB;
+  const Segments segs = hop_segments(P, B, n);
   for (uint32_t seg = static_cast<uint32_t>(block_in_batch(P)); seg < segs.count; seg += static_cast<uint32_t>(blocks_per_batch(P))) {
     const uint32_t e0 = seg * segs.cap;
     const uint32_t e1 = total_e - e0 < segs.cap ? total_e : e0 + segs.cap;
@@ -416,8 +416,8 @@ __global__ void __launch_bounds__(kThreads) k_flag_flat_part(const Launch P) {
   constexpr int kWaves = kThreads / 64;
   __shared__ uint32_t lds[2][kWaves];
   const BatchCtx& B = P.b[batch_of_block(P)];
+  const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);  // on its way with the status
   if (block_has_status(B, P.L)) return;
-  const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
   const uint32_t lg = flat_tile_lg(E), tiles = (E + (1u << lg) - 1u) >> lg;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int turn = 0;  // a wave writes the next sums while others may still read the present ones
@@ -481,9 +481,9 @@ __global__ void __launch_bounds__(kThreads) k_assemble_flat_part(const Launch P)
   __shared__ uint32_t tile_new[kFlatTiles];  // new nodes of the tiles before
   __shared__ uint32_t scan[kThreads / 64];
   const BatchCtx& B = P.b[batch_of_block(P)];
-  if (block_has_status(B, P.L)) return;
-  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);
+  const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);  // both on their way with the status
   const uint32_t E = static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
+  if (block_has_status(B, P.L)) return;
   const uint32_t lg = flat_tile_lg(E), tiles = (E + (1u << lg) - 1u) >> lg, chunks = (E + kWideTile - 1) / kWideTile;
   clear_supers(P, B);
   if (static_cast<uint32_t>(block_in_batch(P)) >= (chunks > 0u ? chunks : 1u)) return;  // the first block also closes an empty hop
