@@ -72,6 +72,7 @@ struct Launch {
   int32_t lgB;     // partition path: log2 of the most hash buckets that any batch starts this hop with
   int32_t lg;      // partition path: log2 of the most buckets, or sub-buckets in all (see hop_shape)
   int32_t block_rows;  // partition path: destinations per segment of this hop
+  int32_t parts;   // partition path: blocks that share a tile in assemble
   int32_t flat;    // partition path over exact offsets: the hop's number of samples is known
   BatchCtx b[SMFG_MAX_BATCHES];
 };

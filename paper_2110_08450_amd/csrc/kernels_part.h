@@ -620,11 +620,30 @@ __global__ void __launch_bounds__(kThreads, LARGE ? 7 : 8) k_dedup_buckets(const
   }
 }
 
+// A tile's destinations and, a turn ahead of their use, its entries: flag_rows asks for a tile's first entries together with
+// the samples of its destinations, and for the others before it looks at those before them.  29 M positions 42.6 -> 25.1 us, 77 K
+// destinations x 20 10.2 -> 5.9, 11 K x 10 6.4 -> 4.3.  The same in assemble costs it registers: 24 -> 28 us for 1.2 M x 5.
+struct Tile {
+  int i0, rows;         // its first destination, and how many there are
+  uint32_t pos0, cnt;   // the same of its positions
+  __device__ __forceinline__ Tile(int tile, int n, uint32_t d)
+      : i0(tile * kTileRows), rows(n - i0 < kTileRows ? n - i0 : kTileRows), pos0(static_cast<uint32_t>(i0) * d),
+        cnt(rows > 0 ? static_cast<uint32_t>(rows) * d : 0u) {}
+};
+template <int U>
+struct TileEntries {
+  uint32_t e[U];  // of positions at, at + kThreads, ... of a tile
+  __device__ __forceinline__ void fetch(const BatchCtx& B, const Tile& t, uint32_t at) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = at + u * kThreads < t.cnt ? static_cast<uint32_t>(B.gsrc[t.pos0 + at + u * kThreads]) : kResolved;
+  }
+};
+
 // flag_rows for the entries dedup_buckets leaves: a valid sample whose entry still is a node id
 // (bit 31 clear) is a first appearance.  Per destination: bit mask of its first appearances; in-tile
 // exclusive scan of (samples, new nodes); per-tile totals.  Streaming: a wave's ballot is the bits of 64 positions,
 // from which each destination then takes its own.  With an LDS atomicOr per first appearance, 20 consecutive
-// ones of which hit one word, 29 M positions took 54 us; 43 so, 2.8 TB/s of entries.
+// ones of which hit one word, 29 M positions took 54 us; 43 so, and 25, 4.7 TB/s of entries, with the entries a turn ahead.
 __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
   __shared__ unsigned long long lds[kThreads / 64];
   __shared__ unsigned long long bits[kTileRows * SMFG_MAX_FANOUT / 64 + 1];  // of the tile's positions
@@ -634,28 +653,30 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
   if (block_has_status(B, P.L)) return;
   const uint32_t d = static_cast<uint32_t>(P.d);
   const int tiles = (n + kTileRows - 1) / kTileRows;
+  if (block_in_batch(P) >= tiles) return;
+  const int tr = threadIdx.x;
+  constexpr int U = 4;
+  TileEntries<U> ahead;
+  int next_k = 0;
+  const auto ask = [&](const Tile& t) {
+    ahead.fetch(B, t, tr);
+    next_k = tr < t.rows ? B.rowk[t.i0 + tr] : 0;
+  };
+  ask(Tile(block_in_batch(P), n, d));
   for (int tile = block_in_batch(P); tile < tiles; tile += nblocks) {
-    const int i0 = tile * kTileRows;
-    const int nrows = n - i0 < kTileRows ? n - i0 : kTileRows;
-    const int tr = threadIdx.x;
-    const int k = tr < nrows ? B.rowk[i0 + tr] : 0;
-    const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
-    const uint32_t cnt = static_cast<uint32_t>(nrows) * d;
+    const Tile t(tile, n, d);
+    const int k = next_k;
     __syncthreads();  // the previous tile's bits have been read
-    constexpr int U = 4;
-    for (uint32_t base = tr & ~63; base < cnt; base += kThreads * U) {  // whole waves
-      uint32_t e[U];
+    for (uint32_t base = tr & ~63; base < t.cnt; base += kThreads * U) {  // whole waves
+      const TileEntries<U> here = ahead;
+      ahead.fetch(B, t, base + kThreads * U + (tr & 63));
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint32_t idx = base + u * kThreads + (tr & 63);
-        e[u] = idx < cnt ? static_cast<uint32_t>(B.gsrc[pos0 + idx]) : kResolved;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const unsigned long long b = __ballot((e[u] & kResolved) == 0u);
-        if ((tr & 63) == 0 && base + u * kThreads < cnt) bits[(base + u * kThreads) >> 6] = b;
+        const unsigned long long b = __ballot((here.e[u] & kResolved) == 0u);
+        if ((tr & 63) == 0 && base + u * kThreads < t.cnt) bits[(base + u * kThreads) >> 6] = b;
       }
     }
+    if (tile + nblocks < tiles) ask(Tile(tile + nblocks, n, d));
     __syncthreads();
     uint32_t m = 0u;
     if (k > 0) {
@@ -667,9 +688,9 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
     const unsigned long long x = (static_cast<unsigned long long>(k) << 32) | static_cast<unsigned long long>(__popc(m));
     unsigned long long total;
     const unsigned long long pre = block_exscan(x, lds, total);
-    if (tr < nrows) {
-      B.rowmn[i0 + tr] = make_uint2(m, static_cast<uint32_t>(pre & 0xFFFFFFFFull));
-      B.rowoff[i0 + tr] = static_cast<int32_t>(pre >> 32);
+    if (tr < t.rows) {
+      B.rowmn[t.i0 + tr] = make_uint2(m, static_cast<uint32_t>(pre & 0xFFFFFFFFull));
+      B.rowoff[t.i0 + tr] = static_cast<int32_t>(pre >> 32);
     }
     if (tr == 0) B.tile_sums[tile] = total;
   }
@@ -679,9 +700,11 @@ __global__ void __launch_bounds__(kThreads) k_flag_rows_part(const Launch P) {
 // first appearances.  A pointer always names a first appearance, so one lookup of that
 // destination's record settles it.  SCAN (hops of at most kAssembleTiles tiles, one per block): every block
 // scans the tile totals for itself, a few kilobytes from the L2, instead of k_scan_tiles before it -
-// 3 to 5 us of a launch that does nothing else, for less than 1 us here.
+// 3 to 5 us of a launch that does nothing else, for less than 1 us here.  Where that leaves compute units idle (SHARED), P.parts blocks share a
+// tile, a run of kThreads U positions each in turn: 11 K destinations x 10 8.6 -> 5.9 us, 77 K x 20 14.1 -> 12.1, 4 K x 20 10.5 -> 6.1.
+// In a variant of its own: the one more count costs the other an eighth of its waves (1.2 M destinations x 5 24 -> 26 us).
 constexpr int kAssembleTiles = 1024;
-template <bool SCAN>
+template <bool SCAN, bool SHARED>
 __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
   constexpr int kPer = kAssembleTiles / kThreads;
   __shared__ uint32_t tile_new[SCAN ? kAssembleTiles : 1];  // new nodes before each tile
@@ -696,8 +719,10 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
   const double inv_d = 1.0 / static_cast<double>(d);
   const int tiles = (n + kTileRows - 1) / kTileRows;
   const int nblocks = blocks_per_batch(P);
+  constexpr int U = 4;
+  const int parts = SHARED ? P.parts : 1, own = block_in_batch(P) / parts, part = block_in_batch(P) - own * parts;
   if (SCAN) {
-    if (block_in_batch(P) >= (tiles > 0 ? tiles : 1)) return;  // the first block also closes an empty hop
+    if (own >= (tiles > 0 ? tiles : 1)) return;  // the first block also closes an empty hop
     unsigned long long x[kPer], mine = 0, total;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -710,14 +735,14 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
     for (int u = 0; u < kPer; ++u) {
       const int t = threadIdx.x * kPer + u;
       tile_new[t] = static_cast<uint32_t>(pre);
-      if (t == block_in_batch(P)) own_lds = pre;
+      if (t == own) own_lds = pre;
       pre += x[u];
     }
     if (!close_hop(P, B, n, total, block_in_batch(P) == 0 && threadIdx.x == 0)) return;
     __syncthreads();
   }
   const auto tile_before = [&](uint32_t t) { return SCAN ? tile_new[t] : static_cast<uint32_t>(B.tile_sums[t] & 0xFFFFFFFFull); };
-  for (int tile = block_in_batch(P); tile < tiles; tile += nblocks) {
+  for (int tile = own; tile < tiles; tile += nblocks) {
     const int i0 = tile * kTileRows;
     const int nrows = n - i0 < kTileRows ? n - i0 : kTileRows;
     const int tr = threadIdx.x;
@@ -728,13 +753,12 @@ __global__ void __launch_bounds__(kThreads) k_assemble_part(const Launch P) {
       const uint2 mn = B.rowmn[i0 + tr];
       row_lds[tr] = make_uint4(static_cast<uint32_t>(B.rowk[i0 + tr]), mn.x, off,
                                static_cast<uint32_t>(n) + static_cast<uint32_t>(tpre & 0xFFFFFFFFull) + mn.y);
-      B.blk_indptr[i0 + tr] = static_cast<int32_t>(off);
+      if (part == 0) B.blk_indptr[i0 + tr] = static_cast<int32_t>(off);
     }
     __syncthreads();
     const uint32_t pos0 = static_cast<uint32_t>(i0) * d;
     const uint32_t cnt = static_cast<uint32_t>(nrows) * d;
-    constexpr int U = 4;
-    for (uint32_t base = threadIdx.x; base < cnt; base += kThreads * U) {
+    for (uint32_t base = static_cast<uint32_t>(part * kThreads * U) + threadIdx.x; base < cnt; base += parts * kThreads * U) {
       uint32_t e[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {

@@ -661,6 +661,14 @@ void launch_dedup(const Launch& P, unsigned G, hipStream_t st) {
   else k_dedup_buckets<false><<<blocks, kThreads, 0, st>>>(P);
 }
 
+// Blocks that share a tile of k_assemble_part: up to a turn of its positions each, while there are 1024 of them at most, half of what the
+// chip holds.
+int assemble_parts(int d, unsigned tiles) {
+  int parts = 1;
+  while (parts * 4 < d && tiles * parts * 2 <= 1024u) parts *= 2;
+  return parts;
+}
+
 // LDS for the bucket counts and offsets of a segment.
 size_t offsets_lds_bytes(int lgB) { return offs_stride(lgB) * sizeof(uint16_t); }
 
@@ -1115,8 +1123,10 @@ static int sample_many(const smfg_graph_t* g, smfg_workspace_t* const* ws, const
       }
       {
         StageTimer t_(SMFG_STAGE_ASSEMBLE, st);
-        if (scans) k_assemble_part<true><<<tile_blocks * G, kThreads, 0, st>>>(P);
-        else k_assemble_part<false><<<tile_blocks * G, kThreads, 0, st>>>(P);
+        P.parts = scans ? assemble_parts(P.d, tile_blocks * G) : 1;
+        if (P.parts > 1) k_assemble_part<true, true><<<tile_blocks * G * P.parts, kThreads, 0, st>>>(P);
+        else if (scans) k_assemble_part<true, false><<<tile_blocks * G, kThreads, 0, st>>>(P);
+        else k_assemble_part<false, false><<<tile_blocks * G, kThreads, 0, st>>>(P);
       }
       continue;
     }

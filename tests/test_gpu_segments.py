@@ -230,6 +230,21 @@ def test_small_hops_settled_in_one_launch_that_fail(seeds):
                                                             smfg.ST_NODE_CAPACITY, smfg.ST_EDGE_CAPACITY]
 
 
+@pytest.mark.parametrize("d,seeds,batches", [(4, 257, 1), (5, 1, 1), (5, 513, 1), (8, 256, 2), (9, 255, 1), (9, 769, 16), (17, 300, 1), (32, 257, 1),
+                                             (32, 4_000, 16), (20, 70_000, 1), (20, 140_000, 1)])
+def test_tiles_shared_by_blocks(d, seeds, batches, monkeypatch):
+    """Tiles of assemble whose positions one, two, four or eight blocks write, the last tile short, with and without a block's
+    worth of positions for each."""
+    monkeypatch.setenv("SMFG_DEDUP", "partition")
+    gg = random_graph(150_000, 2 * d, d)
+    s = [np.random.default_rng(b).permutation(150_000)[:seeds - 3 * b].astype(np.int32) for b in range(min(batches, seeds))]
+    ws = [smfg.workspace_create(gg.g, seeds, (d,)) for _ in s]
+    outs = [smfg.alloc_output(gg.g, seeds, (d,)) for _ in s]
+    smfg.sample_mfg_many(gg.g, ws, [torch.from_numpy(x).to(DEV) for x in s], (d,), range(len(s)), outs)
+    for b in range(0, len(s), 5):
+        assert_same(fetch(outs[b], 1), gg.oracle.sample_mfg(s[b], (d,), b), 1)
+
+
 @pytest.mark.parametrize("level", [1, 2])
 @pytest.mark.parametrize("dim,folded", [(32, True), (3, False)])
 def test_a_gather_without_a_launch_has_no_time(dim, folded, level):
