@@ -53,8 +53,8 @@ __device__ __forceinline__ void group_offsets(int mine, int rows_here, int (&off
 }
 
 // Source ids of the group's samples from e on, one per lane; the last one again past e_end.
-__device__ __forceinline__ uint32_t load_id(const int32_t* __restrict__ indices, int e, int e_end, int lane) {
-  return e < e_end ? static_cast<uint32_t>(indices[e + lane < e_end ? e + lane : e_end - 1]) : 0u;
+__device__ __forceinline__ uint32_t load_id(const int32_t* __restrict__ indices, uint32_t e, uint32_t e_end, uint32_t lane) {
+  return e < e_end ? static_cast<uint32_t>(indices[e + lane < e_end ? e + lane : e_end - 1u]) : 0u;
 }
 
 // Means of the group's rows_here (<= SPAN) destinations, off[0 .. rows_here] their boundaries.  emit(r, c, mean) receives, once
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(kThreads) k_mean_aggregate(const int32_t* __re
 
 // ---- one GraphSAGE layer: out = act([x_dst | mean] W^T + b) -------------------------------------
 //
-// A persistent block takes a range of consecutive destinations, a tile of them after the other.  A lane group of
+// A persistent block takes tiles of consecutive destinations, one after the other.  A lane group of
 // 8, 16 or 32 lanes fetches the rows of a destination's samples, a vector of 8 columns per lane; their mean,
 // rounded to half, and the destination's own row (destination i is source i) make a row of the tile in LDS, which eight
 // waves then multiply, each by its 32 columns of W^T, with v_mfma_f32_32x32x16_f16.  A wave keeps its part of W in
@@ -147,10 +147,12 @@ __global__ void __launch_bounds__(kThreads) k_mean_aggregate(const int32_t* __re
 // 128 -> 256, as much as the rows, and took half as long again.
 //
 // dim <= 128 (k_sage_layer): eight more waves do the fetching, two tiles ahead of the one that is being multiplied, so that
-// rows are on their way all the time; what is left is the HBM's.  154 K destinations x 5, 128 -> 256, half: 80 -> 67 us, 4.3 TB/s of what
-// the layer cannot do without; 96 K x 5 of 104 columns 51 -> 40, 47 K of 96 26 -> 19, 150 K x 10, 64 -> 128 63 -> 54.  With
-// all waves doing both, a tile ahead, 78 us for the first.  Where a block has a tile or less, a chain of dependent reads
-// remains: 12.5 K x 10, 128 -> 256 20 -> 12 us, 1 K x 15 19 -> 10.
+// rows are on their way all the time; what is left is the HBM's.  154 K destinations x 5, 128 -> 256, half: 80 -> 61 us, 4.8 TB/s of what
+// the layer cannot do without (68 us while waits for a tile's rows were waits for the next one's as well); 96 K x 5 of 104 columns 51 -> 40, 47 K
+// of 96 26 -> 19, 150 K x 10, 64 -> 128 63 -> 54.  With all waves doing both, a tile ahead, 78 us for the first.  Where a block has a tile or less, a
+// chain of dependent reads remains: 12.5 K x 10, 128 -> 256 20 -> 12 us, 1 K x 15 19 -> 10.  Blocks of whole neighbourhoods, 128 -> 256: 12 K
+// destinations with 5.1 M samples, 17 000 the most, 3.51 ms by k_sage_layer_cols, 3.67 with a range of destinations per block and 5 rows
+// of a destination at a time, 2.63 with tiles dealt and 10; 11 K with 2.9 M, 50 000 the most, 6.6, 7.9 and 4.2.
 // dim > 128 (k_sage_layer_wide): W takes 128 registers of a wave, which leaves room for eight waves in a compute unit, and all
 // of them fetch, a tile ahead.  300 K x 5, 256 -> 256 283 -> 226 us, 60 K x 15 113 -> 107, 13 K x 10 24 -> 21.5, 1 K x 15 20 -> 10;
 // with four waves that only fetch and eight that only multiply 244, 123, 22 and 15.
@@ -214,15 +216,40 @@ struct LayerArgs {
   void* out;
 };
 
-// The block's destinations: an even share, so that no block has a tile more than the others to do.
-__device__ __forceinline__ void layer_range(const LayerArgs& P, int& b0, int& b1) {
+__device__ __forceinline__ int layer_rows_in_all(const LayerArgs& P) {
   int64_t n = *P.num_dst;
   if (n > P.max_dst) n = P.max_dst;
   if (n > P.max_src) n = P.max_src;  // a destination's own row is row i of x
-  if (n < 0) n = 0;
+  return n < 0 ? 0 : static_cast<int>(n);
+}
+// An even share of consecutive destinations, so that no block has a tile more than the others to do.
+__device__ __forceinline__ void layer_range(const LayerArgs& P, int& b0, int& b1) {
+  const int64_t n = layer_rows_in_all(P);
   b0 = static_cast<int>(n * blockIdx.x / gridDim.x);
   b1 = static_cast<int>(n * (blockIdx.x + 1) / gridDim.x);
 }
+// A block's tiles of at most MOST destinations: an even share in one piece where that is two of them at most, else dealt to the blocks in
+// turn.  In blocks of whole neighbourhoods the destinations with the most samples are neighbours of each other; one range per
+// block left them all to a few.
+template <int MOST>
+struct LayerTiles {
+  uint32_t n, rows, first, step, end;  // destinations in all and of a tile; first one of the block's first tile, from there to the next tile's, end
+  __device__ __forceinline__ explicit LayerTiles(const LayerArgs& P) : n(static_cast<uint32_t>(layer_rows_in_all(P))) {
+    const uint32_t share = (n + gridDim.x - 1u) / gridDim.x;
+    if (share <= 2u * MOST) {
+      rows = step = MOST;
+      first = blockIdx.x * share;
+      end = first + share < n ? first + share : n;
+    } else {
+      const uint32_t turns = (share + MOST - 1u) / MOST;
+      rows = (share + turns - 1u) / turns;
+      step = gridDim.x * rows;
+      first = blockIdx.x * rows;
+      end = n;
+    }
+  }
+  __device__ __forceinline__ uint32_t count(uint32_t i0) const { return i0 >= end ? 0u : end - i0 < rows ? end - i0 : rows; }
+};
 
 // What a lane reads: vectors of 8 columns of rows of x; lanes past the last column read it once more.
 struct LayerColumns {
@@ -331,100 +358,130 @@ struct LayerProduct {
 
 // dim <= 8 * LANES <= 128.  A lane group of the fetching waves has a destination per tile; the rows of two tiles, the ids of
 // a third and the offsets of a fourth are on their way.  Of a destination with more than kDepth samples the first kDepth are
-// fetched ahead, the others as many at a time when these are added (8 of them ahead: 1 % more for a fanout of 5, 2 % less for 64).
+// fetched ahead (8 of them: 1 % more for a fanout of 5, 2 % less for 64), the others while those before them are added, up to 2 kDepth at a time.
 template <typename OutT, int LANES>
 __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P) {
   constexpr int ROWS = layer_rows(LANES), kDepth = 5, kAhead = 2;
+  constexpr bool kHeld = LANES >= 2 * kDepth;  // a group's lanes hold the ids of the second kDepth samples, too
   static_assert(ROWS % 32 == 0, "whole accumulators");
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lda = layer_lda(P.dim);
   _Float16* buf = reinterpret_cast<_Float16*>(lds_raw);  // [2][ROWS][lda]
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int b0, b1;
-  layer_range(P, b0, b1);
-  const int tiles = (b1 - b0 + ROWS - 1) / ROWS;
-  if (tiles == 0) return;
+  const LayerTiles<ROWS> T(P);
+  if (T.first >= T.end) return;
   if (wv < kLayerLoaders) {
-    const int grp = threadIdx.x / LANES, lane = threadIdx.x & (LANES - 1);
+    const uint32_t grp = threadIdx.x / LANES;
+    const int lane = threadIdx.x & (LANES - 1);
     const LayerColumns x(P, lane);
     struct Ahead {
       half8_t rows[kDepth], own;
-      uint32_t ids;  // of the samples from begin on, as many as the group has lanes
+      uint32_t ids, more;  // of the samples from begin on, as many as the group has lanes; unless kHeld, of those behind the first kDepth
       int begin, end;
     } s[kAhead];
-    const auto row_of = [&](int tile) {  // the last one again past the end
-      const uint32_t i = static_cast<uint32_t>(b0) + static_cast<uint32_t>(tile) * ROWS + static_cast<uint32_t>(grp), last = static_cast<uint32_t>(b1 - 1);
-      return i < last ? i : last;
-    };
     int begin, end, next_begin, next_end;
-    uint32_t id;
-    const auto read_offsets = [&](int tile) {
-      next_begin = load_offset(P.indptr, row_of(tile), P.max_dst, P.max_edges);
-      next_end = load_offset(P.indptr, row_of(tile) + 1u, P.max_dst, P.max_edges);
+    uint32_t id, id_more = 0;
+    // the group's destination of the tile whose offsets are read next; past the end where a tile has none for it, and then the last one of
+    // all without samples stands in
+    uint32_t i = grp < T.rows ? T.first + grp : T.end;
+    const auto read_offsets = [&]() {
+      const uint32_t at = i < T.end ? i : T.n - 1u;
+      next_begin = load_offset(P.indptr, at, P.max_dst, P.max_edges);
+      next_end = load_offset(P.indptr, at + (i < T.end ? 1u : 0u), P.max_dst, P.max_edges);
+      i += T.step;
     };
     const auto read_ids = [&]() {
       begin = next_begin;
       end = next_end > begin ? next_end : begin;
       id = load_id(P.indices, begin, end, lane);
+      if (!kHeld) id_more = load_id(P.indices, begin + kDepth, end, lane);
     };
     // rows of a tile; ids and offsets of those behind it first, since waiting for them must not be waiting for the rows
-    const auto issue = [&](Ahead& t, int tile) {
+    const auto issue = [&](Ahead& t) {
+      const uint32_t at = i - 2u * T.step;
       t.ids = id;
+      t.more = id_more;
       t.begin = begin;
       t.end = end;
       read_ids();
-      read_offsets(tile + 2);
+      read_offsets();
       x.rows<LANES>(t.ids, t.rows);
-      t.own = x.row(row_of(tile));
+      t.own = x.row(at < T.end ? at : T.n - 1u);
     };
     const auto finish = [&](Ahead& t, _Float16* a) {
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      int base = t.begin;  // t.ids are those from here on
-      uint32_t more = base + 2 * kDepth > base + LANES ? load_id(P.indices, base + kDepth, t.end, lane) : 0u;
-      for (int e = t.begin; e < t.end; e += kDepth) {
+      const int samples = t.end - t.begin;
+      const auto add = [&](const half8_t (&v)[kDepth], int count) {
 #pragma unroll
         for (int u = 0; u < kDepth; ++u)
-          if (e + u < t.end) layer_add(acc, t.rows[u]);
-        const int next = e + kDepth;
-        if (next < t.end) {
-          if (next + kDepth > base + LANES) {
-            t.ids = more;
-            base = next;
+          if (u < count) layer_add(acc, v[u]);
+      };
+      add(t.rows, samples);
+      if (samples > kDepth) {
+        const uint32_t last = static_cast<uint32_t>(t.end) - 1u;
+        uint32_t at = static_cast<uint32_t>(t.begin + lane);
+        const auto ids_at = [&](int ahead) {  // past the end that of the last sample
+          const uint32_t e = at + static_cast<uint32_t>(ahead);
+          return static_cast<uint32_t>(P.indices[e < last ? e : last]);
+        };
+        half8_t (&here)[kDepth] = t.rows, next[kDepth];
+        int left = samples - kDepth;
+        uint32_t id0 = ids_at(2 * kDepth), id1 = ids_at(3 * kDepth);
+        if constexpr (kHeld) x.rows<LANES>(t.ids, here, kDepth);
+        else x.rows<LANES>(t.more, here);
+        if (left > kDepth) {
+          x.rows<LANES>(id0, next);
+          id0 = ids_at(4 * kDepth);
+          while (left > 2 * kDepth) {
+            add(here, kDepth);
+            x.rows<LANES>(id1, here);
+            id1 = ids_at(5 * kDepth);
+            add(next, kDepth);
+            x.rows<LANES>(id0, next);
+            id0 = ids_at(6 * kDepth);
+            at += 2 * kDepth;
+            left -= 2 * kDepth;
           }
-          x.rows<LANES>(t.ids, t.rows, next - base);
-          if (next + 2 * kDepth > base + LANES) more = load_id(P.indices, next + kDepth, t.end, lane);
         }
+        add(here, left);
+        add(next, left - kDepth);
+        // Nothing under way where the ways meet again, or the waits behind would be for the next tile's rows as well.
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
       }
-      const half8_t mean = layer_mean(acc, t.end - t.begin);
+      const half8_t mean = layer_mean(acc, samples);
       if (x.own) {
         *reinterpret_cast<half8_t*>(a + grp * lda + lane * 8) = t.own;
         *reinterpret_cast<half8_t*>(a + grp * lda + P.dim + lane * 8) = mean;
       }
     };
-    read_offsets(0);
+    read_offsets();
     read_ids();
-    read_offsets(1);
-#pragma unroll
-    for (int k = 0; k < kAhead; ++k) issue(s[k], k);
-    for (int t = 0; t < tiles; t += 2) {
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        if (t + half < tiles) {
-          finish(s[half % kAhead], buf + half * ROWS * lda);
-          issue(s[half % kAhead], t + half + kAhead);
-          __syncthreads();
-        }
-      }
+    read_offsets();
+    static_assert(kAhead == 2, "the halves of buf");
+    issue(s[0]);
+    issue(s[1]);
+    // Two tiles a turn, the last of an odd number with one of no destinations: a way past the second to the next turn would make every
+    // wait for rows one for the tile's behind them.
+    for (uint32_t i0 = T.first; i0 < T.end; i0 += 2u * T.step) {
+      finish(s[0], buf);
+      issue(s[0]);
+      __syncthreads();
+      finish(s[1], buf + ROWS * lda);
+      issue(s[1]);
+      __syncthreads();
     }
     __syncthreads();
     return;
   }
   const LayerProduct<OutT, LANES> product(P, wv - kLayerLoaders, reinterpret_cast<OutT*>(buf + 2 * ROWS * lda));
   __syncthreads();
-  for (int t = 0; t < tiles; ++t) {
-    const int tile0 = b0 + t * ROWS;
-    product.tile(buf + (t & 1) * ROWS * lda, tile0, b1 - tile0 < ROWS ? b1 - tile0 : ROWS);
-    __syncthreads();
+  for (uint32_t i0 = T.first; i0 < T.end; i0 += 2u * T.step) {
+#pragma unroll
+    for (uint32_t half = 0; half < 2u; ++half) {
+      const uint32_t at = i0 + half * T.step;
+      product.tile(buf + half * ROWS * lda, static_cast<int>(at), static_cast<int>(T.count(at)));
+      __syncthreads();
+    }
   }
 }
 
