@@ -288,34 +288,36 @@ __device__ __forceinline__ half8_t layer_mean(const float (&acc)[8], int samples
   return h;
 }
 
-// A wave's part of the multiplication: columns 32 wave .. + 32.
-template <typename OutT, int STEPS>  // STEPS: of 16 reduction indices, at most
+// A wave's part of the multiplication: a slice of 32 columns, in tiles of 64 destinations of every other 32 where there are as many waves as
+// that takes.
+template <typename OutT, int STEPS, int ROWS>  // steps of 16 reduction indices and destinations of a tile, at most
 struct LayerProduct {
   const LayerArgs& P;
-  const int wave, lane, col, hi, nq, lda;
+  const int parts, part, slice, lane, col, hi, nq, lda;
   const bool vectors;
   OutT* const res;  // [32][layer_ldo], the wave's own
   half8_t w[STEPS];
 
-  __device__ __forceinline__ half8_t weights(int slice, int q) const {
+  __device__ __forceinline__ half8_t weights(int q) const {
     return reinterpret_cast<const half8_t*>(P.w)[(static_cast<int64_t>(slice) * nq + (q < nq ? q : 0)) * 64 + lane];
   }
   __device__ __forceinline__ LayerProduct(const LayerArgs& p, int wv, OutT* all_res)
-      : P(p), wave(wv), lane(threadIdx.x & 63), col(lane & 31), hi(lane >> 5), nq(p.dim / 8), lda(layer_lda(p.dim)),
+      : P(p), parts(ROWS == 32 || p.out_dim > 128 ? 1 : 2), part(ROWS == 32 ? 0 : wv * parts / kLayerWaves), slice(ROWS == 32 ? wv : wv - part * (kLayerWaves / parts)),
+        lane(threadIdx.x & 63), col(lane & 31), hi(lane >> 5), nq(p.dim / 8), lda(layer_lda(p.dim)),
         vectors(p.out_dim % (16 / static_cast<int>(sizeof(OutT))) == 0 && reinterpret_cast<uintptr_t>(p.out) % 16 == 0),
         res(all_res + wv * 32 * layer_ldo<OutT>()) {
-    if (wave * 32 < P.out_dim) {
+    if (slice * 32 < P.out_dim) {
 #pragma unroll
-      for (int q = 0; q < STEPS; ++q) w[q] = weights(wave, q);
+      for (int q = 0; q < STEPS; ++q) w[q] = weights(q);
     }
   }
   // destinations tile0 .. tile0 + here, their inputs in a
   __device__ __forceinline__ void tile(const _Float16* a, int tile0, int here) const {
     constexpr int kVec = 16 / static_cast<int>(sizeof(OutT)), kRowLanes = 32 / kVec, ldo = layer_ldo<OutT>();
-    if (wave * 32 >= P.out_dim) return;
-    const int j = wave * 32 + col;
+    if (slice * 32 >= P.out_dim) return;
+    const int j = slice * 32 + col;
     const float bias = P.bias && j < P.out_dim ? P.bias[j] : 0.f;
-    for (int rb = 0; rb < here; rb += 32) {
+    for (int rb = 32 * part; rb < here; rb += 32 * parts) {
       const _Float16* ap = a + (rb + col) * lda + hi * 8;
       float16_t acc;
 #pragma unroll
@@ -338,8 +340,8 @@ struct LayerProduct {
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      OutT* to = static_cast<OutT*>(P.out) + static_cast<int64_t>(tile0 + rb) * P.out_dim + wave * 32;
-      const int rows = here - rb < 32 ? here - rb : 32, cols = P.out_dim - wave * 32 < 32 ? P.out_dim - wave * 32 : 32;
+      OutT* to = static_cast<OutT*>(P.out) + static_cast<int64_t>(tile0 + rb) * P.out_dim + slice * 32;
+      const int rows = here - rb < 32 ? here - rb : 32, cols = P.out_dim - slice * 32 < 32 ? P.out_dim - slice * 32 : 32;
       if (vectors) {
         const int c = lane % kRowLanes * kVec;
 #pragma unroll
@@ -348,7 +350,17 @@ struct LayerProduct {
           if (r < rows && c < cols) *reinterpret_cast<float4_t*>(to + static_cast<int64_t>(r) * P.out_dim + c) = *reinterpret_cast<const float4_t*>(res + r * ldo + c);
         }
       } else if (col < cols) {
-        for (int r = hi; r < rows; r += 2) to[static_cast<int64_t>(r) * P.out_dim + col] = res[r * ldo + col];
+        constexpr int kRead = 8;  // reads of the LDS that no store waits between: 50 K x 3, 64 -> 47, float 16.6 us, 11.7 so
+        OutT* at = to + static_cast<int64_t>(hi) * P.out_dim + col;
+#pragma unroll 1
+        for (int r = hi; r < rows; r += 2 * kRead) {
+          OutT v[kRead];
+#pragma unroll
+          for (int u = 0; u < kRead; ++u) v[u] = res[(r + 2 * u) * ldo + col];
+#pragma unroll
+          for (int u = 0; u < kRead; ++u, at += 2 * P.out_dim)
+            if (r + 2 * u < rows) *at = v[u];
+        }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -363,7 +375,7 @@ template <typename OutT, int LANES>
 __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P) {
   constexpr int ROWS = layer_rows(LANES), kDepth = 5, kAhead = 2;
   constexpr bool kHeld = LANES >= 2 * kDepth;  // a group's lanes hold the ids of the second kDepth samples, too
-  static_assert(ROWS % 32 == 0, "whole accumulators");
+  static_assert(ROWS == 32 || ROWS == 64, "one or two accumulators");
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lda = layer_lda(P.dim);
   _Float16* buf = reinterpret_cast<_Float16*>(lds_raw);  // [2][ROWS][lda]
@@ -473,7 +485,7 @@ __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P)
     __syncthreads();
     return;
   }
-  const LayerProduct<OutT, LANES> product(P, wv - kLayerLoaders, reinterpret_cast<OutT*>(buf + 2 * ROWS * lda));
+  const LayerProduct<OutT, LANES, ROWS> product(P, wv - kLayerLoaders, reinterpret_cast<OutT*>(buf + 2 * ROWS * lda));
   __syncthreads();
   for (uint32_t i0 = T.first; i0 < T.end; i0 += 2u * T.step) {
 #pragma unroll
@@ -493,7 +505,7 @@ __global__ void __launch_bounds__(kLayerWideThreads, 2) k_sage_layer_wide(const 
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lda = layer_lda(P.dim);
   _Float16* buf = reinterpret_cast<_Float16*>(lds_raw);  // [2][kLayerWideRows][lda]
-  const LayerProduct<OutT, LANES> product(P, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), reinterpret_cast<OutT*>(buf + 2 * kLayerWideRows * lda));
+  const LayerProduct<OutT, LANES, kLayerWideRows> product(P, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), reinterpret_cast<OutT*>(buf + 2 * kLayerWideRows * lda));
   int b0, b1;
   layer_range(P, b0, b1);
   if (b0 == b1) return;

@@ -35,7 +35,8 @@ def layer(indptr, indices, x, w, b, relu, out_dtype, spare=3):
     (1, 1, 8, 1, torch.float32), (15, 4, 8, 31, torch.float16), (17, 5, 56, 33, torch.float16), (65, 6, 64, 256, torch.float16),
     (33, 5, 72, 32, torch.float32), (600, 11, 128, 255, torch.float16), (257, 16, 120, 256, torch.float32), (9001, 17, 128, 8, torch.float16),
     (16, 10, 136, 40, torch.float16), (4111, 21, 136, 256, torch.float32), (8229, 4, 256, 172, torch.float16), (300, 33, 248, 17, torch.float16),
-    (130, 7, 16, 257, torch.float16), (70, 40, 128, 300, torch.float32), (33, 12, 256, 512, torch.float16), (20000, 3, 24, 24, torch.float16)])
+    (130, 7, 16, 257, torch.float16), (70, 40, 128, 300, torch.float32), (33, 12, 256, 512, torch.float16), (20000, 3, 24, 24, torch.float16),
+    (9001, 3, 64, 47, torch.float32), (12100, 2, 40, 65, torch.float16), (8500, 4, 128, 33, torch.float16), (8500, 4, 64, 129, torch.float32)])
 def test_layer_edges(n_dst, fanout, dim, out_dim, dtype):
     """Bound: S (2^-11 + (2 dim + k + 2) 2^-24), S = sum of |w| |input| + |bias|: the mean rounded to half, then
     float sums; half an ulp of a half result."""
