@@ -53,8 +53,8 @@ __device__ __forceinline__ void group_offsets(int mine, int rows_here, int (&off
 }
 
 // Source ids of the group's samples from e on, one per lane; the last one again past e_end.
-__device__ __forceinline__ uint32_t load_id(const int32_t* __restrict__ indices, uint32_t e, uint32_t e_end, uint32_t lane) {
-  return e < e_end ? static_cast<uint32_t>(indices[e + lane < e_end ? e + lane : e_end - 1u]) : 0u;
+__device__ __forceinline__ uint32_t load_id(const int32_t* __restrict__ indices, int e, int e_end, int lane) {
+  return e < e_end ? static_cast<uint32_t>(indices[e + lane < e_end ? e + lane : e_end - 1]) : 0u;
 }
 
 // Means of the group's rows_here (<= SPAN) destinations, off[0 .. rows_here] their boundaries.  emit(r, c, mean) receives, once
@@ -406,7 +406,7 @@ __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P)
       begin = next_begin;
       end = next_end > begin ? next_end : begin;
       id = load_id(P.indices, begin, end, lane);
-      if (!kHeld) id_more = load_id(P.indices, begin + kDepth, end, lane);
+      if (!kHeld) id_more = load_id(P.indices, begin < end - kDepth ? begin + kDepth : end, end, lane);
     };
     // rows of a tile; ids and offsets of those behind it first, since waiting for them must not be waiting for the rows
     const auto issue = [&](Ahead& t) {
