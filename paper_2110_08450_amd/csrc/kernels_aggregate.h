@@ -580,8 +580,8 @@ __global__ void __launch_bounds__(kLayerWideThreads, 2) k_sage_layer_wide(const 
   }
 }
 
-// More than kLayerMaxCols output columns: W does not fit the registers of a block, and every tile reads it from the L2.  A block
-// of four waves builds the inputs of ROWS destinations and multiplies them, a wave the column slices 4 apart.  100 K destinations x 5, 200 -> 300, half: 102 us
+// More than kLayerMaxCols output columns, where W does not fit the registers of a block, and more than 128 columns in with a small W
+// (layer_reads_w): every tile reads W from the L2.  A block of four waves builds the inputs of ROWS destinations and multiplies them, a wave the column slices 4 apart.  100 K destinations x 5, 200 -> 300, half: 102 us
 // (150 by k_sage_layer_wide with the columns from 256 on read for every tile); 64 -> 300 47 us (63 by k_sage_layer).
 constexpr int layer_cols_rows(int dim) { return dim <= 128 ? 64 : 32; }  // at most 34 KB of LDS, four blocks to a compute unit
 constexpr int kLayerColsAhead = 8;  // vectors of W requested ahead of their use

@@ -741,9 +741,26 @@ void launch_gather_plain(const smfg_graph* g, int vb, const int32_t* ids, const 
 }
 
 // Up to kLayerMaxCols output columns a block keeps W in its registers, and there is one to a compute unit where there are destinations enough.
+// Beyond 128 columns in, such a block fetches and multiplies by turns, a tile at a time, which costs more than W from the L2 where W
+// is small, a block has several tiles and a destination some 10 samples at most.  k_sage_layer_wide / k_sage_layer_cols, halfs, us:
+//                16 K x 3    24 K x 3    48 K x 3    80 K x 3    154 K x 5    154 K x 8    80 K x 20
+//   136 ->   8   9.2/10.4   12.9/12.2   24.2/19.6   38.0/27.0   76.6/51.3    97.3/74.0    89.9/97.6
+//   136 -> 128  10.7/11.6   14.8/14.3   26.6/23.5   41.0/33.1   78.5/63.3   111.6/86.2    94.9/101
+//   136 -> 192  11.5/13.9   15.7/16.7   27.5/27.8   42.1/39.3   82.2/76.0   115/103       98.2/104
+//   200 -> 128  11.3/12.5   16.0/15.7   28.4/26.7   44.2/38.6   96.3/80.8   125/118      113/138
+//   200 -> 192  12.2/15.5   16.9/18.6   29.7/32.1   45.1/45.6   97.8/103    127/135      115/143
+//   256 ->   8  10.4/11.7   16.0/14.4   28.3/24.5   43.5/34.9  102/78.5     130/105      123/116
+//   256 -> 128  11.9/12.9   17.6/16.4   29.9/27.6   45.9/40.4  107/94.7     136/123      129/124
+//   256 -> 160  12.6/15.2   18.2/18.6   30.7/32.3   46.9/46.9  106/109      136/136      132/132
+// The samples are told by the room for them; whole neighbourhoods, with room for far more, stay with k_sage_layer_wide, which takes
+// half as long for their long rows.
+bool layer_reads_w(int dim, int out_dim, int64_t max_dst, int64_t max_edges) {
+  if (dim <= 128 || max_edges > 10 * max_dst) return false;
+  return max_dst < 65536 ? out_dim <= 128 && max_dst >= 20480 : dim * out_dim <= 32768;
+}
 template <typename OutT>
 void launch_layer(const LayerArgs& P, hipStream_t st) {
-  if (P.out_dim > kLayerMaxCols) {
+  if (P.out_dim > kLayerMaxCols || layer_reads_w(P.dim, P.out_dim, P.max_dst, P.max_edges)) {
     const int rows = layer_cols_rows(P.dim);
     const size_t lds = sizeof(_Float16) * rows * layer_lda(P.dim);
     const unsigned blocks = blocks_for(P.max_dst, rows, 0x7FFFFFFFu);

@@ -40,6 +40,17 @@ def layer(indptr, indices, x, w, b, relu, out_dtype, spare=3):
 def test_layer_edges(n_dst, fanout, dim, out_dim, dtype):
     """Bound: S (2^-11 + (2 dim + k + 2) 2^-24), S = sum of |w| |input| + |bias|: the mean rounded to half, then
     float sums; half an ulp of a half result."""
+    check_layer(n_dst, fanout, dim, out_dim, dtype)
+
+
+@pytest.mark.parametrize("max_dst,dim,out_dim", [(20_479, 136, 33), (20_480, 136, 33), (20_480, 256, 129), (65_535, 136, 129), (65_536, 136, 129),
+                                                 (65_536, 256, 128), (65_536, 256, 129), (65_536, 128, 40)])
+@pytest.mark.parametrize("n_dst", [1, 700])
+def test_layer_either_side_of_reading_w_for_every_tile(max_dst, dim, out_dim, n_dst):
+    check_layer(n_dst, 9, dim, out_dim, torch.float16, max_dst - n_dst)
+
+
+def check_layer(n_dst, fanout, dim, out_dim, dtype, spare=3):
     rng = np.random.default_rng(n_dst + dim)
     n_src = n_dst + 50
     indptr, indices = block_of(rng, n_dst, fanout, n_src)
@@ -47,7 +58,7 @@ def test_layer_edges(n_dst, fanout, dim, out_dim, dtype):
     w = (rng.standard_normal((out_dim, 2 * dim)) / np.sqrt(dim)).astype(np.float16)
     b = rng.standard_normal(out_dim).astype(np.float32)
     relu = n_dst % 2 == 0
-    got = layer(indptr, indices, x, w, b, relu, dtype)
+    got = layer(indptr, indices, x, w, b, relu, dtype, spare)
     want, mag = oracle.sage_layer(indptr, indices, x, w.astype(np.float64), b.astype(np.float64), relu)
     tol = mag * (2.0 ** -11 + (2 * dim + np.diff(indptr)[:, None] + 2) * 2.0 ** -24)
     if dtype == torch.float16:
