@@ -239,11 +239,11 @@ __device__ __forceinline__ void floyd_positions(const Launch& P, const BatchCtx&
 template <bool INSERT>
 __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
   extern __shared__ __align__(16) uint32_t wide_lds[];
-  __shared__ uint2 turn_lds[2];  // .x samples of the tiles before the turn's first one, .y whether the batch has a status
+  __shared__ uint2 turn_lds[2];  // .x samples of the tiles before the turn's first one, .y whether the batch ends here
   const BatchCtx& B = P.b[batch_of_block(P)];
   // A batch that had a status when the block started may count more nodes than its arrays hold; those below are read, and nothing
   // is done with them.  The first wave's answer is the block's: others may set a status meanwhile.
-  const bool stopped = status_of(B, P.L) != 0;
+  const bool stopped = __any(status_of(B, P.L) != 0);
   const int64_t known = B.counts[P.h];
   const int n = static_cast<int>(known < B.node_capacity ? known : B.node_capacity);
   const int lane = threadIdx.x & 63;
@@ -258,6 +258,8 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
   static_assert(kThreads / 64 * kWideRows <= kTileRows, "a block's destinations are in two tiles at most");
   const uint32_t tiles = static_cast<uint32_t>(n + kTileRows - 1) / kTileRows;
   const unsigned long long room = static_cast<unsigned long long>(B.edge_capacity < B.lostto_entries ? B.edge_capacity : B.lostto_entries);
+  // Nothing of a hop with too many samples goes into the table: it may not have as many slots as they have nodes, and that would be told instead.
+  const bool none = INSERT && wave == 0 && n > 0 && samples_before(P, B, tiles, tiles - 1u) + B.tile_sums[tiles - 1u] > room;
   int turn = 0;  // wave 0 writes the next turn's offset while others may still read the present one's
   for (int b0 = block_in_batch(P) * (kThreads / 64) * per; b0 < n; b0 += waves_total * per, turn ^= 1) {
     const int i0 = b0 + wave * per;
@@ -276,10 +278,10 @@ __global__ void __launch_bounds__(kThreads) k_sample_wide(const Launch P) {
     }
     if (wave == 0) {
       const uint32_t before = static_cast<uint32_t>(samples_before(P, B, tiles, static_cast<uint32_t>(b0 / kTileRows)));
-      if (lane == 0) turn_lds[turn] = make_uint2(before, stopped ? 1u : 0u);
+      if (lane == 0) turn_lds[turn] = make_uint2(before, stopped || none ? 1u : 0u);
     }
     __syncthreads();
-    if (turn_lds[turn].y != 0u) return;
+    if (turn_lds[turn].y != 0u) break;
     base_l += turn_lds[turn].x;
     if (mine) {
       if (P.h == 0 && v_l >= P.num_nodes) set_status(B, P.L, SMFG_ST_SEED_OUT_OF_RANGE);

@@ -195,6 +195,34 @@ def test_wide_first_hop_that_does_not_fit(room, stray, status, monkeypatch):
     assert (out.indices[0][min(capacity, edges):] == -7).all()
 
 
+@pytest.mark.parametrize("later", [False, True])
+def test_wide_hop_of_more_samples_than_room_and_nodes_than_slots(later, monkeypatch):
+    """The table strategy, a hop whose samples do not fit, and which hold more nodes than the table has slots: nothing is looked up in a
+    full table (0.1 ms; 30 with the samples that have room looked up), the samples are what is reported, and the next call on the workspace does not notice."""
+    monkeypatch.setenv("SMFG_DEDUP", "table")
+    gg = random_graph(200_000, 60, 33)
+    perm = np.random.default_rng(33).permutation(200_000).astype(np.int32)
+    fanouts, few, many = ((3, -1), 30, 1500) if later else ((-1,), 100, 6000)
+    nodes, room = 8000, 60_000  # 16384 slots
+    ref = gg.oracle.sample_mfg(perm[:many], fanouts, 1)
+    assert ref.num_edges[-1] > room and (not later or ref.num_nodes[1] < nodes)
+    ws = smfg.workspace_create(gg.g, many, fanouts, nodes, room)
+    out = smfg.alloc_output(gg.g, many, fanouts, node_capacity=nodes, edge_capacity=[room] * len(fanouts))
+    took = {}
+    for seeds, status in ((few, 0), (many, smfg.ST_EDGE_CAPACITY), (few, 0), (many, smfg.ST_EDGE_CAPACITY)):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        smfg.sample_mfg(gg.g, ws, torch.from_numpy(perm[:seeds]).to(DEV), fanouts, 1, out)
+        b.record()
+        b.synchronize()
+        took[seeds] = a.elapsed_time(b)
+        got = fetch(out, len(fanouts))
+        assert got["status"] == status
+        if status == 0:
+            assert_same(got, gg.oracle.sample_mfg(perm[:seeds], fanouts, 1), len(fanouts))
+    assert took[many] < 1
+
+
 @pytest.mark.parametrize("fanouts,seeds", [((15,), 68), ((15,), 69), ((1,), 640), ((1,), 641), ((4, 2), 256), ((4, 2), 257), ((31,), 33), ((31,), 34),
                                            ((1,), 2048), ((1,), 2049), ((31, 1), 128), ((31, 1), 129), ((3,), 1024), ((32, 3, 1), 1), ((7, 7), 0)])
 def test_small_hops_settled_in_one_launch(fanouts, seeds):
