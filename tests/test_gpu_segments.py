@@ -174,25 +174,30 @@ def test_wide_hops_of_many_tiles(seeds, fanouts, strategy, monkeypatch):
         assert_same(fetch(out, len(fanouts)), gg.oracle.sample_mfg(s, fanouts, key), len(fanouts))
 
 
-@pytest.mark.parametrize("room,stray,status", [(0, False, smfg.ST_EDGE_CAPACITY), (0, True, smfg.ST_SEED_OUT_OF_RANGE),
-                                               (20, True, smfg.ST_SEED_OUT_OF_RANGE), (20, False, 0)])
-def test_wide_first_hop_that_does_not_fit(room, stray, status, monkeypatch):
-    """Samples beyond the room of a batch, a stray seed, or both: nothing lies behind the buffers' ends, and the stray seed is
-    what is reported."""
-    monkeypatch.setenv("SMFG_DEDUP", "partition")
+@pytest.mark.parametrize("strategy", ["partition", "table"])
+@pytest.mark.parametrize("room,stray,status", [(-10, False, smfg.ST_EDGE_CAPACITY), (-10, True, smfg.ST_SEED_OUT_OF_RANGE),
+                                               (0, True, smfg.ST_SEED_OUT_OF_RANGE), (0, False, 0)])
+def test_wide_first_hop_that_does_not_fit(room, stray, status, strategy, monkeypatch):
+    """Samples beyond the room of a batch, a stray seed, or both: nothing lies behind the buffers' ends, the stray seed is
+    what is reported, and a call that fits is as ever."""
+    monkeypatch.setenv("SMFG_DEDUP", strategy)
     gg = random_graph(5_000, 40, 32)
     s = np.random.default_rng(32).permutation(5_000)[:600].astype(np.int32)
-    edges = gg.oracle.sample_mfg(s, (-1,), 1).num_edges[0]
+    drawn = s[:599] if stray else s  # a stray seed has no samples
+    edges = gg.oracle.sample_mfg(drawn, (-1,), 1).num_edges[0]
+    capacity = edges + room
+    bad = s.copy()
     if stray:
-        s[599] = 5_000
-    capacity = edges - 10 + room
+        bad[599] = 5_000
     ws = smfg.workspace_create(gg.g, 600, (-1,), 0, edges)
     out = smfg.alloc_output(gg.g, 600, (-1,), edge_capacity=[edges])
     out.indices[0].fill_(-7)
     out.c.edge_capacity[0] = capacity
-    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), (-1,), 1, out)
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(bad).to(DEV), (-1,), 1, out)
     assert fetch(out, 1)["status"] == status
-    assert (out.indices[0][min(capacity, edges):] == -7).all()
+    assert (out.indices[0][capacity:] == -7).all()
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s[:500]).to(DEV), (-1,), 1, out)
+    assert_same(fetch(out, 1), gg.oracle.sample_mfg(s[:500], (-1,), 1), 1)
 
 
 @pytest.mark.parametrize("later", [False, True])
