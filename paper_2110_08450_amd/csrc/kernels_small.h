@@ -420,13 +420,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_finish(const SmallLaunc
   off[tid] = own;
   const bool nodes_fit = nodes <= static_cast<uint32_t>(B.node_capacity);
   const bool edges_fit = edges <= static_cast<uint32_t>(B.edge_capacity[h]);
+  const bool bad_seeds = wrong != SMFG_ST_OK;  // as elsewhere, nothing but the seeds is counted then
   if (wrong == SMFG_ST_OK) wrong = !nodes_fit ? SMFG_ST_NODE_CAPACITY : !edges_fit ? SMFG_ST_EDGE_CAPACITY : SMFG_ST_OK;
   if (tid == 0 && i0 == 0) {
     if constexpr (FROM == kSeeds) {  // starts the counts
-      for (int q = 0; q < 2 * P.L + 2; ++q) B.counts[q] = q == 0 ? n : q == 1 ? nodes : q == P.L + 1 ? edges : q == 2 * P.L + 1 ? wrong : 0;
+      for (int q = 0; q < 2 * P.L + 2; ++q)
+        B.counts[q] = q == 0 ? n : q == 2 * P.L + 1 ? wrong : bad_seeds ? 0 : q == 1 ? nodes : q == P.L + 1 ? edges : 0;
     } else {
-      B.counts[P.L + 1 + h] = edges;
-      B.counts[h + 1] = nodes;
+      if (!bad_seeds) {
+        B.counts[P.L + 1 + h] = edges;
+        B.counts[h + 1] = nodes;
+      }
       if (wrong != SMFG_ST_OK) set_status(B, P.L, wrong);
     }
     if (wrong == SMFG_ST_OK) B.blk_indptr[h][n] = static_cast<int32_t>(edges);

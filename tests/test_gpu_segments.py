@@ -296,3 +296,23 @@ def test_a_gather_without_a_launch_has_no_time(dim, folded, level):
     assert prof["assemble"][1] == (6 if level == 2 else 0) == prof["sample_insert"][1]
     again = smfg.profile_end()
     assert all(n == 0 for _, n in again.values())
+
+
+@pytest.mark.parametrize("bad", ["stray", "twice"])
+@pytest.mark.parametrize("strategy", ["", "partition", "table"])
+@pytest.mark.parametrize("seeds,fanouts", [(60, (10, 5)), (200, (10, 5)), (1000, (7, 3))])
+def test_bad_seeds_leave_nothing_counted(seeds, fanouts, strategy, bad, monkeypatch):
+    """Whatever draws the first hop: a batch with a stray or repeated seed counts its seeds and no node, nor a stray one's batch a sample."""
+    monkeypatch.setenv("SMFG_DEDUP", strategy)
+    gg = random_graph(5_000, 60, 34)
+    s = np.random.default_rng(34).permutation(5_000)[:seeds].astype(np.int32)
+    s[seeds // 2] = 5_000 if bad == "stray" else s[0]
+    L, room = len(fanouts), 400_000 if min(fanouts) < 0 else 0
+    ws = smfg.workspace_create(gg.g, seeds, fanouts, 0, room)
+    out = smfg.alloc_output(gg.g, seeds, fanouts)
+    smfg.sample_mfg(gg.g, ws, torch.from_numpy(s).to(DEV), fanouts, 1, out)
+    want = [seeds] + [0] * (2 * L) + [smfg.ST_SEED_OUT_OF_RANGE if bad == "stray" else smfg.ST_DUPLICATE_SEED]
+    got = fetch(out, L)["counts"]
+    if bad == "twice" and max(fanouts[0], 64 * (fanouts[0] < 0)) > 32 and ws.strategy == "partition":
+        got[L + 1] = 0  # told behind the draw, whose samples are counted
+    assert got == want
