@@ -368,7 +368,11 @@ __global__ void __launch_bounds__(kFlatThreads) k_part_flat(const Launch P) {
   const BatchCtx& B = P.b[batch_of_block(P)];
   const uint32_t n = static_cast<uint32_t>(B.counts[P.h]);  // both on their way with the status
   const uint32_t total_e = n + static_cast<uint32_t>(B.counts[P.L + 1 + P.h]);
-  if (block_has_status(B, P.L)) return;
+  if (block_has_status(B, P.L)) {
+    // k_sample_wide counts while it looks for stray seeds; as elsewhere, nothing but the seeds is counted with one
+    if (P.h == 0 && block_in_batch(P) == 0 && threadIdx.x == 0 && status_of(B, P.L) == SMFG_ST_SEED_OUT_OF_RANGE) B.counts[P.L + 1] = 0;
+    return;
+  }
   const int lgB = hop_shape(P, B, n).lgB;
   const Segments segs = hop_segments(P, B, n);
   for (uint32_t seg = static_cast<uint32_t>(block_in_batch(P)); seg < segs.count; seg += static_cast<uint32_t>(blocks_per_batch(P))) {

@@ -300,7 +300,7 @@ def test_a_gather_without_a_launch_has_no_time(dim, folded, level):
 
 @pytest.mark.parametrize("bad", ["stray", "twice"])
 @pytest.mark.parametrize("strategy", ["", "partition", "table"])
-@pytest.mark.parametrize("seeds,fanouts", [(60, (10, 5)), (200, (10, 5)), (1000, (7, 3))])
+@pytest.mark.parametrize("seeds,fanouts", [(60, (10, 5)), (200, (10, 5)), (1000, (7, 3)), (60, (40, 3)), (700, (33, 34)), (700, (-1,))])
 def test_bad_seeds_leave_nothing_counted(seeds, fanouts, strategy, bad, monkeypatch):
     """Whatever draws the first hop: a batch with a stray or repeated seed counts its seeds and no node, nor a stray one's batch a sample."""
     monkeypatch.setenv("SMFG_DEDUP", strategy)
