@@ -162,7 +162,7 @@ int64_t smfg_workspace_bytes(const smfg_workspace_t *ws);
  *                            atomics.  Chosen when no hop of the planned size reaches 32768
  *                            records.
  * A call whose own hops all stay below that, on a workspace of either kind, reads all its records in every
- * one of a few blocks instead (three launches per hop; such calls are launch bound): no table in
+ * one of a few blocks instead (one or two launches per hop and at most one before the first; such calls are launch bound): no table in
  * device memory, no atomics.  On partition workspaces the first hops of a larger call do so as well, unless
  * it is a set of more than four batches that leaves the gather to another call.  The result is the same again.
  * The environment variable SMFG_DEDUP=table or =partition, read when a workspace is created,

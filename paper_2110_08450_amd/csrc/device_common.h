@@ -28,15 +28,16 @@ struct BatchCtx {
   int64_t lostto_entries;
   int32_t* gsrc;         // per (destination, s): global id of the sampled neighbour
   int32_t* rowk;         // samples per destination
-  uint2* rowmn;          // per destination: .x first-appearance bits, .y new nodes of the tile before its first new node
+  uint2* rowmn;          // per destination: .x first-appearance bits, .y new nodes of the tile before its first new node.  Wide path: its
+                         // front holds totals of tiles of tiles, zero between two hops (cleared by the end of a hop, see has_supers)
   int32_t* rowoff;       // samples of the tile before this destination
-  uint64_t* tile_sums;   // per tile: (edges << 32 | new nodes), later their exclusive scan
+  uint64_t* tile_sums;   // per tile: (edges << 32 | new nodes), later their exclusive scan where a launch scans them; wide path: samples
   int64_t* rowstart;     // wide path: first CSR position of the destination's row
   int32_t* rowdeg;       // wide path: degree of the destination
   uint32_t* rank;        // wide path, table strategy: new nodes of the sample's tile before this sample
   uint4* grp;            // wide path, partition strategy: per 64 samples (.x, .y) first-appearance bits,
                          // .z new nodes of the tile before the group
-  uint64_t* stile_sums;  // wide path: per sample tile, new nodes, later their exclusive scan
+  uint64_t* stile_sums;  // wide path: per sample tile, new nodes, under the table strategy later their exclusive scan
   int32_t* blk_indptr;   // hop h
   int32_t* blk_indices;  // hop h
   uint8_t* features;
@@ -50,7 +51,7 @@ struct BatchCtx {
   // partition path (no table): records of a hop grouped by hash bucket
   uint64_t* rec;         // (node << 32 | value) per known node and per sample, in segments sorted by bucket
   uint16_t* hist;        // per segment, the first record of each bucket within it and the end of the last; takes turns
-                         // with rowmn, and in hops of one level with bstart2 and rec2
+                         // with rowmn, on the wide path with its totals, and in hops of one level with bstart2 and rec2
   uint64_t* rec2;        // the records once more, each bucket's of a range of segments sorted by sub-bucket (hops with lg2 > 0)
   uint32_t* bstart2;     // [ranges][buckets][sub-buckets + 1] where each begins in rec2, and the end of the last
   int32_t one_level;     // log2 of the most buckets of the current hop that hist has room for in one level

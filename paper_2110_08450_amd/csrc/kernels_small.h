@@ -278,7 +278,7 @@ struct SmallTable {
 template <>
 struct SmallTable<kSettled> {};
 
-// The entries of a batch's hop -> A.entry; e: those of positions 4 tid .. 4 tid + 3, drawn(i): known node i.  All
+// The entries of a batch's hop -> A.entry; e: those of positions 4 tid .. 4 tid + 3, known(i): known node i.  All
 // threads call; true if a known node is there twice.
 template <int NT, typename Known, typename Table>
 __device__ __forceinline__ bool settle_in_block(Table& A, uint32_t n, uint32_t positions, const uint32_t (&e)[4], Known known) {

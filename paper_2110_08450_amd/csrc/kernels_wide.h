@@ -133,7 +133,7 @@ constexpr uint32_t wide_table_words(int d) {
 constexpr size_t wide_lds_bytes(int d) {
   return sizeof(uint32_t) * (kThreads / 64) * (2 * wide_lds_words(d) + wide_table_words(d));
 }
-static_assert(wide_lds_bytes(SMFG_MAX_WIDE_FANOUT) <= 65536, "LDS of a block");
+static_assert(wide_lds_bytes(SMFG_MAX_WIDE_FANOUT) + 2 * sizeof(uint2) <= 160 * 1024, "LDS of a compute unit, with the offsets of two turns");
 
 // What happens to a drawn sample: recorded (partition strategy), or also inserted into the dedup
 // table right away (table strategy; see k_sample_insert for the three cases).

@@ -6,7 +6,7 @@
 // check of the input arrays).
 //
 // All batches of a call share each launch (the batch is the fastest-varying part of the block index).  A
-// hop is two launches where it is small (and one before the first), four to six under the partition strategy (their
+// hop is one or two launches where it is small (and at most one before the first), four to six under the partition strategy (their
 // files describe both), and four under the table strategy:
 //   sample_insert  per destination: degree, Floyd/Philox row positions, neighbour ids, and an
 //                  insert of each neighbour into the batch's dedup table carrying the sample's
@@ -551,16 +551,16 @@ int small_hops_of(const smfg_workspace* const* ws, const int32_t* num_seeds, int
 }
 // A call that leaves the gather to another one is prepared beside the gather of another set, whose many short
 // blocks keep taking the places that a block of 16 waves waits for.  How much that costs depends on what else
-// runs.  Time per batch without / with small first hops, fanouts (15, 10, 5), 1024 seeds; graphs and tables as
+// runs.  Time per batch without / with small first hops, fanouts (15, 10, 5), 1024 seeds, BatchPipeline; graphs and tables as
 // papers100M (28 GB), products (490 MB) and arxiv (87 MB) have, and an eighth of papers100M with a model behind the
 // pipeline (a layer per hop):
-//                        1 batch                  2 batches             4 batches              8 batches
-//   the call gathers     206/199 180/168 131/119  154/151 128/122 78/71 131/125 104/101 50/47  119/112 91/90 37/36 us
-//   beside a gather      184/194 113/115  87/77   127/146  90/93  48/45 107/124  81/82  32/33  104/117 80/81 27/28 us
-//   ... and a model      1, 2, 3, 4, 6, 8 and 16 batches: 249/263, 228/240, 222/220, 247/245, 219/218, 232/231, 227/224 us
-// The line was drawn where sets of up to four batches gained on all three graphs, with the partition strategy's
-// six launches per hop and eight blocks of k_small_finish per batch; with its four launches and some 32 blocks only
-// sets of one and two on the smallest graph still do, and sets of three and more with a model behind them, a little.
+//                        1 batch                  2 batches              4 batches              8 batches
+//   the call gathers     195/189 157/152 117/109  155/152 120/117 70/67  134/132 101/100 47/46  125/124 92/91 37/36 us
+//   beside a gather      229/195 193/163 128/118  136/155 112/122 73/71  116/135  91/102 47/49  116/125 85/94 35/38 us
+//   ... and a model      1, 2, 3, 4, 6, 8 and 16 batches: 285/261, 270/221, 253/211, 241/209, 231/210, 224/212, 215/211 us
+// A pipeline of single batches is bound by the host's launches, of which they save some.  From two batches on they cost a pipeline that does
+// nothing but prepare up to 16 % (only two on the smallest graph gain, 3 %), and gain one with a model behind it 18 to 2 %, less the more
+// batches.  The line is where the two are about even: at four 5 to 16 % against 13, at eight 8 to 11 against 5.
 constexpr int kCrowdedBatches = 4;
 bool crowded_by_a_gather(const smfg_graph* g, bool gathers, int num_batches) {
   return g->feat && !gathers && num_batches > kCrowdedBatches;
