@@ -382,6 +382,7 @@ __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P)
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const LayerTiles<ROWS> T(P);
   if (T.first >= T.end) return;
+  const bool one = T.end - T.first <= T.step;  // tile: with code of its own, since in a small call every line of code has to be fetched
   if (wv < kLayerLoaders) {
     const uint32_t grp = threadIdx.x / LANES;
     const int lane = threadIdx.x & (LANES - 1);
@@ -471,6 +472,12 @@ __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P)
     read_offsets();
     static_assert(kAhead == 2, "the halves of buf");
     issue(s[0]);
+    if (one) {
+      finish(s[0], buf);
+      __syncthreads();
+      __syncthreads();
+      return;
+    }
     issue(s[1]);
     // Two tiles a turn, the last of an odd number with one of no destinations: a way past the second to the next turn would make every
     // wait for rows one for the tile's behind them.
@@ -488,12 +495,11 @@ __global__ void __launch_bounds__(kLayerThreads) k_sage_layer(const LayerArgs P)
   const LayerProduct<OutT, LANES, ROWS> product(P, wv - kLayerLoaders, reinterpret_cast<OutT*>(buf + 2 * ROWS * lda));
   __syncthreads();
   for (uint32_t i0 = T.first; i0 < T.end; i0 += 2u * T.step) {
-#pragma unroll
-    for (uint32_t half = 0; half < 2u; ++half) {
-      const uint32_t at = i0 + half * T.step;
-      product.tile(buf + half * ROWS * lda, static_cast<int>(at), static_cast<int>(T.count(at)));
-      __syncthreads();
-    }
+    product.tile(buf, static_cast<int>(i0), static_cast<int>(T.count(i0)));
+    __syncthreads();
+    if (one) return;
+    product.tile(buf + ROWS * lda, static_cast<int>(i0 + T.step), static_cast<int>(T.count(i0 + T.step)));
+    __syncthreads();
   }
 }
 
