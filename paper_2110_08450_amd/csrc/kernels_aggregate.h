@@ -216,11 +216,12 @@ struct LayerArgs {
   void* out;
 };
 
-__device__ __forceinline__ int layer_rows_in_all(const LayerArgs& P) {
+__device__ __forceinline__ int64_t layer_rows_in_all(const LayerArgs& P) {
   int64_t n = *P.num_dst;
   if (n > P.max_dst) n = P.max_dst;
   if (n > P.max_src) n = P.max_src;  // a destination's own row is row i of x
-  return n < 0 ? 0 : static_cast<int>(n);
+  if (n < 0) n = 0;
+  return n;
 }
 // An even share of consecutive destinations, so that no block has a tile more than the others to do.
 __device__ __forceinline__ void layer_range(const LayerArgs& P, int& b0, int& b1) {
@@ -350,16 +351,21 @@ struct LayerProduct {
           if (r < rows && c < cols) *reinterpret_cast<float4_t*>(to + static_cast<int64_t>(r) * P.out_dim + c) = *reinterpret_cast<const float4_t*>(res + r * ldo + c);
         }
       } else if (col < cols) {
-        constexpr int kRead = 8;  // reads of the LDS that no store waits between: 50 K x 3, 64 -> 47, float 16.6 us, 11.7 so
-        OutT* at = to + static_cast<int64_t>(hi) * P.out_dim + col;
+        // as many reads of the LDS at a time, while W leaves the registers for it: 50 K x 3, 64 -> 47, float 16.6 -> 11.7 us
+        constexpr int kRead = STEPS <= 16 ? 8 : 1;
+        if constexpr (kRead == 1) {
+          for (int r = hi; r < rows; r += 2) to[static_cast<int64_t>(r) * P.out_dim + col] = res[r * ldo + col];
+        } else {
+          OutT* at = to + static_cast<int64_t>(hi) * P.out_dim + col;
 #pragma unroll 1
-        for (int r = hi; r < rows; r += 2 * kRead) {
-          OutT v[kRead];
+          for (int r = hi; r < rows; r += 2 * kRead) {
+            OutT v[kRead];
 #pragma unroll
-          for (int u = 0; u < kRead; ++u) v[u] = res[(r + 2 * u) * ldo + col];
+            for (int u = 0; u < kRead; ++u) v[u] = res[(r + 2 * u) * ldo + col];
 #pragma unroll
-          for (int u = 0; u < kRead; ++u, at += 2 * P.out_dim)
-            if (r + 2 * u < rows) *at = v[u];
+            for (int u = 0; u < kRead; ++u, at += 2 * P.out_dim)
+              if (r + 2 * u < rows) *at = v[u];
+          }
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
